@@ -63,7 +63,11 @@ extern "C" {
  * row's (column's) leading components, applied to the exact value of the
  * element: d_s = RN(x / u_s) - 128 RN(x / u_(s-1)) (nearest, ties to even;
  * RN(x / u_0) taken as 0), so |d_s| <= 64 and the digits through s sum to x
- * rounded to the grid u_s. */
+ * rounded to the grid u_s.  The product of DD, TD and QD operands in this form
+ * is that of the elements rounded to the last digit's grid u_D, formed exactly
+ * (every digit pair, also those with s + t > D + 1) from its residues modulo
+ * pairwise coprime numbers below 257 and rounded once to the format: fewer
+ * INT8 products than the digit pairs take, and nothing left out. */
 #define MPGEMM_MODE_FLOAT 0
 #define MPGEMM_MODE_INT8 1
 
@@ -164,9 +168,9 @@ int mpgemm_ds_simple(int staging, int m, int n, int k, const double *Ahi, const 
  * is released or mpgemm_batched_cache_clear is called.  Batched calls of one
  * shape on one stream must not be issued from two host threads at once.
  * Both slice forms (the thread's mode for the format).  In the INT8 form each
- * product takes the tile configuration a single call would (two persistent
- * launches, 128 x 128 and 256 x 256 tiles), its diagonals spread over several
- * work items.
+ * product takes a tile configuration by its size (two persistent launches,
+ * 128 x 128 and 256 x 256 tiles), its residue planes spread over several work
+ * items; the result does not depend on either.
  * Return codes: -1 for count < 0; -i (i = 2..10) for a NULL array or an
  * invalid entry of argument i (first failing product); positive codes as above.
  */

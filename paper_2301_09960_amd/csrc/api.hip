@@ -18,6 +18,7 @@
 #include "host.h"
 #include "internal.h"
 #include "layout.h"
+#include "residue.h"
 
 using namespace mp;
 
@@ -255,13 +256,18 @@ struct Plan {
   size_t elem;  // bytes per slice element
   int64_t mbp, nbp, kbp;
   size_t off_resid_a, off_resid_b, off_pack_a, off_pack_b, off_mu_a, off_mu_b, off_exp_a, off_exp_b, off_sums, total;
+  // The product by residues (residue.h); nunits = 0: by slice products.  Its
+  // planes take the slices' place from off_arena on.
+  ResiduePlan res;
+  size_t off_arena, slices_total;
 };
 
-Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D) {
+// comps: components of a longer expansion (0: the format's own).
+Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, int comps = 0) {
   Plan p{};
   p.fmt = fmt;
   p.mode = mode;
-  p.C = kComps[fmt];
+  p.C = comps > 0 ? comps : kComps[fmt];
   p.D = D;
   const bool f32 = fmt == MPGEMM_TS;
   const size_t comp = f32 ? 4 : 8;
@@ -293,17 +299,24 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D) {
     p.mbp = nblocks8_padded(m, int8_tile_blocks(p.int8_cfg));
     p.nbp = nblocks8_padded(n, int8_tile_blocks(p.int8_cfg));
     p.kbp = kblocks8_padded(k);
-    p.off_resid_a = p.off_resid_b = take(0);
-    p.off_pack_a = take((size_t)D * p.mbp * p.kbp * 1024);
-    p.off_pack_b = take((size_t)D * p.nbp * p.kbp * 1024);
     p.off_mu_a = take((size_t)m * 8);
     p.off_mu_b = take((size_t)n * 8);
     p.off_exp_a = take((size_t)m * 4);
     p.off_exp_b = take((size_t)n * 4);
+    p.off_arena = o;
+    p.off_resid_a = p.off_resid_b = take(0);
+    p.off_pack_a = take((size_t)D * p.mbp * p.kbp * 1024);
+    p.off_pack_b = take((size_t)D * p.nbp * p.kbp * 1024);
     const int64_t nchunks = ceil_div(p.kbp, int8_kblocks_per_chunk(D));
     p.off_sums = take((size_t)D * nchunks * p.mbp * p.nbp * 1024 * 4);  // blocked, padded planes
+    // The integers are the elements rounded to the last digit's grid,
+    // u_D = 2^(E - (7 D - 1)).  The DD, TD and QD formats take the residues at
+    // every D; longer expansions, whose moduli would need powers above the
+    // square, the digit products.
+    if (m > 0 && n > 0 && k > 0 && p.C <= 4 && !residue_plan(7 * D - 1, k, p.res)) p.res.nunits = 0;
   }
-  p.total = o;
+  p.slices_total = p.total = o;
+  if (p.res.nunits > 0) p.total = std::max(o, p.off_arena + align256(residue_bytes(p.res, p.int8_cfg, m, n, k)));
   return p;
 }
 
@@ -455,11 +468,34 @@ hipError_t gemm_launch(const Plan &p, char *base, int m, int n, int k, T *Cout, 
   return hipErrorInvalidValue;
 }
 
-// The launch sequence of one product (split, then the fused slice products
-// and accumulation) on the workspace at `base`, laid out by plan p.  With
-// `profile`, records the thread's stage-timing events if they are enabled.
+// The product by residues on the workspace at `base` (`bytes` of it), laid out
+// by plan p; `between` is recorded after the split.
 template <typename T, int C>
-hipError_t launch_product(const Plan &p, char *base, int m, int n, int k, const T *A, int lda, const T *B, int ldb,
+hipError_t residue_launch(const Plan &p, char *base, size_t bytes, const SplitOperand<T> &a, const SplitOperand<T> &b,
+                          int m, int n, int k, T *Cm, int ldc, hipEvent_t between, hipStream_t st) {
+  ResidueCall rc{};
+  rc.plan = p.res;
+  rc.cfg = p.int8_cfg;
+  rc.m = m;
+  rc.n = n;
+  rc.k = k;
+  rc.ldc = ldc;
+  rc.c_stride = (int64_t)ldc * n;
+  rc.exp_a = reinterpret_cast<int *>(base + p.off_exp_a);
+  rc.exp_b = reinterpret_cast<int *>(base + p.off_exp_b);
+  rc.mu_a = base + p.off_mu_a;
+  rc.mu_b = base + p.off_mu_b;
+  rc.arena = base + p.off_arena;
+  rc.arena_bytes = bytes - p.off_arena;
+  return launch_residue<T, C>(rc, a, b, Cm, between, st);
+}
+
+// The launch sequence of one product (split, then the fused slice products
+// and accumulation, or the residues) on the workspace at `base` (`bytes` of
+// it), laid out by plan p.  With `profile`, records the thread's stage-timing
+// events if they are enabled.
+template <typename T, int C>
+hipError_t launch_product(const Plan &p, char *base, size_t bytes, int m, int n, int k, const T *A, int lda, const T *B, int ldb,
                           T *Cm, int ldc, bool profile, hipStream_t st) {
   const SplitOperand<T> a = operand_a(A, m, k, lda, p, base), b = operand_b(B, k, n, ldb, p, base);
   const bool prof = profile && g_prof.on;
@@ -468,9 +504,19 @@ hipError_t launch_product(const Plan &p, char *base, int m, int n, int k, const 
     for (auto &x : ev) x = g_prof.take();
     if (ev[0]) (void)hipEventRecord(ev[0], st);
   }
-  hipError_t e = split_both<T, C>(a, b, p, st);
-  if (ev[1]) (void)hipEventRecord(ev[1], st);
-  if (e == hipSuccess) e = gemm_launch<T, C>(p, base, m, n, k, Cm, ldc, -1, nullptr, 0, st);
+  hipError_t e = hipSuccess;
+  bool done = false;
+  if constexpr (sizeof(T) == 8 && C <= 4) {
+    if (p.res.nunits > 0) {
+      e = residue_launch<T, C>(p, base, bytes, a, b, m, n, k, Cm, ldc, ev[1], st);
+      done = true;
+    }
+  }
+  if (!done) {
+    e = split_both<T, C>(a, b, p, st);
+    if (ev[1]) (void)hipEventRecord(ev[1], st);
+    if (e == hipSuccess) e = gemm_launch<T, C>(p, base, m, n, k, Cm, ldc, -1, nullptr, 0, st);
+  }
   if (ev[2]) (void)hipEventRecord(ev[2], st);
   if (prof) {
     if (ev[0] && ev[1] && ev[2])
@@ -490,10 +536,10 @@ int run_with(int fmt, int mode, int D, int m, int n, int k, const T *A, int lda,
   g_opt.last_slices = D;
   if (m == 0 || n == 0) return 0;
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(T), C, m, n, ldc, (int64_t)ldc * n, st));
-  const Plan p = make_plan(fmt, mode, m, n, k, D);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, C);
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
-  return hip_status(launch_product<T, C>(p, ws.base, m, n, k, A, lda, B, ldb, Cm, ldc, true, st));
+  return hip_status(launch_product<T, C>(p, ws.base, p.total, m, n, k, A, lda, B, ldb, Cm, ldc, true, st));
 }
 
 // Slice counts chosen from the data (mpgemm_set_num_slices(fmt, FLOAT,
@@ -711,7 +757,7 @@ int run_ds(int m, int n, int k, const double *Ahi, const float *Alo, int lda, co
   double *Cdd = reinterpret_cast<double *>(ws.base + p.total + a_bytes + b_bytes);
   hipError_t e = launch_ds_to_dd(m, k, Ahi, Alo, lda, Add, st);
   if (e == hipSuccess) e = launch_ds_to_dd(k, n, Bhi, Blo, ldb, Bdd, st);
-  if (e == hipSuccess) e = launch_product<double, 2>(p, ws.base, m, n, k, Add, m, Bdd, k, Cdd, m, true, st);
+  if (e == hipSuccess) e = launch_product<double, 2>(p, ws.base, p.total, m, n, k, Add, m, Bdd, k, Cdd, m, true, st);
   if (e == hipSuccess) e = launch_dd_to_ds(m, n, Cdd, Chi, Clo, ldc, st);
   return hip_status(e);
 }
@@ -755,10 +801,10 @@ int run_dd_noalloc(int m, int n, int k, const double *A, int lda, const double *
   if (m == 0 || n == 0) return 0;
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(double), 2, m, n, ldc, (int64_t)ldc * n, st));
   const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D);
-  if (p.total > kScratchBytes) return MPGEMM_ERR_TOO_LARGE;
+  if (p.slices_total > kScratchBytes) return MPGEMM_ERR_TOO_LARGE;
   char *base = nullptr;
   if ((s = scratch_of_current_device(&base))) return s;
-  return hip_status(launch_product<double, 2>(p, base, m, n, k, A, lda, B, ldb, Cm, ldc, false, st));
+  return hip_status(launch_product<double, 2>(p, base, kScratchBytes, m, n, k, A, lda, B, ldb, Cm, ldc, false, st));
 }
 
 template <typename T, int C>
@@ -828,7 +874,7 @@ int debug_products_t(int fmt, int mode, int m, int n, int k, const T *A, int lda
   if (mode == MPGEMM_MODE_FLOAT && (a < 1 || b < 1 || a + b > D + 1)) return -12;
   if (mode == MPGEMM_MODE_INT8 && (a < 1 || a > D)) return -12;
   if (m == 0 || n == 0 || k == 0) return 0;
-  const Plan p = make_plan(fmt, mode, m, n, k, D);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, C);
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
   const SplitOperand<T> sa = operand_a(A, m, k, lda, p, ws.base), sb = operand_b(B, k, n, ldb, p, ws.base);
@@ -854,7 +900,7 @@ int certify_run(int fmt, int mode, int D, int m, int n, int k, const T *A, int l
       e = launch_zero_matrix(Cm, sizeof(T), C, m, n, ldc, (int64_t)ldc * n, st);
     return hip_status(e);
   }
-  const Plan p = make_plan(fmt, mode, m, n, k, D);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, C);
   // |A_0| and |B_0| go into the slice buffers in the binary64 packed layout
   SplitOperand<T> ca{}, cb{};
   ca.nbp = nblocks_padded(m);
@@ -867,8 +913,7 @@ int certify_run(int fmt, int mode, int D, int m, int n, int k, const T *A, int l
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
   const SplitOperand<T> a = operand_a(A, m, k, lda, p, ws.base), b = operand_b(B, k, n, ldb, p, ws.base);
-  hipError_t e = split_both<T, C>(a, b, p, st);
-  if (e == hipSuccess) e = gemm_launch<T, C>(p, ws.base, m, n, k, Cm, ldc, -1, nullptr, 0, st);
+  hipError_t e = launch_product<T, C>(p, ws.base, p.total, m, n, k, A, lda, B, ldb, Cm, ldc, false, st);
   ca = a;
   cb = b;
   ca.nbp = nblocks_padded(m);
@@ -1129,7 +1174,7 @@ int mpgemm_nd_num_slices(int c, int k) {
 size_t mpgemm_nd_workspace_bytes(int c, int D, int m, int n, int k) {
   if (c < 2 || c > kMaxNd || D < 0 || D > kMaxDNd || m < 0 || n < 0 || k < 0) return 0;
   if (m == 0 || n == 0 || k == 0) return 0;
-  return make_plan(MPGEMM_QD, MPGEMM_MODE_INT8, m, n, k, D > 0 ? D : nd_auto_slices(c, k)).total;
+  return make_plan(MPGEMM_QD, MPGEMM_MODE_INT8, m, n, k, D > 0 ? D : nd_auto_slices(c, k), c).total;
 }
 
 int mpgemm_nd_debug_split(int c, int operand, int rows, int cols, const double *X, int ldx, int D, int8_t *digits,

@@ -11,10 +11,10 @@
 //     items of the persistent GEMM kernel, in one list per XCD (written once).
 // The graph holds: clear the maxima, one max-exponent launch and dmax pass
 // launches covering all operands, clear the work counter, and one persistent
-// GEMM launch.  In the INT8 form: clear the maxima, the max-exponent launch,
-// one digit-split launch over all operands' blocks, clear the work counter,
-// the persistent INT8 GEMM over (product, tile, k chunk, diagonal group)
-// items and one combine launch over all products.  Kernels take the caller's pointers from the descriptors, so a
+// GEMM launch.  In the INT8 form: clear the maxima and work counters, the
+// max-exponent launch, one residue split over all operands' blocks, the
+// persistent INT8 GEMMs over (product, tile, k chunk, unit group) items and one
+// combine launch over all products.  Kernels take the caller's pointers from the descriptors, so a
 // cached graph is replayed with new pointers after one small host-to-device
 // copy of the descriptors.
 #include <hip/hip_runtime.h>
@@ -27,6 +27,7 @@
 #include "host.h"
 #include "internal.h"
 #include "layout.h"
+#include "residue.h"
 
 namespace mp {
 namespace host {
@@ -53,63 +54,9 @@ struct ProductLayout {
   int m, n, k, D, rho;
   int64_t mbp, nbp, kbp;
   size_t resid_a, resid_b, pack_a, pack_b, mu_a, mu_b, exp_a, exp_b;
-  // INT8 form: k blocks per chunk, chunks, diagonal groups, diagonal sums
-  int kbc = 0, nchunks = 0, groups = 1, cfg = 1;
-  size_t sums = 0;
   // binary64/binary32 slices: operand split by the fused kernel (no residual)
   bool fused_a = false, fused_b = false;
 };
-
-// The part of an operand that decides its split kernel.
-struct OperandShape {
-  int64_t kbp, nbp, nvec;
-};
-
-struct BatchPlan {
-  int device = 0, fmt = 0, mode = 0, layout = 1, int8_tile = 0, split_kernel = 0, last_slice = 0;
-  hipStream_t stream = nullptr;
-  std::vector<int> m, n, k, D;
-  std::vector<ProductLayout> prod;
-  std::vector<int> live;  // products with m, n, k > 0
-  char *ws = nullptr;
-  size_t off_ops = 0, off_descs = 0, desc_bytes = 0, off_prefix0 = 0, off_prefixp = 0, off_prefixf = 0,
-         off_items = 0, off_bounds = 0, off_counter = 0, off_mu = 0, mu_bytes = 0, off_prefixc = 0, total = 0;
-  int nops = 0, tiles0 = 0, tilesp = 0, stripsf = 0, dmax = 0, nitems = 0, nitems3 = 0;
-  int fused_nt = 1024;  // threads of the fused-split workgroups
-  int64_t blocks8 = 0, blocksc = 0;  // INT8 form: split blocks, combine blocks
-  void *stage = nullptr;
-  hipEvent_t stage_done = nullptr;
-  hipGraph_t graph = nullptr;
-  hipGraphExec_t exec = nullptr;
-  uint64_t last_use = 0;
-
-  void release() {
-    if (exec) (void)hipGraphExecDestroy(exec);
-    if (graph) (void)hipGraphDestroy(graph);
-    if (stage_done) (void)hipEventDestroy(stage_done);
-    if (stage) (void)hipHostFree(stage);
-    if (ws) (void)hipFree(ws);
-    exec = nullptr;
-    graph = nullptr;
-    stage_done = nullptr;
-    stage = nullptr;
-    ws = nullptr;
-  }
-};
-
-struct BatchCache {
-  std::vector<BatchPlan *> plans;
-  hipStream_t capture[64] = {};
-  uint64_t clock = 0;
-};
-// Owned by the thread and intentionally not destroyed at thread exit (the HIP
-// runtime may already be gone then); mpgemm_batched_cache_clear frees it.
-thread_local BatchCache *g_batch = nullptr;
-
-BatchCache &cache() {
-  if (!g_batch) g_batch = new BatchCache();
-  return *g_batch;
-}
 
 int tiles64(int64_t a, int64_t b) { return (int)(ceil_div(a, 64) * ceil_div(b, 64)); }
 
@@ -157,6 +104,281 @@ std::vector<Item> xcd_lists(const std::vector<Item> &items, Key key, int *bounds
     bounds[q + 1] = (int)out.size();
   }
   return out;
+}
+
+// The products of a batch that are formed by residues (residue.h): one split
+// over all their operands, one persistent INT8 GEMM per tile configuration over
+// (product, tile, k chunk, unit group) items in per-XCD lists, and one combine.
+struct ResidueBatch {
+  struct Slot {
+    int g;  // product of the batch
+    int m, n, k, cfg, groups = 1;
+    ResiduePlan plan;
+    int64_t mbp, nbp, kbp;
+    size_t a, b, r, exp_a, exp_b, mu_a, mu_b, table;
+  };
+  std::vector<Slot> slots;
+  int nw = 0, nwc = 0, tiles0 = 0, nitems1 = 0, nitems3 = 0;
+  int64_t blocks = 0, blocksc = 0;
+  size_t off_planes = 0, planes_bytes = 0, off_static = 0, off_items = 0, off_bounds = 0, off_counter = 0,
+         off_zero = 0, zero_bytes = 0;
+  std::vector<int> prefix;         // 2 n + 1 max tiles, 2 n + 1 split blocks, n + 1 combine blocks
+  std::vector<uint32_t> tables;    // the distinct combine tables
+  std::vector<int4> items;
+  int bounds[2 * (kXcds + 1)] = {};
+
+  int nops() const { return 2 * (int)slots.size(); }
+  size_t ops_bytes(size_t elem) const { return (size_t)nops() * elem; }
+
+  void add(int g, int m, int n, int k, const ResiduePlan &plan, int cfg) {
+    Slot s;
+    s.g = g;
+    s.m = m;
+    s.n = n;
+    s.k = k;
+    s.cfg = cfg;
+    s.plan = plan;
+    const int tb = int8_tile_blocks(cfg);
+    s.mbp = nblocks8_padded(m, tb);
+    s.nbp = nblocks8_padded(n, tb);
+    s.kbp = kblocks8_padded(k);
+    slots.push_back(s);
+  }
+
+  // Places everything in the workspace (take: bytes -> offset); elem: bytes of a maximum.
+  template <typename Take>
+  void layout(Take take, size_t elem) {
+    for (Slot &s : slots) {
+      nw = std::max(nw, s.plan.nw);
+      nwc = std::max(nwc, s.plan.nwc);
+    }
+    off_planes = take(0);
+    for (Slot &s : slots) {
+      s.a = take((size_t)s.plan.nplanes * s.mbp * s.kbp * 1024);
+      s.b = take((size_t)s.plan.nplanes * s.nbp * s.kbp * 1024);
+    }
+    planes_bytes = take(0) - off_planes;
+    for (Slot &s : slots) {
+      s.r = take((size_t)s.plan.nplanes * s.plan.nchunks * s.mbp * s.nbp * 1024);
+      s.exp_a = take((size_t)s.m * 4);
+      s.exp_b = take((size_t)s.n * 4);
+    }
+    off_zero = take(0);
+    for (Slot &s : slots) {
+      s.mu_a = take((size_t)s.m * elem);
+      s.mu_b = take((size_t)s.n * elem);
+    }
+    off_counter = take(2 * kXcds * 4);
+    zero_bytes = take(0) - off_zero;
+
+    const int n = (int)slots.size();
+    prefix.assign((size_t)2 * (2 * n + 1) + n + 1, 0);
+    int *pre0 = prefix.data(), *preb = pre0 + 2 * n + 1, *prec = preb + 2 * n + 1;
+    std::vector<std::pair<std::pair<int, int>, size_t>> known;
+    for (int i = 0; i < n; ++i) {
+      Slot &s = slots[i];
+      const int64_t kbl = ceil_div((int64_t)s.k, (int64_t)kKBlk8);
+      pre0[2 * i + 1] = pre0[2 * i] + tiles64(s.m, s.k);
+      pre0[2 * i + 2] = pre0[2 * i + 1] + tiles64(s.n, s.k);
+      preb[2 * i + 1] = preb[2 * i] + (int)(ceil_div((int64_t)s.m, (int64_t)kBlk8) * kbl);
+      preb[2 * i + 2] = preb[2 * i + 1] + (int)(ceil_div((int64_t)s.n, (int64_t)kBlk8) * kbl);
+      prec[i + 1] = prec[i] + (int)(s.mbp * s.nbp);
+      const std::pair<int, int> key(s.plan.nunits, s.plan.nsq);
+      size_t at = SIZE_MAX;
+      for (const auto &kn : known)
+        if (kn.first == key) at = kn.second;
+      if (at == SIZE_MAX) {
+        at = tables.size();
+        const std::vector<uint32_t> &t = residue_table(key.first, key.second, nwc);
+        tables.insert(tables.end(), t.begin(), t.end());
+        known.push_back({key, at});
+      }
+      s.table = at;
+    }
+    tiles0 = pre0[2 * n];
+    blocks = preb[2 * n];
+    blocksc = prec[n];
+    make_items();
+    off_static = take(prefix.size() * 4 + tables.size() * 4);
+    off_items = take(items.size() * sizeof(int4));
+    off_bounds = take(sizeof(bounds));
+  }
+
+  void make_items() {
+    // unit groups: items of about 1/4 of a persistent workgroup's fair share
+    int64_t work = 0;
+    for (const Slot &s : slots)
+      work += (s.mbp / 4) * (s.nbp / 4) * s.plan.products() * s.kbp;  // in 128 x 128 tile units
+    const int64_t target = std::max<int64_t>(1, work / (4 * (int64_t)kPersistentGrid));
+    struct Item {
+      int slot, tile, chunk, group;
+      int64_t cost;
+    };
+    std::vector<Item> items1, items3;
+    for (int i = 0; i < (int)slots.size(); ++i) {
+      Slot &s = slots[i];
+      const int tb = int8_tile_blocks(s.cfg);
+      const int64_t unit = (tb / 4) * (tb / 4), kbc = std::min<int64_t>(s.kbp, kChunkBlocks);
+      s.groups = (int)std::min<int64_t>(s.plan.nunits,
+                                        std::max<int64_t>(1, ceil_div(s.plan.products() * kbc * unit, target)));
+      const int ntiles = (int)((s.mbp / tb) * (s.nbp / tb));
+      std::vector<Item> &dst = s.cfg == 1 ? items1 : items3;
+      for (int z = 0; z < s.groups; ++z) {
+        const int nsq = s.plan.nsq, nu = s.plan.nunits;
+        const int pairs = residue_pairs_below(residue_group_start(0, nu, nsq, z + 1, s.groups), nsq) -
+                          residue_pairs_below(residue_group_start(0, nu, nsq, z, s.groups), nsq);
+        if (pairs == 0) continue;
+        for (int c = 0; c < s.plan.nchunks; ++c) {
+          const int64_t kb = std::min<int64_t>(kChunkBlocks, s.kbp - (int64_t)c * kChunkBlocks);
+          for (int t = 0; t < ntiles; ++t) dst.push_back({i, t, c, z, pairs * kb});
+        }
+      }
+    }
+    // one list per XCD for each configuration; a run is one (product, k chunk,
+    // unit group): its tiles
+    auto run_key = [](const Item &it) { return ((int64_t)it.slot << 32) | ((int64_t)it.chunk << 12) | it.group; };
+    items1 = xcd_lists(items1, run_key, bounds);
+    items3 = xcd_lists(items3, run_key, bounds + kXcds + 1);
+    nitems1 = (int)items1.size();
+    nitems3 = (int)items3.size();
+    for (const auto *v : {&items1, &items3})
+      for (const Item &it : *v) items.push_back(make_int4(it.slot, it.tile, it.chunk, it.group));
+  }
+
+  // Static device data of a new plan.  The split writes only blocks that hold
+  // elements: the planes' padding is cleared here, once, and stays zero.
+  bool upload(char *ws) const {
+    if (slots.empty()) return true;
+    return hipMemset(ws + off_planes, 0, planes_bytes) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess &&
+           hipMemcpy(ws + off_static, prefix.data(), prefix.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
+           hipMemcpy(ws + off_static + prefix.size() * 4, tables.data(), tables.size() * 4, hipMemcpyHostToDevice) ==
+               hipSuccess &&
+           hipMemcpy(ws + off_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice) == hipSuccess &&
+           hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
+  }
+
+  // The launch sequence (descriptors at off_ops, off_descs of the workspace).
+  template <typename T, int C>
+  hipError_t launch(char *ws, size_t off_ops, size_t off_descs, hipStream_t st) const {
+    if (slots.empty()) return hipSuccess;
+    const auto *ops = reinterpret_cast<const ResidueOperand<T> *>(ws + off_ops);
+    const auto *descs = reinterpret_cast<const ResidueDesc *>(ws + off_descs);
+    const int n = (int)slots.size();
+    const int *pre0 = reinterpret_cast<const int *>(ws + off_static), *preb = pre0 + 2 * n + 1, *prec = preb + 2 * n + 1;
+    hipError_t e = launch_fill32(ws + off_zero, (int64_t)(zero_bytes / 4), 0u, st);
+    if (e == hipSuccess) e = launch_residue_max_batched<T>(ops, pre0, 2 * n, tiles0, st);
+    if (e == hipSuccess) e = launch_residue_split_batched<T, C>(nw, ops, preb, 2 * n, (int)blocks, st);
+    if (e == hipSuccess)
+      e = launch_gemm_residue_batched(descs, reinterpret_cast<const int4 *>(ws + off_items), nitems1, nitems3,
+                                      reinterpret_cast<const int *>(ws + off_bounds),
+                                      reinterpret_cast<int *>(ws + off_counter), st);
+    if (e == hipSuccess) e = launch_residue_combine_batched<T, C>(nwc, descs, prec, n, blocksc, st);
+    return e;
+  }
+
+  // Descriptors carrying a call's pointers, into the pinned stage.
+  template <typename T>
+  void write(char *ws, ResidueOperand<T> *ops, ResidueDesc *descs, const T *const *A, const int *lda,
+             const T *const *B, const int *ldb, T *const *Cm, const int *ldc) const {
+    const char *tab = ws + off_static + prefix.size() * 4;
+    for (size_t i = 0; i < slots.size(); ++i) {
+      const Slot &s = slots[i];
+      const int g = s.g;
+      for (int side = 0; side < 2; ++side) {
+        ResidueOperand<T> o{};
+        o.X = side == 0 ? A[g] : B[g];
+        o.comp_stride = side == 0 ? (int64_t)lda[g] * s.k : (int64_t)ldb[g] * s.n;
+        o.sv = side == 0 ? 1 : ldb[g];
+        o.sp = side == 0 ? lda[g] : 1;
+        o.nvec = side == 0 ? s.m : s.n;
+        o.len = s.k;
+        o.orient = side;
+        o.bits = s.plan.bits;
+        o.planes = reinterpret_cast<int8_t *>(ws + (side == 0 ? s.a : s.b));
+        o.nbp = side == 0 ? s.mbp : s.nbp;
+        o.kbp = s.kbp;
+        o.mu = ws + (side == 0 ? s.mu_a : s.mu_b);
+        o.exps = reinterpret_cast<int *>(ws + (side == 0 ? s.exp_a : s.exp_b));
+        o.nunits = s.plan.nunits;
+        o.nsq = s.plan.nsq;
+        ops[2 * i + side] = o;
+      }
+      ResidueDesc d{};
+      d.A = reinterpret_cast<const int8_t *>(ws + s.a);
+      d.B = reinterpret_cast<const int8_t *>(ws + s.b);
+      d.R = reinterpret_cast<int8_t *>(ws + s.r);
+      d.table = reinterpret_cast<const uint32_t *>(tab) + s.table;
+      d.EA = reinterpret_cast<const int *>(ws + s.exp_a);
+      d.EB = reinterpret_cast<const int *>(ws + s.exp_b);
+      d.mbp = s.mbp;
+      d.nbp = s.nbp;
+      d.kbp = s.kbp;
+      d.plane = s.mbp * s.nbp * 1024;
+      d.nunits = s.plan.nunits;
+      d.nsq = s.plan.nsq;
+      d.nplanes = s.plan.nplanes;
+      d.nchunks = s.plan.nchunks;
+      d.groups = s.groups;
+      d.bits = s.plan.bits;
+      d.m = s.m;
+      d.n = s.n;
+      d.ldc = ldc[g];
+      d.C = Cm[g];
+      d.c_stride = (int64_t)ldc[g] * s.n;
+      descs[i] = d;
+    }
+  }
+};
+
+// The part of an operand that decides its split kernel.
+struct OperandShape {
+  int64_t kbp, nbp, nvec;
+};
+
+struct BatchPlan {
+  int device = 0, fmt = 0, mode = 0, layout = 1, int8_tile = 0, split_kernel = 0, last_slice = 0;
+  hipStream_t stream = nullptr;
+  std::vector<int> m, n, k, D;
+  std::vector<ProductLayout> prod;
+  std::vector<int> live;  // products with m, n, k > 0
+  char *ws = nullptr;
+  size_t off_ops = 0, off_descs = 0, desc_bytes = 0, off_prefix0 = 0, off_prefixp = 0, off_prefixf = 0,
+         off_items = 0, off_bounds = 0, off_counter = 0, off_mu = 0, mu_bytes = 0, total = 0;
+  int nops = 0, tiles0 = 0, tilesp = 0, stripsf = 0, dmax = 0, nitems = 0;
+  int fused_nt = 1024;  // threads of the fused-split workgroups
+  void *stage = nullptr;
+  hipEvent_t stage_done = nullptr;
+  hipGraph_t graph = nullptr;
+  hipGraphExec_t exec = nullptr;
+  ResidueBatch res;  // the products formed by residues
+  uint64_t last_use = 0;
+
+  void release() {
+    if (exec) (void)hipGraphExecDestroy(exec);
+    if (graph) (void)hipGraphDestroy(graph);
+    if (stage_done) (void)hipEventDestroy(stage_done);
+    if (stage) (void)hipHostFree(stage);
+    if (ws) (void)hipFree(ws);
+    exec = nullptr;
+    graph = nullptr;
+    stage_done = nullptr;
+    stage = nullptr;
+    ws = nullptr;
+  }
+};
+
+struct BatchCache {
+  std::vector<BatchPlan *> plans;
+  hipStream_t capture[64] = {};
+  uint64_t clock = 0;
+};
+// Owned by the thread and intentionally not destroyed at thread exit (the HIP
+// runtime may already be gone then); mpgemm_batched_cache_clear frees it.
+thread_local BatchCache *g_batch = nullptr;
+
+BatchCache &cache() {
+  if (!g_batch) g_batch = new BatchCache();
+  return *g_batch;
 }
 
 template <typename T, int C>
@@ -377,9 +599,7 @@ void write_descriptors(BatchPlan &p, const T *const *A, const int *lda, const T 
   }
 }
 
-// INT8-form batch: the digit split of every operand, one persistent INT8
-// GEMM per tile configuration over (product, tile, k chunk, diagonal group)
-// items in per-XCD lists, and one combine over every product's blocks.
+// INT8-form batch: every product by residues.
 template <int C>
 int build_plan_int8(BatchPlan &p, int cfg_override) {
   const int count = (int)p.m.size();
@@ -389,101 +609,20 @@ int build_plan_int8(BatchPlan &p, int cfg_override) {
     o += align256(bytes);
     return at;
   };
-  p.prod.resize(count);
   p.live.clear();
-  p.dmax = 0;
   for (int g = 0; g < count; ++g) {
-    ProductLayout &L = p.prod[g];
-    L.m = p.m[g];
-    L.n = p.n[g];
-    L.k = p.k[g];
-    L.D = p.D[g];
-    if (L.m <= 0 || L.n <= 0 || L.k <= 0) continue;
+    if (p.m[g] <= 0 || p.n[g] <= 0 || p.k[g] <= 0) continue;
+    ResiduePlan plan;
+    if (!residue_plan(7 * p.D[g] - 1, p.k[g], plan)) return MPGEMM_ERR_TOO_LARGE;  // none: D <= 40, k <= 2^20
     p.live.push_back(g);
-    L.rho = 0;
-    L.cfg = batch_int8_cfg(L.m, L.n, cfg_override);
-    L.mbp = nblocks8_padded(L.m, int8_tile_blocks(L.cfg));
-    L.nbp = nblocks8_padded(L.n, int8_tile_blocks(L.cfg));
-    L.kbp = kblocks8_padded(L.k);
-    L.kbc = int8_kblocks_per_chunk(L.D);
-    L.nchunks = (int)ceil_div(L.kbp, L.kbc);
-    L.resid_a = L.resid_b = 0;
-    L.pack_a = take((size_t)L.D * L.mbp * L.kbp * 1024);
-    L.pack_b = take((size_t)L.D * L.nbp * L.kbp * 1024);
-    L.exp_a = take((size_t)L.m * 4);
-    L.exp_b = take((size_t)L.n * 4);
-    L.sums = take((size_t)L.D * L.nchunks * L.mbp * L.nbp * 1024 * 4);
-    p.dmax = std::max(p.dmax, L.D);
+    p.res.add(g, p.m[g], p.n[g], p.k[g], plan, batch_int8_cfg(p.m[g], p.n[g], cfg_override));
   }
-  p.off_mu = o;
-  size_t mo = 0;
-  for (int g : p.live) {
-    ProductLayout &L = p.prod[g];
-    L.mu_a = p.off_mu + mo;
-    mo += (size_t)L.m * 8;
-    L.mu_b = p.off_mu + mo;
-    mo += (size_t)L.n * 8;
-  }
-  p.mu_bytes = (mo + 3) / 4 * 4;
-  o = p.off_mu + align256(mo);
-  p.nops = 2 * (int)p.live.size();
+  p.res.layout(take, sizeof(double));
+  if (p.res.blocks > 0x7fffffffLL || p.res.blocksc > 0x7fffffffLL / 4) return MPGEMM_ERR_TOO_LARGE;
   p.off_ops = take(0);
-  p.off_descs = p.off_ops + (size_t)p.nops * sizeof(SplitOperand<double>);
-  p.desc_bytes = (size_t)p.nops * sizeof(SplitOperand<double>) + p.live.size() * sizeof(Int8GemmDesc);
-  o = p.off_ops + align256(p.desc_bytes);
-  p.off_prefix0 = take((size_t)(p.nops + 1) * 4);
-  p.off_prefixp = take((size_t)(p.nops + 1) * 4);
-  p.off_prefixc = take((size_t)(p.live.size() + 1) * 4);
-
-  // diagonal groups: items of about 1/4 of a persistent workgroup's fair share
-  auto cum = [](int64_t g) { return g * (g + 1) / 2; };
-  int64_t work = 0;
-  for (int g : p.live) {
-    const ProductLayout &L = p.prod[g];
-    const int tb = int8_tile_blocks(L.cfg);
-    work += (L.mbp / tb) * (L.nbp / tb) * (tb / 4) * (tb / 4) * cum(L.D) * L.kbp;  // in 128 x 128 tile units
-  }
-  const int64_t target = std::max<int64_t>(1, work / (4 * (int64_t)kPersistentGrid));
-  struct Item {
-    int slot, tile, chunk, group;
-    int64_t cost;
-  };
-  std::vector<Item> items, items3;
-  for (int slot = 0; slot < (int)p.live.size(); ++slot) {
-    ProductLayout &L = p.prod[p.live[slot]];
-    const int tb = int8_tile_blocks(L.cfg);
-    const int64_t unit = (tb / 4) * (tb / 4);  // 128 x 128 tiles in one tile
-    L.groups = (int)std::min<int64_t>(L.D, std::max<int64_t>(1, ceil_div(cum(L.D) * L.kbc * unit, target)));
-    const int ntiles = (int)((L.mbp / tb) * (L.nbp / tb));
-    std::vector<Item> &dst = L.cfg == 1 ? items : items3;
-    for (int z = 0; z < L.groups; ++z) {
-      // the same cut as the device: smallest g with cum(g) >= target pairs
-      auto first_reaching = [&](int64_t t) {
-        int64_t gg = 0;
-        while (cum(gg) < t) ++gg;
-        return gg;
-      };
-      const int64_t pairs = cum(L.D);
-      const int64_t b0 = first_reaching(pairs * z / L.groups), b1 = first_reaching(pairs * (z + 1) / L.groups);
-      if (b1 == b0) continue;  // empty group
-      for (int c = 0; c < L.nchunks; ++c) {
-        const int64_t kblocks = std::min<int64_t>(L.kbc, L.kbp - (int64_t)c * L.kbc);
-        for (int t = 0; t < ntiles; ++t) dst.push_back({slot, t, c, z, (cum(b1) - cum(b0)) * kblocks});
-      }
-    }
-  }
-  // one list per XCD for each configuration; a run is one (product, k chunk,
-  // diagonal group): its tiles
-  auto run_key = [](const Item &it) { return ((int64_t)it.slot << 32) | ((int64_t)it.chunk << 12) | it.group; };
-  int bounds[2 * (kXcds + 1)];
-  items = xcd_lists(items, run_key, bounds);
-  items3 = xcd_lists(items3, run_key, bounds + kXcds + 1);
-  p.nitems = (int)items.size();
-  p.nitems3 = (int)items3.size();
-  items.insert(items.end(), items3.begin(), items3.end());
-  p.off_items = take(items.size() * sizeof(int4));
-  p.off_bounds = take(sizeof(bounds));
-  p.off_counter = take(2 * kXcds * 4);
+  p.off_descs = p.off_ops + p.res.ops_bytes(sizeof(ResidueOperand<double>));
+  p.desc_bytes = p.off_descs - p.off_ops + p.res.slots.size() * sizeof(ResidueDesc);
+  take(p.desc_bytes);
   p.total = o;
 
   if (hipMalloc(&p.ws, p.total > 0 ? p.total : 256) != hipSuccess) {
@@ -497,51 +636,13 @@ int build_plan_int8(BatchPlan &p, int cfg_override) {
     return MPGEMM_ERR_WORKSPACE;
   }
   if (hipEventCreateWithFlags(&p.stage_done, hipEventDisableTiming) != hipSuccess) return MPGEMM_ERR_HIP;
-  // the digit split writes only blocks that hold elements: the padding blocks
-  // of the packed planes are cleared here, once, and stay zero on every replay
-  if (hipMemset(p.ws, 0, p.total > 0 ? p.total : 256) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess)
-    return MPGEMM_ERR_HIP;
-
-  std::vector<int> pre0(p.nops + 1, 0), preb(p.nops + 1, 0), prec(p.live.size() + 1, 0);
-  for (int slot = 0; slot < (int)p.live.size(); ++slot) {
-    const ProductLayout &L = p.prod[p.live[slot]];
-    const int64_t kbl = ceil_div((int64_t)L.k, (int64_t)kKBlk8);
-    pre0[2 * slot + 1] = pre0[2 * slot] + tiles64(L.m, L.k);
-    pre0[2 * slot + 2] = pre0[2 * slot + 1] + tiles64(L.n, L.k);
-    preb[2 * slot + 1] = preb[2 * slot] + (int)(ceil_div((int64_t)L.m, (int64_t)kBlk8) * kbl);
-    preb[2 * slot + 2] = preb[2 * slot + 1] + (int)(ceil_div((int64_t)L.n, (int64_t)kBlk8) * kbl);
-    prec[slot + 1] = prec[slot] + (int)(L.mbp * L.nbp);
-  }
-  p.tiles0 = pre0[p.nops];
-  p.blocks8 = preb[p.nops];
-  p.blocksc = prec[p.live.size()];
-  std::vector<int4> it4(items.size());
-  for (size_t i = 0; i < items.size(); ++i)
-    it4[i] = make_int4(items[i].slot, items[i].tile, items[i].chunk, items[i].group);
-  if (hipMemcpy(p.ws + p.off_prefix0, pre0.data(), pre0.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p.ws + p.off_prefixp, preb.data(), preb.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p.ws + p.off_prefixc, prec.data(), prec.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      (it4.size() && hipMemcpy(p.ws + p.off_items, it4.data(), it4.size() * sizeof(int4), hipMemcpyHostToDevice) !=
-                         hipSuccess) ||
-      hipMemcpy(p.ws + p.off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) != hipSuccess)
-    return MPGEMM_ERR_HIP;
+  if (!p.res.upload(p.ws)) return MPGEMM_ERR_HIP;
 
   BatchCache &bc = cache();
   hipStream_t &cs = bc.capture[p.device & 63];
   if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return MPGEMM_ERR_HIP;
   if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return MPGEMM_ERR_HIP;
-  hipError_t e = launch_split_int8_batched<C>(
-      reinterpret_cast<const SplitOperand<double> *>(p.ws + p.off_ops),
-      reinterpret_cast<const int *>(p.ws + p.off_prefix0), reinterpret_cast<const int *>(p.ws + p.off_prefixp),
-      p.nops, p.tiles0, p.blocks8, p.dmax, p.ws + p.off_mu, (int64_t)(p.mu_bytes / 4), cs);
-  if (e == hipSuccess) e = launch_fill32(p.ws + p.off_counter, 2 * kXcds, 0u, cs);
-  if (e == hipSuccess)
-    e = launch_int8_batched<C>(reinterpret_cast<const Int8GemmDesc *>(p.ws + p.off_descs),
-                               reinterpret_cast<const int4 *>(p.ws + p.off_items), p.nitems, p.nitems3,
-                               reinterpret_cast<const int *>(p.ws + p.off_bounds),
-                               reinterpret_cast<int *>(p.ws + p.off_counter),
-                               reinterpret_cast<const int *>(p.ws + p.off_prefixc), (int)p.live.size(), p.blocksc,
-                               cs);
+  const hipError_t e = p.res.template launch<double, C>(p.ws, p.off_ops, p.off_descs, cs);
   hipGraph_t graph = nullptr;
   const hipError_t e2 = hipStreamEndCapture(cs, &graph);
   if (e != hipSuccess || e2 != hipSuccess || !graph) {
@@ -555,66 +656,6 @@ int build_plan_int8(BatchPlan &p, int cfg_override) {
     return MPGEMM_ERR_HIP;
   }
   return 0;
-}
-
-void write_descriptors_int8(BatchPlan &p, const double *const *A, const int *lda, const double *const *B,
-                            const int *ldb, double *const *Cm, const int *ldc) {
-  SplitOperand<double> *ops = static_cast<SplitOperand<double> *>(p.stage);
-  Int8GemmDesc *descs = reinterpret_cast<Int8GemmDesc *>(static_cast<char *>(p.stage) +
-                                                         (size_t)p.nops * sizeof(SplitOperand<double>));
-  for (int slot = 0; slot < (int)p.live.size(); ++slot) {
-    const int g = p.live[slot];
-    const ProductLayout &L = p.prod[g];
-    SplitOperand<double> a{}, b{};
-    a.X = A[g];
-    a.comp_stride = (int64_t)lda[g] * L.k;
-    a.sv = 1;
-    a.sp = lda[g];
-    a.nvec = L.m;
-    a.len = L.k;
-    a.orient = 0;
-    a.packed = p.ws + L.pack_a;
-    a.nbp = L.mbp;
-    a.kbp = L.kbp;
-    a.mu = p.ws + L.mu_a;
-    a.exps = reinterpret_cast<int *>(p.ws + L.exp_a);
-    a.D = L.D;
-    b.X = B[g];
-    b.comp_stride = (int64_t)ldb[g] * L.n;
-    b.sv = ldb[g];
-    b.sp = 1;
-    b.nvec = L.n;
-    b.len = L.k;
-    b.orient = 1;
-    b.packed = p.ws + L.pack_b;
-    b.nbp = L.nbp;
-    b.kbp = L.kbp;
-    b.mu = p.ws + L.mu_b;
-    b.exps = reinterpret_cast<int *>(p.ws + L.exp_b);
-    b.D = L.D;
-    ops[2 * slot] = a;
-    ops[2 * slot + 1] = b;
-    Int8GemmDesc d{};
-    d.Apk = reinterpret_cast<const int8_t *>(p.ws + L.pack_a);
-    d.Bpk = reinterpret_cast<const int8_t *>(p.ws + L.pack_b);
-    d.EA = reinterpret_cast<const int *>(p.ws + L.exp_a);
-    d.EB = reinterpret_cast<const int *>(p.ws + L.exp_b);
-    d.S = reinterpret_cast<int32_t *>(p.ws + L.sums);
-    d.mbp = L.mbp;
-    d.nbp = L.nbp;
-    d.kbp = L.kbp;
-    d.plane = L.mbp * L.nbp * 1024;
-    d.kbc = L.kbc;
-    d.nchunks = L.nchunks;
-    d.groups = L.groups;
-    d.D = L.D;
-    d.m = L.m;
-    d.n = L.n;
-    d.ldc = ldc[g];
-    d.C = Cm[g];
-    d.c_stride = (int64_t)ldc[g] * L.n;
-    descs[slot] = d;
-  }
 }
 
 template <typename T, int C>
@@ -704,7 +745,10 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
   if (hipEventSynchronize(plan->stage_done) != hipSuccess) return MPGEMM_ERR_HIP;
   if constexpr (sizeof(T) == 8) {
     if (mode == MPGEMM_MODE_INT8)
-      write_descriptors_int8(*plan, A, lda, B, ldb, Cm, ldc);
+      plan->res.write<T>(plan->ws, static_cast<ResidueOperand<T> *>(plan->stage),
+                         reinterpret_cast<ResidueDesc *>(static_cast<char *>(plan->stage) +
+                                                         plan->res.ops_bytes(sizeof(ResidueOperand<T>))),
+                         A, lda, B, ldb, Cm, ldc);
     else
       write_descriptors<T, C>(*plan, A, lda, B, ldb, Cm, ldc);
   } else {

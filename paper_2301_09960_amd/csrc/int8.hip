@@ -16,8 +16,11 @@
 // k per step) move global -> LDS by direct loads into a ring of 2 to 4
 // stages, as in the floating-point kernel.  After the last pair of a diagonal
 // the 32-bit tile is written to the S_g plane in a blocked layout (16-byte
-// stores per lane).  k_gemm_int8_batched runs the same tiles as items of a
-// persistent launch over many products.
+// stores per lane).
+//
+// The DD, TD and QD products take the residues of residue.hip instead (32
+// INT8 products for 136 digit pairs at DD, k = 4096); this kernel forms the
+// longer expansions and the diagonal sums that mpgemm_debug_products returns.
 //
 // k_int8_combine: per element, C = sum_g S_g 2^(E_i + F_j + 2 - 7 (g + 1)):
 // runs of consecutive diagonals summed exactly in 64-bit integers, each run
@@ -26,6 +29,7 @@
 // sums per element per chunk and writes C once).
 #include <algorithm>
 
+#include "int8_tile.h"
 #include "internal.h"
 #include "layout.h"
 #include "mp_device.h"
@@ -33,284 +37,41 @@
 namespace mp {
 namespace {
 
-constexpr int kGroupM = 8;
-
-typedef int i4v __attribute__((ext_vector_type(4)));
-typedef int i16v __attribute__((ext_vector_type(16)));
-typedef unsigned int u4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ void tile_coords(int bid, int nblocks, int tiles_m, int tiles_n, int &tm, int &tn) {
-  const int q = nblocks / 8, r = nblocks % 8;
-  const int xcd = bid % 8, local = bid / 8;
-  const int L = xcd * q + (xcd < r ? xcd : r) + local;
-  const int per_group = kGroupM * tiles_n;
-  const int group = L / per_group;
-  const int first_m = group * kGroupM;
-  const int gsize = (tiles_m - first_m) < kGroupM ? (tiles_m - first_m) : kGroupM;
-  const int in_group = L % per_group;
-  tm = first_m + in_group % gsize;
-  tn = in_group / gsize;
-}
-
-__device__ __forceinline__ void load_lds16(const void *src, void *lds_dst) {
-  __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds_dst, 16, 0, 0);
-}
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
-// Waits until this wavefront's loads of the step about to be computed have
-// landed: with an NS-stage ring, min(NS - 2, later) later steps (kL loads
-// each) may stay in flight.
-template <int NS, int kL>
-__device__ __forceinline__ void wait_step(int64_t later) {
-  static_assert(NS >= 2 && NS <= 4, "wait chain covers rings of 2 to 4 stages");
-  if constexpr (NS >= 4) {
-    if (later >= 2)
-      wait_vm<2 * kL>();
-    else if (later == 1)
-      wait_vm<kL>();
-    else
-      wait_vm<0>();
-  } else if constexpr (NS == 3) {
-    if (later >= 1)
-      wait_vm<kL>();
-    else
-      wait_vm<0>();
-  } else {
-    wait_vm<0>();
+// Work of one tile: the diagonals g0 .. g1 - 1 of the digit planes, each
+// written as an exact 32-bit partial sum (blocked layout, below).
+struct SumsWork {
+  int g0, g1;
+  int32_t *S;
+  int64_t plane, mbp;
+  int chunk, nchunks;
+  __device__ int pairs() const { return (g1 - 1) * g1 / 2 - (g0 - 1) * g0 / 2; }
+  __device__ void first(PairCursor &c) const { c = {0, g0, 1}; }
+  __device__ void next(PairCursor &c) const {
+    if (++c.s > c.g) {
+      ++c.g;
+      c.s = 1;
+    }
   }
-}
-
-// Tile configurations (in 32 x 32 blocks): TB x TB tile of C, WM x WN
-// wavefronts, KSB 32-wide k blocks per pipeline step, NS LDS stages.
-//   config 1: 128 x 128 tile, 4 wavefronts of 64 x 64 (small products), k
-//             steps of 128 in a 2-stage ring (two workgroups per CU), each
-//             step's loads over its first half
-//   config 2: 256 x 256 tile, 4 wavefronts of 128 x 128 (accumulators in AGPRs;
-//             LDS traffic per instruction halved)
-//   config 4: 256 x 256 tile, 16 wavefronts of 64 x 64 (more wavefronts to
-//             hide latency, more LDS reads per instruction), k steps of 128
-//   config 3: 256 x 256 tile, 8 wavefronts of 128 x 64, k steps of 128 in a
-//             2-stage ring (half the barriers of 64-wide steps, and 64 KiB
-//             requested per step)
-// KSB is 1 or 2 times kKStepBlocks8, the k padding unit of the INT8 slices (64
-// k): with 4-block steps a pair's last step in a k chunk may hold 2 blocks.
-template <int CFG> struct Int8Cfg;
-template <> struct Int8Cfg<1> { static constexpr int TB = 4, WM = 2, WN = 2, KSB = 4, NS = 2, SPACING = 1; };
-template <> struct Int8Cfg<2> { static constexpr int TB = 8, WM = 2, WN = 2, KSB = 2, NS = 4, SPACING = 0; };
-template <> struct Int8Cfg<3> { static constexpr int TB = 8, WM = 2, WN = 4, KSB = 4, NS = 2, SPACING = 3; };
-template <> struct Int8Cfg<4> { static constexpr int TB = 8, WM = 4, WN = 4, KSB = 4, NS = 2, SPACING = 0; };
-
-// Matrix-core instructions between two loads of the next step: spread over the
-// whole step by default, fewer where a configuration issues its loads earlier.
-template <typename G>
-constexpr int load_spacing(int even) {
-  return G::SPACING > 0 ? G::SPACING : even;
-}
-
-template <int CFG>
-constexpr int int8_stage_bytes() {
-  return 2 * Int8Cfg<CFG>::TB * Int8Cfg<CFG>::KSB * 1024;  // A panel, then B panel
-}
-
-// Diagonal sums S_g of one tile (tm, tn) and k chunk, as in the file comment:
-// operand panels (TB blocks x KSB k blocks of A_s and of B_t) move
-// global -> LDS by direct loads into a ring of NS stages, NS - 1 steps ahead;
-// each step waits for its own loads and passes one barrier.
-//
-// Each wavefront moves kL 1 KiB pieces of one operand per step.  Their global
-// offsets from the step's panel base and their LDS offsets are fixed for the
-// whole tile, so a load costs one 64-bit add; and the loads of the next step
-// are spread between this step's matrix-core instructions (one per kEvery),
-// which keeps the matrix cores fed where a burst of LDS-direct loads would
-// stall them.  The 256 x 256 configuration with its 2-stage ring issues them
-// over the first three quarters of the step (one per 3 instructions instead of
-// one per 4), so that the last ones land before the step ends.
-template <int CFG>
-__device__ __forceinline__ void gemm_int8_tile(const int8_t *__restrict__ Apk, const int8_t *__restrict__ Bpk,
-                                               int64_t mbp, int64_t nbp, int64_t kbp, int64_t kb0, int nks, int last,
-                                               int D, int m, int n, int32_t *__restrict__ S, int64_t plane, int chunk,
-                                               int nchunks, int tm, int tn, int g0, int g1, int8_t *lds) {
-  using G = Int8Cfg<CFG>;
-  constexpr int TB = G::TB, WM = G::WM, WN = G::WN, KSB = G::KSB, NS = G::NS;
-  constexpr int BI = TB / WM, BJ = TB / WN;
-  constexpr int NW = WM * WN;
-  constexpr int kPanel = TB * KSB * 1024;
-  constexpr int kInst = 2 * TB * KSB;  // 1 KiB wavefront instructions per step
-  constexpr int kL = kInst / NW;
-  constexpr int kMma = KSB * BI * BJ;  // matrix-core instructions per wavefront per step
-  constexpr int kEvery = load_spacing<G>(kMma / kL);
-  static_assert(kInst % NW == 0, "staging split");
-  static_assert((TB * KSB) % kL == 0, "a wavefront's loads of a step come from one operand");
-  static_assert(kMma % kL == 0, "one load per fixed number of matrix-core instructions");
-  static_assert(kEvery * kL <= kMma, "every load of the next step is issued within this step");
-  // a pair's k blocks in the chunk are a multiple of kKStepBlocks8: its steps
-  // are full but the last, which holds `last` blocks (KSB / 2 or KSB)
-  static_assert(KSB % kKStepBlocks8 == 0 && KSB <= 2 * kKStepBlocks8, "k steps and the k padding unit");
-
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-  // wavefront -> (wm, wn).  With 2 x 4 wavefronts (two per SIMD: w and w + 4)
-  // the two of a SIMD differ in both wm and wn, so that a tile padded in m or
-  // in n leaves each SIMD a wavefront with work.
-  int wm, wn;
-  if constexpr (WM == 2 && WN == 4) {
-    const int sw = wave & 3, hw = wave >> 2;
-    wm = (sw & 1) ^ hw;
-    wn = (sw >> 1) + 2 * hw;
-  } else {
-    wm = wave % WM;
-    wn = wave / WM;
-  }
-  // diagonals g0 .. g1 - 1 (g pairs each)
-  const int64_t total = ((int64_t)(g1 - 1) * g1 / 2 - (int64_t)(g0 - 1) * g0 / 2) * nks;
-
-  // this wavefront's share of a step: operand op_w, pieces j = 0..kL-1
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int op_w = (wave_u * kL) / (TB * KSB);
-  uint32_t goff[kL];  // byte offset from the step's panel base (per lane; k <= 2^20 keeps it below 2^32)
-  int loff[kL];       // byte offset in the stage (uniform)
-  uint32_t beyond[kL];  // in a pair's short last step the piece lies past the pair's k: load piece kb - KSB / 2
+  __device__ int a_plane(const PairCursor &c) const { return c.s - 1; }
+  __device__ int b_plane(const PairCursor &c) const { return c.g - c.s; }
+  __device__ bool diagonal_ends(const PairCursor &c) const { return c.s == c.g; }
+  template <int BI, int BJ>
+  __device__ __forceinline__ void finish(const PairCursor &c, i16v (&acc)[BJ][BI], int64_t bi0, int64_t bj0,
+                                         int lane) const {
+    int32_t *out = S + ((int64_t)(c.g - 1) * nchunks + chunk) * plane;
 #pragma unroll
-  for (int j = 0; j < kL; ++j) {
-    const int r = (wave_u * kL + j) % (TB * KSB);
-    const int blk = r / KSB, kb = r % KSB;
-    goff[j] = (uint32_t)(((int64_t)blk * kbp + kb) * 1024) + 16u * (uint32_t)lane;
-    loff[j] = op_w * kPanel + (blk * KSB + kb) * 1024;
-    beyond[j] = kb >= KSB / 2 ? (uint32_t)(KSB / 2) * 1024u : 0u;
-  }
-  // every step loads kL pieces (the wait counts assume it): a pair's short
-  // last step re-loads pieces of its own range into stage slots that no
-  // matrix-core instruction reads
-  auto piece = [&](int j, int ks) -> uint32_t { return goff[j] - (ks == nks - 1 && last < KSB ? beyond[j] : 0u); };
-
-  int lg = g0, ls = 1, lks = 0;  // load cursor: diagonal, pair within it, k step
-  int64_t issued = 0;
-  // panel base of the step at the load cursor (A_ls or B_(lg+1-ls)), and its ring slot
-  auto panel_base = [&]() -> const int8_t * {
-    return op_w == 0 ? Apk + (((int64_t)(ls - 1) * mbp + (int64_t)tm * TB) * kbp + kb0 + (int64_t)lks * KSB) * 1024
-                     : Bpk + (((int64_t)(lg - ls) * nbp + (int64_t)tn * TB) * kbp + kb0 + (int64_t)lks * KSB) * 1024;
-  };
-  auto advance = [&]() {
-    ++issued;
-    if (++lks == nks) {
-      lks = 0;
-      if (++ls > lg) {
-        ++lg;
-        ls = 1;
+    for (int y = 0; y < BJ; ++y)
+#pragma unroll
+      for (int x = 0; x < BI; ++x) {
+        i4v *dst = reinterpret_cast<i4v *>(out + (((bj0 + y) * mbp + bi0 + x) * 64 + lane) * 16);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) dst[v] = i4v{acc[y][x][4 * v], acc[y][x][4 * v + 1], acc[y][x][4 * v + 2],
+                                                 acc[y][x][4 * v + 3]};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[y][x][r] = 0;
       }
-    }
-  };
-
-  i16v acc[BJ][BI];
-#pragma unroll
-  for (int y = 0; y < BJ; ++y)
-#pragma unroll
-    for (int x = 0; x < BI; ++x)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[y][x][r] = 0;
-
-  wait_vm<0>();
-#pragma unroll
-  for (int s0 = 0; s0 < NS - 1; ++s0)
-    if (issued < total) {
-      const int8_t *src = panel_base();
-      int8_t *dst = lds + (issued % NS) * int8_stage_bytes<CFG>();
-#pragma unroll
-      for (int j = 0; j < kL; ++j) load_lds16(src + piece(j, lks), dst + loff[j]);
-      advance();
-    }
-
-  // A wavefront whose blocks are all padding (rows from m or columns from n
-  // on) has no matrix-core work: it only moves its share of the panels, at the
-  // places and about the pace (64 cycles per two instructions) of the others,
-  // and passes the same barriers.  It leaves its blocks of the S_g planes
-  // unwritten; the combine reads no element outside m x n.
-  if (__builtin_amdgcn_readfirstlane(((int64_t)tm * TB + wm * BI) * 32 >= m || ((int64_t)tn * TB + wn * BJ) * 32 >= n
-                                         ? 1
-                                         : 0)) {
-    for (int64_t step = 0; step < total; ++step) {
-      wait_step<NS, kL>(total - 1 - step);
-      __builtin_amdgcn_s_barrier();
-      const bool more = issued < total;
-      const int8_t *nsrc = more ? panel_base() : Apk;
-      int8_t *ndst = lds + (issued % NS) * int8_stage_bytes<CFG>();
-      const uint32_t next_short = lks == nks - 1 && last < KSB ? 1u : 0u;
-#pragma unroll
-      for (int mma = 0; mma < kMma; ++mma) {
-        if (mma % kEvery == 0 && mma / kEvery < kL && more)
-          load_lds16(nsrc + (goff[mma / kEvery] - next_short * beyond[mma / kEvery]), ndst + loff[mma / kEvery]);
-        if (mma % 2 == 1) __builtin_amdgcn_s_sleep(1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (more) advance();
-    }
-    __builtin_amdgcn_s_barrier();
-    return;
   }
-
-  int cg = g0, cs = 1, cks = 0;  // compute cursor
-  for (int64_t step = 0; step < total; ++step) {
-    wait_step<NS, kL>(total - 1 - step);
-    __builtin_amdgcn_s_barrier();
-    // the step NS - 1 ahead goes into the slot computed in the previous step
-    const bool more = issued < total;
-    const int8_t *nsrc = more ? panel_base() : Apk;
-    int8_t *ndst = lds + (issued % NS) * int8_stage_bytes<CFG>();
-
-    const int8_t *stage = lds + (step % NS) * int8_stage_bytes<CFG>();
-    // a pair's short last step holds the first KSB / 2 k blocks (the only
-    // short length): its second half is skipped, on a uniform branch
-    const bool short_step = cks == nks - 1 && last < KSB;
-    const uint32_t next_short = lks == nks - 1 && last < KSB ? 1u : 0u;  // the step being loaded is short
-#pragma unroll
-    for (int kb = 0; kb < KSB; ++kb) {
-      const bool run = kb < KSB / 2 || !short_step;
-      i4v fa[BI], fb[BJ];
-      if (run) {
-#pragma unroll
-        for (int x = 0; x < BI; ++x)
-          fa[x] = *reinterpret_cast<const i4v *>(stage + ((wm * BI + x) * KSB + kb) * 1024 + 16 * lane);
-#pragma unroll
-        for (int y = 0; y < BJ; ++y)
-          fb[y] = *reinterpret_cast<const i4v *>(stage + kPanel + ((wn * BJ + y) * KSB + kb) * 1024 + 16 * lane);
-      }
-#pragma unroll
-      for (int y = 0; y < BJ; ++y)
-#pragma unroll
-        for (int x = 0; x < BI; ++x) {
-          const int mma = (kb * BJ + y) * BI + x;
-          if (mma % kEvery == 0 && mma / kEvery < kL && more)
-            load_lds16(nsrc + (goff[mma / kEvery] - next_short * beyond[mma / kEvery]), ndst + loff[mma / kEvery]);
-          if (run) acc[y][x] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fb[y], fa[x], acc[y][x], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);  // keep the loads where they were placed
-        }
-    }
-    if (more) advance();
-    if (++cks == nks) {
-      cks = 0;
-      if (++cs > cg) {  // diagonal cg complete: write its exact partial sum (blocked layout)
-        int32_t *out = S + ((int64_t)(cg - 1) * nchunks + chunk) * plane;
-#pragma unroll
-        for (int y = 0; y < BJ; ++y)
-#pragma unroll
-          for (int x = 0; x < BI; ++x) {
-            const int64_t bi = (int64_t)tm * TB + wm * BI + x, bj = (int64_t)tn * TB + wn * BJ + y;
-            i4v *dst = reinterpret_cast<i4v *>(out + ((bj * mbp + bi) * 64 + lane) * 16);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) dst[v] = i4v{acc[y][x][4 * v], acc[y][x][4 * v + 1], acc[y][x][4 * v + 2],
-                                                     acc[y][x][4 * v + 3]};
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[y][x][r] = 0;
-          }
-        ++cg;
-        cs = 1;
-      }
-    }
-  }
-  __builtin_amdgcn_s_barrier();
-}
+};
 
 // Diagonals [g0, g1) of group z of `groups`: the D (D + 1) / 2 pairs cut into
 // nearly equal parts at diagonal boundaries (a group may be empty).
@@ -335,7 +96,7 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
   __shared__ __attribute__((aligned(16))) int8_t lds[Int8Cfg<CFG>::NS * int8_stage_bytes<CFG>()];
   constexpr int TB = Int8Cfg<CFG>::TB;
   int tm, tn;
-  tile_coords(blockIdx.x, gridDim.x, (int)(mbp / TB), (int)(nbp / TB), tm, tn);
+  int8_tile_coords(blockIdx.x, gridDim.x, (int)(mbp / TB), (int)(nbp / TB), tm, tn);
   const int chunk = blockIdx.y, nchunks = gridDim.y;
   const int64_t kb0 = (int64_t)chunk * kb_chunk;
   const int64_t kb1 = kb0 + kb_chunk < kbp ? kb0 + kb_chunk : kbp;
@@ -344,8 +105,8 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
   // diagonal group blockIdx.z of gridDim.z
   int g0, g1;
   diagonal_group(D, blockIdx.z, gridDim.z, g0, g1);
-  gemm_int8_tile<CFG>(Apk, Bpk, mbp, nbp, kbp, kb0, nks, last, D, m, n, S, plane, chunk, nchunks, tm, tn, g0, g1,
-                      lds);
+  const SumsWork work{g0, g1, S, plane, mbp, chunk, nchunks};
+  gemm_int8_tile<CFG>(work, Apk, Bpk, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, lds);
 }
 
 // Diagonal-sum planes are blocked: the 32 x 32 block (bi, bj) of C holds, for
@@ -444,56 +205,6 @@ __global__ __launch_bounds__(256) void k_int8_combine(const int32_t *__restrict_
     combine_one<C>(t, S, plane, nchunks, D, run, EA, EB, mbp, m, n, Cout, ldc, c_stride, debug_g, Sdbg, lddbg);
 }
 
-// Persistent INT8 GEMM of a batch in tile configuration CFG: each workgroup
-// takes (product, tile, k chunk, diagonal group) items from a shared counter;
-// items are ordered by decreasing work.
-template <int CFG>
-__global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k_gemm_int8_batched(
-    const Int8GemmDesc *__restrict__ descs, const int4 *__restrict__ items, const int *__restrict__ bounds,
-    int *__restrict__ counters) {
-  __shared__ __attribute__((aligned(16))) int8_t lds[Int8Cfg<CFG>::NS * int8_stage_bytes<CFG>()];
-  __shared__ int next;
-  constexpr int TB = Int8Cfg<CFG>::TB;
-  for (;;) {
-    if (threadIdx.x == 0) next = take_item(counters, bounds, blockIdx.x);
-    __syncthreads();
-    const int it = next;
-    __syncthreads();
-    if (it < 0) break;
-    const int4 w = items[it];
-    const Int8GemmDesc &d = descs[w.x];
-    const int tiles_m = (int)(d.mbp / TB);
-    const int tm = w.y % tiles_m, tn = w.y / tiles_m;
-    const int chunk = w.z;
-    const int64_t kb0 = (int64_t)chunk * d.kbc;
-    const int64_t kb1 = kb0 + d.kbc < d.kbp ? kb0 + d.kbc : d.kbp;
-    constexpr int KSB = Int8Cfg<CFG>::KSB;
-    const int nks = (int)ceil_div(kb1 - kb0, KSB), last = (int)(kb1 - kb0) - (nks - 1) * KSB;
-    int g0, g1;
-    diagonal_group(d.D, w.w, d.groups, g0, g1);
-    gemm_int8_tile<CFG>(d.Apk, d.Bpk, d.mbp, d.nbp, d.kbp, kb0, nks, last, d.D, d.m, d.n, d.S, d.plane, chunk,
-                        d.nchunks, tm, tn, g0, g1, lds);
-  }
-}
-
-// Combine of a batch: workgroup b takes 32 x 32 block b - prefix[p] of product p.
-template <int C>
-__global__ __launch_bounds__(256) void k_int8_combine_batched(const Int8GemmDesc *__restrict__ descs,
-                                                              const int *__restrict__ prefix, int nprod) {
-  int lo = 0, hi = nprod - 1;  // last p with prefix[p] <= blockIdx.x
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) / 2;
-    if (prefix[mid] <= (int)blockIdx.x)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  const Int8GemmDesc &d = descs[lo];
-  const int64_t t = ((int64_t)blockIdx.x - prefix[lo]) * 256 + threadIdx.x;
-  combine_one<C>(t, d.S, d.plane, d.nchunks, d.D, combine_run(d.D, d.kbp), d.EA, d.EB, d.mbp, d.m, d.n, d.C, d.ldc,
-                 d.c_stride, 0, nullptr, 0);
-}
-
 }  // namespace
 
 // Longest k chunk (in 32-wide k blocks, a multiple of the k step) whose
@@ -560,33 +271,6 @@ hipError_t launch_gemm_int8(const void *Apk, const void *Bpk, const int *EA, con
   return hipGetLastError();
 }
 
-template <int C>
-hipError_t launch_int8_batched(const Int8GemmDesc *descs, const int4 *items, int nitems1, int nitems3,
-                               const int *bounds, int *counters, const int *prefix_blocks, int nprod, int64_t blocks,
-                               hipStream_t st) {
-  // items [0, nitems1): 128 x 128 tiles, two workgroups per CU; then the 256 x 256 ones, one per CU
-  if (nitems1 > 0) {
-    hipLaunchKernelGGL(k_gemm_int8_batched<1>, dim3(std::min(nitems1, 512)),
-                       dim3(64 * Int8Cfg<1>::WM * Int8Cfg<1>::WN), 0, st, descs, items, bounds, counters);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-  }
-  if (nitems3 > 0) {
-    hipLaunchKernelGGL(k_gemm_int8_batched<3>, dim3(std::min(nitems3, 256)),
-                       dim3(64 * Int8Cfg<3>::WM * Int8Cfg<3>::WN), 0, st, descs, items + nitems1, bounds + kXcds + 1,
-                       counters + kXcds);
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess) return err;
-  }
-  if (blocks > 0) {
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_int8_combine_batched<C>), dim3((unsigned)blocks), dim3(256), 0, st, descs, prefix_blocks,
-                       nprod);
-    return hipGetLastError();
-  }
-  return hipSuccess;
-}
-
 #define MP_INT8_INST(C)                                                                                     \
   template hipError_t launch_gemm_int8<C>(const void *, const void *, const int *, const int *, int32_t *, int64_t, \
                                           int64_t, int64_t, int, int, int, double *, int, int64_t, int, int64_t *, \
@@ -604,12 +288,6 @@ MP_INT8_INST(11)
 MP_INT8_INST(12)
 MP_INT8_INST(13)
 MP_INT8_INST(14)
-template hipError_t launch_int8_batched<2>(const Int8GemmDesc *, const int4 *, int, int, const int *, int *,
-                                           const int *, int, int64_t, hipStream_t);
-template hipError_t launch_int8_batched<3>(const Int8GemmDesc *, const int4 *, int, int, const int *, int *,
-                                           const int *, int, int64_t, hipStream_t);
-template hipError_t launch_int8_batched<4>(const Int8GemmDesc *, const int4 *, int, int, const int *, int *,
-                                           const int *, int, int64_t, hipStream_t);
 #undef MP_INT8_INST
 
 }  // namespace mp

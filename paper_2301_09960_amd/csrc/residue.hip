@@ -1,0 +1,1057 @@
+// Products of exact integers by residues modulo pairwise coprime bases
+// (residue.h): split into residue planes, one INT8 matrix product per plane,
+// and the Chinese remainder combination into the components of C.
+//
+// k_residue_split: one workgroup per 32 x 32 block of an operand and range of
+// bases.  The element's integer W is formed in 32-bit words (window.h), rounded
+// to nearest on 32 guard bits, and its residue modulo s is the dot product of
+// its bytes with the residues of 256^j (v_dot4_u32_u8, four bytes each),
+// reduced by one binary32 quotient.  Each plane of the block is written by one
+// coalesced 4-byte store per thread.
+//
+// k_gemm_residue: gemm_int8_tile over the units of a plan.  A unit's exact sum
+// is reduced modulo its base in registers and leaves as one byte per entry (the
+// digit GEMM writes four): 7 vector instructions per entry after
+// k / 32 matrix-core instructions per 32 x 32 block.
+//
+// k_residue_combine: V = sum_p t_p w_p over the planes in base-256 digits
+// (v_dot4_i32_i8: four planes at once), carried into words, then X = V - q M
+// with q = rint(V / M) in binary64, and the leading words of X as binary64
+// chunks renormalized into the components.
+//
+// Measured at n = 4096, E = 16 (before: the digit pairs of int8.hip): DD 32
+// products, 8.43 -> 3.00 ms (GEMM 8.14 -> 2.09 ms, 2.10 POP/s); QD 73 products,
+// 28.2 -> 6.86 ms (GEMM 27.1 -> 4.64 ms).  256 DD products of 64 to 1024 as one
+// batch: 4.68 -> 4.02 ms.
+#include "residue.h"
+
+#include <algorithm>
+#include <cmath>
+#include <cstddef>
+#include <map>
+#include <mutex>
+#include <tuple>
+
+#include "int8_tile.h"
+#include "mp_device.h"
+#include "window.h"
+
+namespace mp {
+namespace {
+
+constexpr int kThreads = 256;
+
+// ---------------------------------------------------------------------------
+// Constants of the bases.
+// ---------------------------------------------------------------------------
+struct Bases {
+  int s[kNumBases];
+};
+constexpr Bases make_bases() {
+  Bases b{};
+  int n = 0;
+  for (int c = 256; c > 1 && n < kNumBases; --c) {
+    bool ok = true;
+    for (int i = 0; i < n && ok; ++i) {
+      int x = b.s[i], y = c;
+      while (y) {
+        const int t = x % y;
+        x = y;
+        y = t;
+      }
+      ok = x == 1;
+    }
+    if (ok) b.s[n++] = c;
+  }
+  return b;
+}
+constexpr Bases kHostBases = make_bases();
+static_assert(kHostBases.s[0] == 256 && kHostBases.s[kNumBases - 1] == 29, "the greedy coprime sequence");
+
+struct BaseInfo {
+  int s;
+  int c16;        // 2^16 mod s, balanced
+  float inv;      // 1 / s
+  uint32_t sinv;  // odd s: s^-1 mod 2^32
+};
+struct BaseTables {
+  BaseInfo info[kNumBases];
+  // residues of 256^(4 w + b) modulo s (byte b of word w), and modulo s^2 in two bytes
+  uint32_t pow[kNumBases][kMaxWindowWords];
+  uint32_t pow2lo[kNumBases][kMaxWindowWords], pow2hi[kNumBases][kMaxWindowWords];
+  // the offset 2^(32 NW - 1) that makes W unsigned, taken off again: modulo s and s^2
+  uint32_t init[kMaxWindowWords + 1][kNumBases], init2[kMaxWindowWords + 1][kNumBases];
+};
+constexpr BaseTables make_tables() {
+  BaseTables t{};
+  for (int u = 0; u < kNumBases; ++u) {
+    const int s = kHostBases.s[u], s2 = s * s;
+    int c16 = 65536 % s;
+    if (2 * c16 > s) c16 -= s;
+    uint32_t inv = 1;
+    if (s % 2)
+      for (int i = 0; i < 5; ++i) inv *= 2u - (uint32_t)s * inv;  // Newton: s inv = 1 mod 2^32
+    t.info[u] = {s, c16, 1.0f / (float)s, inv};
+    int64_t p = 1, p2 = 1;  // 256^j
+    for (int w = 0; w < kMaxWindowWords; ++w)
+      for (int b = 0; b < 4; ++b) {
+        t.pow[u][w] |= (uint32_t)(p % s) << (8 * b);
+        t.pow2lo[u][w] |= (uint32_t)(p2 % s2 & 255) << (8 * b);
+        t.pow2hi[u][w] |= (uint32_t)(p2 % s2 >> 8) << (8 * b);
+        p = p * 256 % s;
+        p2 = p2 * 256 % s2;
+      }
+    int64_t h = 1, h2 = 1;  // 2^e
+    for (int e = 1; e <= 32 * kMaxWindowWords; ++e) {
+      if (e % 32 == 0) {  // h = 2^(e - 1)
+        t.init[e / 32][u] = (uint32_t)(s - h);
+        t.init2[e / 32][u] = (uint32_t)(s2 - h2);
+      }
+      h = h * 2 % s;
+      h2 = h2 * 2 % s2;
+    }
+  }
+  return t;
+}
+__constant__ BaseTables kBase = make_tables();
+
+__host__ __device__ inline int plane_of(int u, int nsq) { return u < nsq ? 2 * u : nsq + u; }
+
+// Low byte of the balanced residue of r modulo the base (|r| < 2^22.2; for
+// s = 256 the low byte of r).  q = rint(r / s) comes out of the low bits of
+// r / s + 1.5 2^23: the quotient's error, below |r| 2^-24 / s < 0.3 / s, is less
+// than the distance 1 / (2 s) of r / s from a half, so q is exact for odd s.
+// The bits hold q + 2^22 in 24 bits, and 2^22 s is a multiple of 256.
+__device__ __forceinline__ uint32_t residue_byte(int r, const BaseInfo &b) {
+  const int qb = __float_as_int(__builtin_fmaf((float)r, b.inv, 12582912.0f));
+  return (uint32_t)(__mul24(qb, -b.s) + r);
+}
+// r = v mod s with |r| < 2^22.2, for |v| < 2^31.
+__device__ __forceinline__ int fold16(int v, const BaseInfo &b) {
+  return __mul24(v >> 16, b.c16) + (v & 0xffff);
+}
+// The low bytes of a, b, c, d in one word.
+__device__ __forceinline__ uint32_t pack4(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
+  const uint32_t lo = __builtin_amdgcn_perm(b, a, 0x0c0c0400u), hi = __builtin_amdgcn_perm(d, c, 0x0c0c0400u);
+  return __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+}
+// (v - t) / s for t = v mod s in the low byte of `byte` (balanced): exact.
+__device__ __forceinline__ int divide_out(int v, uint32_t byte, const BaseInfo &b) {
+  const int d = v - (int)(int8_t)byte;
+  return b.s == 256 ? d >> 8 : (int)((uint32_t)d * b.sinv);
+}
+
+// ---------------------------------------------------------------------------
+// Split.
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ void parts_of(double x, int64_t &M, int &q) { binary64_parts(x, M, q); }
+__device__ __forceinline__ void parts_of(float x, int64_t &M, int &q) {
+  const uint32_t b = __float_as_uint(x);
+  const int ef = (int)((b >> 23) & 0xff);
+  const int64_t f = (int64_t)(b & 0x7fffffu);
+  const int64_t m = ef == 0 ? f : (f | (int64_t(1) << 23));
+  q = ef == 0 ? -149 : ef - 150;
+  M = (b >> 31) ? -m : m;
+}
+
+// The exponent of a vector with maximum bits mu.
+template <typename T>
+__device__ __forceinline__ int vector_exponent(typename bits_of<T>::type mu, int float_form) {
+  using U = typename bits_of<T>::type;
+  if (mu == 0) return kZeroExp;
+  if (mu >= (sizeof(T) == 8 ? (U)0x7ff0000000000000ULL : (U)0x7f800000u)) return kNonFinite;
+  const T x = from_bits(mu, T(0));
+  if (float_form) return ceil_log2(x);
+  int ex;
+  if constexpr (sizeof(T) == 8)
+    (void)frexp(x, &ex);
+  else
+    (void)frexpf(x, &ex);
+  return ex;
+}
+
+// One block: bases [u0, u1) into planes counted from base u_first's.  The
+// FLOAT form's checks (below) run with `check`.
+//
+// The FLOAT form stands for D passes of Algorithm 1, whose grid follows the
+// largest residual of the vector: pass a + 1 starts at the residual's exponent,
+// at most b + 2 bits below pass a's wherever some element's residual is at
+// least a quarter of pass a's grid.  With bits = D (b + 2) - 2 the fixed grid
+// here is then no coarser than the last slice's.  An element has such a
+// residual under a grid at bit g if its bits g - 1 and g - 2 differ; so a
+// vector is safe if every element is exact on the fixed grid, or if its first
+// 32 elements between them have such a change of bits at every place
+// (random mantissas do).  A vector that is neither, or that holds lower
+// components as large as leading ones, sets the flag: the product is then
+// formed from the slices.
+template <typename T, int C, int NW, int ORIENT>
+__device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u0, int u1,
+                              bool check) {
+  using U = typename bits_of<T>::type;
+  const int64_t nb = live_only ? ceil_div((int64_t)op.nvec, (int64_t)kBlk8) : op.nbp;
+  const int64_t kbn = live_only ? ceil_div((int64_t)op.len, (int64_t)kKBlk8) : op.kbp;
+  // A (rows, contiguous along the row index): walk row blocks fastest;
+  // B (columns, contiguous along k): walk k blocks fastest.
+  const int64_t vb = ORIENT == 0 ? blk % nb : blk / kbn;
+  const int64_t kb = ORIENT == 0 ? blk / nb : blk % kbn;
+  const int t = threadIdx.x, l = t >> 2;
+  const int v = (int)(vb * kBlk8) + (l & 31);
+  const int p0 = (int)(kb * kKBlk8) + 16 * (l >> 5) + 4 * (t & 3);
+
+  int E = kZeroExp;
+  if (v < op.nvec) E = vector_exponent<T>(static_cast<const U *>(op.mu)[v], op.float_form);
+  const bool finite = E != kZeroExp && E != kNonFinite;
+  const int P = finite ? E - op.bits - 32 : 0;  // place of the window's lowest bit: 32 guard bits
+  uint32_t W[4][NW];  // W + 2^(32 NW - 1)
+  bool inexact = false, odd = false;
+  uint32_t change[NW] = {};
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    uint32_t w[NW + 1];
+#pragma unroll
+    for (int i = 0; i <= NW; ++i) w[i] = 0u;
+    const bool live = finite && v < op.nvec && p0 + j < op.len;
+    const T *x = op.X + (live ? (int64_t)v * op.sv + (int64_t)(p0 + j) * op.sp : 0);
+#pragma unroll
+    for (int r = 0; r < C; ++r) {
+      const T xr = live ? x[r * op.comp_stride] : T(0);
+      int64_t M;
+      int q;
+      parts_of(xr, M, q);
+      int off = q - P;
+      if (M != 0) {
+        if (check && r > 0 && q + (sizeof(T) == 8 ? 53 : 24) > E - 20) odd = true;  // also infinities and NaN
+        if (off < 0) {
+          const int sh = off > -63 ? -off : 63;
+          if (check) inexact = inexact || (M & ((int64_t(1) << sh) - 1)) != 0;
+          M >>= sh;
+          off = 0;
+        }
+        window_add<NW + 1>(w, M, off);
+      }
+    }
+    inexact = inexact || w[0] != 0u;
+    uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits
+    uint32_t below = 0u;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      const uint64_t sum = (uint64_t)w[i + 1] + carry;
+      W[j][i] = (uint32_t)sum;
+      carry = (uint32_t)(sum >> 32);
+      change[i] |= W[j][i] ^ ((W[j][i] << 1) | below);
+      below = W[j][i] >> 31;
+    }
+    W[j][NW - 1] ^= 0x80000000u;
+  }
+
+  const int64_t plane = op.nbp * op.kbp * 1024;
+  const int first = plane_of(u_first, op.nsq);
+  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
+  auto put = [&](int pl, const uint32_t (&b)[4]) {
+    *reinterpret_cast<uint32_t *>(dst + (int64_t)(pl - first) * plane) = pack4(b[0], b[1], b[2], b[3]);
+  };
+  for (int u = u0; u < u1; ++u) {
+    const BaseInfo bi = kBase.info[u];
+    uint32_t byte[4];
+    if (u < op.nsq) {  // two s-adic digits of the residue modulo s^2
+      uint32_t next[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        uint32_t lo = kBase.init2[NW][u], hi = 0u;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+          lo = __builtin_amdgcn_udot4(W[j][i], kBase.pow2lo[u][i], lo, false);
+          hi = __builtin_amdgcn_udot4(W[j][i], kBase.pow2hi[u][i], hi, false);
+        }
+        const int r = (int)(lo + (hi << 8));  // < 2^30
+        byte[j] = residue_byte(fold16(r, bi), bi);
+        next[j] = residue_byte(fold16(divide_out(r, byte[j], bi), bi), bi);
+      }
+      put(2 * u, byte);
+      put(2 * u + 1, next);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        uint32_t r = kBase.init[NW][u];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) r = __builtin_amdgcn_udot4(W[j][i], kBase.pow[u][i], r, false);
+        byte[j] = residue_byte((int)r, bi);  // r < 36 255 255 < 2^21.2
+      }
+      put(op.nsq + u, byte);
+    }
+  }
+
+  if (p0 == 0 && v < op.nvec && u0 == u_first) op.exps[v] = E;
+  if (!check) return;
+  __shared__ uint32_t seen[kBlk8][NW];
+  __shared__ int rounded[kBlk8];
+  for (int i = t; i < kBlk8 * NW; i += kThreads) seen[i / NW][i % NW] = 0u;
+  if (t < kBlk8) rounded[t] = 0;
+  __syncthreads();
+  if (inexact) rounded[l & 31] = 1;
+  if (odd) *op.flag = 1;
+  if (kb == 0) {
+#pragma unroll
+    for (int i = 0; i < NW; ++i) atomicOr(&seen[l & 31][i], change[i]);
+  }
+  __syncthreads();
+  if (t < kBlk8) {
+    const int vt = (int)(vb * kBlk8) + t;
+    if (vt < op.nvec) {
+      int add = rounded[t];
+      if (kb == 0) {  // a change at every place 1 .. bits - guard_bits
+        bool full = true;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+          const int top = op.bits - op.guard_bits + 1 - 32 * i;  // places below `top` in this word
+          uint32_t need = top >= 32 ? 0xffffffffu : top > 0 ? (1u << top) - 1u : 0u;
+          if (i == 0) need &= ~1u;
+          full = full && (seen[t][i] & need) == need;
+        }
+        if (!full) add |= 2;
+      }
+      // bit 0: an element was rounded; bit 1: places without a change
+      if (add & ~*(volatile int *)&op.state[vt]) {
+        const int old = atomicOr(&op.state[vt], add);
+        if ((old | add) == 3) *op.flag = 1;
+      }
+    }
+  }
+}
+
+__device__ __forceinline__ int find_range(const int *prefix, int n, int b) {
+  int lo = 0, hi = n - 1;  // the last i with prefix[i] <= b
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) / 2;
+    if (prefix[mid] <= b)
+      lo = mid;
+    else
+      hi = mid - 1;
+  }
+  return lo;
+}
+
+// Workgroup (x, y): block x - prefix[i] of operand i, part y of the bases
+// [u_first, u_end) (u_end < 0: every base of the operand).
+template <typename T, int C, int NW>
+__global__ __launch_bounds__(kThreads) void k_residue_split(const ResidueOperand<T> *__restrict__ ops,
+                                                            const int *__restrict__ prefix, int nops, int live_only,
+                                                            int u_first, int u_end) {
+  const int i = __builtin_amdgcn_readfirstlane(find_range(prefix, nops, blockIdx.x));
+  const ResidueOperand<T> op = ops[i];
+  const int64_t blk = (int64_t)blockIdx.x - prefix[i];
+  const int end = u_end < 0 ? op.nunits : u_end, count = end - u_first;
+  const int u0 = u_first + count * (int)blockIdx.y / (int)gridDim.y;
+  const int u1 = u_first + count * ((int)blockIdx.y + 1) / (int)gridDim.y;
+  const bool check = op.float_form != 0 && u_first == 0 && blockIdx.y == 0;
+  if (op.orient == 0)
+    residue_block<T, C, NW, 0>(op, blk, live_only != 0, u_first, u0, u1, check);
+  else
+    residue_block<T, C, NW, 1>(op, blk, live_only != 0, u_first, u0, u1, check);
+}
+
+// ---------------------------------------------------------------------------
+// GEMM.
+// ---------------------------------------------------------------------------
+// Work of one tile: units u0 .. u1 - 1 of the plan.  Operand planes are counted
+// from unit u_first's first plane, result planes from the k chunk's first.
+// Products are at most 2^14 in magnitude: 32768 k of them twice (the two pairs of
+// a square's second diagonal) and a carry stay below 2^31, so longer k is cut into
+// chunks with result planes of their own, which the combine adds up.
+struct ResidueWork {
+  int u0, u1, u_first, nsq;
+  int8_t *R;
+  int64_t plane, mbp;
+  __device__ int pairs() const { return residue_pairs_below(u1, nsq) - residue_pairs_below(u0, nsq); }
+  __device__ void first(PairCursor &c) const { c = {u0, 1, 1}; }
+  __device__ void next(PairCursor &c) const {
+    if (++c.s > c.g) {
+      c.s = 1;
+      if (++c.g > (c.u < nsq ? 2 : 1)) {
+        c.g = 1;
+        ++c.u;
+      }
+    }
+  }
+  __device__ int at(const PairCursor &c) const { return plane_of(c.u, nsq) - plane_of(u_first, nsq); }
+  __device__ int a_plane(const PairCursor &c) const { return at(c) + c.s - 1; }
+  __device__ int b_plane(const PairCursor &c) const { return at(c) + c.g - c.s; }
+  __device__ bool diagonal_ends(const PairCursor &c) const { return c.s == c.g; }
+  template <int BI, int BJ>
+  __device__ __forceinline__ void finish(const PairCursor &c, i16v (&acc)[BJ][BI], int64_t bi0, int64_t bj0,
+                                         int lane) const {
+    const BaseInfo b = kBase.info[c.u];
+    int8_t *out = R + (int64_t)(plane_of(c.u, nsq) + c.g - 1) * plane;
+#pragma unroll
+    for (int y = 0; y < BJ; ++y)
+#pragma unroll
+      for (int x = 0; x < BI; ++x) {
+        i4v o;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          uint32_t t[4];
+#pragma unroll
+          for (int r = 0; r < 4; ++r) t[r] = residue_byte(fold16(acc[y][x][4 * v + r], b), b);
+          o[v] = (int)pack4(t[0], t[1], t[2], t[3]);
+          __builtin_amdgcn_sched_barrier(0);  // a few entries at a time: the accumulators leave few registers
+        }
+        *reinterpret_cast<i4v *>(out + (((bj0 + y) * mbp + bi0 + x) * 64 + lane) * 16) = o;
+      }
+    if (c.u < nsq && c.g == 1) {
+#pragma unroll
+      for (int y = 0; y < BJ; ++y)
+#pragma unroll
+        for (int x = 0; x < BI; ++x)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            int v = acc[y][x][r];
+            asm volatile("" : "+v"(v));  // the byte is formed again rather than kept from above
+            acc[y][x][r] = divide_out(v, residue_byte(fold16(v, b), b), b);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+    } else {
+#pragma unroll
+      for (int y = 0; y < BJ; ++y)
+#pragma unroll
+        for (int x = 0; x < BI; ++x)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[y][x][r] = 0;
+    }
+  }
+};
+
+template <int CFG>
+__global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k_gemm_residue(
+    const int8_t *__restrict__ A, const int8_t *__restrict__ B, int64_t mbp, int64_t nbp, int64_t kbp, int u_first,
+    int u_end, int nsq, int nplanes, int m, int n, int8_t *__restrict__ R, int64_t plane) {
+  __shared__ __attribute__((aligned(16))) int8_t lds[Int8Cfg<CFG>::NS * int8_stage_bytes<CFG>()];
+  constexpr int TB = Int8Cfg<CFG>::TB, KSB = Int8Cfg<CFG>::KSB;
+  int tm, tn;
+  int8_tile_coords(blockIdx.x, gridDim.x, (int)(mbp / TB), (int)(nbp / TB), tm, tn);
+  const int u0 = residue_group_start(u_first, u_end, nsq, blockIdx.z, gridDim.z);
+  const int u1 = residue_group_start(u_first, u_end, nsq, blockIdx.z + 1, gridDim.z);
+  const int64_t kb0 = (int64_t)blockIdx.y * kChunkBlocks;
+  const int64_t kb1 = kb0 + kChunkBlocks < kbp ? kb0 + kChunkBlocks : kbp;
+  const int nks = (int)ceil_div(kb1 - kb0, KSB), last = (int)(kb1 - kb0) - (nks - 1) * KSB;
+  const ResidueWork work{u0, u1, u_first, nsq, R + (int64_t)blockIdx.y * nplanes * plane, plane, mbp};
+  gemm_int8_tile<CFG>(work, A, B, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, lds);
+}
+
+// Persistent GEMM of a batch in tile configuration CFG: each workgroup takes
+// (product, tile, k chunk, unit group) items from its XCD's list, then helps the
+// other lists; lists are ordered by decreasing work.
+template <int CFG>
+__global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k_gemm_residue_batched(
+    const ResidueDesc *__restrict__ descs, const int4 *__restrict__ items, const int *__restrict__ bounds,
+    int *__restrict__ counters) {
+  __shared__ __attribute__((aligned(16))) int8_t lds[Int8Cfg<CFG>::NS * int8_stage_bytes<CFG>()];
+  __shared__ int next;
+  constexpr int TB = Int8Cfg<CFG>::TB, KSB = Int8Cfg<CFG>::KSB;
+  for (;;) {
+    if (threadIdx.x == 0) next = take_item(counters, bounds, blockIdx.x);
+    __syncthreads();
+    const int it = __builtin_amdgcn_readfirstlane(next);
+    __syncthreads();
+    if (it < 0) break;
+    const int4 w = items[it];
+    const ResidueDesc &d = descs[w.x];
+    const int tiles_m = (int)(d.mbp / TB);
+    const int tm = w.y % tiles_m, tn = w.y / tiles_m;
+    const int64_t kb0 = (int64_t)w.z * kChunkBlocks;
+    const int64_t kb1 = kb0 + kChunkBlocks < d.kbp ? kb0 + kChunkBlocks : d.kbp;
+    const int nks = (int)ceil_div(kb1 - kb0, KSB), last = (int)(kb1 - kb0) - (nks - 1) * KSB;
+    const ResidueWork work{residue_group_start(0, d.nunits, d.nsq, w.w, d.groups),
+                           residue_group_start(0, d.nunits, d.nsq, w.w + 1, d.groups),
+                           0,
+                           d.nsq,
+                           d.R + (int64_t)w.z * d.nplanes * d.plane,
+                           d.plane,
+                           d.mbp};
+    gemm_int8_tile<CFG>(work, d.A, d.B, d.mbp, d.nbp, d.kbp, kb0, nks, last, d.m, d.n, tm, tn, lds);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Combine.
+// ---------------------------------------------------------------------------
+typedef const __attribute__((address_space(4))) uint32_t *const_words;  // scalar loads
+
+// Entries per thread: their digit sums (4 NWC words each) share the registers.
+template <int NWC>
+constexpr int combine_entries() {
+  return NWC <= 6 ? 4 : NWC <= 14 ? 2 : 1;
+}
+// 48-bit chunks of X that enter the result, from its leading nonzero word on
+// (up to 31 leading zero bits): at least 53 c + 20 bits (TS: 24 c + 8).
+template <typename T, int C>
+constexpr int combine_chunks() {
+  return sizeof(T) == 4 ? 3 : C + 2;
+}
+
+// w up by SH words, and its place down, if its top SH words are zero.
+template <int NWC, int SH>
+__device__ __forceinline__ void raise_words(uint32_t (&w)[NWC], int &place) {
+  if constexpr (SH < NWC) {
+    uint32_t any = 0u;
+#pragma unroll
+    for (int i = NWC - SH; i < NWC; ++i) any |= w[i];
+    const bool up = any == 0u;
+#pragma unroll
+    for (int i = NWC - 1; i >= 0; --i) w[i] = up ? (i >= SH ? w[i >= SH ? i - SH : 0] : 0u) : w[i];
+    place -= up ? 32 * SH : 0;
+  }
+}
+
+template <int NWC, typename T, int C>
+__device__ __forceinline__ void combine_entry(const int (&S)[4 * NWC], const_words mod, double inv_m, int e0,
+                                              T (&out)[C]) {
+  // carry the digit sums into words
+  uint32_t w[NWC];
+  int64_t c = 0;
+#pragma unroll
+  for (int i = 0; i < NWC; ++i) {
+    c += (int64_t)S[4 * i] + ((int64_t)S[4 * i + 1] << 8) + ((int64_t)S[4 * i + 2] << 16) +
+         ((int64_t)S[4 * i + 3] << 24);
+    w[i] = (uint32_t)c;
+    c >>= 32;
+  }
+  // X = V - q M: |X| < 0.48 M and |V| < 2^18 M, so q is rounded safely
+  double v = (double)(int32_t)w[NWC - 1];
+#pragma unroll
+  for (int i = NWC - 2; i >= 0; --i) v = __builtin_fma(v, 4294967296.0, (double)w[i]);
+  const int64_t q = (int64_t)(int)rint(v * inv_m);
+  c = 0;
+#pragma unroll
+  for (int i = 0; i < NWC; ++i) {
+    c += (int64_t)(uint64_t)w[i] - q * (int64_t)(uint64_t)mod[i];
+    w[i] = (uint32_t)c;
+    c >>= 32;
+  }
+  // magnitude and sign
+  const uint32_t neg = (uint32_t)((int32_t)w[NWC - 1] >> 31);
+  uint32_t up = neg & 1u;
+#pragma unroll
+  for (int i = 0; i < NWC; ++i) {
+    const uint64_t s = (uint64_t)(w[i] ^ neg) + up;
+    w[i] = (uint32_t)s;
+    up = (uint32_t)(s >> 32);
+  }
+  // the leading nonzero word to the top
+  int ex = 32 * NWC - 48;  // place of the first chunk's lowest bit
+  raise_words<NWC, 16>(w, ex);
+  raise_words<NWC, 8>(w, ex);
+  raise_words<NWC, 4>(w, ex);
+  raise_words<NWC, 2>(w, ex);
+  raise_words<NWC, 1>(w, ex);
+  constexpr int K = combine_chunks<T, C>();
+  double d[K];
+#pragma unroll
+  for (int j = 0; j < K; ++j) {
+    auto word = [&](int i) -> uint32_t { return i < NWC ? w[NWC - 1 - i] : 0u; };
+    const int i = 3 * (j / 2);
+    const uint32_t hi = j % 2 == 0 ? word(i) >> 16 : word(i + 1) & 0xffffu;
+    const uint32_t lo = j % 2 == 0 ? (word(i) << 16) | (word(i + 1) >> 16) : word(i + 2);
+    const double x = __builtin_fma((double)hi, 4294967296.0, (double)lo);
+    d[j] = (neg ? -x : x) * __builtin_ldexp(1.0, -48 * j);
+  }
+  renorm<double, K>(d);
+  if constexpr (sizeof(T) == 8) {
+#pragma unroll
+    for (int r = 0; r < C; ++r) out[r] = ldexp(d[r], ex + e0);
+  } else {
+    // nearest binary32 of the rest, three times (the differences are exact
+    // while the rest fits binary64; the last rest is rounded once)
+    double s = d[0], t = d[1];
+#pragma unroll
+    for (int r = 0; r < C; ++r) {
+      const float f = (float)s;
+      out[r] = ldexpf(f, ex + e0);
+      double err;
+      s = two_sum(s - (double)f, t, err);
+      t = r == 0 ? err + d[2] : err;
+    }
+  }
+}
+
+// Workgroup: 256 runs of combine_entries<NWC>() consecutive entries of one 32 x 32
+// block of C (its part, where a block takes several workgroups).  Lane and entry
+// order follow the matrix-core layout of the planes (int8.hip).
+template <typename T, int C, int NWC>
+__global__ __launch_bounds__(kThreads) void k_residue_combine(const ResidueDesc *__restrict__ descs,
+                                                              const int *__restrict__ prefix, int nprod) {
+  constexpr int N = combine_entries<NWC>();
+  constexpr int kParts = 4 / N;  // workgroups per block
+  const int b = (int)blockIdx.x / kParts, part = (int)blockIdx.x % kParts;
+  const int p = __builtin_amdgcn_readfirstlane(find_range(prefix, nprod, b));
+  const ResidueDesc d = descs[p];
+  const int64_t blk = (int64_t)b - prefix[p];
+  const int off = (part * kThreads + (int)threadIdx.x) * N;
+  const int lane = off / 16, quad = off % 16 / 4, e0 = off % 4;
+  const int64_t bi = blk % d.mbp, bj = blk / d.mbp;
+  const int i = (int)(bi * 32 + lane % 32);
+  const int j = (int)(bj * 32 + 8 * quad + 4 * (lane / 32) + e0);
+  if (i >= d.m || j >= d.n) return;
+
+  int S[N][4 * NWC];
+#pragma unroll
+  for (int e = 0; e < N; ++e)
+#pragma unroll
+    for (int y = 0; y < 4 * NWC; ++y) S[e][y] = 0;
+  const int8_t *src = d.R + blk * 1024 + off;
+  const int groups = (d.nplanes + 3) / 4;
+  const const_words tab = (const_words)d.table;
+#pragma unroll 1
+  for (int ch = 0; ch < d.nchunks; ++ch, src += d.nplanes * d.plane) {
+    auto load = [&](int pl) -> uint32_t {
+      const int8_t *at = src + (int64_t)(pl < d.nplanes ? pl : d.nplanes - 1) * d.plane;
+      if constexpr (N == 4) return *reinterpret_cast<const uint32_t *>(at);
+      if constexpr (N == 2) return *reinterpret_cast<const uint16_t *>(at);
+      return *reinterpret_cast<const uint8_t *>(at);
+    };
+    uint32_t x[4];
+#pragma unroll
+    for (int y = 0; y < 4; ++y) x[y] = load(y);
+#pragma unroll 1
+    for (int g = 0; g < groups; ++g) {
+      uint32_t nx[4];  // the next group's bytes (the last one's again at the end)
+#pragma unroll
+      for (int y = 0; y < 4; ++y) nx[y] = load(4 * g + 4 + y);
+      // the bytes of one entry in the four planes
+      uint32_t z[N];
+      const uint32_t lo = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u);
+      const uint32_t hi = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
+      z[0] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+      if constexpr (N >= 2) z[1] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+      if constexpr (N == 4) {
+        const uint32_t lo2 = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u);
+        const uint32_t hi2 = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
+        z[2] = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
+        z[3] = __builtin_amdgcn_perm(hi2, lo2, 0x07060302u);
+      }
+#pragma unroll
+      for (int y = 0; y < 4 * NWC; ++y) {
+        const int k = (int)tab[g * 4 * NWC + y];
+#pragma unroll
+        for (int e = 0; e < N; ++e) S[e][y] = __builtin_amdgcn_sdot4((int)z[e], k, S[e][y], false);
+      }
+#pragma unroll
+      for (int y = 0; y < 4; ++y) x[y] = nx[y];
+    }
+  }
+  const const_words mod = tab + groups * 4 * NWC;
+  const double inv_m = __longlong_as_double((long long)((uint64_t)mod[NWC] | ((uint64_t)mod[NWC + 1] << 32)));
+  const int Ei = d.EA[i];
+#pragma unroll
+  for (int e = 0; e < N; ++e) {
+    if (j + e >= d.n) continue;
+    const int Fj = d.EB[j + e];
+    T out[C];
+    if (Ei == kNonFinite || Fj == kNonFinite) {
+#pragma unroll
+      for (int r = 0; r < C; ++r) out[r] = (T)__builtin_nan("");
+    } else if (Ei == kZeroExp || Fj == kZeroExp) {
+#pragma unroll
+      for (int r = 0; r < C; ++r) out[r] = T(0);
+    } else {
+      combine_entry<NWC, T, C>(S[e], mod, inv_m, Ei + Fj - 2 * d.bits, out);
+    }
+    T *dst = static_cast<T *>(d.C) + i + (int64_t)(j + e) * d.ldc;
+#pragma unroll
+    for (int r = 0; r < C; ++r) dst[r * d.c_stride] = out[r];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Host data on its way to the device inside kernel arguments: no copy, so the
+// sequence can be captured and keeps no host buffer.  Also clears two regions.
+// ---------------------------------------------------------------------------
+constexpr int kUploadWords = 960;
+struct Upload {
+  uint32_t w[kUploadWords];
+};
+__global__ __launch_bounds__(kThreads) void k_upload(Upload data, int n, uint32_t *dst, uint32_t *z0, int64_t n0,
+                                                     uint32_t *z1, int64_t n1) {
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t i = t; i < n; i += step) dst[i] = data.w[i];
+  for (int64_t i = t; i < n0; i += step) z0[i] = 0u;
+  for (int64_t i = t; i < n1; i += step) z1[i] = 0u;
+}
+
+// Big integers of 32-bit words, for the tables.
+using Big = std::vector<uint32_t>;
+void big_mul(Big &x, uint32_t f) {
+  uint64_t c = 0;
+  for (auto &w : x) {
+    c += (uint64_t)w * f;
+    w = (uint32_t)c;
+    c >>= 32;
+  }
+  if (c) x.push_back((uint32_t)c);
+}
+uint32_t big_div(Big &x, uint32_t f) {  // x /= f, returns the remainder
+  uint64_t r = 0;
+  for (size_t i = x.size(); i-- > 0;) {
+    r = (r << 32) | x[i];
+    x[i] = (uint32_t)(r / f);
+    r %= f;
+  }
+  return (uint32_t)r;
+}
+double big_value(const Big &x) {
+  double v = 0.0;
+  for (size_t i = x.size(); i-- > 0;) v = v * 4294967296.0 + (double)x[i];
+  return v;
+}
+
+double log2_modulus(int nunits, int nsq) {
+  double l = 0.0;
+  for (int u = 0; u < nunits; ++u) l += (u < nsq ? 2 : 1) * std::log2((double)kHostBases.s[u]);
+  return l;
+}
+
+}  // namespace
+
+bool residue_plan(int bits, int64_t k, ResiduePlan &p) {
+  if (bits < 1 || bits > kMaxResidueBits || k < 1) return false;
+  const double need = 2.0 * bits + std::log2((double)k) + 1.07;  // M > 2.1 k 2^(2 bits)
+  p.bits = bits;
+  p.nunits = 0;
+  for (int n = 1; n <= kNumBases; ++n) {
+    double l = log2_modulus(n, 0);
+    int sq = 0;
+    while (l < need && sq < n) l += std::log2((double)kHostBases.s[sq++]);
+    if (l < need) continue;
+    if (p.nunits == 0 || n + 2 * sq < p.products()) {
+      p.nunits = n;
+      p.nsq = sq;
+    }
+  }
+  if (p.nunits == 0) return false;
+  p.nplanes = p.nunits + p.nsq;
+  p.nw = (bits + 2 + 31) / 32;
+  p.nchunks = (int)ceil_div(kblocks8_padded(k), (int64_t)kChunkBlocks);
+  // |V| <= 64 nplanes nchunks M, a sign, and a bit for the logarithms' rounding
+  const double top = log2_modulus(p.nunits, p.nsq) + 8.0 + std::log2((double)p.nplanes * p.nchunks);
+  p.nwc = 0;
+  for (int w : kCombineWords)
+    if (32.0 * w >= top && p.nwc == 0) p.nwc = w;
+  return p.nwc != 0;
+}
+
+const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
+  static std::mutex mu;
+  static std::map<std::tuple<int, int, int>, std::vector<uint32_t>> tables;
+  std::lock_guard<std::mutex> lock(mu);
+  std::vector<uint32_t> &t = tables[std::make_tuple(nunits, nsq, nwc)];
+  if (!t.empty()) return t;
+  Big M{1};
+  for (int u = 0; u < nunits; ++u)
+    for (int e = 0; e < (u < nsq ? 2 : 1); ++e) big_mul(M, (uint32_t)kHostBases.s[u]);
+  M.resize(nwc, 0u);
+  const int nplanes = nunits + nsq, groups = (nplanes + 3) / 4;
+  t.assign((size_t)groups * 4 * nwc + nwc + 2, 0u);
+  for (int u = 0; u < nunits; ++u) {
+    const uint32_t s = (uint32_t)kHostBases.s[u], mod = u < nsq ? s * s : s;
+    Big Mu = M;
+    big_div(Mu, mod);
+    Big tmp = Mu;
+    const uint32_t r = big_div(tmp, mod);
+    uint32_t inv = 1;  // (M / mod)^-1 mod mod
+    while ((uint64_t)inv * r % mod != 1) ++inv;
+    for (int g = 0; g < (u < nsq ? 2 : 1); ++g) {
+      Big w = Mu;
+      big_mul(w, g == 0 ? inv : (uint32_t)((uint64_t)inv * s % mod));
+      w.resize(nwc, 0u);
+      // w - M where that is the smaller in magnitude, two's complement
+      Big other(nwc);
+      uint64_t borrow = 0;
+      bool larger = false;  // 2 w > M
+      for (int i = 0; i < nwc; ++i) {
+        const uint64_t d = (uint64_t)w[i] - M[i] - borrow;
+        other[i] = (uint32_t)d;
+        borrow = (d >> 32) & 1;
+      }
+      for (int i = nwc - 1; i >= 0; --i) {  // compare w with M - w = -other
+        uint64_t neg = (uint64_t)(~other[i]);
+        bool low_zero = true;
+        for (int j = 0; j < i; ++j) low_zero = low_zero && other[j] == 0;
+        if (low_zero) ++neg;
+        const uint32_t mw = (uint32_t)neg;
+        if (w[i] != mw) {
+          larger = w[i] > mw;
+          break;
+        }
+      }
+      if (larger) w = other;
+      const int pl = plane_of(u, nsq) + g;
+      int carry = 0;
+      for (int j = 0; j < 4 * nwc; ++j) {
+        int digit = (int)((w[j / 4] >> (8 * (j % 4))) & 255u) + carry;
+        carry = digit >= 128 ? 1 : 0;
+        if (carry) digit -= 256;
+        t[(size_t)(pl / 4) * 4 * nwc + j] |= (uint32_t)(uint8_t)(int8_t)digit << (8 * (pl % 4));
+      }
+    }
+  }
+  for (int i = 0; i < nwc; ++i) t[(size_t)groups * 4 * nwc + i] = M[i];
+  const double inv_m = 1.0 / big_value(M);
+  uint64_t bits;
+  __builtin_memcpy(&bits, &inv_m, 8);
+  t[(size_t)groups * 4 * nwc + nwc] = (uint32_t)bits;
+  t[(size_t)groups * 4 * nwc + nwc + 1] = (uint32_t)(bits >> 32);
+  return t;
+}
+
+namespace {
+
+size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
+
+size_t header_bytes(const ResiduePlan &p) {
+  const size_t words = (size_t)((p.nplanes + 3) / 4) * 4 * p.nwc + p.nwc + 2;
+  return up256(2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 8 * 4 + words * 4);
+}
+
+struct Shape {
+  int64_t mbp, nbp, kbp, a_plane, b_plane, r_plane;
+};
+Shape shape_of(int cfg, int64_t m, int64_t n, int64_t k) {
+  const int tb = int8_tile_blocks(cfg);
+  Shape s;
+  s.mbp = nblocks8_padded(m, tb);
+  s.nbp = nblocks8_padded(n, tb);
+  s.kbp = kblocks8_padded(k);
+  s.a_plane = s.mbp * s.kbp * 1024;
+  s.b_plane = s.nbp * s.kbp * 1024;
+  s.r_plane = s.mbp * s.nbp * 1024;
+  return s;
+}
+
+template <typename T, int C>
+hipError_t split_launch(int nw, dim3 grid, const ResidueOperand<T> *ops, const int *prefix, int nops, int live_only,
+                        int u_first, int u_end, hipStream_t st) {
+  switch (nw) {
+#define MP_RESIDUE_SPLIT_CASE(NW)                                                                                  \
+  case NW:                                                                                                         \
+    hipLaunchKernelGGL((k_residue_split<T, C, NW>), grid, dim3(kThreads), 0, st, ops, prefix, nops, live_only, u_first, \
+                       u_end);                                                                                     \
+    return hipGetLastError();
+    MP_RESIDUE_SPLIT_CASE(1)
+    MP_RESIDUE_SPLIT_CASE(2)
+    MP_RESIDUE_SPLIT_CASE(3)
+    MP_RESIDUE_SPLIT_CASE(4)
+    MP_RESIDUE_SPLIT_CASE(5)
+    MP_RESIDUE_SPLIT_CASE(6)
+    MP_RESIDUE_SPLIT_CASE(7)
+    MP_RESIDUE_SPLIT_CASE(8)
+    MP_RESIDUE_SPLIT_CASE(9)
+#undef MP_RESIDUE_SPLIT_CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+template <typename T, int C>
+hipError_t combine_launch(int nwc, int64_t blocks, const ResidueDesc *descs, const int *prefix, int nprod,
+                          hipStream_t st) {
+  switch (nwc) {
+#define MP_RESIDUE_COMBINE_CASE(NWC)                                                                             \
+  case NWC: {                                                                                                    \
+    const int64_t wgs = blocks * (4 / combine_entries<NWC>());                                                   \
+    if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;                                                         \
+    hipLaunchKernelGGL((k_residue_combine<T, C, NWC>), dim3((unsigned)wgs), dim3(kThreads), 0, st, descs, prefix, nprod); \
+    return hipGetLastError();                                                                                    \
+  }
+    MP_RESIDUE_COMBINE_CASE(2)
+    MP_RESIDUE_COMBINE_CASE(4)
+    MP_RESIDUE_COMBINE_CASE(6)
+    MP_RESIDUE_COMBINE_CASE(8)
+    MP_RESIDUE_COMBINE_CASE(10)
+    MP_RESIDUE_COMBINE_CASE(12)
+    MP_RESIDUE_COMBINE_CASE(14)
+    MP_RESIDUE_COMBINE_CASE(16)
+    MP_RESIDUE_COMBINE_CASE(18)
+    MP_RESIDUE_COMBINE_CASE(20)
+#undef MP_RESIDUE_COMBINE_CASE
+    default:
+      return hipErrorInvalidValue;
+  }
+}
+
+hipError_t gemm_launch(int cfg, const ResiduePlan &p, const int8_t *A, const int8_t *B, const Shape &s, int u_first,
+                       int u_end, int m, int n, int8_t *R, hipStream_t st) {
+  const int tb = int8_tile_blocks(cfg);
+  const int64_t tiles = (s.mbp / tb) * (s.nbp / tb);
+  if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
+  // small products: the units (independent results) spread over gridDim.z
+  // until the grid fills the chip (256 workgroups of the 256 x 256 tiles, one
+  // per CU; 512 of the smaller ones)
+  const int64_t nchunks = ceil_div(s.kbp, (int64_t)kChunkBlocks);
+  const int64_t wgs = tiles * nchunks, want = cfg == 1 ? 512 : 256;
+  const int groups = wgs >= want ? 1 : (int)std::min<int64_t>(u_end - u_first, ceil_div(want, wgs));
+  const dim3 grid((unsigned)tiles, (unsigned)nchunks, (unsigned)groups);
+  if (cfg == 1)
+    hipLaunchKernelGGL(k_gemm_residue<1>, grid, dim3(64 * Int8Cfg<1>::WM * Int8Cfg<1>::WN), 0, st, A, B, s.mbp, s.nbp,
+                       s.kbp, u_first, u_end, p.nsq, p.nplanes, m, n, R, s.r_plane);
+  else  // every 256 x 256 configuration
+    hipLaunchKernelGGL(k_gemm_residue<3>, grid, dim3(64 * Int8Cfg<3>::WM * Int8Cfg<3>::WN), 0, st, A, B, s.mbp, s.nbp,
+                       s.kbp, u_first, u_end, p.nsq, p.nplanes, m, n, R, s.r_plane);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+size_t residue_bytes(const ResiduePlan &p, int cfg, int64_t m, int64_t n, int64_t k) {
+  const Shape s = shape_of(cfg, m, n, k);
+  return header_bytes(p) + (size_t)p.nplanes * (size_t)(s.a_plane + s.b_plane + p.nchunks * s.r_plane);
+}
+
+template <typename T, int C>
+hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,
+                          hipEvent_t between, hipStream_t st) {
+  using U = typename bits_of<T>::type;
+  const ResiduePlan &p = rc.plan;
+  const Shape s = shape_of(rc.cfg, rc.m, rc.n, rc.k);
+  // arena: the uploaded descriptors and table, the result planes, then as many
+  // operand planes as fit (all of them, except in a fixed scratch)
+  const size_t head = header_bytes(p), result = (size_t)p.nplanes * p.nchunks * s.r_plane;
+  if (rc.arena_bytes < head + result) return hipErrorInvalidValue;
+  const int64_t fit = (int64_t)((rc.arena_bytes - head - result) / (size_t)(s.a_plane + s.b_plane));
+  const int room = (int)std::min<int64_t>(p.nplanes, fit);
+  if (room < (p.nsq > 0 ? 2 : 1)) return hipErrorInvalidValue;
+  int8_t *R = reinterpret_cast<int8_t *>(rc.arena + head);
+  int8_t *Ap = R + result, *Bp = Ap + (size_t)room * s.a_plane;
+
+  const std::vector<uint32_t> &table = residue_table(p.nunits, p.nsq, p.nwc);
+  struct Head {
+    ResidueOperand<T> op[2];
+    ResidueDesc d;
+    int prefix[4];  // of the split blocks, then of the product
+  } h{};
+  static_assert(sizeof(Head) <= 2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 8 * 4, "header size");
+  static_assert(sizeof(Head) % 4 == 0, "uploaded in words");
+  for (int i = 0; i < 2; ++i) {
+    const SplitOperand<T> &o = i == 0 ? a : b;
+    ResidueOperand<T> &r = h.op[i];
+    r.X = o.X;
+    r.comp_stride = o.comp_stride;
+    r.sv = o.sv;
+    r.sp = o.sp;
+    r.nvec = o.nvec;
+    r.len = o.len;
+    r.orient = o.orient;
+    r.bits = p.bits;
+    r.float_form = rc.float_form;
+    r.guard_bits = rc.guard_bits;
+    r.planes = i == 0 ? Ap : Bp;
+    r.nbp = i == 0 ? s.mbp : s.nbp;
+    r.kbp = s.kbp;
+    r.mu = i == 0 ? rc.mu_a : rc.mu_b;
+    r.exps = i == 0 ? rc.exp_a : rc.exp_b;
+    r.state = nullptr;
+    r.flag = rc.flag;
+    r.nunits = p.nunits;
+    r.nsq = p.nsq;
+  }
+  const int64_t ba = s.mbp * s.kbp, bb = s.nbp * s.kbp;
+  if (ba + bb > 0x7fffffffLL) return hipErrorInvalidValue;
+  h.prefix[0] = 0;
+  h.prefix[1] = (int)ba;
+  h.d.R = R;
+  h.d.table = reinterpret_cast<const uint32_t *>(rc.arena + sizeof(Head));
+  h.d.EA = rc.exp_a;
+  h.d.EB = rc.exp_b;
+  h.d.mbp = s.mbp;
+  h.d.nbp = s.nbp;
+  h.d.kbp = s.kbp;
+  h.d.plane = s.r_plane;
+  h.d.nunits = p.nunits;
+  h.d.nsq = p.nsq;
+  h.d.nplanes = p.nplanes;
+  h.d.bits = p.bits;
+  h.d.nchunks = p.nchunks;
+  h.d.m = rc.m;
+  h.d.n = rc.n;
+  h.d.ldc = rc.ldc;
+  h.d.C = Cout;
+  h.d.c_stride = rc.c_stride;
+
+  hipError_t err = hipSuccess;
+  const size_t words = sizeof(Head) / 4 + table.size();
+  for (size_t at = 0; at < words; at += kUploadWords) {
+    Upload up;
+    const size_t n = std::min<size_t>(kUploadWords, words - at), hw = sizeof(Head) / 4;
+    for (size_t i = 0; i < n; ++i)
+      up.w[i] = at + i < hw ? reinterpret_cast<const uint32_t *>(&h)[at + i] : table[at + i - hw];
+    const bool first = at == 0;
+    const int64_t n0 = first ? (int64_t)rc.m * sizeof(U) / 4 : 0, n1 = first ? (int64_t)rc.n * sizeof(U) / 4 : 0;
+    const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(std::max(n0, n1), kThreads)));
+    hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n,
+                       reinterpret_cast<uint32_t *>(rc.arena) + at, static_cast<uint32_t *>(rc.mu_a), n0,
+                       static_cast<uint32_t *>(rc.mu_b), n1);
+    if ((err = hipGetLastError()) != hipSuccess) return err;
+  }
+  SplitOperand<T> ma = a, mb = b;
+  ma.mu = rc.mu_a;
+  mb.mu = rc.mu_b;
+  if ((err = launch_split_max0(ma, mb, st)) != hipSuccess) return err;
+  const auto *ops = reinterpret_cast<const ResidueOperand<T> *>(rc.arena);
+  const auto *descs = reinterpret_cast<const ResidueDesc *>(rc.arena + offsetof(Head, d));
+  const auto *prefix = reinterpret_cast<const int *>(rc.arena + offsetof(Head, prefix));
+  for (int u0 = 0; u0 < p.nunits;) {
+    int u1 = u0 + 1;
+    while (u1 < p.nunits && plane_of(u1 + 1, p.nsq) - plane_of(u0, p.nsq) <= room) ++u1;
+    // a grid of few blocks spreads the bases over gridDim.y
+    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((u1 - u0) / 8, 1024 / (ba + bb)));
+    if ((err = split_launch<T, C>(p.nw, dim3((unsigned)(ba + bb), (unsigned)parts), ops, prefix, 2, 0, u0, u1, st)) !=
+        hipSuccess)
+      return err;
+    if (between && u0 == 0) (void)hipEventRecord(between, st);
+    if ((err = gemm_launch(rc.cfg, p, Ap, Bp, s, u0, u1, rc.m, rc.n, R, st)) != hipSuccess) return err;
+    u0 = u1;
+  }
+  return combine_launch<T, C>(p.nwc, s.mbp * s.nbp, descs, prefix + 2, 1, st);
+}
+
+template <typename T, int C>
+hipError_t launch_residue_split_batched(int nw, const ResidueOperand<T> *ops, const int *prefix, int nops, int blocks,
+                                        hipStream_t st) {
+  if (blocks <= 0) return hipSuccess;
+  return split_launch<T, C>(nw, dim3((unsigned)blocks), ops, prefix, nops, 1, 0, -1, st);
+}
+
+hipError_t launch_gemm_residue_batched(const ResidueDesc *descs, const int4 *items, int nitems1, int nitems3,
+                                       const int *bounds, int *counters, hipStream_t st) {
+  // 128 x 128 tiles: two workgroups per CU; 256 x 256: one
+  if (nitems1 > 0) {
+    hipLaunchKernelGGL(k_gemm_residue_batched<1>, dim3(std::min(nitems1, 512)),
+                       dim3(64 * Int8Cfg<1>::WM * Int8Cfg<1>::WN), 0, st, descs, items, bounds, counters);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
+  if (nitems3 > 0)
+    hipLaunchKernelGGL(k_gemm_residue_batched<3>, dim3(std::min(nitems3, 256)),
+                       dim3(64 * Int8Cfg<3>::WM * Int8Cfg<3>::WN), 0, st, descs, items + nitems1, bounds + kXcds + 1,
+                       counters + kXcds);
+  return hipGetLastError();
+}
+
+template <typename T, int C>
+hipError_t launch_residue_combine_batched(int nwc, const ResidueDesc *descs, const int *prefix, int nprod,
+                                          int64_t blocks, hipStream_t st) {
+  if (blocks <= 0) return hipSuccess;
+  return combine_launch<T, C>(nwc, blocks, descs, prefix, nprod, st);
+}
+
+#define MP_RESIDUE_INST(T, C)                                                                                   \
+  template hipError_t launch_residue<T, C>(const ResidueCall &, const SplitOperand<T> &, const SplitOperand<T> &, T *, \
+                                           hipEvent_t, hipStream_t);                                            \
+  template hipError_t launch_residue_split_batched<T, C>(int, const ResidueOperand<T> *, const int *, int, int, \
+                                                         hipStream_t);                                          \
+  template hipError_t launch_residue_combine_batched<T, C>(int, const ResidueDesc *, const int *, int, int64_t, \
+                                                           hipStream_t);
+MP_RESIDUE_INST(double, 2)
+MP_RESIDUE_INST(double, 3)
+MP_RESIDUE_INST(double, 4)
+#undef MP_RESIDUE_INST
+
+}  // namespace mp

@@ -18,6 +18,8 @@
 #include "internal.h"
 #include "layout.h"
 #include "mp_device.h"
+#include "residue.h"
+#include "window.h"
 
 namespace mp {
 namespace {
@@ -102,8 +104,8 @@ __device__ __forceinline__ void reduce_max(const TileCoord &tc, const U (&m)[kPe
   }
 }
 
-template <typename T, int C, int ORIENT>
-__device__ void max0_body(const SplitOperand<T> &op, int idx) {
+template <typename T, int ORIENT, typename Op>
+__device__ void max0_body(const Op &op, int idx) {
   using U = typename bits_of<T>::type;
   const TileCoord tc = tile_of<ORIENT>(idx, op.nvec, op.len);
   U m[kPerThread];
@@ -116,12 +118,12 @@ __device__ void max0_body(const SplitOperand<T> &op, int idx) {
   reduce_max<ORIENT>(tc, m, static_cast<U *>(op.mu), op.nvec);
 }
 
-template <typename T, int C>
+template <typename T>
 __global__ __launch_bounds__(kThreads) void k_split_max0(SplitOperand<T> a, SplitOperand<T> b, int blocks_a) {
   if ((int)blockIdx.x < blocks_a)
-    max0_body<T, C, 0>(a, blockIdx.x);
+    max0_body<T, 0>(a, blockIdx.x);
   else
-    max0_body<T, C, 1>(b, blockIdx.x - blocks_a);
+    max0_body<T, 1>(b, blockIdx.x - blocks_a);
 }
 
 template <typename T, int C, int ORIENT>
@@ -204,16 +206,16 @@ __device__ __forceinline__ int find_operand(const int *prefix, int nops, int b) 
   return lo;
 }
 
-template <typename T, int C>
-__global__ __launch_bounds__(kThreads) void k_split_max0_batched(const SplitOperand<T> *ops, const int *prefix,
+template <typename T, typename Op>
+__global__ __launch_bounds__(kThreads) void k_split_max0_batched(const Op *ops, const int *prefix,
                                                                  int nops) {
   const int i = find_operand(prefix, nops, blockIdx.x);
-  const SplitOperand<T> &op = ops[i];
+  const Op &op = ops[i];
   const int local = blockIdx.x - prefix[i];
   if (op.orient == 0)
-    max0_body<T, C, 0>(op, local);
+    max0_body<T, 0>(op, local);
   else
-    max0_body<T, C, 1>(op, local);
+    max0_body<T, 1>(op, local);
 }
 
 template <typename T, int C>
@@ -407,12 +409,7 @@ hipError_t launch_split_plain(const SplitOperand<T> &a, const SplitOperand<T> &b
   if (err != hipSuccess) return err;
   err = launch_fill32(b.mu, (int64_t)D * b.nvec * sizeof(U) / 4, 0u, st);
   if (err != hipSuccess) return err;
-  const int ba0 = a.nvec > 0 && a.len > 0 ? tiles(a.nvec, a.len) : 0;
-  const int bb0 = b.nvec > 0 && b.len > 0 ? tiles(b.nvec, b.len) : 0;
-  if (ba0 + bb0 > 0) {
-    hipLaunchKernelGGL((k_split_max0<T, C>), dim3(ba0 + bb0), dim3(kThreads), 0, st, a, b, ba0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-  }
+  if ((err = launch_split_max0(a, b, st)) != hipSuccess) return err;
   const int ba = a.nvec > 0 ? tiles(a.nbp * kBlk, a.kbp * kKBlk) : 0;
   const int bb = b.nvec > 0 ? tiles(b.nbp * kBlk, b.kbp * kKBlk) : 0;
   for (int pass = 0; pass < D; ++pass) {
@@ -442,7 +439,7 @@ hipError_t launch_split_plain_batched(const SplitOperand<T> *ops, const int *pre
   if (tiles_max0 <= 0 && tiles_pass <= 0) return hipSuccess;
   if ((err = launch_fill32(mu_all, mu_words, 0u, st)) != hipSuccess) return err;
   if (tiles_max0 > 0) {
-    hipLaunchKernelGGL((k_split_max0_batched<T, C>), dim3(tiles_max0), dim3(kThreads), 0, st, ops, prefix_max0, nops);
+    hipLaunchKernelGGL((k_split_max0_batched<T, SplitOperand<T>>), dim3(tiles_max0), dim3(kThreads), 0, st, ops, prefix_max0, nops);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   for (int pass = 0; pass < dmax && tiles_pass > 0; ++pass) {
@@ -514,37 +511,6 @@ int window_words(int D) {
   return 0;
 }
 
-// x = M 2^q exactly, |M| < 2^53 (zero gives M = 0).
-__device__ __forceinline__ void binary64_parts(double x, int64_t &M, int &q) {
-  const uint64_t b = (uint64_t)__double_as_longlong(x);
-  const int ef = (int)((b >> 52) & 0x7ff);
-  const int64_t f = (int64_t)(b & 0xfffffffffffffULL);
-  const int64_t m = ef == 0 ? f : (f | (int64_t(1) << 52));
-  q = ef == 0 ? -1074 : ef - 1075;
-  M = (b >> 63) ? -m : m;
-}
-
-// w += M 2^off over all NW words (two's complement; off >= 0).  With
-// off = 32 q + sh, M 2^sh spans three words x0, x1, x2 (the sign beyond), and
-// word i receives the one of them numbered i - q: selects, no branches.
-template <int NW>
-__device__ __forceinline__ void window_add(uint32_t (&w)[NW], int64_t M, int off) {
-  const int q = off >> 5, sh = off & 31;
-  const uint64_t u = (uint64_t)M << sh;
-  const uint32_t sign = (uint32_t)(M >> 63);
-  const uint32_t x0 = (uint32_t)u, x1 = (uint32_t)(u >> 32);
-  const uint32_t x2 = sh ? (uint32_t)(M >> (64 - sh)) : sign;
-  uint32_t carry = 0;
-#pragma unroll
-  for (int i = 0; i < NW; ++i) {
-    const int d = i - q;
-    const uint32_t part = d < 0 ? 0u : d == 0 ? x0 : d == 1 ? x1 : d == 2 ? x2 : sign;
-    const uint64_t sum = (uint64_t)w[i] + part + carry;
-    w[i] = (uint32_t)sum;
-    carry = (uint32_t)(sum >> 32);
-  }
-}
-
 // N = floor(x / 2^P) of the c components x[r * stride] (a normalized
 // expansion) into w, and whether x - N 2^P is nonzero.  The loop over the
 // components is unrolled for the DD/TD/QD formats (CMAX <= 4) only.
@@ -602,14 +568,10 @@ __device__ __forceinline__ uint32_t window_bits7(const uint32_t (&w)[NW], int j)
   return v & 127u;
 }
 
-// LIVE: blk numbers only the blocks that hold an element of the operand (the
-// padding blocks of the packed planes were cleared once and are not written);
-// otherwise every packed block, padding included.
-template <int CMAX, int NW, int ORIENT, bool LIVE = false>
+template <int CMAX, int NW, int ORIENT>
 __device__ void int8_block(const SplitOperand<double> &op, int64_t blk, int D, int c) {
   constexpr int Dw = window_digits<NW>();
-  const int64_t nb = LIVE ? ceil_div((int64_t)op.nvec, (int64_t)kBlk8) : op.nbp;
-  const int64_t kbn = LIVE ? ceil_div((int64_t)op.len, (int64_t)kKBlk8) : op.kbp;
+  const int64_t nb = op.nbp, kbn = op.kbp;
   // A (rows, contiguous along the row index): walk row blocks fastest;
   // B (columns, contiguous along k): walk k blocks fastest.
   const int64_t vb = ORIENT == 0 ? blk % nb : blk / kbn;
@@ -693,21 +655,6 @@ __global__ __launch_bounds__(kThreads) void k_split_int8(SplitOperand<double> a,
     int8_block<CMAX, NW, 1>(b, blk - blocks_a, D, c);
 }
 
-// Batched: workgroup b takes live block b - prefix[i] of operand i (ops[i].D
-// digits; the window holds the batch's largest D).  The batch's packed planes
-// are cleared when its plan is built, so padding blocks are never written.
-template <int C, int NW>
-__global__ __launch_bounds__(kThreads) void k_split_int8_batched(const SplitOperand<double> *ops, const int *prefix,
-                                                                 int nops) {
-  const int i = find_operand(prefix, nops, blockIdx.x);
-  const SplitOperand<double> &op = ops[i];
-  const int64_t local = (int64_t)blockIdx.x - prefix[i];
-  if (op.orient == 0)
-    int8_block<C, NW, 0, true>(op, local, op.D, C);
-  else
-    int8_block<C, NW, 1, true>(op, local, op.D, C);
-}
-
 // Digit kernel for c components and D digits: the DD/TD/QD formats in their own
 // instantiations, longer expansions in one generic one (up to 14 components).
 template <int C>
@@ -742,17 +689,35 @@ hipError_t launch_int8_digits(const SplitOperand<double> &a, const SplitOperand<
 
 }  // namespace
 
+template <typename T>
+hipError_t launch_split_max0(const SplitOperand<T> &a, const SplitOperand<T> &b, hipStream_t st) {
+  const int ba0 = a.nvec > 0 && a.len > 0 ? tiles(a.nvec, a.len) : 0;
+  const int bb0 = b.nvec > 0 && b.len > 0 ? tiles(b.nvec, b.len) : 0;
+  if (ba0 + bb0 <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_split_max0<T>, dim3(ba0 + bb0), dim3(kThreads), 0, st, a, b, ba0);
+  return hipGetLastError();
+}
+template hipError_t launch_split_max0<double>(const SplitOperand<double> &, const SplitOperand<double> &, hipStream_t);
+template hipError_t launch_split_max0<float>(const SplitOperand<float> &, const SplitOperand<float> &, hipStream_t);
+
+template <typename T>
+hipError_t launch_residue_max_batched(const ResidueOperand<T> *ops, const int *prefix, int nops, int tiles,
+                                      hipStream_t st) {
+  if (tiles <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_split_max0_batched<T, ResidueOperand<T>>), dim3(tiles), dim3(kThreads), 0, st, ops, prefix,
+                     nops);
+  return hipGetLastError();
+}
+template hipError_t launch_residue_max_batched<double>(const ResidueOperand<double> *, const int *, int, int,
+                                                       hipStream_t);
+template hipError_t launch_residue_max_batched<float>(const ResidueOperand<float> *, const int *, int, int, hipStream_t);
+
 template <int C>
 hipError_t launch_split_int8(const SplitOperand<double> &a, const SplitOperand<double> &b, int D, hipStream_t st) {
   hipError_t err = launch_fill32(a.mu, (int64_t)a.nvec * 2, 0u, st);
   if (err != hipSuccess) return err;
   if ((err = launch_fill32(b.mu, (int64_t)b.nvec * 2, 0u, st)) != hipSuccess) return err;
-  const int ba0 = a.nvec > 0 && a.len > 0 ? tiles(a.nvec, a.len) : 0;
-  const int bb0 = b.nvec > 0 && b.len > 0 ? tiles(b.nvec, b.len) : 0;
-  if (ba0 + bb0 > 0) {
-    hipLaunchKernelGGL((k_split_max0<double, C>), dim3(ba0 + bb0), dim3(kThreads), 0, st, a, b, ba0);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-  }
+  if ((err = launch_split_max0(a, b, st)) != hipSuccess) return err;
   // one workgroup of kThreads (= 1024 / 4) threads per 32 x 32 block
   static_assert(kThreads * 4 == kBlk8 * kKBlk8, "thread per 4 bytes of a block");
   const int64_t ba = a.nvec > 0 ? a.nbp * a.kbp : 0;
@@ -763,46 +728,6 @@ hipError_t launch_split_int8(const SplitOperand<double> &a, const SplitOperand<d
   }
   return hipSuccess;
 }
-
-template <int C>
-hipError_t launch_split_int8_batched(const SplitOperand<double> *ops, const int *prefix_max0, const int *prefix_blk,
-                                     int nops, int tiles_max0, int64_t blocks, int dmax, void *mu_all,
-                                     int64_t mu_words, hipStream_t st) {
-  hipError_t err = launch_fill32(mu_all, mu_words, 0u, st);
-  if (err != hipSuccess) return err;
-  if (tiles_max0 > 0) {
-    hipLaunchKernelGGL((k_split_max0_batched<double, C>), dim3(tiles_max0), dim3(kThreads), 0, st, ops, prefix_max0,
-                       nops);
-    if ((err = hipGetLastError()) != hipSuccess) return err;
-  }
-  if (blocks > 0) {
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    switch (window_words(dmax)) {
-#define MP_DIGITS_BATCHED_CASE(NW)                                                                           \
-  case NW:                                                                                                   \
-    hipLaunchKernelGGL((k_split_int8_batched<C, NW>), dim3((unsigned)blocks), dim3(kThreads), 0, st, ops,     \
-                       prefix_blk, nops);                                                                    \
-    return hipGetLastError();
-      MP_DIGITS_BATCHED_CASE(4)
-      MP_DIGITS_BATCHED_CASE(5)
-      MP_DIGITS_BATCHED_CASE(6)
-      MP_DIGITS_BATCHED_CASE(7)
-      MP_DIGITS_BATCHED_CASE(8)
-      MP_DIGITS_BATCHED_CASE(9)
-#undef MP_DIGITS_BATCHED_CASE
-      default:
-        return hipErrorInvalidValue;
-    }
-  }
-  return hipSuccess;
-}
-
-template hipError_t launch_split_int8_batched<2>(const SplitOperand<double> *, const int *, const int *, int, int,
-                                                 int64_t, int, void *, int64_t, hipStream_t);
-template hipError_t launch_split_int8_batched<3>(const SplitOperand<double> *, const int *, const int *, int, int,
-                                                 int64_t, int, void *, int64_t, hipStream_t);
-template hipError_t launch_split_int8_batched<4>(const SplitOperand<double> *, const int *, const int *, int, int,
-                                                 int64_t, int, void *, int64_t, hipStream_t);
 
 #define MP_SPLIT_INT8_LONG(C) \
   template hipError_t launch_split_int8<C>(const SplitOperand<double> &, const SplitOperand<double> &, int, hipStream_t);
