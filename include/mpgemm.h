@@ -55,7 +55,16 @@ extern "C" {
 #define MPGEMM_TS 3
 
 /* Slice forms.  FLOAT: binary64 slices on FP64 matrix cores (binary32 slices
- * on FP32 matrix cores for TS), Algorithm 1 as written.  INT8: signed 7-bit
+ * on FP32 matrix cores for TS), Algorithm 1 as written.  With the automatic
+ * slice count D (and k >= 48) the product that D slices stand for is formed
+ * another way: the elements are rounded once to a fixed grid below their row's
+ * (column's) largest, no coarser than the grid of the D-th slice, and those
+ * integers are multiplied exactly by residues, as in the INT8 form below.  The
+ * device checks for every row and column that D slices do not reach further
+ * down (they follow the largest residual, and can where the entries of a row
+ * are short and far apart); if one might, the product is formed from the
+ * slices.  A D set by the caller, the printed last slice, the data-chosen pairs
+ * and the parity hooks always take the slices.  INT8: signed 7-bit
  * digit slices on INT8 matrix cores with exact 32-bit integer sums (DD, TD, QD
  * only); more slices, each product far cheaper.  Digit s (s = 1..D) of an
  * element of a row of A (column of B) is the extraction step of Algorithm 1 on

@@ -259,11 +259,35 @@ struct Plan {
   // The product by residues (residue.h); nunits = 0: by slice products.  Its
   // planes take the slices' place from off_arena on.
   ResiduePlan res;
-  size_t off_arena, slices_total;
+  size_t off_res_clear, res_clear_bytes;  // maxima and states, cleared together
+  size_t off_res_mu_a, off_res_mu_b, off_res_st_a, off_res_st_b, off_res_exp_a, off_res_exp_b, off_arena, off_flag;
+  size_t slices_total;  // without the residues
 };
 
-// comps: components of a longer expansion (0: the format's own).
-Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, int comps = 0) {
+// Smallest inner dimension for which the FLOAT form goes by residues: its check
+// reads changes of bits off the first 32 elements of a vector (residue.hip), and
+// fewer would often miss one.
+constexpr int kMinFloatResidueK = 48;
+
+// Grid of the FLOAT form's integers below the vector's exponent: a pass of
+// Algorithm 1 falls b + 1 bits (residue.hip), D (b + 1) - 1 in all, and three
+// more bits for passes that fall further.  TS takes enough for its 76 bits over a
+// spread of 40: its 13 passes of 7 bits outlast its mantissas, so they would
+// follow the smallest elements down.
+int float_residue_bits(int fmt, int D, int64_t k) {
+  const int S = fmt == MPGEMM_TS ? 24 : 53, b = S - rho_of(S, k);
+  return std::max(D * (b + 1) + 2, fmt == MPGEMM_TS ? 116 : 0);
+}
+
+bool float_residue_plan(int fmt, int D, int64_t k, ResiduePlan &p) {
+  return k >= kMinFloatResidueK && residue_plan(float_residue_bits(fmt, D, k), k, p);
+}
+
+bool automatic_slices(int fmt, int mode) { return g_opt.slices[fmt][mode] <= 0; }
+
+// comps: components of a longer expansion (0: the format's own).  automatic: D
+// is the library's choice for the bound, not a count the caller set.
+Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool automatic, int comps = 0) {
   Plan p{};
   p.fmt = fmt;
   p.mode = mode;
@@ -292,6 +316,31 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, int co
     p.off_mu_b = take((size_t)D * n * comp);
     p.off_exp_a = take((size_t)D * m * 4);
     p.off_exp_b = take((size_t)D * n * 4);
+    p.slices_total = o;
+    // The integers of float_residue_bits.  Vectors whose slices may reach
+    // further down make the call fall back on the slices, whose workspace the
+    // residues share.  A count that the caller set is Algorithm 1 with that many
+    // slices.
+    if (automatic && m > 0 && n > 0 && g_opt.last_slice == 0 && float_residue_plan(fmt, D, k, p.res)) {
+      p.int8_cfg = int8_tile_config(m, n, g_opt.int8_tile);
+      o = 0;
+      p.off_res_clear = 0;
+      p.off_res_mu_a = take((size_t)m * comp);
+      p.off_res_mu_b = take((size_t)n * comp);
+      p.off_res_st_a = take((size_t)m * 4);
+      p.off_res_st_b = take((size_t)n * 4);
+      p.res_clear_bytes = o;
+      p.off_res_exp_a = take((size_t)m * 4);
+      p.off_res_exp_b = take((size_t)n * 4);
+      p.off_arena = o;
+      take(residue_bytes(p.res, p.int8_cfg, m, n, k));
+      p.off_flag = std::max(o, p.slices_total);
+      p.total = p.off_flag + 256;
+    } else {
+      p.res.nunits = 0;
+      p.total = p.slices_total;
+    }
+    return p;
   } else {
     p.elem = 1;
     p.rho = 0;
@@ -303,6 +352,11 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, int co
     p.off_mu_b = take((size_t)n * 8);
     p.off_exp_a = take((size_t)m * 4);
     p.off_exp_b = take((size_t)n * 4);
+    p.off_res_clear = p.off_res_mu_a = p.off_mu_a;
+    p.off_res_mu_b = p.off_mu_b;
+    p.res_clear_bytes = p.off_exp_a - p.off_mu_a;
+    p.off_res_exp_a = p.off_exp_a;
+    p.off_res_exp_b = p.off_exp_b;
     p.off_arena = o;
     p.off_resid_a = p.off_resid_b = take(0);
     p.off_pack_a = take((size_t)D * p.mbp * p.kbp * 1024);
@@ -450,7 +504,7 @@ hipError_t split_both(const SplitOperand<T> &a, const SplitOperand<T> &b, const 
 
 template <typename T, int C>
 hipError_t gemm_launch(const Plan &p, char *base, int m, int n, int k, T *Cout, int ldc, int dbg_pair, void *dbg_out,
-                       int lddbg, hipStream_t st) {
+                       int lddbg, const int *run_if, hipStream_t st) {
   if (p.mode == MPGEMM_MODE_INT8) {
     if constexpr (sizeof(T) == 8)
       return launch_gemm_int8<C>(base + p.off_pack_a, base + p.off_pack_b,
@@ -464,40 +518,52 @@ hipError_t gemm_launch(const Plan &p, char *base, int m, int n, int k, T *Cout, 
   if constexpr (C <= 4)
     return launch_gemm_plain<T, C>(base + p.off_pack_a, base + p.off_pack_b, p.mbp, p.nbp, p.kbp, m, n, p.D, Cout,
                                    ldc, (int64_t)ldc * n, dbg_pair, static_cast<double *>(dbg_out), lddbg,
-                                   layout_for(p.fmt), st);
+                                   layout_for(p.fmt), run_if, st);
   return hipErrorInvalidValue;
 }
 
 // The product by residues on the workspace at `base` (`bytes` of it), laid out
-// by plan p; `between` is recorded after the split.
+// by plan p; `between` is recorded after the split.  flag: FLOAT form, a device
+// word outside that workspace's shared part.
 template <typename T, int C>
-hipError_t residue_launch(const Plan &p, char *base, size_t bytes, const SplitOperand<T> &a, const SplitOperand<T> &b,
-                          int m, int n, int k, T *Cm, int ldc, hipEvent_t between, hipStream_t st) {
+hipError_t residue_launch(const Plan &p, char *base, size_t bytes, int *flag, const SplitOperand<T> &a,
+                          const SplitOperand<T> &b, int m, int n, int k, T *Cm, int ldc, hipEvent_t between,
+                          hipStream_t st) {
   ResidueCall rc{};
   rc.plan = p.res;
   rc.cfg = p.int8_cfg;
+  rc.float_form = p.mode == MPGEMM_MODE_FLOAT;
+  rc.slice_bits = rc.float_form ? (sizeof(T) == 8 ? 53 : 24) - p.rho : 0;
+  rc.passes = p.D;
   rc.m = m;
   rc.n = n;
   rc.k = k;
   rc.ldc = ldc;
   rc.c_stride = (int64_t)ldc * n;
-  rc.exp_a = reinterpret_cast<int *>(base + p.off_exp_a);
-  rc.exp_b = reinterpret_cast<int *>(base + p.off_exp_b);
-  rc.mu_a = base + p.off_mu_a;
-  rc.mu_b = base + p.off_mu_b;
+  rc.exp_a = reinterpret_cast<int *>(base + p.off_res_exp_a);
+  rc.exp_b = reinterpret_cast<int *>(base + p.off_res_exp_b);
+  rc.mu_a = base + p.off_res_mu_a;
+  rc.mu_b = base + p.off_res_mu_b;
+  rc.state_a = reinterpret_cast<int *>(base + p.off_res_st_a);
+  rc.state_b = reinterpret_cast<int *>(base + p.off_res_st_b);
+  rc.clear = reinterpret_cast<uint32_t *>(base + p.off_res_clear);
+  rc.clear_words = (int64_t)(p.res_clear_bytes / 4);
+  rc.flag = rc.float_form ? flag : nullptr;
   rc.arena = base + p.off_arena;
   rc.arena_bytes = bytes - p.off_arena;
   return launch_residue<T, C>(rc, a, b, Cm, between, st);
 }
 
-// The launch sequence of one product (split, then the fused slice products
-// and accumulation, or the residues) on the workspace at `base` (`bytes` of
-// it), laid out by plan p.  With `profile`, records the thread's stage-timing
-// events if they are enabled.
+// The launch sequence of one product on the workspace at `base` (`bytes` of
+// it), laid out by plan p: the residues where the plan has them, and the slices
+// (split, then the fused slice products and accumulation) otherwise, or in the
+// FLOAT form where the residue split finds on the device that it must have them.
+// With `profile`, records the thread's stage-timing events if they are enabled.
+// With `keep_slices` the slices and their exponents are formed in any case.
 template <typename T, int C>
-hipError_t launch_product(const Plan &p, char *base, size_t bytes, int m, int n, int k, const T *A, int lda, const T *B, int ldb,
-                          T *Cm, int ldc, bool profile, hipStream_t st) {
-  const SplitOperand<T> a = operand_a(A, m, k, lda, p, base), b = operand_b(B, k, n, ldb, p, base);
+hipError_t launch_product(const Plan &p, char *base, size_t bytes, int *flag, int m, int n, int k, const T *A, int lda,
+                          const T *B, int ldb, T *Cm, int ldc, bool profile, bool keep_slices, hipStream_t st) {
+  SplitOperand<T> a = operand_a(A, m, k, lda, p, base), b = operand_b(B, k, n, ldb, p, base);
   const bool prof = profile && g_prof.on;
   std::array<hipEvent_t, 3> ev{nullptr, nullptr, nullptr};
   if (prof) {
@@ -505,17 +571,16 @@ hipError_t launch_product(const Plan &p, char *base, size_t bytes, int m, int n,
     if (ev[0]) (void)hipEventRecord(ev[0], st);
   }
   hipError_t e = hipSuccess;
-  bool done = false;
-  if constexpr (sizeof(T) == 8 && C <= 4) {
-    if (p.res.nunits > 0) {
-      e = residue_launch<T, C>(p, base, bytes, a, b, m, n, k, Cm, ldc, ev[1], st);
-      done = true;
-    }
+  const bool residues = C <= 4 && p.res.nunits > 0;
+  if constexpr (C <= 4) {
+    if (residues) e = residue_launch<T, C>(p, base, bytes, flag, a, b, m, n, k, Cm, ldc, ev[1], st);
   }
-  if (!done) {
-    e = split_both<T, C>(a, b, p, st);
-    if (ev[1]) (void)hipEventRecord(ev[1], st);
-    if (e == hipSuccess) e = gemm_launch<T, C>(p, base, m, n, k, Cm, ldc, -1, nullptr, 0, st);
+  if (!residues || p.mode == MPGEMM_MODE_FLOAT) {
+    const int *run_if = residues ? flag : nullptr;
+    a.run_if = b.run_if = keep_slices ? nullptr : run_if;
+    if (e == hipSuccess) e = split_both<T, C>(a, b, p, st);
+    if (!residues && ev[1]) (void)hipEventRecord(ev[1], st);
+    if (e == hipSuccess) e = gemm_launch<T, C>(p, base, m, n, k, Cm, ldc, -1, nullptr, 0, run_if, st);
   }
   if (ev[2]) (void)hipEventRecord(ev[2], st);
   if (prof) {
@@ -528,18 +593,26 @@ hipError_t launch_product(const Plan &p, char *base, size_t bytes, int m, int n,
   return e;
 }
 
+// launch_product on a workspace of p.total bytes.
+template <typename T, int C>
+hipError_t launch_product(const Plan &p, char *base, int m, int n, int k, const T *A, int lda, const T *B, int ldb,
+                          T *Cm, int ldc, bool profile, bool keep_slices, hipStream_t st) {
+  return launch_product<T, C>(p, base, p.off_flag > 0 ? p.off_flag : p.total, reinterpret_cast<int *>(base + p.off_flag),
+                              m, n, k, A, lda, B, ldb, Cm, ldc, profile, keep_slices, st);
+}
+
 // One product in the given form with D slices (arguments already validated).
 template <typename T, int C>
-int run_with(int fmt, int mode, int D, int m, int n, int k, const T *A, int lda, const T *B, int ldb, T *Cm, int ldc,
+int run_with(int fmt, int mode, int D, bool automatic, int m, int n, int k, const T *A, int lda, const T *B, int ldb, T *Cm, int ldc,
              hipStream_t st) {
   int s;
   g_opt.last_slices = D;
   if (m == 0 || n == 0) return 0;
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(T), C, m, n, ldc, (int64_t)ldc * n, st));
-  const Plan p = make_plan(fmt, mode, m, n, k, D, C);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, automatic, C);
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
-  return hip_status(launch_product<T, C>(p, ws.base, p.total, m, n, k, A, lda, B, ldb, Cm, ldc, true, st));
+  return hip_status(launch_product<T, C>(p, ws.base, m, n, k, A, lda, B, ldb, Cm, ldc, true, false, st));
 }
 
 // Slice counts chosen from the data (mpgemm_set_num_slices(fmt, FLOAT,
@@ -560,8 +633,8 @@ struct DataPlan {
 
 DataPlan make_data_plan(int fmt, int64_t m, int64_t n, int64_t k, bool raw_outside) {
   DataPlan d{};
-  d.p = make_plan(fmt, MPGEMM_MODE_FLOAT, m, n, k, kMaxPairLim);
-  size_t o = d.p.total;
+  d.p = make_plan(fmt, MPGEMM_MODE_FLOAT, m, n, k, kMaxPairLim, false);
+  size_t o = d.p.slices_total;
   auto take = [&](size_t bytes) {
     const size_t at = o;
     o += align256(bytes);
@@ -747,7 +820,7 @@ int run_ds(int m, int n, int k, const double *Ahi, const float *Alo, int lda, co
     if (e == hipSuccess) e = launch_zero_matrix(Clo, 4, 1, m, n, ldc, 0, st);
     return hip_status(e);
   }
-  const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D);
+  const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
   const size_t a_bytes = align256((size_t)2 * m * k * 8), b_bytes = align256((size_t)2 * k * n * 8);
   const size_t c_bytes = align256((size_t)2 * m * n * 8);
   Workspace ws;
@@ -757,7 +830,7 @@ int run_ds(int m, int n, int k, const double *Ahi, const float *Alo, int lda, co
   double *Cdd = reinterpret_cast<double *>(ws.base + p.total + a_bytes + b_bytes);
   hipError_t e = launch_ds_to_dd(m, k, Ahi, Alo, lda, Add, st);
   if (e == hipSuccess) e = launch_ds_to_dd(k, n, Bhi, Blo, ldb, Bdd, st);
-  if (e == hipSuccess) e = launch_product<double, 2>(p, ws.base, p.total, m, n, k, Add, m, Bdd, k, Cdd, m, true, st);
+  if (e == hipSuccess) e = launch_product<double, 2>(p, ws.base, m, n, k, Add, m, Bdd, k, Cdd, m, true, false, st);
   if (e == hipSuccess) e = launch_dd_to_ds(m, n, Cdd, Chi, Clo, ldc, st);
   return hip_status(e);
 }
@@ -768,7 +841,7 @@ int run_ds(int m, int n, int k, const double *Ahi, const float *Alo, int lda, co
 // its device address is looked up once per device with hipGetSymbolAddress
 // and that address is what the kernels receive.
 constexpr size_t kScratchBytes = MPGEMM_NOALLOC_SCRATCH_BYTES;
-static __device__ __align__(256) char scratch[kScratchBytes];
+static __device__ __align__(256) char scratch[kScratchBytes + 256];  // and the fallback flag
 std::mutex g_scratch_mu;
 char *g_scratch_ptr[64] = {};
 
@@ -800,11 +873,12 @@ int run_dd_noalloc(int m, int n, int k, const double *A, int lda, const double *
   g_opt.last_slices = D;
   if (m == 0 || n == 0) return 0;
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(double), 2, m, n, ldc, (int64_t)ldc * n, st));
-  const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D);
+  const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
   if (p.slices_total > kScratchBytes) return MPGEMM_ERR_TOO_LARGE;
   char *base = nullptr;
   if ((s = scratch_of_current_device(&base))) return s;
-  return hip_status(launch_product<double, 2>(p, base, kScratchBytes, m, n, k, A, lda, B, ldb, Cm, ldc, false, st));
+  return hip_status(launch_product<double, 2>(p, base, kScratchBytes, reinterpret_cast<int *>(base + kScratchBytes), m, n, k, A,
+                                               lda, B, ldb, Cm, ldc, false, false, st));
 }
 
 template <typename T, int C>
@@ -814,7 +888,7 @@ int run(int fmt, int m, int n, int k, const T *A, int lda, const T *B, int ldb, 
   if ((s = check_device_cached())) return s;
   const int mode = g_opt.mode[fmt];
   if (data_mode(fmt, mode)) return run_data<T, C>(fmt, m, n, k, A, lda, B, ldb, Cm, ldc, nullptr, nullptr, st);
-  return run_with<T, C>(fmt, mode, slices_for(fmt, mode, k), m, n, k, A, lda, B, ldb, Cm, ldc, st);
+  return run_with<T, C>(fmt, mode, slices_for(fmt, mode, k), automatic_slices(fmt, mode), m, n, k, A, lda, B, ldb, Cm, ldc, st);
 }
 
 // Longer binary64 expansions (c = 2 .. kMaxNd components), INT8 form: the
@@ -828,7 +902,7 @@ int run_nd(int D, int m, int n, int k, const double *A, int lda, const double *B
   int s = validate(m, n, k, A, lda, B, ldb, Cm, ldc);
   if (s) return s < 0 ? s - 2 : s;  // shifted past (c, D)
   if ((s = check_device_cached())) return s;
-  return run_with<double, C>(MPGEMM_QD, MPGEMM_MODE_INT8, D > 0 ? D : nd_auto_slices(C, k), m, n, k, A, lda, B, ldb,
+  return run_with<double, C>(MPGEMM_QD, MPGEMM_MODE_INT8, D > 0 ? D : nd_auto_slices(C, k), D == 0, m, n, k, A, lda, B, ldb,
                              Cm, ldc, st);
 }
 
@@ -846,7 +920,7 @@ int debug_split_t(int fmt, int mode, int operand, int rows, int cols, const T *X
   const int m = operand == 0 ? rows : 0, k = operand == 0 ? cols : rows, n = operand == 0 ? 0 : cols;
   if (D == 0) D = slices_for(fmt, mode, k);
   if (rows == 0 || cols == 0) return 0;
-  const Plan p = make_plan(fmt, mode, m, n, k, D);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, false);
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
   SplitOperand<T> a = operand_a(operand == 0 ? X : (const T *)nullptr, m, k, ldx, p, ws.base);
@@ -874,20 +948,20 @@ int debug_products_t(int fmt, int mode, int m, int n, int k, const T *A, int lda
   if (mode == MPGEMM_MODE_FLOAT && (a < 1 || b < 1 || a + b > D + 1)) return -12;
   if (mode == MPGEMM_MODE_INT8 && (a < 1 || a > D)) return -12;
   if (m == 0 || n == 0 || k == 0) return 0;
-  const Plan p = make_plan(fmt, mode, m, n, k, D, C);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, false, C);
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
   const SplitOperand<T> sa = operand_a(A, m, k, lda, p, ws.base), sb = operand_b(B, k, n, ldb, p, ws.base);
   hipError_t e = split_both<T, C>(sa, sb, p, st);
   const int sel = mode == MPGEMM_MODE_FLOAT ? (a - 1) * D + (b - 1) : a;
-  if (e == hipSuccess) e = gemm_launch<T, C>(p, ws.base, m, n, k, nullptr, m, sel, out, ldo, st);
+  if (e == hipSuccess) e = gemm_launch<T, C>(p, ws.base, m, n, k, nullptr, m, sel, out, ldo, nullptr, st);
   return hip_status(e);
 }
 
 // C = AB as run() computes it in the binary64/binary32 form, then the
 // a-posteriori certificate (certify.hip) from the same split.
 template <typename T, int C>
-int certify_run(int fmt, int mode, int D, int m, int n, int k, const T *A, int lda, const T *B, int ldb, T *Cm,
+int certify_run(int fmt, int mode, int D, bool automatic, int m, int n, int k, const T *A, int lda, const T *B, int ldb, T *Cm,
                 int ldc, double *cert, double *worst, hipStream_t st) {
   int s;
   if (mode == MPGEMM_MODE_FLOAT && g_opt.last_slice != 0) return MPGEMM_ERR_UNSUPPORTED;
@@ -900,7 +974,7 @@ int certify_run(int fmt, int mode, int D, int m, int n, int k, const T *A, int l
       e = launch_zero_matrix(Cm, sizeof(T), C, m, n, ldc, (int64_t)ldc * n, st);
     return hip_status(e);
   }
-  const Plan p = make_plan(fmt, mode, m, n, k, D, C);
+  const Plan p = make_plan(fmt, mode, m, n, k, D, automatic, C);
   // |A_0| and |B_0| go into the slice buffers in the binary64 packed layout
   SplitOperand<T> ca{}, cb{};
   ca.nbp = nblocks_padded(m);
@@ -913,7 +987,7 @@ int certify_run(int fmt, int mode, int D, int m, int n, int k, const T *A, int l
   Workspace ws;
   if ((s = acquire(ws, p.total, st))) return s;
   const SplitOperand<T> a = operand_a(A, m, k, lda, p, ws.base), b = operand_b(B, k, n, ldb, p, ws.base);
-  hipError_t e = launch_product<T, C>(p, ws.base, p.total, m, n, k, A, lda, B, ldb, Cm, ldc, false, st);
+  hipError_t e = launch_product<T, C>(p, ws.base, m, n, k, A, lda, B, ldb, Cm, ldc, false, true, st);
   ca = a;
   cb = b;
   ca.nbp = nblocks_padded(m);
@@ -938,7 +1012,7 @@ int certify_t(int fmt, int m, int n, int k, const T *A, int lda, const T *B, int
   if ((s = check_device_cached())) return s;
   const int mode = g_opt.mode[fmt];
   if (data_mode(fmt, mode)) return run_data<T, C>(fmt, m, n, k, A, lda, B, ldb, Cm, ldc, cert, worst, st);
-  return certify_run<T, C>(fmt, mode, slices_for(fmt, mode, k), m, n, k, A, lda, B, ldb, Cm, ldc, cert, worst, st);
+  return certify_run<T, C>(fmt, mode, slices_for(fmt, mode, k), automatic_slices(fmt, mode), m, n, k, A, lda, B, ldb, Cm, ldc, cert, worst, st);
 }
 
 // The certified product at D = d_first, d_first + 1, ... d_last, stopping at
@@ -962,7 +1036,7 @@ int certify_adaptive_t(int fmt, int m, int n, int k, const T *A, int lda, const 
   const double target = std::ldexp(1.0, -kBoundBits[fmt]);
   int status = MPGEMM_ERR_UNSUPPORTED;
   for (int D = d_first; D <= d_last; ++D) {
-    s = certify_run<T, C>(fmt, mode, D, m, n, k, A, lda, B, ldb, Cm, ldc, cert, worst, st);
+    s = certify_run<T, C>(fmt, mode, D, false, m, n, k, A, lda, B, ldb, Cm, ldc, cert, worst, st);
     if (s == MPGEMM_ERR_UNSUPPORTED) continue;
     if (s) return s;
     *d_used = D;
@@ -987,7 +1061,7 @@ int certify_nd_t(int D, int m, int n, int k, const double *A, int lda, const dou
   if (!cert && m > 0 && n > 0) return -12;
   if (!worst) return -13;
   if ((s = check_device_cached())) return s;
-  return certify_run<double, C>(MPGEMM_QD, MPGEMM_MODE_INT8, D > 0 ? D : nd_auto_slices(C, k), m, n, k, A, lda, B,
+  return certify_run<double, C>(MPGEMM_QD, MPGEMM_MODE_INT8, D > 0 ? D : nd_auto_slices(C, k), D == 0, m, n, k, A, lda, B,
                                 ldb, Cm, ldc, cert, worst, st);
 }
 
@@ -1022,7 +1096,7 @@ int lu_t(int fmt, int n, double *A, int lda, int K, hipStream_t stream) {
     // A22 -= L21 U12, with L21 (r x Kb) and U12 (Kb x r) copied contiguous
     if ((e = launch_lu_copy(C, A, lda, plane, j0 + Kb, j0, r, Kb, bl, stream)) != hipSuccess) break;
     if ((e = launch_lu_copy(C, A, lda, plane, j0, j0 + Kb, Kb, r, bu, stream)) != hipSuccess) break;
-    s = run_with<double, C>(fmt, mode, slices_for(fmt, mode, Kb), r, r, Kb, bl, r, bu, Kb, P, r, stream);
+    s = run_with<double, C>(fmt, mode, slices_for(fmt, mode, Kb), automatic_slices(fmt, mode), r, r, Kb, bl, r, bu, Kb, P, r, stream);
     if (s == 0) e = launch_lu_sub(C, A, lda, plane, j0 + Kb, j0 + Kb, r, r, P, stream);
   }
   if (buf) (void)hipFreeAsync(buf, stream);
@@ -1174,7 +1248,7 @@ int mpgemm_nd_num_slices(int c, int k) {
 size_t mpgemm_nd_workspace_bytes(int c, int D, int m, int n, int k) {
   if (c < 2 || c > kMaxNd || D < 0 || D > kMaxDNd || m < 0 || n < 0 || k < 0) return 0;
   if (m == 0 || n == 0 || k == 0) return 0;
-  return make_plan(MPGEMM_QD, MPGEMM_MODE_INT8, m, n, k, D > 0 ? D : nd_auto_slices(c, k), c).total;
+  return make_plan(MPGEMM_QD, MPGEMM_MODE_INT8, m, n, k, D > 0 ? D : nd_auto_slices(c, k), true, c).total;
 }
 
 int mpgemm_nd_debug_split(int c, int operand, int rows, int cols, const double *X, int ldx, int D, int8_t *digits,
@@ -1284,7 +1358,7 @@ size_t mpgemm_workspace_bytes(int fmt, int mode, int m, int n, int k, int D) {
   if (D == kSlicesData || (D == 0 && data_mode(fmt, mode)))
     return mode == MPGEMM_MODE_FLOAT ? make_data_plan(fmt, m, n, k, false).total : 0;
   if (D <= 0) D = slices_for(fmt, mode, k);
-  return make_plan(fmt, mode, m, n, k, D).total;
+  return make_plan(fmt, mode, m, n, k, D, true).total;  // of either kind of call
 }
 int mpgemm_set_workspace(void *dev_ptr, size_t bytes) {
   if (dev_ptr && (reinterpret_cast<uintptr_t>(dev_ptr) & 255)) return -1;

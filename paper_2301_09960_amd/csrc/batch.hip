@@ -3,19 +3,20 @@
 //
 // A batch plan (per host thread, device, stream and shape: format, slice
 // form, and every product's m, n, k and D) owns one device workspace holding
-// every product's residuals, packed slices, maxima and exponents, plus
-//   - the split descriptors of all 2 x count operands and the GEMM
-//     descriptors (rewritten before every launch: they carry the caller's
-//     pointers),
-//   - prefix sums of the split tiles per operand and the (product, tile) work
-//     items of the persistent GEMM kernel, in one list per XCD (written once).
-// The graph holds: clear the maxima, one max-exponent launch and dmax pass
-// launches covering all operands, clear the work counter, and one persistent
-// GEMM launch.  In the INT8 form: clear the maxima and work counters, the
-// max-exponent launch, one residue split over all operands' blocks, the
-// persistent INT8 GEMMs over (product, tile, k chunk, unit group) items and one
-// combine launch over all products.  Kernels take the caller's pointers from the descriptors, so a
-// cached graph is replayed with new pointers after one small host-to-device
+// every product's planes, maxima and exponents, plus
+//   - the descriptors of all operands and products (rewritten before every
+//     launch: they carry the caller's pointers),
+//   - prefix sums of the split work per operand and the work items of the
+//     persistent GEMM kernels, in one list per XCD (written once).
+// The graph holds, for the products by residues: clear the maxima and work
+// counters, one max-exponent launch, one residue split over all operands'
+// blocks, the persistent INT8 GEMMs over (product, tile, k chunk, unit group)
+// items and the combine; for those by slices: the split (fused, or clear the
+// maxima, the max-exponent launch and dmax pass launches), clear the work
+// counter, and one persistent GEMM over (product, tile) items.  In the FLOAT form
+// the residue products' slice launches follow, and end at once unless the split
+// flagged a product.  Kernels take the caller's pointers from the descriptors, so
+// a cached graph is replayed with new pointers after one small host-to-device
 // copy of the descriptors.
 #include <hip/hip_runtime.h>
 
@@ -49,14 +50,6 @@ int batch_int8_cfg(int64_t m, int64_t n, int cfg_override) {
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
-
-struct ProductLayout {
-  int m, n, k, D, rho;
-  int64_t mbp, nbp, kbp;
-  size_t resid_a, resid_b, pack_a, pack_b, mu_a, mu_b, exp_a, exp_b;
-  // binary64/binary32 slices: operand split by the fused kernel (no residual)
-  bool fused_a = false, fused_b = false;
-};
 
 int tiles64(int64_t a, int64_t b) { return (int)(ceil_div(a, 64) * ceil_div(b, 64)); }
 
@@ -112,16 +105,18 @@ std::vector<Item> xcd_lists(const std::vector<Item> &items, Key key, int *bounds
 struct ResidueBatch {
   struct Slot {
     int g;  // product of the batch
-    int m, n, k, cfg, groups = 1;
+    int m, n, k, D, cfg, groups = 1;
     ResiduePlan plan;
     int64_t mbp, nbp, kbp;
-    size_t a, b, r, exp_a, exp_b, mu_a, mu_b, table;
+    size_t a, b, r, exp_a, exp_b, mu_a, mu_b, st_a, st_b, table;
   };
   std::vector<Slot> slots;
   int nw = 0, nwc = 0, tiles0 = 0, nitems1 = 0, nitems3 = 0;
   int64_t blocks = 0, blocksc = 0;
   size_t off_planes = 0, planes_bytes = 0, off_static = 0, off_items = 0, off_bounds = 0, off_counter = 0,
          off_zero = 0, zero_bytes = 0;
+  bool float_form = false;
+  size_t off_flags = 0;            // FLOAT form: a word set if any product is flagged, then one per product
   std::vector<int> prefix;         // 2 n + 1 max tiles, 2 n + 1 split blocks, n + 1 combine blocks
   std::vector<uint32_t> tables;    // the distinct combine tables
   std::vector<int4> items;
@@ -130,12 +125,13 @@ struct ResidueBatch {
   int nops() const { return 2 * (int)slots.size(); }
   size_t ops_bytes(size_t elem) const { return (size_t)nops() * elem; }
 
-  void add(int g, int m, int n, int k, const ResiduePlan &plan, int cfg) {
+  void add(int g, int m, int n, int k, int D, const ResiduePlan &plan, int cfg) {
     Slot s;
     s.g = g;
     s.m = m;
     s.n = n;
     s.k = k;
+    s.D = D;
     s.cfg = cfg;
     s.plan = plan;
     const int tb = int8_tile_blocks(cfg);
@@ -147,7 +143,8 @@ struct ResidueBatch {
 
   // Places everything in the workspace (take: bytes -> offset); elem: bytes of a maximum.
   template <typename Take>
-  void layout(Take take, size_t elem) {
+  void layout(Take take, size_t elem, bool float_slices) {
+    float_form = float_slices;
     for (Slot &s : slots) {
       nw = std::max(nw, s.plan.nw);
       nwc = std::max(nwc, s.plan.nwc);
@@ -167,7 +164,10 @@ struct ResidueBatch {
     for (Slot &s : slots) {
       s.mu_a = take((size_t)s.m * elem);
       s.mu_b = take((size_t)s.n * elem);
+      s.st_a = take(float_form ? (size_t)s.m * 4 : 0);
+      s.st_b = take(float_form ? (size_t)s.n * 4 : 0);
     }
+    off_flags = take(float_form ? (slots.size() + 1) * 4 : 0);
     off_counter = take(2 * kXcds * 4);
     zero_bytes = take(0) - off_zero;
 
@@ -294,6 +294,14 @@ struct ResidueBatch {
         o.len = s.k;
         o.orient = side;
         o.bits = s.plan.bits;
+        o.float_form = float_form;
+        if (float_form) {
+          o.slice_bits = (sizeof(T) == 8 ? 53 : 24) - rho_of(sizeof(T) == 8 ? 53 : 24, s.k);
+          o.passes = s.D;
+          o.state = reinterpret_cast<int *>(ws + (side == 0 ? s.st_a : s.st_b));
+          o.any = reinterpret_cast<int *>(ws + off_flags);
+          o.flag = o.any + i + 1;
+        }
         o.planes = reinterpret_cast<int8_t *>(ws + (side == 0 ? s.a : s.b));
         o.nbp = side == 0 ? s.mbp : s.nbp;
         o.kbp = s.kbp;
@@ -335,23 +343,209 @@ struct OperandShape {
   int64_t kbp, nbp, nvec;
 };
 
+// The products of a batch that are formed from slices: the split of all their
+// operands and one persistent slice-product kernel over (product, tile) items
+// in per-XCD lists.  A FLOAT-form batch has two: the products that do not go by
+// residues, and, behind them, those that do, whose kernels run only for the
+// products that the residue split flagged.
+template <typename T, int C>
+struct PlainBatch {
+  struct Slot {
+    int g;  // product of the batch
+    int m, n, k, D, rho;
+    int64_t mbp, nbp, kbp;
+    size_t resid_a, resid_b, pack_a, pack_b, mu_a, mu_b, exp_a, exp_b;
+    bool fused_a, fused_b;  // operand split by the fused kernel (no residual)
+    size_t flag;            // offset of its condition word (SIZE_MAX: always formed)
+  };
+  std::vector<Slot> slots;
+  size_t off_static = 0, off_items = 0, off_bounds = 0, off_counter = 0, off_mu = 0, mu_bytes = 0;
+  size_t off_any = SIZE_MAX;  // condition word of all launches
+  int tiles0 = 0, tilesp = 0, stripsf = 0, dpass = 0;
+  int fused_nt = 512;  // threads of the fused-split workgroups
+  std::vector<int> prefix;  // 2 n + 1 max tiles, 2 n + 1 pass tiles, 2 n + 1 fused strips
+  std::vector<int2> items;
+  int bounds[kXcds + 1] = {};
+
+  size_t ops_bytes() const { return 2 * slots.size() * sizeof(SplitOperand<T>); }
+  size_t stage_bytes() const { return ops_bytes() + slots.size() * sizeof(PlainGemmDesc); }
+
+  void add(int g, int m, int n, int k, int D) {
+    Slot s{};
+    s.g = g;
+    s.m = m;
+    s.n = n;
+    s.k = k;
+    s.D = D;
+    s.rho = rho_of(sizeof(T) == 8 ? 53 : 24, k);
+    s.mbp = nblocks_padded(m);
+    s.nbp = nblocks_padded(n);
+    s.kbp = kblocks_padded(k);
+    s.flag = SIZE_MAX;
+    slots.push_back(s);
+  }
+
+  template <typename Take>
+  void layout(Take take, int split_kernel) {
+    const size_t w = sizeof(T);
+    // one fused-split launch: 512-thread workgroups when every product's vectors
+    // allow them, else 1024
+    for (const Slot &s : slots)
+      if (fused_threads<T, C>(s.kbp * kKBlk) == 1024) fused_nt = 1024;
+    for (Slot &s : slots) {
+      s.fused_a = split_kernel == 0 && fused_strips<T, C>(OperandShape{s.kbp, s.mbp, s.m}, fused_nt) >= 0;
+      s.fused_b = split_kernel == 0 && fused_strips<T, C>(OperandShape{s.kbp, s.nbp, s.n}, fused_nt) >= 0;
+      s.resid_a = take(s.D > 1 && !s.fused_a ? (size_t)C * s.m * s.k * w : 0);
+      s.resid_b = take(s.D > 1 && !s.fused_b ? (size_t)C * s.k * s.n * w : 0);
+      s.pack_a = take((size_t)s.D * s.mbp * s.kbp * 256 * w);
+      s.pack_b = take((size_t)s.D * s.nbp * s.kbp * 256 * w);
+      s.exp_a = take((size_t)s.D * s.m * 4);
+      s.exp_b = take((size_t)s.D * s.n * 4);
+    }
+    // one region for all maxima (cleared by a single fill)
+    size_t mo = 0;
+    for (Slot &s : slots) {
+      s.mu_a = mo;
+      mo += (size_t)s.D * s.m * w;
+      s.mu_b = mo;
+      mo += (size_t)s.D * s.n * w;
+    }
+    off_mu = take(mo);
+    mu_bytes = (mo + 3) / 4 * 4;
+    for (Slot &s : slots) {
+      s.mu_a += off_mu;
+      s.mu_b += off_mu;
+    }
+
+    // prefix sums of the split work.  An operand whose vectors fit a fused
+    // workgroup is split by the fused kernel alone; the others by the max and
+    // pass kernels.
+    const int n = 2 * (int)slots.size();
+    prefix.assign((size_t)3 * (n + 1), 0);
+    int *pre0 = prefix.data(), *prep = pre0 + n + 1, *pref = prep + n + 1;
+    for (int i = 0; i < n; ++i) {
+      const Slot &s = slots[i / 2];
+      const bool side_b = i % 2 == 1, fused = side_b ? s.fused_b : s.fused_a;
+      const int64_t nvec = side_b ? s.n : s.m, nbp = side_b ? s.nbp : s.mbp;
+      pref[i + 1] = pref[i] + (fused ? fused_strips<T, C>(OperandShape{s.kbp, nbp, nvec}, fused_nt) : 0);
+      pre0[i + 1] = pre0[i] + (fused ? 0 : tiles64(nvec, s.k));
+      prep[i + 1] = prep[i] + (fused ? 0 : tiles64(nbp * kBlk, s.kbp * kKBlk));
+      if (!fused) dpass = std::max(dpass, s.D);
+    }
+    tiles0 = pre0[n];
+    tilesp = prep[n];
+    stripsf = pref[n];
+
+    // work items: (slot, tile)
+    struct Item {
+      int slot, tile;
+      int64_t cost;
+    };
+    std::vector<Item> list;
+    for (int i = 0; i < (int)slots.size(); ++i) {
+      const Slot &s = slots[i];
+      const int ntiles = (int)((s.mbp / kTileBlocks) * (s.nbp / kTileBlocks));
+      const int64_t cost = (int64_t)s.D * (s.D + 1) / 2 * s.kbp;
+      for (int t = 0; t < ntiles; ++t) list.push_back({i, t, cost});
+    }
+    list = xcd_lists(list, [](const Item &it) { return (int64_t)it.slot; }, bounds);
+    for (const Item &it : list) items.push_back(make_int2(it.slot, it.tile));
+    off_static = take(prefix.size() * 4);
+    off_items = take(items.size() * sizeof(int2));
+    off_bounds = take(sizeof(bounds));
+    off_counter = take(kXcds * 4);
+  }
+
+  bool upload(char *ws) const {
+    if (slots.empty()) return true;
+    return hipMemcpy(ws + off_static, prefix.data(), prefix.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
+           hipMemcpy(ws + off_items, items.data(), items.size() * sizeof(int2), hipMemcpyHostToDevice) == hipSuccess &&
+           hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
+  }
+
+  // The launch sequence, with the descriptors at `off` of the workspace.
+  hipError_t launch(char *ws, size_t off, int gemm_layout, hipStream_t st) const {
+    if (slots.empty()) return hipSuccess;
+    const int n = 2 * (int)slots.size();
+    const int *pre0 = reinterpret_cast<const int *>(ws + off_static), *prep = pre0 + n + 1, *pref = prep + n + 1;
+    const int *any = off_any == SIZE_MAX ? nullptr : reinterpret_cast<const int *>(ws + off_any);
+    hipError_t e = launch_split_plain_batched<T, C>(reinterpret_cast<const SplitOperand<T> *>(ws + off), pre0, prep,
+                                                    pref, n, tiles0, tilesp, stripsf, fused_nt, dpass, ws + off_mu,
+                                                    (int64_t)(mu_bytes / 4), any, st);
+    if (e == hipSuccess) e = launch_fill32(ws + off_counter, kXcds, 0u, st);
+    if (e == hipSuccess)
+      e = launch_gemm_plain_batched<T, C>(reinterpret_cast<const PlainGemmDesc *>(ws + off + ops_bytes()),
+                                          reinterpret_cast<const int2 *>(ws + off_items),
+                                          reinterpret_cast<const int *>(ws + off_bounds),
+                                          reinterpret_cast<int *>(ws + off_counter),
+                                          std::min((int)items.size(), kPersistentGrid), gemm_layout, any, st);
+    return e;
+  }
+
+  // Descriptors carrying a call's pointers, into the pinned stage.
+  void write(char *ws, char *stage, int last_slice, const T *const *A, const int *lda, const T *const *B,
+             const int *ldb, T *const *Cm, const int *ldc) const {
+    auto *ops = reinterpret_cast<SplitOperand<T> *>(stage);
+    auto *descs = reinterpret_cast<PlainGemmDesc *>(stage + ops_bytes());
+    for (size_t i = 0; i < slots.size(); ++i) {
+      const Slot &s = slots[i];
+      const int g = s.g;
+      const int *run_if = s.flag == SIZE_MAX ? nullptr : reinterpret_cast<const int *>(ws + s.flag);
+      for (int side = 0; side < 2; ++side) {
+        SplitOperand<T> o{};
+        o.X = side == 0 ? A[g] : B[g];
+        o.comp_stride = side == 0 ? (int64_t)lda[g] * s.k : (int64_t)ldb[g] * s.n;
+        o.sv = side == 0 ? 1 : ldb[g];
+        o.sp = side == 0 ? lda[g] : 1;
+        o.nvec = side == 0 ? s.m : s.n;
+        o.len = s.k;
+        o.orient = side;
+        o.resid = reinterpret_cast<T *>(ws + (side == 0 ? s.resid_a : s.resid_b));
+        o.packed = ws + (side == 0 ? s.pack_a : s.pack_b);
+        o.nbp = side == 0 ? s.mbp : s.nbp;
+        o.kbp = s.kbp;
+        o.mu = ws + (side == 0 ? s.mu_a : s.mu_b);
+        o.exps = reinterpret_cast<int *>(ws + (side == 0 ? s.exp_a : s.exp_b));
+        o.D = s.D;
+        o.rho = s.rho;
+        o.last_literal = last_slice;
+        o.run_if = run_if;
+        ops[2 * i + side] = o;
+      }
+      PlainGemmDesc d{};
+      d.Apk = ws + s.pack_a;
+      d.Bpk = ws + s.pack_b;
+      d.mbp = s.mbp;
+      d.nbp = s.nbp;
+      d.kbp = s.kbp;
+      d.m = s.m;
+      d.n = s.n;
+      d.D = s.D;
+      d.ldc = ldc[g];
+      d.C = Cm[g];
+      d.c_stride = (int64_t)ldc[g] * s.n;
+      d.run_if = run_if;
+      descs[i] = d;
+    }
+  }
+};
+
+// The plan of a batch, without its format's part.
 struct BatchPlan {
   int device = 0, fmt = 0, mode = 0, layout = 1, int8_tile = 0, split_kernel = 0, last_slice = 0;
+  bool automatic = true;  // slice counts chosen by the library
   hipStream_t stream = nullptr;
   std::vector<int> m, n, k, D;
-  std::vector<ProductLayout> prod;
-  std::vector<int> live;  // products with m, n, k > 0
+  ResidueBatch res;  // the products formed by residues
+  bool empty = true;
   char *ws = nullptr;
-  size_t off_ops = 0, off_descs = 0, desc_bytes = 0, off_prefix0 = 0, off_prefixp = 0, off_prefixf = 0,
-         off_items = 0, off_bounds = 0, off_counter = 0, off_mu = 0, mu_bytes = 0, total = 0;
-  int nops = 0, tiles0 = 0, tilesp = 0, stripsf = 0, dmax = 0, nitems = 0;
-  int fused_nt = 1024;  // threads of the fused-split workgroups
+  size_t off_desc = 0, desc_bytes = 0, total = 0;
   void *stage = nullptr;
   hipEvent_t stage_done = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  ResidueBatch res;  // the products formed by residues
   uint64_t last_use = 0;
+  virtual ~BatchPlan() {}
 
   void release() {
     if (exec) (void)hipGraphExecDestroy(exec);
@@ -381,282 +575,95 @@ BatchCache &cache() {
   return *g_batch;
 }
 
+// A plan of one format: the products by slices, by residues, and, in the FLOAT
+// form, the residue products again by slices where the split flagged them.
 template <typename T, int C>
-int build_plan(BatchPlan &p, hipStream_t st) {
-  const size_t w = sizeof(T);
-  const int S = sizeof(T) == 8 ? 53 : 24;
-  const int count = (int)p.m.size();
-  size_t o = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = o;
-    o += align256(bytes);
-    return at;
-  };
-  p.prod.resize(count);
-  p.live.clear();
-  p.dmax = 0;
-  // one fused-split launch for the batch: 512-thread workgroups when every
-  // product's vectors allow them, else 1024
-  p.fused_nt = 512;
-  for (int g = 0; g < count; ++g)
-    if (p.m[g] > 0 && p.n[g] > 0 && p.k[g] > 0 && fused_threads<T, C>(kblocks_padded(p.k[g]) * kKBlk) == 1024)
-      p.fused_nt = 1024;
-  for (int g = 0; g < count; ++g) {
-    ProductLayout &L = p.prod[g];
-    L.m = p.m[g];
-    L.n = p.n[g];
-    L.k = p.k[g];
-    L.D = p.D[g];
-    if (L.m <= 0 || L.n <= 0 || L.k <= 0) continue;
-    p.live.push_back(g);
-    L.rho = rho_of(S, L.k);
-    L.mbp = nblocks_padded(L.m);
-    L.nbp = nblocks_padded(L.n);
-    L.kbp = kblocks_padded(L.k);
-    L.fused_a = p.split_kernel == 0 && fused_strips<T, C>(OperandShape{L.kbp, L.mbp, L.m}, p.fused_nt) >= 0;
-    L.fused_b = p.split_kernel == 0 && fused_strips<T, C>(OperandShape{L.kbp, L.nbp, L.n}, p.fused_nt) >= 0;
-    L.resid_a = take(L.D > 1 && !L.fused_a ? (size_t)C * L.m * L.k * w : 0);
-    L.resid_b = take(L.D > 1 && !L.fused_b ? (size_t)C * L.k * L.n * w : 0);
-    L.pack_a = take((size_t)L.D * L.mbp * L.kbp * 256 * w);
-    L.pack_b = take((size_t)L.D * L.nbp * L.kbp * 256 * w);
-    L.exp_a = take((size_t)L.D * L.m * 4);
-    L.exp_b = take((size_t)L.D * L.n * 4);
-    p.dmax = std::max(p.dmax, L.D);
-  }
-  // one region for all maxima (cleared by a single fill)
-  p.off_mu = o;
-  size_t mo = 0;
-  for (int g : p.live) {
-    ProductLayout &L = p.prod[g];
-    L.mu_a = p.off_mu + mo;
-    mo += (size_t)L.D * L.m * w;
-    L.mu_b = p.off_mu + mo;
-    mo += (size_t)L.D * L.n * w;
-  }
-  p.mu_bytes = (mo + 3) / 4 * 4;
-  o = p.off_mu + align256(mo);
-  p.nops = 2 * (int)p.live.size();
-  p.off_ops = take(0);
-  p.off_descs = p.off_ops + (size_t)p.nops * sizeof(SplitOperand<T>);
-  p.desc_bytes = (size_t)p.nops * sizeof(SplitOperand<T>) + p.live.size() * sizeof(PlainGemmDesc);
-  o = p.off_ops + align256(p.desc_bytes);
-  p.off_prefix0 = take((size_t)(p.nops + 1) * 4);
-  p.off_prefixp = take((size_t)(p.nops + 1) * 4);
-  p.off_prefixf = take((size_t)(p.nops + 1) * 4);
+struct FormatPlan : BatchPlan {
+  PlainBatch<T, C> plain, fallback;
+  size_t off_plain = 0, off_fallback = 0, off_ops = 0, off_res = 0;  // descriptors, from off_desc
 
-  // work items: (product slot, tile)
-  struct Item {
-    int slot, tile;
-    int64_t cost;
-  };
-  std::vector<Item> items;
-  for (int slot = 0; slot < (int)p.live.size(); ++slot) {
-    const ProductLayout &L = p.prod[p.live[slot]];
-    const int ntiles = (int)((L.mbp / kTileBlocks) * (L.nbp / kTileBlocks));
-    const int64_t cost = (int64_t)L.D * (L.D + 1) / 2 * L.kbp;
-    for (int t = 0; t < ntiles; ++t) items.push_back({slot, t, cost});
-  }
-  int bounds[kXcds + 1];
-  items = xcd_lists(items, [](const Item &it) { return (int64_t)it.slot; }, bounds);
-  p.nitems = (int)items.size();
-  p.off_items = take(items.size() * sizeof(int2));
-  p.off_bounds = take(sizeof(bounds));
-  p.off_counter = take(kXcds * 4);
-  p.total = o;
-
-  if (hipMalloc(&p.ws, p.total > 0 ? p.total : 256) != hipSuccess) {
-    (void)hipGetLastError();
-    p.ws = nullptr;
-    return MPGEMM_ERR_WORKSPACE;
-  }
-  if (hipHostMalloc(&p.stage, p.desc_bytes > 0 ? p.desc_bytes : 64, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    p.stage = nullptr;
-    return MPGEMM_ERR_WORKSPACE;
-  }
-  if (hipEventCreateWithFlags(&p.stage_done, hipEventDisableTiming) != hipSuccess) return MPGEMM_ERR_HIP;
-
-  // static device data: prefix sums of the split work and the work list.  An
-  // operand whose vectors fit a fused workgroup is split by the fused kernel
-  // alone; the others by the max and pass kernels.
-  std::vector<int> pre0(p.nops + 1, 0), prep(p.nops + 1, 0), pref(p.nops + 1, 0);
-  int dpass = 0;
-  for (int slot = 0; slot < (int)p.live.size(); ++slot) {
-    const ProductLayout &L = p.prod[p.live[slot]];
-    for (int side = 0; side < 2; ++side) {
-      const int i = 2 * slot + side;
-      const int64_t nvec = side == 0 ? L.m : L.n, nbp = side == 0 ? L.mbp : L.nbp;
-      const bool fused = side == 0 ? L.fused_a : L.fused_b;
-      pref[i + 1] = pref[i] + (fused ? fused_strips<T, C>(OperandShape{L.kbp, nbp, nvec}, p.fused_nt) : 0);
-      pre0[i + 1] = pre0[i] + (fused ? 0 : tiles64(nvec, L.k));
-      prep[i + 1] = prep[i] + (fused ? 0 : tiles64(nbp * kBlk, L.kbp * kKBlk));
-      if (!fused) dpass = std::max(dpass, L.D);
+  int build() {
+    const int count = (int)m.size();
+    size_t o = 0;
+    auto take = [&](size_t bytes) {
+      const size_t at = o;
+      o += align256(bytes);
+      return at;
+    };
+    for (int g = 0; g < count; ++g) {
+      if (m[g] <= 0 || n[g] <= 0 || k[g] <= 0) continue;
+      empty = false;
+      ResiduePlan rp;
+      if (mode == MPGEMM_MODE_INT8) {
+        if (!residue_plan(7 * D[g] - 1, k[g], rp)) return MPGEMM_ERR_TOO_LARGE;  // none: D <= 40, k <= 2^20
+      } else if (!automatic || last_slice != 0 || !float_residue_plan(fmt, D[g], k[g], rp)) {
+        plain.add(g, m[g], n[g], k[g], D[g]);
+        continue;
+      } else {
+        fallback.add(g, m[g], n[g], k[g], D[g]);
+      }
+      res.add(g, m[g], n[g], k[g], D[g], rp, batch_int8_cfg(m[g], n[g], int8_tile));
     }
-  }
-  p.tiles0 = pre0[p.nops];
-  p.tilesp = prep[p.nops];
-  p.stripsf = pref[p.nops];
-  std::vector<int2> it2(items.size());
-  for (size_t i = 0; i < items.size(); ++i) it2[i] = make_int2(items[i].slot, items[i].tile);
-  if (hipMemcpy(p.ws + p.off_prefix0, pre0.data(), pre0.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p.ws + p.off_prefixp, prep.data(), prep.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(p.ws + p.off_prefixf, pref.data(), pref.size() * 4, hipMemcpyHostToDevice) != hipSuccess ||
-      (it2.size() && hipMemcpy(p.ws + p.off_items, it2.data(), it2.size() * sizeof(int2), hipMemcpyHostToDevice) !=
-                         hipSuccess) ||
-      hipMemcpy(p.ws + p.off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) != hipSuccess)
-    return MPGEMM_ERR_HIP;
+    plain.layout(take, split_kernel);
+    fallback.layout(take, split_kernel);
+    res.layout(take, sizeof(T), mode == MPGEMM_MODE_FLOAT);
+    if (res.blocks > 0x7fffffffLL || res.blocksc > 0x7fffffffLL / 4) return MPGEMM_ERR_TOO_LARGE;
+    for (size_t i = 0; i < fallback.slots.size(); ++i) fallback.slots[i].flag = res.off_flags + 4 * (i + 1);
+    fallback.off_any = res.off_flags;
+    off_desc = take(0);
+    off_plain = 0;
+    off_fallback = off_plain + plain.stage_bytes();
+    off_ops = off_fallback + fallback.stage_bytes();
+    off_res = off_ops + res.ops_bytes(sizeof(ResidueOperand<T>));
+    desc_bytes = off_res + res.slots.size() * sizeof(ResidueDesc);
+    take(desc_bytes);
+    total = o;
 
-  // capture the launch sequence on a private stream
-  BatchCache &bc = cache();
-  hipStream_t &cs = bc.capture[p.device & 63];
-  if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return MPGEMM_ERR_HIP;
-  if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return MPGEMM_ERR_HIP;
-  hipError_t e = launch_split_plain_batched<T, C>(
-      reinterpret_cast<const SplitOperand<T> *>(p.ws + p.off_ops), reinterpret_cast<const int *>(p.ws + p.off_prefix0),
-      reinterpret_cast<const int *>(p.ws + p.off_prefixp), reinterpret_cast<const int *>(p.ws + p.off_prefixf),
-      p.nops, p.tiles0, p.tilesp, p.stripsf, p.fused_nt, dpass, p.ws + p.off_mu, (int64_t)(p.mu_bytes / 4), cs);
-  if (e == hipSuccess) e = launch_fill32(p.ws + p.off_counter, kXcds, 0u, cs);
-  if (e == hipSuccess)
-    e = launch_gemm_plain_batched<T, C>(reinterpret_cast<const PlainGemmDesc *>(p.ws + p.off_descs),
-                                        reinterpret_cast<const int2 *>(p.ws + p.off_items),
-                                        reinterpret_cast<const int *>(p.ws + p.off_bounds),
-                                        reinterpret_cast<int *>(p.ws + p.off_counter),
-                                        std::min(p.nitems, kPersistentGrid), p.layout, cs);
-  hipGraph_t graph = nullptr;
-  const hipError_t e2 = hipStreamEndCapture(cs, &graph);
-  if (e != hipSuccess || e2 != hipSuccess || !graph) {
-    if (graph) (void)hipGraphDestroy(graph);
-    (void)hipGetLastError();
-    return MPGEMM_ERR_HIP;
-  }
-  p.graph = graph;
-  if (hipGraphInstantiate(&p.exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    return MPGEMM_ERR_HIP;
-  }
-  (void)st;
-  return 0;
-}
+    if (hipMalloc(&ws, total > 0 ? total : 256) != hipSuccess) {
+      (void)hipGetLastError();
+      ws = nullptr;
+      return MPGEMM_ERR_WORKSPACE;
+    }
+    if (hipHostMalloc(&stage, desc_bytes > 0 ? desc_bytes : 64, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      stage = nullptr;
+      return MPGEMM_ERR_WORKSPACE;
+    }
+    if (hipEventCreateWithFlags(&stage_done, hipEventDisableTiming) != hipSuccess) return MPGEMM_ERR_HIP;
+    if (!plain.upload(ws) || !fallback.upload(ws) || !res.upload(ws)) return MPGEMM_ERR_HIP;
 
-// Descriptors carrying this call's pointers, written into the pinned stage.
-template <typename T, int C>
-void write_descriptors(BatchPlan &p, const T *const *A, const int *lda, const T *const *B, const int *ldb,
-                       T *const *Cm, const int *ldc) {
-  SplitOperand<T> *ops = static_cast<SplitOperand<T> *>(p.stage);
-  PlainGemmDesc *descs = reinterpret_cast<PlainGemmDesc *>(static_cast<char *>(p.stage) +
-                                                           (size_t)p.nops * sizeof(SplitOperand<T>));
-  for (int slot = 0; slot < (int)p.live.size(); ++slot) {
-    const int g = p.live[slot];
-    const ProductLayout &L = p.prod[g];
-    SplitOperand<T> a{}, b{};
-    a.X = A[g];
-    a.comp_stride = (int64_t)lda[g] * L.k;
-    a.sv = 1;
-    a.sp = lda[g];
-    a.nvec = L.m;
-    a.len = L.k;
-    a.orient = 0;
-    a.resid = reinterpret_cast<T *>(p.ws + L.resid_a);
-    a.packed = p.ws + L.pack_a;
-    a.nbp = L.mbp;
-    a.kbp = L.kbp;
-    a.mu = p.ws + L.mu_a;
-    a.exps = reinterpret_cast<int *>(p.ws + L.exp_a);
-    a.D = L.D;
-    a.rho = L.rho;
-    a.last_literal = p.last_slice;
-    b.X = B[g];
-    b.comp_stride = (int64_t)ldb[g] * L.n;
-    b.sv = ldb[g];
-    b.sp = 1;
-    b.nvec = L.n;
-    b.len = L.k;
-    b.orient = 1;
-    b.resid = reinterpret_cast<T *>(p.ws + L.resid_b);
-    b.packed = p.ws + L.pack_b;
-    b.nbp = L.nbp;
-    b.kbp = L.kbp;
-    b.mu = p.ws + L.mu_b;
-    b.exps = reinterpret_cast<int *>(p.ws + L.exp_b);
-    b.D = L.D;
-    b.rho = L.rho;
-    b.last_literal = p.last_slice;
-    ops[2 * slot] = a;
-    ops[2 * slot + 1] = b;
-    PlainGemmDesc d{};
-    d.Apk = p.ws + L.pack_a;
-    d.Bpk = p.ws + L.pack_b;
-    d.mbp = L.mbp;
-    d.nbp = L.nbp;
-    d.kbp = L.kbp;
-    d.m = L.m;
-    d.n = L.n;
-    d.D = L.D;
-    d.ldc = ldc[g];
-    d.C = Cm[g];
-    d.c_stride = (int64_t)ldc[g] * L.n;
-    descs[slot] = d;
+    // capture the launch sequence on a private stream
+    BatchCache &bc = cache();
+    hipStream_t &cs = bc.capture[device & 63];
+    if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return MPGEMM_ERR_HIP;
+    if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return MPGEMM_ERR_HIP;
+    hipError_t e = plain.launch(ws, off_desc + off_plain, layout, cs);
+    if (e == hipSuccess) e = res.template launch<T, C>(ws, off_desc + off_ops, off_desc + off_res, cs);
+    if (e == hipSuccess) e = fallback.launch(ws, off_desc + off_fallback, layout, cs);
+    hipGraph_t captured = nullptr;
+    const hipError_t e2 = hipStreamEndCapture(cs, &captured);
+    if (e != hipSuccess || e2 != hipSuccess || !captured) {
+      if (captured) (void)hipGraphDestroy(captured);
+      (void)hipGetLastError();
+      return MPGEMM_ERR_HIP;
+    }
+    graph = captured;
+    if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
+      (void)hipGetLastError();
+      return MPGEMM_ERR_HIP;
+    }
+    return 0;
   }
-}
 
-// INT8-form batch: every product by residues.
-template <int C>
-int build_plan_int8(BatchPlan &p, int cfg_override) {
-  const int count = (int)p.m.size();
-  size_t o = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = o;
-    o += align256(bytes);
-    return at;
-  };
-  p.live.clear();
-  for (int g = 0; g < count; ++g) {
-    if (p.m[g] <= 0 || p.n[g] <= 0 || p.k[g] <= 0) continue;
-    ResiduePlan plan;
-    if (!residue_plan(7 * p.D[g] - 1, p.k[g], plan)) return MPGEMM_ERR_TOO_LARGE;  // none: D <= 40, k <= 2^20
-    p.live.push_back(g);
-    p.res.add(g, p.m[g], p.n[g], p.k[g], plan, batch_int8_cfg(p.m[g], p.n[g], cfg_override));
+  // Descriptors carrying this call's pointers, into the pinned stage.
+  void write(const T *const *A, const int *lda, const T *const *B, const int *ldb, T *const *Cm, const int *ldc) {
+    char *to = static_cast<char *>(stage);
+    plain.write(ws, to + off_plain, last_slice, A, lda, B, ldb, Cm, ldc);
+    fallback.write(ws, to + off_fallback, last_slice, A, lda, B, ldb, Cm, ldc);
+    res.write<T>(ws, reinterpret_cast<ResidueOperand<T> *>(to + off_ops), reinterpret_cast<ResidueDesc *>(to + off_res),
+                 A, lda, B, ldb, Cm, ldc);
   }
-  p.res.layout(take, sizeof(double));
-  if (p.res.blocks > 0x7fffffffLL || p.res.blocksc > 0x7fffffffLL / 4) return MPGEMM_ERR_TOO_LARGE;
-  p.off_ops = take(0);
-  p.off_descs = p.off_ops + p.res.ops_bytes(sizeof(ResidueOperand<double>));
-  p.desc_bytes = p.off_descs - p.off_ops + p.res.slots.size() * sizeof(ResidueDesc);
-  take(p.desc_bytes);
-  p.total = o;
-
-  if (hipMalloc(&p.ws, p.total > 0 ? p.total : 256) != hipSuccess) {
-    (void)hipGetLastError();
-    p.ws = nullptr;
-    return MPGEMM_ERR_WORKSPACE;
-  }
-  if (hipHostMalloc(&p.stage, p.desc_bytes > 0 ? p.desc_bytes : 64, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    p.stage = nullptr;
-    return MPGEMM_ERR_WORKSPACE;
-  }
-  if (hipEventCreateWithFlags(&p.stage_done, hipEventDisableTiming) != hipSuccess) return MPGEMM_ERR_HIP;
-  if (!p.res.upload(p.ws)) return MPGEMM_ERR_HIP;
-
-  BatchCache &bc = cache();
-  hipStream_t &cs = bc.capture[p.device & 63];
-  if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return MPGEMM_ERR_HIP;
-  if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return MPGEMM_ERR_HIP;
-  const hipError_t e = p.res.template launch<double, C>(p.ws, p.off_ops, p.off_descs, cs);
-  hipGraph_t graph = nullptr;
-  const hipError_t e2 = hipStreamEndCapture(cs, &graph);
-  if (e != hipSuccess || e2 != hipSuccess || !graph) {
-    if (graph) (void)hipGraphDestroy(graph);
-    (void)hipGetLastError();
-    return MPGEMM_ERR_HIP;
-  }
-  p.graph = graph;
-  if (hipGraphInstantiate(&p.exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-    (void)hipGetLastError();
-    return MPGEMM_ERR_HIP;
-  }
-  return 0;
-}
+};
 
 template <typename T, int C>
 int run_batched(int fmt, int count, const int *m, const int *n, const int *k, const T *const *A, const int *lda,
@@ -677,6 +684,7 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
   const int mode = thread_mode(fmt);
   if (mode != MPGEMM_MODE_FLOAT && (mode != MPGEMM_MODE_INT8 || sizeof(T) != 8)) return MPGEMM_ERR_UNSUPPORTED;
   const int layout = layout_for(fmt);
+  const bool automatic = automatic_slices(fmt, mode);
   if (count == 0) return 0;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return MPGEMM_ERR_HIP;
@@ -693,15 +701,15 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
     }
 
   BatchCache &bc = cache();
-  BatchPlan *plan = nullptr;
+  FormatPlan<T, C> *plan = nullptr;
   for (BatchPlan *p : bc.plans)
     if (p->device == dev && p->stream == st && p->fmt == fmt && p->mode == mode && p->layout == layout &&
         p->int8_tile == int8_tile_override() && p->split_kernel == split_kernel_override() &&
-        p->last_slice == last_slice_option() &&
+        p->last_slice == last_slice_option() && p->automatic == automatic &&
         (int)p->m.size() == count &&
         std::equal(p->m.begin(), p->m.end(), m) && std::equal(p->n.begin(), p->n.end(), n) &&
         std::equal(p->k.begin(), p->k.end(), k) && p->D == Ds) {
-      plan = p;
+      plan = static_cast<FormatPlan<T, C> *>(p);  // the format decides T and C
       break;
     }
   if (!plan) {
@@ -713,7 +721,7 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
       delete *oldest;
       bc.plans.erase(oldest);
     }
-    plan = new BatchPlan();
+    plan = new FormatPlan<T, C>();
     plan->device = dev;
     plan->stream = st;
     plan->fmt = fmt;
@@ -722,15 +730,12 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
     plan->int8_tile = int8_tile_override();
     plan->split_kernel = split_kernel_override();
     plan->last_slice = last_slice_option();
+    plan->automatic = automatic;
     plan->m.assign(m, m + count);
     plan->n.assign(n, n + count);
     plan->k.assign(k, k + count);
     plan->D = Ds;
-    if (mode == MPGEMM_MODE_INT8) {
-      if constexpr (sizeof(T) == 8) s = build_plan_int8<C>(*plan, int8_tile_override());
-    } else {
-      s = build_plan<T, C>(*plan, st);
-    }
+    s = plan->build();
     if (s) {
       plan->release();
       delete plan;
@@ -739,25 +744,15 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
     bc.plans.push_back(plan);
   }
   plan->last_use = ++bc.clock;
-  if (plan->live.empty()) return 0;
+  if (plan->empty) return 0;
 
   // the stage may still feed the previous launch's descriptor copy
   if (hipEventSynchronize(plan->stage_done) != hipSuccess) return MPGEMM_ERR_HIP;
-  if constexpr (sizeof(T) == 8) {
-    if (mode == MPGEMM_MODE_INT8)
-      plan->res.write<T>(plan->ws, static_cast<ResidueOperand<T> *>(plan->stage),
-                         reinterpret_cast<ResidueDesc *>(static_cast<char *>(plan->stage) +
-                                                         plan->res.ops_bytes(sizeof(ResidueOperand<T>))),
-                         A, lda, B, ldb, Cm, ldc);
-    else
-      write_descriptors<T, C>(*plan, A, lda, B, ldb, Cm, ldc);
-  } else {
-    write_descriptors<T, C>(*plan, A, lda, B, ldb, Cm, ldc);
-  }
+  plan->write(A, lda, B, ldb, Cm, ldc);
   hipEvent_t ev[3];
   profile_mark3(ev);
   if (ev[0]) (void)hipEventRecord(ev[0], st);
-  if (hipMemcpyAsync(plan->ws + plan->off_ops, plan->stage, plan->desc_bytes, hipMemcpyHostToDevice, st) !=
+  if (hipMemcpyAsync(plan->ws + plan->off_desc, plan->stage, plan->desc_bytes, hipMemcpyHostToDevice, st) !=
           hipSuccess ||
       hipEventRecord(plan->stage_done, st) != hipSuccess)
     return MPGEMM_ERR_HIP;

@@ -308,7 +308,7 @@ hipError_t launch_abs_lead_product(const SplitOperand<T> &a, const SplitOperand<
   if (e != hipSuccess) return e;
   // |A_0| |B_0| as one pair on the binary64 slice-product kernel, into two planes of raw
   return launch_gemm_plain<double, 2>(pack_a, pack_b, a.nbp, b.nbp, a.kbp, m, n, 1, raw, m, (int64_t)m * n, -1,
-                                      nullptr, 0, layout, st);
+                                      nullptr, 0, layout, nullptr, st);
 }
 
 template <typename T>

@@ -427,8 +427,10 @@ __device__ __forceinline__ void gemm_plain_tile(const T *__restrict__ Apk, const
 template <typename T, int C, int LAYOUT>
 __global__ __launch_bounds__(64 * Layout<LAYOUT>::WM * Layout<LAYOUT>::WN, waves_of(LAYOUT, C, (int)sizeof(T))) void k_gemm_plain(
     const T *__restrict__ Apk, const T *__restrict__ Bpk, int64_t mbp, int64_t nbp, int64_t kbp, int m, int n, int D,
-    T *__restrict__ Cout, int ldc, int64_t c_stride, int single_pair, double *__restrict__ Cdbg, int lddbg) {
+    T *__restrict__ Cout, int ldc, int64_t c_stride, int single_pair, double *__restrict__ Cdbg, int lddbg,
+    const int *__restrict__ run_if) {
   __shared__ __attribute__((aligned(16))) T lds[stages_of<T>()][stage_elems<T>()];
+  if (!runs(run_if)) return;
   int tm, tn;
   tile_coords(blockIdx.x, gridDim.x, (int)(mbp / kTileBlocks), (int)(nbp / kTileBlocks), tm, tn);
   gemm_plain_tile<T, C, LAYOUT>(Apk, Bpk, mbp, nbp, kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg, tm,
@@ -470,9 +472,10 @@ __global__ __launch_bounds__(64 * Layout<LAYOUT>::WM * Layout<LAYOUT>::WN, waves
 template <typename T, int C, int LAYOUT>
 __global__ __launch_bounds__(64 * Layout<LAYOUT>::WM * Layout<LAYOUT>::WN, waves_of(LAYOUT, C, (int)sizeof(T))) void k_gemm_plain_batched(
     const PlainGemmDesc *__restrict__ descs, const int2 *__restrict__ items, const int *__restrict__ bounds,
-    int *__restrict__ counters) {
+    int *__restrict__ counters, const int *__restrict__ run_if) {
   __shared__ __attribute__((aligned(16))) T lds[stages_of<T>()][stage_elems<T>()];
   __shared__ int next;
+  if (!runs(run_if)) return;
   for (;;) {
     if (threadIdx.x == 0) next = take_item(counters, bounds, blockIdx.x);
     __syncthreads();
@@ -481,6 +484,7 @@ __global__ __launch_bounds__(64 * Layout<LAYOUT>::WM * Layout<LAYOUT>::WN, waves
     if (it < 0) break;
     const int2 w = items[it];
     const PlainGemmDesc &d = descs[w.x];
+    if (!runs(d.run_if)) continue;
     const int tiles_m = (int)(d.mbp / kTileBlocks);
     gemm_plain_tile<T, C, LAYOUT>(static_cast<const T *>(d.Apk), static_cast<const T *>(d.Bpk), d.mbp, d.nbp, d.kbp,
                                   d.m, d.n, d.D, static_cast<T *>(d.C), d.ldc, d.c_stride, -1, (double *)nullptr,
@@ -495,7 +499,7 @@ constexpr int threads_of(int layout) { return layout == 1 ? 256 : layout == 2 ? 
 template <typename T, int C>
 hipError_t launch_gemm_plain(const void *Apk, const void *Bpk, int64_t mbp, int64_t nbp, int64_t kbp, int m, int n,
                              int D, T *Cout, int ldc, int64_t c_stride, int single_pair, double *Cdbg, int lddbg,
-                             int layout, hipStream_t st) {
+                             int layout, const int *run_if, hipStream_t st) {
   const int64_t tiles = (mbp / kTileBlocks) * (nbp / kTileBlocks);
   if (tiles <= 0) return hipSuccess;
   const T *a = static_cast<const T *>(Apk);
@@ -503,15 +507,15 @@ hipError_t launch_gemm_plain(const void *Apk, const void *Bpk, int64_t mbp, int6
   switch (layout) {
     case 2:
       hipLaunchKernelGGL((k_gemm_plain<T, C, 2>), dim3((unsigned)tiles), dim3(threads_of(2)), 0, st, a, b, mbp, nbp,
-                         kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg);
+                         kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg, run_if);
       break;
     case 3:
       hipLaunchKernelGGL((k_gemm_plain<T, C, 3>), dim3((unsigned)tiles), dim3(threads_of(3)), 0, st, a, b, mbp, nbp,
-                         kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg);
+                         kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg, run_if);
       break;
     default:
       hipLaunchKernelGGL((k_gemm_plain<T, C, 1>), dim3((unsigned)tiles), dim3(threads_of(1)), 0, st, a, b, mbp, nbp,
-                         kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg);
+                         kbp, m, n, D, Cout, ldc, c_stride, single_pair, Cdbg, lddbg, run_if);
   }
   return hipGetLastError();
 }
@@ -543,29 +547,29 @@ hipError_t launch_gemm_plain_pruned(const void *Apk, const void *Bpk, int64_t mb
 
 template <typename T, int C>
 hipError_t launch_gemm_plain_batched(const PlainGemmDesc *descs, const int2 *items, const int *bounds,
-                                     int *counters, int grid, int layout, hipStream_t st) {
+                                     int *counters, int grid, int layout, const int *run_if, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
   switch (layout) {
     case 2:
       hipLaunchKernelGGL((k_gemm_plain_batched<T, C, 2>), dim3((unsigned)grid), dim3(threads_of(2)), 0, st, descs,
-                         items, bounds, counters);
+                         items, bounds, counters, run_if);
       break;
     case 3:
       hipLaunchKernelGGL((k_gemm_plain_batched<T, C, 3>), dim3((unsigned)grid), dim3(threads_of(3)), 0, st, descs,
-                         items, bounds, counters);
+                         items, bounds, counters, run_if);
       break;
     default:
       hipLaunchKernelGGL((k_gemm_plain_batched<T, C, 1>), dim3((unsigned)grid), dim3(threads_of(1)), 0, st, descs,
-                         items, bounds, counters);
+                         items, bounds, counters, run_if);
   }
   return hipGetLastError();
 }
 
 #define MP_GEMM_INST(T, C)                                                                                            \
   template hipError_t launch_gemm_plain<T, C>(const void *, const void *, int64_t, int64_t, int64_t, int, int, int, \
-                                              T *, int, int64_t, int, double *, int, int, hipStream_t);              \
+                                              T *, int, int64_t, int, double *, int, int, const int *, hipStream_t); \
   template hipError_t launch_gemm_plain_batched<T, C>(const PlainGemmDesc *, const int2 *, const int *, int *, int, \
-                                                      int, hipStream_t);                                            \
+                                                      int, const int *, hipStream_t);                                            \
   template hipError_t launch_gemm_plain_pruned<T, C>(const void *, const void *, int64_t, int64_t, int64_t, int, int, \
                                                      int, T *, int, int64_t, const int8_t *, int, hipStream_t);
 MP_GEMM_INST(double, 2)

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "residue.h"
+
 namespace mp {
 namespace host {
 
@@ -19,6 +21,8 @@ int split_kernel_override();
 int last_slice_option();
 int slices_for(int fmt, int mode, int64_t k);
 void set_last_slices(int D);
+// The slice count of (fmt, mode) is the library's choice on this thread.
+bool automatic_slices(int fmt, int mode);
 
 // The shift ceil((S + log2 k) / 2) of Algorithm 1.
 int rho_of(int S, int64_t k);
@@ -35,6 +39,10 @@ int hip_status(hipError_t e);
 bool profiling();
 void profile_mark3(hipEvent_t (&ev)[3]);
 void profile_commit(hipEvent_t (&ev)[3]);
+
+// The residue plan of a FLOAT-form product with the automatic count D; false
+// where it goes by slices.
+bool float_residue_plan(int fmt, int D, int64_t k, ResiduePlan &p);
 
 }  // namespace host
 }  // namespace mp

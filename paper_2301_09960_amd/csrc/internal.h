@@ -47,7 +47,11 @@ struct SplitOperand {
   int *exps;             // D x nvec exponents (FLOAT) or nvec (INT8)
   int D, rho;            // slice count and shift (used by the batched kernels)
   int last_literal;      // 1: the last slice is the residual's leading component (FLOAT only)
+  const int *run_if;     // device word: the kernels do nothing while it is 0 (null: they run)
 };
+
+// Whether a kernel with this condition has work (uniform).
+__device__ __forceinline__ bool runs(const int *run_if) { return !run_if || *run_if != 0; }
 
 // One product of a batch, as read by the persistent GEMM kernel.
 struct PlainGemmDesc {
@@ -56,6 +60,7 @@ struct PlainGemmDesc {
   int m, n, D, ldc;
   void *C;
   int64_t c_stride;
+  const int *run_if;  // as in SplitOperand
 };
 
 // Fused plain split: a workgroup of 512 or 1024 threads holds the residual of
@@ -107,19 +112,20 @@ hipError_t launch_split_plain(const SplitOperand<T> &a, const SplitOperand<T> &b
 // prefix_max0 / prefix_pass the running sums of the 64 x 64 tiles each
 // remaining operand needs in the max and pass kernels (0 for fused operands).
 // Operand i runs ops[i].D passes; pass launches cover dmax passes.  mu_all /
-// mu_words: one region holding every operand's maxima, cleared first.
+// mu_words: one region holding every operand's maxima, cleared first.  run_if
+// as in SplitOperand, for the whole launch.
 template <typename T, int C>
 hipError_t launch_split_plain_batched(const SplitOperand<T> *ops, const int *prefix_max0, const int *prefix_pass,
                                       const int *prefix_fused, int nops, int tiles_max0, int tiles_pass,
                                       int strips_fused, int fused_nt, int dmax, void *mu_all, int64_t mu_words,
-                                      hipStream_t st);
+                                      const int *run_if, hipStream_t st);
 
 // Persistent GEMM over a batch: items (product index, tile index) in device
 // memory, in kXcds per-XCD lists (bounds: kXcds + 1 running offsets; counters:
 // kXcds words, cleared by the caller; take_item).
 template <typename T, int C>
 hipError_t launch_gemm_plain_batched(const PlainGemmDesc *descs, const int2 *items, const int *bounds, int *counters,
-                                     int grid, int layout, hipStream_t st);
+                                     int grid, int layout, const int *run_if, hipStream_t st);
 
 // Largest |leading component| of each vector of both operands, as a bit
 // pattern into op.mu (nvec words, cleared first by the caller).
@@ -134,11 +140,12 @@ hipError_t launch_split_int8(const SplitOperand<double> &a, const SplitOperand<d
 // single_pair >= 0 selects debug mode: only pair (a, b) = (single_pair / D,
 // single_pair % D) (0-based) is formed and written raw as binary64 into Cdbg.
 // `layout` selects the wavefront layout of the 64 x 64 tile (1: 4 waves of
-// 32 x 32, 2: 8 waves of 32 x 16, 3: 16 waves of 16 x 16).
+// 32 x 32, 2: 8 waves of 32 x 16, 3: 16 waves of 16 x 16).  run_if as in
+// SplitOperand.
 template <typename T, int C>
 hipError_t launch_gemm_plain(const void *Apk, const void *Bpk, int64_t mbp, int64_t nbp, int64_t kbp, int m, int n,
                              int D, T *Cout, int ldc, int64_t c_stride, int single_pair, double *Cdbg, int lddbg,
-                             int layout, hipStream_t st);
+                             int layout, const int *run_if, hipStream_t st);
 
 // The fused GEMM with a pair set per 64 x 64 tile: tile (tm, tn) forms the
 // pairs (a, b) (0-based) with b < lims[(tn * tiles_m + tm) * D + a], a

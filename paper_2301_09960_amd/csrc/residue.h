@@ -63,13 +63,13 @@ struct ResidueOperand {
   int64_t comp_stride, sv, sp;
   int nvec, len, orient;
   int bits, float_form;
-  int guard_bits;        // float_form: bits per slice of the form it stands for
+  int slice_bits, passes;  // float_form: b and D of the slices it stands for
   int8_t *planes;        // residue planes (layout.h, INT8 blocks)
   int64_t nbp, kbp;
   void *mu;              // maxima (launch_split_max0)
   int *exps;
   int *state;            // float_form: one word per vector, cleared first
-  int *flag;             // float_form: set when the slices must be used instead
+  int *flag, *any;       // float_form: set when the slices must be used instead (any may be null)
   int nunits, nsq;
 };
 
@@ -84,17 +84,22 @@ struct ResidueDesc {
   int64_t c_stride;
 };
 
-// One product by residues.  arena: device memory; a call takes residue_bytes(),
-// with less of it the operand planes are formed a group of bases at a time.
+// One product by residues.  clear: device memory holding the maxima and, in the
+// FLOAT form, the states, cleared by the call.  arena: a call takes
+// residue_bytes() of it; with less, the product is formed in parts (bases, then
+// blocks of C), with the same result.
 struct ResidueCall {
   ResiduePlan plan;
   int cfg;               // INT8 tile configuration
-  int float_form, guard_bits;
+  int float_form, slice_bits, passes;
   int m, n, k, ldc;
   int64_t c_stride;
   int *exp_a, *exp_b;    // m and n exponents
   void *mu_a, *mu_b;     // m and n maxima
-  int *flag;             // float_form
+  int *state_a, *state_b;  // FLOAT form: m and n words
+  uint32_t *clear;
+  int64_t clear_words;
+  int *flag;             // FLOAT form: cleared, then set if the slices must form the product
   char *arena;
   size_t arena_bytes;
 };

@@ -174,16 +174,37 @@ __device__ __forceinline__ int vector_exponent(typename bits_of<T>::type mu, int
 // FLOAT form's checks (below) run with `check`.
 //
 // The FLOAT form stands for D passes of Algorithm 1, whose grid follows the
-// largest residual of the vector: pass a + 1 starts at the residual's exponent,
-// at most b + 2 bits below pass a's wherever some element's residual is at
-// least a quarter of pass a's grid.  With bits = D (b + 2) - 2 the fixed grid
-// here is then no coarser than the last slice's.  An element has such a
-// residual under a grid at bit g if its bits g - 1 and g - 2 differ; so a
-// vector is safe if every element is exact on the fixed grid, or if its first
-// 32 elements between them have such a change of bits at every place
-// (random mantissas do).  A vector that is neither, or that holds lower
-// components as large as leading ones, sets the flag: the product is then
-// formed from the slices.
+// largest residual of the vector: pass 1 rounds to 2^(E - b), and pass a + 1 to
+// b bits below the exponent e of the residual that pass a left, |r| <= 2^(g - 1)
+// under a grid 2^g.  The fixed grid here must be no coarser than the last
+// pass's.  An element whose bits i and i - 1 differ, with nonzero bits below
+// them, leaves |r| > 2^(i - 1) under any grid above 2^i, so e >= i and the next
+// grid is at least 2^(i - b); with i = g - 1, the usual case, a pass falls b + 1
+// bits.  The places where some of the first 32 elements of the vector has such a
+// change give a lower bound of all D grids (last_grid_covered); random mantissas
+// have one at nearly every place.  A vector is safe if that bound says so, or if
+// every element of it is exact on the fixed grid.  A vector that is neither, or
+// that holds lower components as large as leading ones, sets the flag: the
+// product is then formed from the slices.
+template <int NW>
+__device__ __forceinline__ bool last_grid_covered(const uint32_t *changes, int bits, int b, int passes) {
+  int g = bits - b;  // places count from the fixed grid
+  for (int a = 1; a < passes; ++a) {
+    int i = -1;  // the highest change below the grid
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const int top = g - 32 * w;  // places below g in this word
+      const uint32_t m = top >= 32 ? 0xffffffffu : top > 0 ? (1u << top) - 1u : 0u;
+      const uint32_t c = changes[w] & m;
+      if (c) i = 32 * w + 31 - __clz((int)c);
+    }
+    if (i < 0) return false;
+    g = i - b;
+    if (g < 1) return false;  // one place to spare for the rounding of the leading components
+  }
+  return true;
+}
+
 template <typename T, int C, int NW, int ORIENT>
 __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u0, int u1,
                               bool check) {
@@ -232,14 +253,25 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     }
     inexact = inexact || w[0] != 0u;
     uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits
-    uint32_t below = 0u;
 #pragma unroll
     for (int i = 0; i < NW; ++i) {
       const uint64_t sum = (uint64_t)w[i + 1] + carry;
       W[j][i] = (uint32_t)sum;
       carry = (uint32_t)(sum >> 32);
-      change[i] |= W[j][i] ^ ((W[j][i] << 1) | below);
-      below = W[j][i] >> 31;
+    }
+    if (check && kb == 0) {  // the changes of bits but the last ones of the element
+      bool more = false;     // a change further down
+#pragma unroll
+      for (int i = 0; i < NW; ++i) {
+        uint32_t c = W[j][i] ^ ((W[j][i] << 1) | (i > 0 ? W[j][i > 0 ? i - 1 : 0] >> 31 : 0u));
+        const bool here = c != 0u;
+        if (!more && here) {  // the lowest change, and the place above it
+          const uint32_t low = c & (0u - c);
+          c &= ~(low | (low << 1));
+        }
+        more = more || here;
+        change[i] |= c;
+      }
     }
     W[j][NW - 1] ^= 0x80000000u;
   }
@@ -289,7 +321,11 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   if (t < kBlk8) rounded[t] = 0;
   __syncthreads();
   if (inexact) rounded[l & 31] = 1;
-  if (odd) *op.flag = 1;
+  auto fall_back = [&]() {
+    *op.flag = 1;
+    if (op.any) *op.any = 1;
+  };
+  if (odd) fall_back();
   if (kb == 0) {
 #pragma unroll
     for (int i = 0; i < NW; ++i) atomicOr(&seen[l & 31][i], change[i]);
@@ -299,21 +335,11 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     const int vt = (int)(vb * kBlk8) + t;
     if (vt < op.nvec) {
       int add = rounded[t];
-      if (kb == 0) {  // a change at every place 1 .. bits - guard_bits
-        bool full = true;
-#pragma unroll
-        for (int i = 0; i < NW; ++i) {
-          const int top = op.bits - op.guard_bits + 1 - 32 * i;  // places below `top` in this word
-          uint32_t need = top >= 32 ? 0xffffffffu : top > 0 ? (1u << top) - 1u : 0u;
-          if (i == 0) need &= ~1u;
-          full = full && (seen[t][i] & need) == need;
-        }
-        if (!full) add |= 2;
-      }
-      // bit 0: an element was rounded; bit 1: places without a change
+      if (kb == 0 && !last_grid_covered<NW>(seen[t], op.bits, op.slice_bits, op.passes)) add |= 2;
+      // bit 0: an element was rounded; bit 1: the slices may reach further down
       if (add & ~*(volatile int *)&op.state[vt]) {
         const int old = atomicOr(&op.state[vt], add);
-        if ((old | add) == 3) *op.flag = 1;
+        if ((old | add) == 3) fall_back();
       }
     }
   }
@@ -907,17 +933,44 @@ size_t residue_bytes(const ResiduePlan &p, int cfg, int64_t m, int64_t n, int64_
 
 template <typename T, int C>
 hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,
-                          hipEvent_t between, hipStream_t st) {
-  using U = typename bits_of<T>::type;
+                          hipEvent_t between, bool first, hipStream_t st) {
   const ResiduePlan &p = rc.plan;
   const Shape s = shape_of(rc.cfg, rc.m, rc.n, rc.k);
   // arena: the uploaded descriptors and table, the result planes, then as many
-  // operand planes as fit (all of them, except in a fixed scratch)
+  // operand planes as fit (all of them, except in a fixed scratch, where a
+  // product whose result planes alone take half of it goes in blocks of C)
   const size_t head = header_bytes(p), result = (size_t)p.nplanes * p.nchunks * s.r_plane;
-  if (rc.arena_bytes < head + result) return hipErrorInvalidValue;
-  const int64_t fit = (int64_t)((rc.arena_bytes - head - result) / (size_t)(s.a_plane + s.b_plane));
-  const int room = (int)std::min<int64_t>(p.nplanes, fit);
-  if (room < (p.nsq > 0 ? 2 : 1)) return hipErrorInvalidValue;
+  const int64_t left = (int64_t)rc.arena_bytes - (int64_t)head - (int64_t)result;
+  const int room = (int)std::min<int64_t>(p.nplanes, left < 0 ? 0 : left / (s.a_plane + s.b_plane));
+  if (room < p.nplanes && (2 * result > rc.arena_bytes || room < 2)) {
+    // halves of the longer side of C, at a tile edge
+    ResidueCall lo = rc, hi = rc;
+    SplitOperand<T> a2 = a, b2 = b;
+    T *C2 = Cout;
+    if (rc.m >= rc.n) {
+      lo.m = (int)(ceil_div(rc.m, 2 * 256) * 256);
+      if (lo.m >= rc.m) return hipErrorInvalidValue;  // one tile: does not fit
+      hi.m = rc.m - lo.m;
+      hi.exp_a += lo.m;
+      a2.X += lo.m * a.sv;
+      C2 += lo.m;
+    } else {
+      lo.n = (int)(ceil_div(rc.n, 2 * 256) * 256);
+      if (lo.n >= rc.n) return hipErrorInvalidValue;
+      hi.n = rc.n - lo.n;
+      hi.exp_b += lo.n;
+      b2.X += lo.n * b.sv;
+      C2 += (int64_t)lo.n * rc.ldc;
+    }
+    SplitOperand<T> a1 = a, b1 = b;
+    a1.nvec = lo.m;
+    b1.nvec = lo.n;
+    a2.nvec = hi.m;
+    b2.nvec = hi.n;
+    hipError_t err = launch_residue<T, C>(lo, a1, b1, Cout, between, first, st);
+    if (err == hipSuccess) err = launch_residue<T, C>(hi, a2, b2, C2, nullptr, false, st);
+    return err;
+  }
   int8_t *R = reinterpret_cast<int8_t *>(rc.arena + head);
   int8_t *Ap = R + result, *Bp = Ap + (size_t)room * s.a_plane;
 
@@ -941,13 +994,14 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     r.orient = o.orient;
     r.bits = p.bits;
     r.float_form = rc.float_form;
-    r.guard_bits = rc.guard_bits;
+    r.slice_bits = rc.slice_bits;
+    r.passes = rc.passes;
     r.planes = i == 0 ? Ap : Bp;
     r.nbp = i == 0 ? s.mbp : s.nbp;
     r.kbp = s.kbp;
     r.mu = i == 0 ? rc.mu_a : rc.mu_b;
     r.exps = i == 0 ? rc.exp_a : rc.exp_b;
-    r.state = nullptr;
+    r.state = i == 0 ? rc.state_a : rc.state_b;
     r.flag = rc.flag;
     r.nunits = p.nunits;
     r.nsq = p.nsq;
@@ -982,12 +1036,11 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     const size_t n = std::min<size_t>(kUploadWords, words - at), hw = sizeof(Head) / 4;
     for (size_t i = 0; i < n; ++i)
       up.w[i] = at + i < hw ? reinterpret_cast<const uint32_t *>(&h)[at + i] : table[at + i - hw];
-    const bool first = at == 0;
-    const int64_t n0 = first ? (int64_t)rc.m * sizeof(U) / 4 : 0, n1 = first ? (int64_t)rc.n * sizeof(U) / 4 : 0;
-    const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(std::max(n0, n1), kThreads)));
+    const int64_t n0 = at == 0 ? rc.clear_words : 0, n1 = at == 0 && first && rc.flag ? 1 : 0;
+    const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(n0, kThreads)));
     hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n,
-                       reinterpret_cast<uint32_t *>(rc.arena) + at, static_cast<uint32_t *>(rc.mu_a), n0,
-                       static_cast<uint32_t *>(rc.mu_b), n1);
+                       reinterpret_cast<uint32_t *>(rc.arena) + at, rc.clear, n0,
+                       reinterpret_cast<uint32_t *>(rc.flag), n1);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   SplitOperand<T> ma = a, mb = b;
@@ -1010,6 +1063,12 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     u0 = u1;
   }
   return combine_launch<T, C>(p.nwc, s.mbp * s.nbp, descs, prefix + 2, 1, st);
+}
+
+template <typename T, int C>
+hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,
+                          hipEvent_t between, hipStream_t st) {
+  return launch_residue<T, C>(rc, a, b, Cout, between, true, st);
 }
 
 template <typename T, int C>
@@ -1052,6 +1111,7 @@ hipError_t launch_residue_combine_batched(int nwc, const ResidueDesc *descs, con
 MP_RESIDUE_INST(double, 2)
 MP_RESIDUE_INST(double, 3)
 MP_RESIDUE_INST(double, 4)
+MP_RESIDUE_INST(float, 3)
 #undef MP_RESIDUE_INST
 
 }  // namespace mp

@@ -120,6 +120,7 @@ __device__ void max0_body(const Op &op, int idx) {
 
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_split_max0(SplitOperand<T> a, SplitOperand<T> b, int blocks_a) {
+  if (!runs(a.run_if)) return;
   if ((int)blockIdx.x < blocks_a)
     max0_body<T, 0>(a, blockIdx.x);
   else
@@ -185,6 +186,7 @@ __device__ void pass_body(const SplitOperand<T> &op, int idx, int pass, int rho,
 template <typename T, int C>
 __global__ __launch_bounds__(kThreads) void k_split_pass(SplitOperand<T> a, SplitOperand<T> b, int blocks_a, int pass,
                                                          int rho, int first, int last) {
+  if (!runs(a.run_if)) return;
   if ((int)blockIdx.x < blocks_a)
     pass_body<T, C, 0>(a, blockIdx.x, pass, rho, first != 0, last != 0);
   else
@@ -207,8 +209,9 @@ __device__ __forceinline__ int find_operand(const int *prefix, int nops, int b) 
 }
 
 template <typename T, typename Op>
-__global__ __launch_bounds__(kThreads) void k_split_max0_batched(const Op *ops, const int *prefix,
-                                                                 int nops) {
+__global__ __launch_bounds__(kThreads) void k_split_max0_batched(const Op *ops, const int *prefix, int nops,
+                                                                 const int *run_if) {
+  if (!runs(run_if)) return;
   const int i = find_operand(prefix, nops, blockIdx.x);
   const Op &op = ops[i];
   const int local = blockIdx.x - prefix[i];
@@ -220,7 +223,8 @@ __global__ __launch_bounds__(kThreads) void k_split_max0_batched(const Op *ops, 
 
 template <typename T, int C>
 __global__ __launch_bounds__(kThreads) void k_split_pass_batched(const SplitOperand<T> *ops, const int *prefix,
-                                                                 int nops, int pass) {
+                                                                 int nops, int pass, const int *run_if) {
+  if (!runs(run_if)) return;
   const int i = find_operand(prefix, nops, blockIdx.x);
   const SplitOperand<T> &op = ops[i];
   if (pass >= op.D) return;  // uniform over the block
@@ -355,6 +359,7 @@ __device__ void fused_strip(const SplitOperand<T> &op, int strip, int D, int rho
 template <typename T, int C, int NT>
 __global__ __launch_bounds__(NT) void k_split_fused(SplitOperand<T> a, SplitOperand<T> b, int strips_a, int D,
                                                     int rho) {
+  if (!runs(a.run_if)) return;
   const int w = xcd_contiguous(blockIdx.x, gridDim.x);
   if (w < strips_a)
     fused_strip<T, C, NT>(a, w, D, rho);
@@ -365,10 +370,13 @@ __global__ __launch_bounds__(NT) void k_split_fused(SplitOperand<T> a, SplitOper
 // Batched: workgroup b takes strip b - prefix[i] of operand i (operands split
 // by the pass kernels own no strips).
 template <typename T, int C, int NT>
-__global__ __launch_bounds__(NT) void k_split_fused_batched(const SplitOperand<T> *ops, const int *prefix, int nops) {
+__global__ __launch_bounds__(NT) void k_split_fused_batched(const SplitOperand<T> *ops, const int *prefix, int nops,
+                                                            const int *run_if) {
+  if (!runs(run_if)) return;
   const int w = xcd_contiguous(blockIdx.x, gridDim.x);
   const int i = __builtin_amdgcn_readfirstlane(find_operand(prefix, nops, w));
   const SplitOperand<T> op = ops[i];  // uniform: kept in scalar registers
+  if (!runs(op.run_if)) return;
   fused_strip<T, C, NT>(op, w - prefix[i], op.D, op.rho);
 }
 
@@ -424,27 +432,28 @@ template <typename T, int C>
 hipError_t launch_split_plain_batched(const SplitOperand<T> *ops, const int *prefix_max0, const int *prefix_pass,
                                       const int *prefix_fused, int nops, int tiles_max0, int tiles_pass,
                                       int strips_fused, int fused_nt, int dmax, void *mu_all, int64_t mu_words,
-                                      hipStream_t st) {
+                                      const int *run_if, hipStream_t st) {
   hipError_t err = hipSuccess;
   if (nops <= 0) return err;
   if (strips_fused > 0) {
     if (fused_nt == 512)
       hipLaunchKernelGGL((k_split_fused_batched<T, C, 512>), dim3(strips_fused), dim3(512), 0, st, ops, prefix_fused,
-                         nops);
+                         nops, run_if);
     else
       hipLaunchKernelGGL((k_split_fused_batched<T, C, 1024>), dim3(strips_fused), dim3(1024), 0, st, ops,
-                         prefix_fused, nops);
+                         prefix_fused, nops, run_if);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   if (tiles_max0 <= 0 && tiles_pass <= 0) return hipSuccess;
   if ((err = launch_fill32(mu_all, mu_words, 0u, st)) != hipSuccess) return err;
   if (tiles_max0 > 0) {
-    hipLaunchKernelGGL((k_split_max0_batched<T, SplitOperand<T>>), dim3(tiles_max0), dim3(kThreads), 0, st, ops, prefix_max0, nops);
+    hipLaunchKernelGGL((k_split_max0_batched<T, SplitOperand<T>>), dim3(tiles_max0), dim3(kThreads), 0, st, ops, prefix_max0,
+                       nops, run_if);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   for (int pass = 0; pass < dmax && tiles_pass > 0; ++pass) {
     hipLaunchKernelGGL((k_split_pass_batched<T, C>), dim3(tiles_pass), dim3(kThreads), 0, st, ops, prefix_pass, nops,
-                       pass);
+                       pass, run_if);
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
   return hipSuccess;
@@ -453,7 +462,7 @@ hipError_t launch_split_plain_batched(const SplitOperand<T> *ops, const int *pre
 #define MP_SPLIT_BATCHED(T, C)                                                                                 \
   template hipError_t launch_split_plain_batched<T, C>(const SplitOperand<T> *, const int *, const int *,         \
                                                        const int *, int, int, int, int, int, int, void *,     \
-                                                       int64_t, hipStream_t);
+                                                       int64_t, const int *, hipStream_t);
 MP_SPLIT_BATCHED(double, 2)
 MP_SPLIT_BATCHED(double, 3)
 MP_SPLIT_BATCHED(double, 4)
@@ -705,7 +714,7 @@ hipError_t launch_residue_max_batched(const ResidueOperand<T> *ops, const int *p
                                       hipStream_t st) {
   if (tiles <= 0) return hipSuccess;
   hipLaunchKernelGGL((k_split_max0_batched<T, ResidueOperand<T>>), dim3(tiles), dim3(kThreads), 0, st, ops, prefix,
-                     nops);
+                     nops, (const int *)nullptr);
   return hipGetLastError();
 }
 template hipError_t launch_residue_max_batched<double>(const ResidueOperand<double> *, const int *, int, int,

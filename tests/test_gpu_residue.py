@@ -110,3 +110,127 @@ def test_integers_are_exact(mp):
     want = b.astype(object) @ a.astype(object)
     got = np.vectorize(lambda x, y: int(x) + int(y), otypes=[object])(C[0], C[1])
     assert np.all(got == want)
+
+
+def slices(mp, fmt, A, B):
+    """The product from binary64/binary32 slices: a slice count set by the
+    caller is Algorithm 1 with that many slices."""
+    D = mp.num_slices(fmt, "float", A.shape[1])
+    return mp.gemm(fmt, A, B, slices=D)
+
+
+FLOAT_SHAPES = [(1, 1, 48), (64, 64, 64), (33, 130, 96), (130, 65, 1000), (257, 300, 129)]
+
+
+@pytest.mark.parametrize("fmt", ["dd", "td", "qd", "ts"])
+@pytest.mark.parametrize("m,n,k", FLOAT_SHAPES)
+@pytest.mark.parametrize("E", [0, 16])
+def test_float_form_no_less_exact_than_slices(mp, orc, fmt, m, n, k, E):
+    """The automatic FLOAT form by residues against the same call from slices:
+    the error of every entry within the rounding of the operands to D (b + 1) + 2
+    bits and of C, and its root mean square no larger than the slices'."""
+    A, B = W.gen_pair(fmt, m, n, k, E=E, seed=m + k + E)
+    dA, dB = dev(A), dev(B)
+    C = mp.gemm(fmt, dA, dB).cpu().numpy()
+    S = slices(mp, fmt, dA, dB).cpu().numpy()
+    D = mp.last_num_slices()
+    rows = list(range(m)) if m * n * k < 1e6 else [0, m // 2, m - 1]
+    diff, absab, _ = orc.exact_check(A, B, C, rows=rows)
+    diff_s, _, _ = orc.exact_check(A, B, S, rows=rows)
+    single = fmt == "ts"
+    b = (24 if single else 53) - orc.rho(24 if single else 53, k)
+    bits = max(D * (b + 1) + 2, 116 if single else 0)
+    wide = A[:, :, rows].astype(np.float64), B.astype(np.float64)
+    assert np.all(diff <= rounding_bound(*wide, bits - 1, COMPS[fmt] * (24 / 53 if single else 1), absab))
+    rms, rms_s = np.sqrt(np.mean(diff ** 2)), np.sqrt(np.mean(diff_s ** 2))
+    say(f"float {fmt} {m}x{n}x{k} E={E} D={D}: rms {rms:.3g}, slices {rms_s:.3g}")
+    # both round C to the format once; the slack covers entries of a few roundings
+    assert rms <= 1.05 * rms_s + 2.0 ** -(24 * 3 + 8 if single else 53 * COMPS[fmt] + 6) * absab.max()
+
+
+def with_gap(fmt, m, n, k, row):
+    """Short leading data, and in one row an element 2^-90 below with full
+    mantissas: Algorithm 1 follows it down, a fixed grid would cut it off."""
+    A, B = W.gen_pair(fmt, m, n, k, E=4, seed=k)
+    A[0] = np.rint(A[0] * 2.0 ** 8) * 2.0 ** -8
+    A[1:] = 0
+    A[:, k - 1, row] = W.gen_matrix(fmt, 1, 1, E=0, seed=3)[:, 0, 0] * A.dtype.type(2.0 ** -90)
+    return A, B
+
+
+@pytest.mark.parametrize("fmt,m,n,k", [("dd", 40, 33, 64), ("dd", 130, 70, 300), ("qd", 50, 40, 200),
+                                       ("dd", 33, 20, 8300)])
+def test_gaps_fall_back_to_the_slices(mp, fmt, m, n, k):
+    """A vector whose slices reach below the fixed grid: the result is the
+    slices', bit for bit (also with slices made one pass at a time)."""
+    import torch
+    A, B = with_gap(fmt, m, n, k, m // 2)
+    if fmt == "qd":
+        A[:, k - 1, m // 2] *= 2.0 ** -120
+    dA, dB = dev(A), dev(B)
+    assert torch.equal(mp.gemm(fmt, dA, dB), slices(mp, fmt, dA, dB))
+    # the same in a column of B
+    tA, tB = dB.permute(0, 2, 1).contiguous(), dA.permute(0, 2, 1).contiguous()  # (c, k, n), (c, m, k)
+    assert torch.equal(mp.gemm(fmt, tA, tB), slices(mp, fmt, tA, tB))
+    # components that are not normalized
+    dA2 = dA.clone()
+    dA2[1] = dA2[0] * 0.75
+    assert torch.equal(mp.gemm(fmt, dA2, dB), slices(mp, fmt, dA2, dB))
+
+
+def test_infinities_and_nans_stay_in_their_rows(mp):
+    import torch
+    m, n, k = 70, 66, 128
+    A, B = W.gen_pair("td", m, n, k, E=8, seed=2)
+    clean = mp.gemm("td", dev(A), dev(B))
+    A[0, 5, 3] = np.inf
+    A[0, 7, 64] = np.nan
+    B[0, 65, 100] = -np.inf
+    B[:, 4, :] = 0
+    dA, dB = dev(A), dev(B)
+    C, S = mp.gemm("td", dA, dB), slices(mp, "td", dA, dB)
+    assert torch.equal(torch.isnan(C[0]), torch.isnan(S[0]))
+    keep = ~torch.isnan(C[0])
+    keep[4, :] = False
+    assert torch.equal(C[:, keep], clean[:, keep])
+    assert bool(torch.all(C[:, 4, :3] == 0))
+
+
+def test_batch_falls_back_per_product(mp):
+    """Flagged products of a batch take the slices, the others the residues,
+    each as its single call does; replayed with other operands."""
+    import torch
+    sh = [(64, 64, 64), (40, 33, 64), (130, 70, 300), (20, 20, 16), (65, 129, 700)]
+    for round_ in range(3):
+        pairs = []
+        for i, (m, n, k) in enumerate(sh):
+            gap = (i + round_) % 2 == 0 and k >= 48
+            pairs.append(with_gap("dd", m, n, k, 1) if gap else W.gen_pair("dd", m, n, k, E=8, seed=i + round_))
+        As, Bs = [dev(a) for a, _ in pairs], [dev(b) for _, b in pairs]
+        Cs = mp.gemm_batched("dd", As, Bs)
+        torch.cuda.synchronize()
+        for i, (a, b) in enumerate(zip(As, Bs)):
+            assert torch.equal(Cs[i], mp.gemm("dd", a, b)), (round_, sh[i])
+
+
+@pytest.mark.parametrize("mode,m,n,k", [("float", 1500, 1400, 100), ("int8", 100, 90, 9000)])
+def test_fixed_scratch_takes_the_product_in_parts(mp, mode, m, n, k):
+    """Shapes whose planes exceed the scratch of mpgemm_dd_noalloc: blocks of C
+    (float), groups of bases (int8), the same C."""
+    import ctypes
+    import torch
+    A, B = W.gen_pair("dd", m, n, k, E=8, seed=4)
+    dA, dB = dev(A), dev(B)
+    old = mp.get_mode("dd")
+    mp.set_mode("dd", mode)
+    try:
+        want = mp.gemm("dd", dA, dB)
+        got = torch.zeros_like(want)
+        P = ctypes.c_void_p
+        assert mp.workspace_bytes("dd", mode, m, n, k) > 64 << 20
+        st = mp.lib().mpgemm_dd_noalloc(m, n, k, P(dA.data_ptr()), m, P(dB.data_ptr()), k, P(got.data_ptr()), m,
+                                        P(torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+    finally:
+        mp.set_mode("dd", old)
+    assert st == 0 and torch.equal(got, want)
