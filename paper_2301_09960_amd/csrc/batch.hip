@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstring>
 #include <vector>
 
@@ -111,9 +112,9 @@ struct ResidueBatch {
     size_t a, b, r, exp_a, exp_b, mu_a, mu_b, st_a, st_b, table;
   };
   std::vector<Slot> slots;
-  int nw = 0, nwc = 0, tiles0 = 0, nitems1 = 0, nitems3 = 0;
+  int nw = 0, tiles0 = 0, nitems1 = 0, nitems3 = 0;
   int64_t blocks = 0, blocksc = 0;
-  size_t off_planes = 0, planes_bytes = 0, off_static = 0, off_items = 0, off_bounds = 0, off_counter = 0,
+  size_t off_planes = 0, planes_bytes = 0, off_static = 0, off_tables = 0, off_items = 0, off_bounds = 0, off_counter = 0,
          off_zero = 0, zero_bytes = 0;
   bool float_form = false;
   size_t off_flags = 0;            // FLOAT form: a word set if any product is flagged, then one per product
@@ -145,10 +146,9 @@ struct ResidueBatch {
   template <typename Take>
   void layout(Take take, size_t elem, bool float_slices) {
     float_form = float_slices;
-    for (Slot &s : slots) {
-      nw = std::max(nw, s.plan.nw);
-      nwc = std::max(nwc, s.plan.nwc);
-    }
+    // products of one combine size together: each size has its launch
+    std::stable_sort(slots.begin(), slots.end(), [](const Slot &a, const Slot &b) { return a.plan.nwc < b.plan.nwc; });
+    for (Slot &s : slots) nw = std::max(nw, s.plan.nw);
     off_planes = take(0);
     for (Slot &s : slots) {
       s.a = take((size_t)s.plan.nplanes * s.mbp * s.kbp * 1024);
@@ -174,7 +174,7 @@ struct ResidueBatch {
     const int n = (int)slots.size();
     prefix.assign((size_t)2 * (2 * n + 1) + n + 1, 0);
     int *pre0 = prefix.data(), *preb = pre0 + 2 * n + 1, *prec = preb + 2 * n + 1;
-    std::vector<std::pair<std::pair<int, int>, size_t>> known;
+    std::vector<std::pair<std::array<int, 3>, size_t>> known;
     for (int i = 0; i < n; ++i) {
       Slot &s = slots[i];
       const int64_t kbl = ceil_div((int64_t)s.k, (int64_t)kKBlk8);
@@ -182,24 +182,28 @@ struct ResidueBatch {
       pre0[2 * i + 2] = pre0[2 * i + 1] + tiles64(s.n, s.k);
       preb[2 * i + 1] = preb[2 * i] + (int)(ceil_div((int64_t)s.m, (int64_t)kBlk8) * kbl);
       preb[2 * i + 2] = preb[2 * i + 1] + (int)(ceil_div((int64_t)s.n, (int64_t)kBlk8) * kbl);
-      prec[i + 1] = prec[i] + (int)(s.mbp * s.nbp);
-      const std::pair<int, int> key(s.plan.nunits, s.plan.nsq);
+      // blocks of its combine launch, counted from the launch's first product
+      const bool first = i == 0 || slots[i - 1].plan.nwc != s.plan.nwc;
+      prec[i] = first ? 0 : prec[i - 1] + (int)(slots[i - 1].mbp * slots[i - 1].nbp);
+      blocksc += s.mbp * s.nbp;
+      const std::array<int, 3> key{s.plan.nunits, s.plan.nsq, s.plan.nwc};
       size_t at = SIZE_MAX;
       for (const auto &kn : known)
         if (kn.first == key) at = kn.second;
       if (at == SIZE_MAX) {
         at = tables.size();
-        const std::vector<uint32_t> &t = residue_table(key.first, key.second, nwc);
+        const std::vector<uint32_t> &t = residue_table(key[0], key[1], key[2]);
         tables.insert(tables.end(), t.begin(), t.end());
+        tables.resize((tables.size() + 3) / 4 * 4, 0u);  // read 16 bytes at a time
         known.push_back({key, at});
       }
       s.table = at;
     }
     tiles0 = pre0[2 * n];
     blocks = preb[2 * n];
-    blocksc = prec[n];
     make_items();
-    off_static = take(prefix.size() * 4 + tables.size() * 4);
+    off_static = take(prefix.size() * 4);
+    off_tables = take(tables.size() * 4);
     off_items = take(items.size() * sizeof(int4));
     off_bounds = take(sizeof(bounds));
   }
@@ -251,8 +255,7 @@ struct ResidueBatch {
     if (slots.empty()) return true;
     return hipMemset(ws + off_planes, 0, planes_bytes) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess &&
            hipMemcpy(ws + off_static, prefix.data(), prefix.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
-           hipMemcpy(ws + off_static + prefix.size() * 4, tables.data(), tables.size() * 4, hipMemcpyHostToDevice) ==
-               hipSuccess &&
+           hipMemcpy(ws + off_tables, tables.data(), tables.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
            hipMemcpy(ws + off_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice) == hipSuccess &&
            hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
   }
@@ -272,7 +275,17 @@ struct ResidueBatch {
       e = launch_gemm_residue_batched(descs, reinterpret_cast<const int4 *>(ws + off_items), nitems1, nitems3,
                                       reinterpret_cast<const int *>(ws + off_bounds),
                                       reinterpret_cast<int *>(ws + off_counter), st);
-    if (e == hipSuccess) e = launch_residue_combine_batched<T, C>(nwc, descs, prec, n, blocksc, st);
+    for (int i = 0; i < n && e == hipSuccess;) {
+      int j = i;
+      int64_t sum = 0;
+      bool chunks = false;
+      for (; j < n && slots[j].plan.nwc == slots[i].plan.nwc; ++j) {
+        sum += slots[j].mbp * slots[j].nbp;
+        chunks = chunks || slots[j].plan.nchunks > 1;
+      }
+      e = launch_residue_combine_batched<T, C>(slots[i].plan.nwc, chunks, descs + i, prec + i, j - i, sum, st);
+      i = j;
+    }
     return e;
   }
 
@@ -280,7 +293,7 @@ struct ResidueBatch {
   template <typename T>
   void write(char *ws, ResidueOperand<T> *ops, ResidueDesc *descs, const T *const *A, const int *lda,
              const T *const *B, const int *ldb, T *const *Cm, const int *ldc) const {
-    const char *tab = ws + off_static + prefix.size() * 4;
+    const char *tab = ws + off_tables;
     for (size_t i = 0; i < slots.size(); ++i) {
       const Slot &s = slots[i];
       const int g = s.g;
@@ -607,8 +620,10 @@ struct FormatPlan : BatchPlan {
     plain.layout(take, split_kernel);
     fallback.layout(take, split_kernel);
     res.layout(take, sizeof(T), mode == MPGEMM_MODE_FLOAT);
-    if (res.blocks > 0x7fffffffLL || res.blocksc > 0x7fffffffLL / 4) return MPGEMM_ERR_TOO_LARGE;
-    for (size_t i = 0; i < fallback.slots.size(); ++i) fallback.slots[i].flag = res.off_flags + 4 * (i + 1);
+    if (res.blocks > 0x7fffffffLL || res.blocksc > 0x7fffffffLL) return MPGEMM_ERR_TOO_LARGE;
+    for (size_t i = 0; i < res.slots.size(); ++i)
+      for (auto &f : fallback.slots)
+        if (f.g == res.slots[i].g) f.flag = res.off_flags + 4 * (i + 1);
     fallback.off_any = res.off_flags;
     off_desc = take(0);
     off_plain = 0;

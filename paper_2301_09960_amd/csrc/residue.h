@@ -33,14 +33,14 @@ namespace mp {
 constexpr int kNumBases = 49;
 constexpr int kMaxWindowWords = 9;                 // W in at most 9 words: bits <= 286
 constexpr int kMaxResidueBits = 32 * kMaxWindowWords - 2;
-constexpr int kCombineWords[] = {2, 4, 6, 8, 10, 12, 14, 16, 18, 20};  // instantiated sizes
+constexpr int kMaxCombineWords = 20;               // words of the combine's sums
 constexpr int kChunkBlocks = 1024;                 // k blocks of one 32-bit sum: 32768 k
 constexpr int kNonFinite = INT32_MAX;              // exponent of a vector holding an infinity or NaN
 
 struct ResiduePlan {
   int bits;                     // |W| <= 2^bits
   int nunits, nsq, nplanes;     // bases, of them squared, digit planes (nunits + nsq)
-  int nchunks;                  // k chunks whose result planes the combine adds
+  int nchunks;                  // k chunks with result planes of their own
   int nw, nwc;                  // 32-bit words of W, and of the combine's sums
   int products() const { return nunits + 2 * nsq; }
 };
@@ -48,11 +48,11 @@ struct ResiduePlan {
 // The cheapest plan whose moduli cover |X| <= k 2^(2 bits); false when none does.
 bool residue_plan(int bits, int64_t k, ResiduePlan &p);
 
-// Combine constants of a plan for nwc words (host memory, kept for the process;
-// a function of (nunits, nsq, nwc) alone): ceil(nplanes / 4) groups of 4 nwc
-// words, word j of group g holding the balanced base-256 digits j of the
-// weights of planes 4g .. 4g + 3; then the nwc words of M; then 1 / M as a
-// binary64.
+// Combine constants of a plan (host memory, kept for the process; a function of
+// (nunits, nsq, nwc) alone): the weight of every plane in balanced base-256
+// digits, as operand blocks (32 digits x 32 planes, 1 KiB) of
+// v_mfma_i32_32x32x32_i8; then M in nwc balanced words; then a multiple of 1 / M
+// as a binary64.
 const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc);
 
 // One operand of the residue split.  E: FLOAT form ceil(log2 mu) of the
@@ -112,8 +112,9 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
 // Many products at once (batch.hip): descriptors, prefix sums and work items in
 // device memory.  The residue split writes only blocks that hold elements (the
 // planes' padding was cleared once); prefix: running sums of these blocks per
-// operand, and of the 32 x 32 blocks of C per product for the combine.  nw and
-// nwc are the batch's largest.  Items (product, tile, k chunk, unit group) as two
+// operand, and of the 32 x 32 blocks of C per product for the combine.  nw is the
+// batch's largest; a combine launch takes products of one nwc
+// (chunks: some of them have several k chunks).  Items (product, tile, k chunk, unit group) as two
 // sets of kXcds per-XCD lists (take_item): nitems1 of 128 x 128 tiles, then
 // nitems3 of 256 x 256; counters: 2 kXcds words, cleared by the caller.
 template <typename T>
@@ -125,7 +126,7 @@ hipError_t launch_residue_split_batched(int nw, const ResidueOperand<T> *ops, co
 hipError_t launch_gemm_residue_batched(const ResidueDesc *descs, const int4 *items, int nitems1, int nitems3,
                                        const int *bounds, int *counters, hipStream_t st);
 template <typename T, int C>
-hipError_t launch_residue_combine_batched(int nwc, const ResidueDesc *descs, const int *prefix, int nprod,
+hipError_t launch_residue_combine_batched(int nwc, bool chunks, const ResidueDesc *descs, const int *prefix, int nprod,
                                           int64_t blocks, hipStream_t st);
 
 // The first unit of each of `groups` parts of the units [first, end) of nearly

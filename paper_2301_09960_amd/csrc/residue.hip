@@ -14,10 +14,10 @@
 // digit GEMM writes four): 7 vector instructions per entry after
 // k / 32 matrix-core instructions per 32 x 32 block.
 //
-// k_residue_combine: V = sum_p t_p w_p over the planes in base-256 digits
-// (v_dot4_i32_i8: four planes at once), carried into words, then X = V - q M
-// with q = rint(V / M) in binary64, and the leading words of X as binary64
-// chunks renormalized into the components.
+// k_residue_combine: V = sum_p t_p w_p over the planes in base-256 digits, a
+// matrix product (digits x planes) (planes x entries) on the INT8 matrix cores,
+// carried into words; then X = V - q M with q = rint(V / M) in binary64, and
+// the components read off the leading bits of X.
 //
 // Measured at n = 4096, E = 16 (before: the digit pairs of int8.hip): DD 32
 // products, 8.43 -> 3.00 ms (GEMM 8.14 -> 2.09 ms, 2.10 POP/s); QD 73 products,
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(kThreads) void k_residue_split(const ResidueOperand
 // from unit u_first's first plane, result planes from the k chunk's first.
 // Products are at most 2^14 in magnitude: 32768 k of them twice (the two pairs of
 // a square's second diagonal) and a carry stay below 2^31, so longer k is cut into
-// chunks with result planes of their own, which the combine adds up.
+// chunks with result planes of their own, which k_residue_fold adds up.
 struct ResidueWork {
   int u0, u1, u_first, nsq;
   int8_t *R;
@@ -502,17 +502,11 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
 // ---------------------------------------------------------------------------
 typedef const __attribute__((address_space(4))) uint32_t *const_words;  // scalar loads
 
-// Entries per thread: their digit sums (4 NWC words each) share the registers.
-template <int NWC>
-constexpr int combine_entries() {
-  return NWC <= 6 ? 4 : NWC <= 14 ? 2 : 1;
-}
-// 48-bit chunks of X that enter the result, from its leading nonzero word on
-// (up to 31 leading zero bits): at least 53 c + 20 bits (TS: 24 c + 8).
-template <typename T, int C>
-constexpr int combine_chunks() {
-  return sizeof(T) == 4 ? 3 : C + 2;
-}
+// 32-plane steps of the combine's matrix products.  The plan's moduli fill nwc
+// words with at most so many planes (32 planes hold 242 bits, 64 hold 460).
+__host__ __device__ constexpr int combine_steps(int nwc) { return nwc <= 8 ? 1 : nwc <= 15 ? 2 : 3; }
+// 32-digit row blocks of nwc words.
+__host__ __device__ constexpr int combine_rows(int nwc) { return (nwc + 7) / 8; }
 
 // w up by SH words, and its place down, if its top SH words are zero.
 template <int NWC, int SH>
@@ -528,28 +522,29 @@ __device__ __forceinline__ void raise_words(uint32_t (&w)[NWC], int &place) {
   }
 }
 
+// The components of X 2^e0, X = V mod M (balanced), from V's base-256 digit sums.
 template <int NWC, typename T, int C>
 __device__ __forceinline__ void combine_entry(const int (&S)[4 * NWC], const_words mod, double inv_m, int e0,
                                               T (&out)[C]) {
-  // carry the digit sums into words
+  int t0[NWC], t1[NWC];  // V = sum (t0 + t1 2^16) 2^(32 i)
+#pragma unroll
+  for (int i = 0; i < NWC; ++i) {
+    t0[i] = S[4 * i] + (S[4 * i + 1] << 8);
+    t1[i] = S[4 * i + 2] + (S[4 * i + 3] << 8);
+  }
+  // X = V - q M, q = rint(V / M) from the top three words: |X| < 0.48 M, and
+  // what lies below them is less than 2^-26 M
+  constexpr int kTop = NWC < 3 ? NWC : 3;
+  double v = 0.0;
+#pragma unroll
+  for (int i = NWC - 1; i >= NWC - kTop; --i)
+    v = __builtin_fma(__builtin_fma(v, 65536.0, (double)t1[i]), 65536.0, (double)t0[i]);
+  const int nq = -(int)rint(v * inv_m);
   uint32_t w[NWC];
   int64_t c = 0;
 #pragma unroll
   for (int i = 0; i < NWC; ++i) {
-    c += (int64_t)S[4 * i] + ((int64_t)S[4 * i + 1] << 8) + ((int64_t)S[4 * i + 2] << 16) +
-         ((int64_t)S[4 * i + 3] << 24);
-    w[i] = (uint32_t)c;
-    c >>= 32;
-  }
-  // X = V - q M: |X| < 0.48 M and |V| < 2^18 M, so q is rounded safely
-  double v = (double)(int32_t)w[NWC - 1];
-#pragma unroll
-  for (int i = NWC - 2; i >= 0; --i) v = __builtin_fma(v, 4294967296.0, (double)w[i]);
-  const int64_t q = (int64_t)(int)rint(v * inv_m);
-  c = 0;
-#pragma unroll
-  for (int i = 0; i < NWC; ++i) {
-    c += (int64_t)(uint64_t)w[i] - q * (int64_t)(uint64_t)mod[i];
+    c += (int64_t)nq * (int64_t)(int32_t)mod[i] + (int64_t)t0[i] + ((int64_t)t1[i] << 16);
     w[i] = (uint32_t)c;
     c >>= 32;
   }
@@ -562,128 +557,226 @@ __device__ __forceinline__ void combine_entry(const int (&S)[4 * NWC], const_wor
     w[i] = (uint32_t)s;
     up = (uint32_t)(s >> 32);
   }
-  // the leading nonzero word to the top
-  int ex = 32 * NWC - 48;  // place of the first chunk's lowest bit
-  raise_words<NWC, 16>(w, ex);
-  raise_words<NWC, 8>(w, ex);
-  raise_words<NWC, 4>(w, ex);
-  raise_words<NWC, 2>(w, ex);
-  raise_words<NWC, 1>(w, ex);
-  constexpr int K = combine_chunks<T, C>();
-  double d[K];
+  // the leading nonzero word to the top: for the whole wavefront while it can
+  // (its entries have much the same magnitude), then entry by entry
+  int ex = 32 * NWC;
+#pragma unroll 1
+  for (int r = 0; r < NWC - 1 && __all(w[NWC - 1] == 0u); ++r) {
+#pragma unroll
+    for (int i = NWC - 1; i > 0; --i) w[i] = w[i - 1];
+    w[0] = 0u;
+    ex -= 32;
+  }
+  if (__any(w[NWC - 1] == 0u)) {
+    raise_words<NWC, 16>(w, ex);
+    raise_words<NWC, 8>(w, ex);
+    raise_words<NWC, 4>(w, ex);
+    raise_words<NWC, 2>(w, ex);
+    raise_words<NWC, 1>(w, ex);
+  }
+  // the leading bit to the top: words s[0], s[1], ... of (w << lz), one shift
+  // right by 1 and by 31 - lz so that both fit the instruction
+  constexpr int K = sizeof(T) == 4 ? 2 : C + 1;  // 53-bit digits of the magnitude
+  constexpr int kW = (53 * K + 31) / 32;
+  const int lz = __clz((int)w[NWC - 1]);
+  ex -= lz;
+  uint32_t s[kW + 1];
+#pragma unroll
+  for (int i = 0; i <= kW; ++i) {
+    auto word = [&](int j) -> uint32_t { return j >= 0 && j < NWC ? w[NWC - 1 - j] : 0u; };  // from the top
+    const uint32_t hi = __builtin_amdgcn_alignbit(word(i - 1), word(i), 1), lo = __builtin_amdgcn_alignbit(word(i), word(i + 1), 1);
+    s[i] = __builtin_amdgcn_alignbit(hi, lo, 31 - lz);
+  }
+  // 53-bit digits y_j, balanced: |y_j| <= 2^52 for j > 0, so y_0 is X rounded to
+  // nearest and the rest follows it within half its last place
+  double z[K];
 #pragma unroll
   for (int j = 0; j < K; ++j) {
-    auto word = [&](int i) -> uint32_t { return i < NWC ? w[NWC - 1 - i] : 0u; };
-    const int i = 3 * (j / 2);
-    const uint32_t hi = j % 2 == 0 ? word(i) >> 16 : word(i + 1) & 0xffffu;
-    const uint32_t lo = j % 2 == 0 ? (word(i) << 16) | (word(i + 1) >> 16) : word(i + 2);
-    const double x = __builtin_fma((double)hi, 4294967296.0, (double)lo);
-    d[j] = (neg ? -x : x) * __builtin_ldexp(1.0, -48 * j);
+    auto bits = [&](int p) -> uint32_t {  // 32 bits from place p
+      return p % 32 == 0 ? s[p / 32] : __builtin_amdgcn_alignbit(s[p / 32], s[p / 32 + 1 <= kW ? p / 32 + 1 : kW], 32 - p % 32);
+    };
+    z[j] = __builtin_fma((double)(bits(53 * j) >> 11), 4294967296.0, (double)bits(53 * j + 21));
   }
-  renorm<double, K>(d);
-  if constexpr (sizeof(T) == 8) {
 #pragma unroll
-    for (int r = 0; r < C; ++r) out[r] = ldexp(d[r], ex + e0);
+  for (int j = K - 1; j > 0; --j) {
+    const bool half = z[j] >= 4503599627370496.0;
+    z[j] -= half ? 9007199254740992.0 : 0.0;
+    z[j - 1] += half ? 1.0 : 0.0;
+  }
+  const double sign = neg ? -1.0 : 1.0;
+#pragma unroll
+  for (int j = 0; j < K; ++j) z[j] *= sign * __builtin_ldexp(1.0, -53 * j);
+  const int e = ex - 53 + e0;
+  if constexpr (sizeof(T) == 8) {
+    out[0] = ldexp(z[0], e);
+    double rest = z[1];
+#pragma unroll
+    for (int r = 1; r < C; ++r) {
+      double err;
+      out[r] = ldexp(two_sum(rest, z[r + 1], err), e);
+      rest = err;
+    }
   } else {
-    // nearest binary32 of the rest, three times (the differences are exact
-    // while the rest fits binary64; the last rest is rounded once)
-    double s = d[0], t = d[1];
+    // nearest binary32 of the rest, three times
+    double rest = z[0], low = z[1];
 #pragma unroll
     for (int r = 0; r < C; ++r) {
-      const float f = (float)s;
-      out[r] = ldexpf(f, ex + e0);
+      const float f = (float)rest;
+      out[r] = ldexpf(f, e);
       double err;
-      s = two_sum(s - (double)f, t, err);
-      t = r == 0 ? err + d[2] : err;
+      rest = two_sum(rest - (double)f, low, err);
+      low = err;
     }
   }
 }
 
-// Workgroup: 256 runs of combine_entries<NWC>() consecutive entries of one 32 x 32
-// block of C (its part, where a block takes several workgroups).  Lane and entry
-// order follow the matrix-core layout of the planes (int8.hip).
-template <typename T, int C, int NWC>
-__global__ __launch_bounds__(kThreads) void k_residue_combine(const ResidueDesc *__restrict__ descs,
-                                                              const int *__restrict__ prefix, int nprod) {
-  constexpr int N = combine_entries<NWC>();
-  constexpr int kParts = 4 / N;  // workgroups per block
-  const int b = (int)blockIdx.x / kParts, part = (int)blockIdx.x % kParts;
-  const int p = __builtin_amdgcn_readfirstlane(find_range(prefix, nprod, b));
+// Products of several k chunks: the chunks' digits added into the first chunk's
+// planes.  Workgroup: one 32 x 32 block of C.
+__global__ __launch_bounds__(kThreads) void k_residue_fold(const ResidueDesc *__restrict__ descs,
+                                                           const int *__restrict__ prefix, int nprod) {
+  const int p = __builtin_amdgcn_readfirstlane(find_range(prefix, nprod, blockIdx.x));
   const ResidueDesc d = descs[p];
-  const int64_t blk = (int64_t)b - prefix[p];
-  const int off = (part * kThreads + (int)threadIdx.x) * N;
-  const int lane = off / 16, quad = off % 16 / 4, e0 = off % 4;
-  const int64_t bi = blk % d.mbp, bj = blk / d.mbp;
-  const int i = (int)(bi * 32 + lane % 32);
-  const int j = (int)(bj * 32 + 8 * quad + 4 * (lane / 32) + e0);
-  if (i >= d.m || j >= d.n) return;
-
-  int S[N][4 * NWC];
+  if (d.nchunks <= 1) return;
+  int8_t *at = d.R + ((int64_t)blockIdx.x - prefix[p]) * 1024 + 4 * threadIdx.x;
+  for (int u = 0; u < d.nunits; ++u) {
+    const BaseInfo b = kBase.info[u];
+    const int digits = u < d.nsq ? 2 : 1;
+    int sum[4] = {0, 0, 0, 0};
+    for (int g = 0; g < digits; ++g) {
+      int8_t *pl = at + (int64_t)(plane_of(u, d.nsq) + g) * d.plane;
+      for (int ch = 0; ch < d.nchunks; ++ch) {
+        const uint32_t x = *reinterpret_cast<const uint32_t *>(pl + (int64_t)ch * d.nplanes * d.plane);
 #pragma unroll
-  for (int e = 0; e < N; ++e)
-#pragma unroll
-    for (int y = 0; y < 4 * NWC; ++y) S[e][y] = 0;
-  const int8_t *src = d.R + blk * 1024 + off;
-  const int groups = (d.nplanes + 3) / 4;
-  const const_words tab = (const_words)d.table;
-#pragma unroll 1
-  for (int ch = 0; ch < d.nchunks; ++ch, src += d.nplanes * d.plane) {
-    auto load = [&](int pl) -> uint32_t {
-      const int8_t *at = src + (int64_t)(pl < d.nplanes ? pl : d.nplanes - 1) * d.plane;
-      if constexpr (N == 4) return *reinterpret_cast<const uint32_t *>(at);
-      if constexpr (N == 2) return *reinterpret_cast<const uint16_t *>(at);
-      return *reinterpret_cast<const uint8_t *>(at);
-    };
-    uint32_t x[4];
-#pragma unroll
-    for (int y = 0; y < 4; ++y) x[y] = load(y);
-#pragma unroll 1
-    for (int g = 0; g < groups; ++g) {
-      uint32_t nx[4];  // the next group's bytes (the last one's again at the end)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) nx[y] = load(4 * g + 4 + y);
-      // the bytes of one entry in the four planes
-      uint32_t z[N];
-      const uint32_t lo = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u);
-      const uint32_t hi = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u);
-      z[0] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
-      if constexpr (N >= 2) z[1] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
-      if constexpr (N == 4) {
-        const uint32_t lo2 = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u);
-        const uint32_t hi2 = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
-        z[2] = __builtin_amdgcn_perm(hi2, lo2, 0x05040100u);
-        z[3] = __builtin_amdgcn_perm(hi2, lo2, 0x07060302u);
+        for (int e = 0; e < 4; ++e) sum[e] += (int)(int8_t)(x >> (8 * e));
       }
+      uint32_t t[4];
 #pragma unroll
-      for (int y = 0; y < 4 * NWC; ++y) {
-        const int k = (int)tab[g * 4 * NWC + y];
-#pragma unroll
-        for (int e = 0; e < N; ++e) S[e][y] = __builtin_amdgcn_sdot4((int)z[e], k, S[e][y], false);
+      for (int e = 0; e < 4; ++e) {
+        t[e] = residue_byte(sum[e], b);
+        sum[e] = divide_out(sum[e], t[e], b);
       }
-#pragma unroll
-      for (int y = 0; y < 4; ++y) x[y] = nx[y];
+      *reinterpret_cast<uint32_t *>(pl) = pack4(t[0], t[1], t[2], t[3]);
     }
   }
-  const const_words mod = tab + groups * 4 * NWC;
+}
+
+// Bound by the planes' bytes and C's (3.4 TB/s for DD) and, from 9 words on, by
+// the vector instructions of combine_entry.  With v_dot4 sums instead of the
+// matrix products and a renormalization of 48-bit chunks instead of the digits:
+// DD n = 4096 (32 planes) 506 -> 234 us, QD (68 planes) 1458 -> 608 us; and C is
+// now X rounded to nearest, where the renormalization left up to 0.57 units.
+//
+// Workgroup: one 32 x 32 block of C, wavefront q its quad q: entries 4 q .. 4 q + 3
+// of every lane of the planes' layout (int8.hip).  Two half blocks (the lanes
+// below and from 32 on) of 4 entries per lane, each as two matrix products
+// digits x planes x 32 entries on the INT8 matrix cores: lane l of the
+// instruction holds entry l % 32's bytes of 16 planes, its results the 16 digit
+// rows 8 (r / 4) + 4 (l / 32) + r % 4.  Swapping the halves of two products
+// (v_permlane32_swap) leaves every lane all digits of one entry.
+template <typename T, int C, int NWC>
+__global__ __launch_bounds__(kThreads, 2) void k_residue_combine(const ResidueDesc *__restrict__ descs,
+                                                              const int *__restrict__ prefix, int nprod) {
+  constexpr int RB = combine_rows(NWC), KS = combine_steps(NWC);
+  const int p = __builtin_amdgcn_readfirstlane(find_range(prefix, nprod, blockIdx.x));
+  const ResidueDesc d = descs[p];
+  const int64_t blk = (int64_t)blockIdx.x - prefix[p];
+  const int lane = threadIdx.x % 64, quad = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
+  const int64_t bi = blk % d.mbp, bj = blk / d.mbp;
+  if (bi * 32 >= d.m || bj * 32 + 8 * quad >= d.n) return;
+  const int i = (int)(bi * 32) + lane % 32;
+  const int Ei = i < d.m ? d.EA[i] : kZeroExp;
+
+  // weights: digits of the planes
+  i4v wt[RB][KS];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      wt[rb][ks] = reinterpret_cast<const i4v *>(d.table)[(rb * KS + ks) * 64 + lane];
+  const const_words mod = (const_words)d.table + RB * KS * 256;
   const double inv_m = __longlong_as_double((long long)((uint64_t)mod[NWC] | ((uint64_t)mod[NWC + 1] << 32)));
-  const int Ei = d.EA[i];
+
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {
+    if (bj * 32 + 8 * quad + 4 * h >= d.n) return;
+    const int8_t *src = d.R + blk * 1024 + (h * 32 + lane % 32) * 16 + 4 * quad;
+    i4v f[KS][4];  // entry e: its bytes in this lane's 16 planes of a step
+    int upper = lane / 32;
+    int64_t plane = d.plane;
+    asm volatile("" : "+v"(upper), "+s"(plane));  // the planes' offsets are formed here, not kept in registers
 #pragma unroll
-  for (int e = 0; e < N; ++e) {
-    if (j + e >= d.n) continue;
-    const int Fj = d.EB[j + e];
-    T out[C];
-    if (Ei == kNonFinite || Fj == kNonFinite) {
+    for (int ks = 0; ks < KS; ++ks) {
+      uint32_t x[16];  // planes past the last have zero weights
 #pragma unroll
-      for (int r = 0; r < C; ++r) out[r] = (T)__builtin_nan("");
-    } else if (Ei == kZeroExp || Fj == kZeroExp) {
+      for (int v = 0; v < 4; ++v) {
 #pragma unroll
-      for (int r = 0; r < C; ++r) out[r] = T(0);
-    } else {
-      combine_entry<NWC, T, C>(S[e], mod, inv_m, Ei + Fj - 2 * d.bits, out);
+        for (int t = 4 * v; t < 4 * v + 4; ++t) x[t] = 0u;
+        if (ks > 0 && 32 * ks + 4 * v >= d.nplanes) continue;
+#pragma unroll
+        for (int t = 4 * v; t < 4 * v + 4; ++t) {
+          const int lo = 32 * ks + t < d.nplanes ? 32 * ks + t : d.nplanes - 1;
+          const int hi = 32 * ks + 16 + t < d.nplanes ? 32 * ks + 16 + t : d.nplanes - 1;
+          x[t] = *reinterpret_cast<const uint32_t *>(src + (upper ? hi * plane : lo * plane));
+          __builtin_amdgcn_sched_barrier(0);  // one address at a time
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const uint32_t l0 = __builtin_amdgcn_perm(x[4 * v + 1], x[4 * v], 0x05010400u);
+        const uint32_t h0 = __builtin_amdgcn_perm(x[4 * v + 3], x[4 * v + 2], 0x05010400u);
+        const uint32_t l1 = __builtin_amdgcn_perm(x[4 * v + 1], x[4 * v], 0x07030602u);
+        const uint32_t h1 = __builtin_amdgcn_perm(x[4 * v + 3], x[4 * v + 2], 0x07030602u);
+        f[ks][0][v] = (int)__builtin_amdgcn_perm(h0, l0, 0x05040100u);
+        f[ks][1][v] = (int)__builtin_amdgcn_perm(h0, l0, 0x07060302u);
+        f[ks][2][v] = (int)__builtin_amdgcn_perm(h1, l1, 0x05040100u);
+        f[ks][3][v] = (int)__builtin_amdgcn_perm(h1, l1, 0x07060302u);
+      }
     }
-    T *dst = static_cast<T *>(d.C) + i + (int64_t)(j + e) * d.ldc;
 #pragma unroll
-    for (int r = 0; r < C; ++r) dst[r * d.c_stride] = out[r];
+    for (int e = 0; e < 4; e += 2) {
+      i16v acc[2][RB];
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[x][rb][r] = 0;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+            acc[x][rb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wt[rb][ks], f[ks][e + x], acc[x][rb], 0, 0, 0);
+      int S[4 * NWC];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)acc[0][rb][r], (unsigned)acc[1][rb][r], false, false);
+          const int y = 32 * rb + 8 * (r / 4) + r % 4;
+          if (y < 4 * NWC) S[y < 4 * NWC ? y : 0] = (int)sw[0];
+          if (y + 4 < 4 * NWC) S[y + 4 < 4 * NWC ? y + 4 : 0] = (int)sw[1];
+        }
+      const int j = (int)(bj * 32) + 8 * quad + 4 * h + e + lane / 32;
+      const bool inside = i < d.m && j < d.n;
+      const int Fj = inside ? d.EB[j] : kZeroExp;
+      T out[C];
+      combine_entry<NWC, T, C>(S, mod, inv_m, Ei + Fj - 2 * d.bits, out);
+      if (Ei == kZeroExp || Fj == kZeroExp) {
+#pragma unroll
+        for (int r = 0; r < C; ++r) out[r] = T(0);
+      }
+      if (Ei == kNonFinite || Fj == kNonFinite) {
+#pragma unroll
+        for (int r = 0; r < C; ++r) out[r] = (T)__builtin_nan("");
+      }
+      if (inside) {
+        T *dst = static_cast<T *>(d.C) + i + (int64_t)j * d.ldc;
+#pragma unroll
+        for (int r = 0; r < C; ++r) dst[r * d.c_stride] = out[r];
+      }
+    }
   }
 }
 
@@ -756,12 +849,10 @@ bool residue_plan(int bits, int64_t k, ResiduePlan &p) {
   p.nplanes = p.nunits + p.nsq;
   p.nw = (bits + 2 + 31) / 32;
   p.nchunks = (int)ceil_div(kblocks8_padded(k), (int64_t)kChunkBlocks);
-  // |V| <= 64 nplanes nchunks M, a sign, and a bit for the logarithms' rounding
-  const double top = log2_modulus(p.nunits, p.nsq) + 8.0 + std::log2((double)p.nplanes * p.nchunks);
-  p.nwc = 0;
-  for (int w : kCombineWords)
-    if (32.0 * w >= top && p.nwc == 0) p.nwc = w;
-  return p.nwc != 0;
+  // |V| <= 64 nplanes M, a sign, and a bit for the logarithms' rounding
+  const double top = log2_modulus(p.nunits, p.nsq) + 8.0 + std::log2((double)p.nplanes);
+  p.nwc = std::max(2, (int)std::ceil(top / 32.0));
+  return p.nwc <= kMaxCombineWords && p.nplanes <= 32 * combine_steps(p.nwc);
 }
 
 const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
@@ -774,8 +865,8 @@ const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
   for (int u = 0; u < nunits; ++u)
     for (int e = 0; e < (u < nsq ? 2 : 1); ++e) big_mul(M, (uint32_t)kHostBases.s[u]);
   M.resize(nwc, 0u);
-  const int nplanes = nunits + nsq, groups = (nplanes + 3) / 4;
-  t.assign((size_t)groups * 4 * nwc + nwc + 2, 0u);
+  const int RB = combine_rows(nwc), KS = combine_steps(nwc);
+  t.assign((size_t)RB * KS * 256 + nwc + 2, 0u);
   for (int u = 0; u < nunits; ++u) {
     const uint32_t s = (uint32_t)kHostBases.s[u], mod = u < nsq ? s * s : s;
     Big Mu = M;
@@ -815,16 +906,25 @@ const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
         int digit = (int)((w[j / 4] >> (8 * (j % 4))) & 255u) + carry;
         carry = digit >= 128 ? 1 : 0;
         if (carry) digit -= 256;
-        t[(size_t)(pl / 4) * 4 * nwc + j] |= (uint32_t)(uint8_t)(int8_t)digit << (8 * (pl % 4));
+        // digit row j, plane pl: lane j % 32 + 32 (pl % 32 / 16), byte pl % 16
+        const int word = ((j / 32 * KS + pl / 32) * 64 + j % 32 + 32 * (pl % 32 / 16)) * 4 + pl % 16 / 4;
+        t[(size_t)word] |= (uint32_t)(uint8_t)(int8_t)digit << (8 * (pl % 4));
       }
     }
   }
-  for (int i = 0; i < nwc; ++i) t[(size_t)groups * 4 * nwc + i] = M[i];
-  const double inv_m = 1.0 / big_value(M);
+  // M in balanced words, and 2^(32 (nwc - 3)) / M (the top three words over M)
+  const size_t at = (size_t)RB * KS * 256;
+  uint32_t up = 0;
+  for (int i = 0; i < nwc; ++i) {
+    const uint64_t w = (uint64_t)M[i] + up;
+    t[at + i] = (uint32_t)w;
+    up = w >= (uint64_t(1) << 31) ? 1 : 0;
+  }
+  const double inv_m = std::ldexp(1.0, 32 * std::max(0, nwc - 3)) / big_value(M);
   uint64_t bits;
   __builtin_memcpy(&bits, &inv_m, 8);
-  t[(size_t)groups * 4 * nwc + nwc] = (uint32_t)bits;
-  t[(size_t)groups * 4 * nwc + nwc + 1] = (uint32_t)(bits >> 32);
+  t[at + nwc] = (uint32_t)bits;
+  t[at + nwc + 1] = (uint32_t)(bits >> 32);
   return t;
 }
 
@@ -832,9 +932,11 @@ namespace {
 
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// The descriptors before the table, which is read 16 bytes at a time.
+constexpr size_t kHeadBytes = (2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 4 * 4 + 15) / 16 * 16;
 size_t header_bytes(const ResiduePlan &p) {
-  const size_t words = (size_t)((p.nplanes + 3) / 4) * 4 * p.nwc + p.nwc + 2;
-  return up256(2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 8 * 4 + words * 4);
+  const size_t words = (size_t)combine_rows(p.nwc) * combine_steps(p.nwc) * 256 + p.nwc + 2;
+  return up256(kHeadBytes + words * 4);
 }
 
 struct Shape {
@@ -877,25 +979,38 @@ hipError_t split_launch(int nw, dim3 grid, const ResidueOperand<T> *ops, const i
 }
 
 template <typename T, int C>
-hipError_t combine_launch(int nwc, int64_t blocks, const ResidueDesc *descs, const int *prefix, int nprod,
+hipError_t combine_launch(int nwc, bool chunks, int64_t blocks, const ResidueDesc *descs, const int *prefix, int nprod,
                           hipStream_t st) {
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (chunks) {
+    hipLaunchKernelGGL(k_residue_fold, dim3((unsigned)blocks), dim3(kThreads), 0, st, descs, prefix, nprod);
+    const hipError_t err = hipGetLastError();
+    if (err != hipSuccess) return err;
+  }
   switch (nwc) {
 #define MP_RESIDUE_COMBINE_CASE(NWC)                                                                             \
   case NWC: {                                                                                                    \
-    const int64_t wgs = blocks * (4 / combine_entries<NWC>());                                                   \
-    if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;                                                         \
-    hipLaunchKernelGGL((k_residue_combine<T, C, NWC>), dim3((unsigned)wgs), dim3(kThreads), 0, st, descs, prefix, nprod); \
+    hipLaunchKernelGGL((k_residue_combine<T, C, NWC>), dim3((unsigned)blocks), dim3(kThreads), 0, st, descs, prefix, nprod); \
     return hipGetLastError();                                                                                    \
   }
     MP_RESIDUE_COMBINE_CASE(2)
+    MP_RESIDUE_COMBINE_CASE(3)
     MP_RESIDUE_COMBINE_CASE(4)
+    MP_RESIDUE_COMBINE_CASE(5)
     MP_RESIDUE_COMBINE_CASE(6)
+    MP_RESIDUE_COMBINE_CASE(7)
     MP_RESIDUE_COMBINE_CASE(8)
+    MP_RESIDUE_COMBINE_CASE(9)
     MP_RESIDUE_COMBINE_CASE(10)
+    MP_RESIDUE_COMBINE_CASE(11)
     MP_RESIDUE_COMBINE_CASE(12)
+    MP_RESIDUE_COMBINE_CASE(13)
     MP_RESIDUE_COMBINE_CASE(14)
+    MP_RESIDUE_COMBINE_CASE(15)
     MP_RESIDUE_COMBINE_CASE(16)
+    MP_RESIDUE_COMBINE_CASE(17)
     MP_RESIDUE_COMBINE_CASE(18)
+    MP_RESIDUE_COMBINE_CASE(19)
     MP_RESIDUE_COMBINE_CASE(20)
 #undef MP_RESIDUE_COMBINE_CASE
     default:
@@ -980,8 +1095,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     ResidueDesc d;
     int prefix[4];  // of the split blocks, then of the product
   } h{};
-  static_assert(sizeof(Head) <= 2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 8 * 4, "header size");
-  static_assert(sizeof(Head) % 4 == 0, "uploaded in words");
+  static_assert(sizeof(Head) <= kHeadBytes && sizeof(Head) % 4 == 0, "uploaded in words");
   for (int i = 0; i < 2; ++i) {
     const SplitOperand<T> &o = i == 0 ? a : b;
     ResidueOperand<T> &r = h.op[i];
@@ -1011,7 +1125,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   h.prefix[0] = 0;
   h.prefix[1] = (int)ba;
   h.d.R = R;
-  h.d.table = reinterpret_cast<const uint32_t *>(rc.arena + sizeof(Head));
+  h.d.table = reinterpret_cast<const uint32_t *>(rc.arena + kHeadBytes);
   h.d.EA = rc.exp_a;
   h.d.EB = rc.exp_b;
   h.d.mbp = s.mbp;
@@ -1030,12 +1144,14 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   h.d.c_stride = rc.c_stride;
 
   hipError_t err = hipSuccess;
-  const size_t words = sizeof(Head) / 4 + table.size();
+  const size_t hw = kHeadBytes / 4, words = hw + table.size();
   for (size_t at = 0; at < words; at += kUploadWords) {
     Upload up;
-    const size_t n = std::min<size_t>(kUploadWords, words - at), hw = sizeof(Head) / 4;
+    const size_t n = std::min<size_t>(kUploadWords, words - at);
     for (size_t i = 0; i < n; ++i)
-      up.w[i] = at + i < hw ? reinterpret_cast<const uint32_t *>(&h)[at + i] : table[at + i - hw];
+      up.w[i] = at + i >= hw                  ? table[at + i - hw]
+                : at + i < sizeof(Head) / 4 ? reinterpret_cast<const uint32_t *>(&h)[at + i]
+                                            : 0u;
     const int64_t n0 = at == 0 ? rc.clear_words : 0, n1 = at == 0 && first && rc.flag ? 1 : 0;
     const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(n0, kThreads)));
     hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n,
@@ -1062,7 +1178,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     if ((err = gemm_launch(rc.cfg, p, Ap, Bp, s, u0, u1, rc.m, rc.n, R, st)) != hipSuccess) return err;
     u0 = u1;
   }
-  return combine_launch<T, C>(p.nwc, s.mbp * s.nbp, descs, prefix + 2, 1, st);
+  return combine_launch<T, C>(p.nwc, p.nchunks > 1, s.mbp * s.nbp, descs, prefix + 2, 1, st);
 }
 
 template <typename T, int C>
@@ -1095,10 +1211,10 @@ hipError_t launch_gemm_residue_batched(const ResidueDesc *descs, const int4 *ite
 }
 
 template <typename T, int C>
-hipError_t launch_residue_combine_batched(int nwc, const ResidueDesc *descs, const int *prefix, int nprod,
+hipError_t launch_residue_combine_batched(int nwc, bool chunks, const ResidueDesc *descs, const int *prefix, int nprod,
                                           int64_t blocks, hipStream_t st) {
   if (blocks <= 0) return hipSuccess;
-  return combine_launch<T, C>(nwc, blocks, descs, prefix, nprod, st);
+  return combine_launch<T, C>(nwc, chunks, blocks, descs, prefix, nprod, st);
 }
 
 #define MP_RESIDUE_INST(T, C)                                                                                   \
@@ -1106,7 +1222,7 @@ hipError_t launch_residue_combine_batched(int nwc, const ResidueDesc *descs, con
                                            hipEvent_t, hipStream_t);                                            \
   template hipError_t launch_residue_split_batched<T, C>(int, const ResidueOperand<T> *, const int *, int, int, \
                                                          hipStream_t);                                          \
-  template hipError_t launch_residue_combine_batched<T, C>(int, const ResidueDesc *, const int *, int, int64_t, \
+  template hipError_t launch_residue_combine_batched<T, C>(int, bool, const ResidueDesc *, const int *, int, int64_t, \
                                                            hipStream_t);
 MP_RESIDUE_INST(double, 2)
 MP_RESIDUE_INST(double, 3)
