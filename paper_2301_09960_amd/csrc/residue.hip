@@ -2,12 +2,12 @@
 // (residue.h): split into residue planes, one INT8 matrix product per plane,
 // and the Chinese remainder combination into the components of C.
 //
-// k_residue_split: one workgroup per 32 x 32 block of an operand and range of
-// bases.  The element's integer W is formed in 32-bit words (window.h), rounded
-// to nearest on 32 guard bits, and its residue modulo s is the dot product of
-// its bytes with the residues of 256^j (v_dot4_u32_u8, four bytes each),
-// reduced by one binary32 quotient.  Each plane of the block is written by one
-// coalesced 4-byte store per thread.
+// k_residue_split: one workgroup per 32 x 32 block of an operand.  The element's
+// integer W is formed in 32-bit words, rounded to nearest on 32 guard bits, and
+// written in signed bytes; its residues modulo 32 bases are a matrix product
+// (bases x bytes) (bytes x elements) with the residues of 256^j on the INT8 matrix
+// cores, each reduced by one binary32 quotient.  Each plane of the block is
+// written by one coalesced 4-byte store per thread.
 //
 // k_gemm_residue: gemm_int8_tile over the units of a plan.  A unit's exact sum
 // is reduced modulo its base in registers and leaves as one byte per entry (the
@@ -68,6 +68,7 @@ constexpr Bases make_bases() {
 constexpr Bases kHostBases = make_bases();
 static_assert(kHostBases.s[0] == 256 && kHostBases.s[kNumBases - 1] == 29, "the greedy coprime sequence");
 
+constexpr int kSplitRows = 64;
 struct BaseInfo {
   int s;
   int c16;        // 2^16 mod s, balanced
@@ -75,47 +76,60 @@ struct BaseInfo {
   uint32_t sinv;  // odd s: s^-1 mod 2^32
 };
 struct BaseTables {
-  BaseInfo info[kNumBases];
-  // residues of 256^(4 w + b) modulo s (byte b of word w), and modulo s^2 in two bytes
-  uint32_t pow[kNumBases][kMaxWindowWords];
-  uint32_t pow2lo[kNumBases][kMaxWindowWords], pow2hi[kNumBases][kMaxWindowWords];
-  // the offset 2^(32 NW - 1) that makes W unsigned, taken off again: modulo s and s^2
-  uint32_t init[kMaxWindowWords + 1][kNumBases], init2[kMaxWindowWords + 1][kNumBases];
+  BaseInfo info[kSplitRows];  // bases, then ones
 };
 constexpr BaseTables make_tables() {
   BaseTables t{};
-  for (int u = 0; u < kNumBases; ++u) {
-    const int s = kHostBases.s[u], s2 = s * s;
+  for (int u = 0; u < kSplitRows; ++u) {
+    const int s = u < kNumBases ? kHostBases.s[u] : 1;
     int c16 = 65536 % s;
     if (2 * c16 > s) c16 -= s;
     uint32_t inv = 1;
     if (s % 2)
       for (int i = 0; i < 5; ++i) inv *= 2u - (uint32_t)s * inv;  // Newton: s inv = 1 mod 2^32
     t.info[u] = {s, c16, 1.0f / (float)s, inv};
-    int64_t p = 1, p2 = 1;  // 256^j
-    for (int w = 0; w < kMaxWindowWords; ++w)
-      for (int b = 0; b < 4; ++b) {
-        t.pow[u][w] |= (uint32_t)(p % s) << (8 * b);
-        t.pow2lo[u][w] |= (uint32_t)(p2 % s2 & 255) << (8 * b);
-        t.pow2hi[u][w] |= (uint32_t)(p2 % s2 >> 8) << (8 * b);
-        p = p * 256 % s;
-        p2 = p2 * 256 % s2;
-      }
-    int64_t h = 1, h2 = 1;  // 2^e
-    for (int e = 1; e <= 32 * kMaxWindowWords; ++e) {
-      if (e % 32 == 0) {  // h = 2^(e - 1)
-        t.init[e / 32][u] = (uint32_t)(s - h);
-        t.init2[e / 32][u] = (uint32_t)(s2 - h2);
-      }
-      h = h * 2 % s;
-      h2 = h2 * 2 % s2;
-    }
   }
   return t;
 }
 __constant__ BaseTables kBase = make_tables();
 
-__host__ __device__ inline int plane_of(int u, int nsq) { return u < nsq ? 2 * u : nsq + u; }
+// Operands of the split's matrix products: rows u < 64 hold the balanced residues
+// c of 256^j modulo base u, rows 64 + u the balanced (256^j - c) / s modulo s, so
+// that 256^j = c + s h modulo s^2.  Bytes j = 0 .. 31 as blocks of 32 rows for the
+// 32x32x32 instruction (lane l: row l % 32, bytes 16 (l / 32) + t), and j = 0 .. 15
+// and 32 .. 47 for the 32x32x16 one (bytes 8 (l / 32) + t).
+struct SplitRows {
+  int8_t k32[4][64][16], k16[2][4][64][8];
+};
+constexpr SplitRows make_rows() {
+  SplitRows t{};
+  for (int u = 0; u < kNumBases; ++u) {
+    const int64_t s = kHostBases.s[u];
+    int64_t p = 1;  // 256^j mod s^2
+    for (int j = 0; j < 48; ++j) {
+      int64_t c = p % s;
+      if (2 * c > s) c -= s;
+      int64_t h = ((p - c) / s) % s;
+      if (2 * h > s) h -= s;
+      for (int g = 0; g < 2; ++g) {
+        const int64_t v = g == 0 ? c : h;
+        const int rb = 2 * g + u / 32, row = u % 32;
+        if (j < 32) t.k32[rb][row + 32 * (j / 16)][j % 16] = (int8_t)v;
+        if (j < 16) t.k16[0][rb][row + 32 * (j / 8)][j % 8] = (int8_t)v;
+        if (j >= 32) t.k16[1][rb][row + 32 * ((j - 32) / 8)][j % 8] = (int8_t)v;
+      }
+      p = p * 256 % (s * s);
+    }
+  }
+  return t;
+}
+__device__ const SplitRows kRows = make_rows();
+
+// Planes: the first digits of a plan's (or a group's) n bases, then the second
+// digits of the squared ones: digit g of base u is plane u + g n.
+__host__ __device__ inline int group_planes(int u0, int u1, int nsq) {
+  return u1 - u0 + (u0 < nsq ? (u1 < nsq ? u1 : nsq) - u0 : 0);
+}
 
 // Low byte of the balanced residue of r modulo the base (|r| < 2^22.2; for
 // s = 256 the low byte of r).  q = rint(r / s) comes out of the low bits of
@@ -170,8 +184,9 @@ __device__ __forceinline__ int vector_exponent(typename bits_of<T>::type mu, int
   return ex;
 }
 
-// One block: bases [u0, u1) into planes counted from base u_first's.  The
-// FLOAT form's checks (below) run with `check`.
+// One block: bases [u_first, u_end) into planes counted from base u_first's; of
+// the row blocks of 32 bases this workgroup takes every parts-th from part on.
+// The FLOAT form's checks (below) run with `check`.
 //
 // The FLOAT form stands for D passes of Algorithm 1, whose grid follows the
 // largest residual of the vector: pass 1 rounds to 2^(E - b), and pass a + 1 to
@@ -205,9 +220,43 @@ __device__ __forceinline__ bool last_grid_covered(const uint32_t *changes, int b
   return true;
 }
 
+// Adds M 2^off (two's complement, off >= 0) into the words w: the three words of
+// M 2^(off % 32), the sign above and zeros below, moved up by off / 32 in steps of
+// 1, 2, 4 and 8 words.
+template <int N>
+__device__ __forceinline__ void window_add_shifted(uint32_t (&w)[N], int64_t M, int off) {
+  const int q = off >> 5, sh = off & 31;
+  const uint64_t u = (uint64_t)M << sh;
+  const int hi = (int)(M >> 32);
+  const uint32_t sign = (uint32_t)(hi >> 31);
+  uint32_t a[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) a[i] = sign;
+  a[0] = (uint32_t)u;
+  if constexpr (N > 1) a[1] = (uint32_t)(u >> 32);
+  if constexpr (N > 2) a[2] = (uint32_t)((hi >> (31 - sh)) >> 1);
+  int filled = 3;  // words that may differ from the sign
+#pragma unroll
+  for (int st = 1; st < N; st *= 2) {
+    const bool up = (q & st) != 0;
+    filled += st;
+#pragma unroll
+    for (int i = N - 1; i >= 0; --i)
+      if (i < filled) a[i] = up ? (i >= st ? a[i >= st ? i - st : 0] : 0u) : a[i];
+  }
+  uint32_t carry = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) w[i] = __builtin_addc(w[i], a[i], carry, &carry);
+}
+
+// Bound by memory for DD (1.6 GB at 3.3 TB/s, the planes in 1 KiB pieces; n = 4096)
+// and by vector instructions from TD on: 4 per residue (conversion, quotient,
+// remainder, byte) against 4 + words / 4 with v_dot4 sums, and the words placed by
+// a shift in powers of two instead of one select chain per word.  Against those:
+// DD n = 4096 (32 planes) 616 -> 496 us, QD (68 planes) 1566 -> 1334 us.
 template <typename T, int C, int NW, int ORIENT>
-__device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u0, int u1,
-                              bool check) {
+__device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u_end,
+                              int part, int parts, bool check) {
   using U = typename bits_of<T>::type;
   const int64_t nb = live_only ? ceil_div((int64_t)op.nvec, (int64_t)kBlk8) : op.nbp;
   const int64_t kbn = live_only ? ceil_div((int64_t)op.len, (int64_t)kKBlk8) : op.kbp;
@@ -215,7 +264,7 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   // B (columns, contiguous along k): walk k blocks fastest.
   const int64_t vb = ORIENT == 0 ? blk % nb : blk / kbn;
   const int64_t kb = ORIENT == 0 ? blk / nb : blk % kbn;
-  const int t = threadIdx.x, l = t >> 2;
+  const int t = threadIdx.x, l = t >> 2, lane = t % 64;
   const int v = (int)(vb * kBlk8) + (l & 31);
   const int p0 = (int)(kb * kKBlk8) + 16 * (l >> 5) + 4 * (t & 3);
 
@@ -223,47 +272,52 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   if (v < op.nvec) E = vector_exponent<T>(static_cast<const U *>(op.mu)[v], op.float_form);
   const bool finite = E != kZeroExp && E != kNonFinite;
   const int P = finite ? E - op.bits - 32 : 0;  // place of the window's lowest bit: 32 guard bits
-  uint32_t W[4][NW];  // W + 2^(32 NW - 1)
+  // Matrix operands of the elements (columns): words 0 .. 7 for the 32x32x32
+  // instruction (with up to 4 words 0 .. 3 for the 32x32x16 one), words 8 .. 11.
+  // x: the elements of lanes 0 .. 31, y: of lanes 32 .. 63.
+  constexpr bool kSmall = NW <= 4, kMore = NW > 8;
+  constexpr int kQ = kSmall ? 2 : 4;  // words per lane of the first instruction
+  uint32_t ox[4][kQ], oy[4][kQ], mx[4][2], my[4][2];
   bool inexact = false, odd = false;
   uint32_t change[NW] = {};
+  T xs[4][C];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    uint32_t w[NW + 1];
-#pragma unroll
-    for (int i = 0; i <= NW; ++i) w[i] = 0u;
     const bool live = finite && v < op.nvec && p0 + j < op.len;
     const T *x = op.X + (live ? (int64_t)v * op.sv + (int64_t)(p0 + j) * op.sp : 0);
 #pragma unroll
+    for (int r = 0; r < C; ++r) xs[j][r] = live ? x[r * op.comp_stride] : T(0);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    __builtin_amdgcn_sched_barrier(0);  // one element after another: their words together take too many registers
+    uint32_t w[NW + 1];
+#pragma unroll
+    for (int i = 0; i <= NW; ++i) w[i] = 0u;
+#pragma unroll
     for (int r = 0; r < C; ++r) {
-      const T xr = live ? x[r * op.comp_stride] : T(0);
+      const T xr = xs[j][r];
       int64_t M;
       int q;
       parts_of(xr, M, q);
-      int off = q - P;
-      if (M != 0) {
-        if (check && r > 0 && q + (sizeof(T) == 8 ? 53 : 24) > E - 20) odd = true;  // also infinities and NaN
-        if (off < 0) {
-          const int sh = off > -63 ? -off : 63;
-          if (check) inexact = inexact || (M & ((int64_t(1) << sh) - 1)) != 0;
-          M >>= sh;
-          off = 0;
-        }
-        window_add<NW + 1>(w, M, off);
+      const int off = q - P;
+      const int sh = off >= 0 ? 0 : off > -63 ? -off : 63;
+      if (check) {
+        if (r > 0 && M != 0 && q + (sizeof(T) == 8 ? 53 : 24) > E - 20) odd = true;  // also infinities and NaN
+        inexact = inexact || (M & ((int64_t(1) << sh) - 1)) != 0;
       }
+      window_add_shifted<NW + 1>(w, M >> sh, off < 0 ? 0 : off);
     }
     inexact = inexact || w[0] != 0u;
+    uint32_t W[12];  // signed bytes with the sum W: W + 0x80..80, each byte less 128
     uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits
 #pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      const uint64_t sum = (uint64_t)w[i + 1] + carry;
-      W[j][i] = (uint32_t)sum;
-      carry = (uint32_t)(sum >> 32);
-    }
+    for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(w[i + 1], 0u, carry, &carry);
     if (check && kb == 0) {  // the changes of bits but the last ones of the element
       bool more = false;     // a change further down
 #pragma unroll
       for (int i = 0; i < NW; ++i) {
-        uint32_t c = W[j][i] ^ ((W[j][i] << 1) | (i > 0 ? W[j][i > 0 ? i - 1 : 0] >> 31 : 0u));
+        uint32_t c = W[i] ^ ((W[i] << 1) | (i > 0 ? W[i > 0 ? i - 1 : 0] >> 31 : 0u));
         const bool here = c != 0u;
         if (!more && here) {  // the lowest change, and the place above it
           const uint32_t low = c & (0u - c);
@@ -273,47 +327,125 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
         change[i] |= c;
       }
     }
-    W[j][NW - 1] ^= 0x80000000u;
-  }
-
-  const int64_t plane = op.nbp * op.kbp * 1024;
-  const int first = plane_of(u_first, op.nsq);
-  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
-  auto put = [&](int pl, const uint32_t (&b)[4]) {
-    *reinterpret_cast<uint32_t *>(dst + (int64_t)(pl - first) * plane) = pack4(b[0], b[1], b[2], b[3]);
-  };
-  for (int u = u0; u < u1; ++u) {
-    const BaseInfo bi = kBase.info[u];
-    uint32_t byte[4];
-    if (u < op.nsq) {  // two s-adic digits of the residue modulo s^2
-      uint32_t next[4];
+    carry = 0u;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t lo = kBase.init2[NW][u], hi = 0u;
+    for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(W[i], 0x80808080u, carry, &carry) ^ 0x80808080u;
 #pragma unroll
-        for (int i = 0; i < NW; ++i) {
-          lo = __builtin_amdgcn_udot4(W[j][i], kBase.pow2lo[u][i], lo, false);
-          hi = __builtin_amdgcn_udot4(W[j][i], kBase.pow2hi[u][i], hi, false);
-        }
-        const int r = (int)(lo + (hi << 8));  // < 2^30
-        byte[j] = residue_byte(fold16(r, bi), bi);
-        next[j] = residue_byte(fold16(divide_out(r, byte[j], bi), bi), bi);
+    for (int i = NW; i < 12; ++i) W[i] = 0u;
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+      const auto sw = __builtin_amdgcn_permlane32_swap(W[i], W[i + kQ], false, false);
+      ox[j][i] = sw[0];
+      oy[j][i] = sw[1];
+    }
+    if constexpr (kMore) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const auto sw = __builtin_amdgcn_permlane32_swap(W[8 + i], W[10 + i], false, false);
+        mx[j][i] = sw[0];
+        my[j][i] = sw[1];
       }
-      put(2 * u, byte);
-      put(2 * u + 1, next);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        uint32_t r = kBase.init[NW][u];
-#pragma unroll
-        for (int i = 0; i < NW; ++i) r = __builtin_amdgcn_udot4(W[j][i], kBase.pow[u][i], r, false);
-        byte[j] = residue_byte((int)r, bi);  // r < 36 255 255 < 2^21.2
-      }
-      put(op.nsq + u, byte);
     }
   }
 
-  if (p0 == 0 && v < op.nvec && u0 == u_first) op.exps[v] = E;
+  const int64_t plane = op.nbp * op.kbp * 1024;
+  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
+  auto product = [&](int rb, int j, bool y) {  // 32 bases of row block rb, 32 elements j
+    i16v acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0;
+    uint32_t o[kQ];
+#pragma unroll
+    for (int i = 0; i < kQ; ++i) {
+      o[i] = y ? oy[j][i] : ox[j][i];
+      asm volatile("" : "+v"(o[i]));  // formed at its place: all products at once take too many registers
+    }
+    if constexpr (kSmall) {
+      const int64_t a = *reinterpret_cast<const int64_t *>(kRows.k16[0][rb][lane]);
+      acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(a, (int64_t)((uint64_t)o[0] | ((uint64_t)o[1] << 32)), acc, 0, 0, 0);
+    } else {
+      const i4v a = *reinterpret_cast<const i4v *>(kRows.k32[rb][lane]);
+      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, i4v{(int)o[0], (int)o[1], (int)o[kQ - 2], (int)o[kQ - 1]}, acc, 0, 0, 0);
+    }
+    if constexpr (kMore) {
+      const uint32_t(&m)[2] = y ? my[j] : mx[j];
+      const int64_t a = *reinterpret_cast<const int64_t *>(kRows.k16[1][rb][lane]);
+      acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(a, (int64_t)((uint64_t)m[0] | ((uint64_t)m[1] << 32)), acc, 0, 0, 0);
+    }
+    return acc;
+  };
+  auto insert = [](uint32_t word, uint32_t byte, int j) -> uint32_t {
+    return j == 0 ? byte : __builtin_amdgcn_perm(byte, word, j == 1 ? 0x03020400u : j == 2 ? 0x03040100u : 0x04020100u);
+  };
+  // Row blocks of 32 bases: the (first) digits of blocks 0 and 1, then the second
+  // digits of those with squared bases.  Row r of a result: base 32 rb + 8 (r / 4)
+  // + r % 4 in lanes 0 .. 31, four more from 32 on.
+  const int second = (op.nsq + 31) / 32;
+  for (int pass = part; pass < 2 + second; pass += parts) {
+    const bool digit2 = pass >= 2;
+    const int rb = digit2 ? pass - 2 : pass, end = digit2 && u_end > op.nsq ? op.nsq : u_end;
+    if (32 * rb >= end || 32 * rb + 32 <= u_first) continue;
+    float inv[16];
+    int ns[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const BaseInfo b = kBase.info[32 * rb + 8 * (r / 4) + 4 * (lane / 32) + r % 4];
+      inv[r] = b.inv;
+      ns[r] = -b.s;
+    }
+    auto quotient = [&](int x, int r) { return __float_as_int(__builtin_fmaf((float)x, inv[r], 12582912.0f)); };
+    uint32_t word[2][16] = {};
+    i16v c = product(rb, 0, false);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {  // elements j of half y; the next product runs beside the reduction
+      const int j = i % 4, y = i / 4;
+      i16v c1 = c;
+      if (i < 7) c = product(rb, (i + 1) % 4, i + 1 >= 4);
+      if (digit2) {  // c-sum + s h-sum, without its digit 0
+        const i16v h = product(rb + 2, j, y != 0);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+          if (a > 0 && 32 * rb + 8 * a >= end) break;
+#pragma unroll
+          for (int r = 4 * a; r < 4 * a + 4; ++r) {
+            int q = quotient(c1[r], r) - 0x4B400000;
+            if (r == 0 && ns[0] == -256) q = (c1[0] + 128) >> 8;  // the byte 0x80 stands for -128
+            c1[r] = q + h[r];
+          }
+        }
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        if (a > 0 && 32 * rb + 8 * a >= end) break;  // no bases from here on
+#pragma unroll
+        for (int r = 4 * a; r < 4 * a + 4; ++r) {
+          word[y][r] = insert(j == 0 ? 0u : word[y][r], (uint32_t)(__mul24(quotient(c1[r], r), ns[r]) + c1[r]), j);
+          asm volatile("" : "+v"(word[y][r]));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // the rows in the order of their planes
+    int8_t *to = dst + (int64_t)(32 * rb - u_first + (digit2 ? u_end - u_first : 0)) * plane;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      uint32_t w8[8];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const auto w2 = __builtin_amdgcn_permlane32_swap(word[0][4 * a + r], word[1][4 * a + r], false, false);
+        w8[r] = w2[0];
+        w8[r + 4] = w2[1];
+      }
+#pragma unroll
+      for (int r = 0; r < 8; ++r) {
+        const int u = 32 * rb + 8 * a + r;
+        if (u >= u_first && u < end) *reinterpret_cast<uint32_t *>(to) = w8[r];
+        to += plane;
+      }
+    }
+  }
+
+  if (p0 == 0 && v < op.nvec && part == 0) op.exps[v] = E;
   if (!check) return;
   __shared__ uint32_t seen[kBlk8][NW];
   __shared__ int rounded[kBlk8];
@@ -357,35 +489,33 @@ __device__ __forceinline__ int find_range(const int *prefix, int n, int b) {
   return lo;
 }
 
-// Workgroup (x, y): block x - prefix[i] of operand i, part y of the bases
-// [u_first, u_end) (u_end < 0: every base of the operand).
+// Workgroup (x, y): block x - prefix[i] of operand i, every gridDim.y-th row
+// block of the bases [u_first, u_end) (u_end < 0: every base of the operand).
 template <typename T, int C, int NW>
-__global__ __launch_bounds__(kThreads) void k_residue_split(const ResidueOperand<T> *__restrict__ ops,
+__global__ __launch_bounds__(kThreads, 2) void k_residue_split(const ResidueOperand<T> *__restrict__ ops,
                                                             const int *__restrict__ prefix, int nops, int live_only,
                                                             int u_first, int u_end) {
   const int i = __builtin_amdgcn_readfirstlane(find_range(prefix, nops, blockIdx.x));
   const ResidueOperand<T> op = ops[i];
   const int64_t blk = (int64_t)blockIdx.x - prefix[i];
-  const int end = u_end < 0 ? op.nunits : u_end, count = end - u_first;
-  const int u0 = u_first + count * (int)blockIdx.y / (int)gridDim.y;
-  const int u1 = u_first + count * ((int)blockIdx.y + 1) / (int)gridDim.y;
+  const int end = u_end < 0 ? op.nunits : u_end, part = blockIdx.y, parts = gridDim.y;
   const bool check = op.float_form != 0 && u_first == 0 && blockIdx.y == 0;
   if (op.orient == 0)
-    residue_block<T, C, NW, 0>(op, blk, live_only != 0, u_first, u0, u1, check);
+    residue_block<T, C, NW, 0>(op, blk, live_only != 0, u_first, end, part, parts, check);
   else
-    residue_block<T, C, NW, 1>(op, blk, live_only != 0, u_first, u0, u1, check);
+    residue_block<T, C, NW, 1>(op, blk, live_only != 0, u_first, end, part, parts, check);
 }
 
 // ---------------------------------------------------------------------------
 // GEMM.
 // ---------------------------------------------------------------------------
-// Work of one tile: units u0 .. u1 - 1 of the plan.  Operand planes are counted
-// from unit u_first's first plane, result planes from the k chunk's first.
+// Work of one tile: bases u0 .. u1 - 1 of the plan.  Operand planes are those of
+// a group of bases, result planes the plan's in this k chunk.
 // Products are at most 2^14 in magnitude: 32768 k of them twice (the two pairs of
 // a square's second diagonal) and a carry stay below 2^31, so longer k is cut into
 // chunks with result planes of their own, which k_residue_fold adds up.
 struct ResidueWork {
-  int u0, u1, u_first, nsq;
+  int u0, u1, u_first, count, nsq, nunits;  // bases [u_first, u_first + count) of nunits have operand planes
   int8_t *R;
   int64_t plane, mbp;
   __device__ int pairs() const { return residue_pairs_below(u1, nsq) - residue_pairs_below(u0, nsq); }
@@ -399,15 +529,14 @@ struct ResidueWork {
       }
     }
   }
-  __device__ int at(const PairCursor &c) const { return plane_of(c.u, nsq) - plane_of(u_first, nsq); }
-  __device__ int a_plane(const PairCursor &c) const { return at(c) + c.s - 1; }
-  __device__ int b_plane(const PairCursor &c) const { return at(c) + c.g - c.s; }
+  __device__ int a_plane(const PairCursor &c) const { return c.u - u_first + (c.s - 1) * count; }
+  __device__ int b_plane(const PairCursor &c) const { return c.u - u_first + (c.g - c.s) * count; }
   __device__ bool diagonal_ends(const PairCursor &c) const { return c.s == c.g; }
   template <int BI, int BJ>
   __device__ __forceinline__ void finish(const PairCursor &c, i16v (&acc)[BJ][BI], int64_t bi0, int64_t bj0,
                                          int lane) const {
     const BaseInfo b = kBase.info[c.u];
-    int8_t *out = R + (int64_t)(plane_of(c.u, nsq) + c.g - 1) * plane;
+    int8_t *out = R + (int64_t)(c.u + (c.g - 1) * nunits) * plane;
 #pragma unroll
     for (int y = 0; y < BJ; ++y)
 #pragma unroll
@@ -459,7 +588,7 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
   const int64_t kb0 = (int64_t)blockIdx.y * kChunkBlocks;
   const int64_t kb1 = kb0 + kChunkBlocks < kbp ? kb0 + kChunkBlocks : kbp;
   const int nks = (int)ceil_div(kb1 - kb0, KSB), last = (int)(kb1 - kb0) - (nks - 1) * KSB;
-  const ResidueWork work{u0, u1, u_first, nsq, R + (int64_t)blockIdx.y * nplanes * plane, plane, mbp};
+  const ResidueWork work{u0, u1, u_first, u_end - u_first, nsq, nplanes - nsq, R + (int64_t)blockIdx.y * nplanes * plane, plane, mbp};
   gemm_int8_tile<CFG>(work, A, B, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, lds);
 }
 
@@ -489,7 +618,9 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
     const ResidueWork work{residue_group_start(0, d.nunits, d.nsq, w.w, d.groups),
                            residue_group_start(0, d.nunits, d.nsq, w.w + 1, d.groups),
                            0,
+                           d.nunits,
                            d.nsq,
+                           d.nunits,
                            d.R + (int64_t)w.z * d.nplanes * d.plane,
                            d.plane,
                            d.mbp};
@@ -643,7 +774,7 @@ __global__ __launch_bounds__(kThreads) void k_residue_fold(const ResidueDesc *__
     const int digits = u < d.nsq ? 2 : 1;
     int sum[4] = {0, 0, 0, 0};
     for (int g = 0; g < digits; ++g) {
-      int8_t *pl = at + (int64_t)(plane_of(u, d.nsq) + g) * d.plane;
+      int8_t *pl = at + (int64_t)(u + g * d.nunits) * d.plane;
       for (int ch = 0; ch < d.nchunks; ++ch) {
         const uint32_t x = *reinterpret_cast<const uint32_t *>(pl + (int64_t)ch * d.nplanes * d.plane);
 #pragma unroll
@@ -840,7 +971,7 @@ bool residue_plan(int bits, int64_t k, ResiduePlan &p) {
     int sq = 0;
     while (l < need && sq < n) l += std::log2((double)kHostBases.s[sq++]);
     if (l < need) continue;
-    if (p.nunits == 0 || n + 2 * sq < p.products()) {
+    if (p.nunits == 0 || n + 2 * sq <= p.products()) {  // of equal ones that with fewer squares
       p.nunits = n;
       p.nsq = sq;
     }
@@ -900,7 +1031,7 @@ const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
         }
       }
       if (larger) w = other;
-      const int pl = plane_of(u, nsq) + g;
+      const int pl = u + g * nunits;
       int carry = 0;
       for (int j = 0; j < 4 * nwc; ++j) {
         int digit = (int)((w[j / 4] >> (8 * (j % 4))) & 255u) + carry;
@@ -1168,9 +1299,9 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   const auto *prefix = reinterpret_cast<const int *>(rc.arena + offsetof(Head, prefix));
   for (int u0 = 0; u0 < p.nunits;) {
     int u1 = u0 + 1;
-    while (u1 < p.nunits && plane_of(u1 + 1, p.nsq) - plane_of(u0, p.nsq) <= room) ++u1;
-    // a grid of few blocks spreads the bases over gridDim.y
-    const int parts = (int)std::max<int64_t>(1, std::min<int64_t>((u1 - u0) / 8, 1024 / (ba + bb)));
+    while (u1 < p.nunits && group_planes(u0, u1 + 1, p.nsq) <= room) ++u1;
+    // a grid of few blocks spreads the row blocks over gridDim.y
+    const int parts = u1 > 32 && ba + bb <= 512 ? 2 : 1;
     if ((err = split_launch<T, C>(p.nw, dim3((unsigned)(ba + bb), (unsigned)parts), ops, prefix, 2, 0, u0, u1, st)) !=
         hipSuccess)
       return err;
