@@ -77,6 +77,8 @@ struct BaseInfo {
 };
 struct BaseTables {
   BaseInfo info[kSplitRows];  // bases, then ones
+  float inv[kSplitRows];
+  int ns[kSplitRows];  // -s
 };
 constexpr BaseTables make_tables() {
   BaseTables t{};
@@ -88,6 +90,8 @@ constexpr BaseTables make_tables() {
     if (s % 2)
       for (int i = 0; i < 5; ++i) inv *= 2u - (uint32_t)s * inv;  // Newton: s inv = 1 mod 2^32
     t.info[u] = {s, c16, 1.0f / (float)s, inv};
+    t.inv[u] = 1.0f / (float)s;
+    t.ns[u] = -s;
   }
   return t;
 }
@@ -249,14 +253,27 @@ __device__ __forceinline__ void window_add_shifted(uint32_t (&w)[N], int64_t M, 
   for (int i = 0; i < N; ++i) w[i] = __builtin_addc(w[i], a[i], carry, &carry);
 }
 
+template <int NW>
+struct SplitLds {
+  static constexpr bool kSmall = NW <= 4, kMore = NW > 8;
+  static constexpr int kQ = kSmall ? 2 : 4;  // words per lane of the first instruction
+  __attribute__((aligned(16))) uint32_t first[kThreads / 64][4][64][2 * kQ];
+  __attribute__((aligned(16))) uint32_t more[kMore ? kThreads / 64 : 1][4][64][4];
+  uint32_t seen[kBlk8][NW];
+  int rounded[kBlk8];
+};
+
 // Bound by memory for DD (1.6 GB at 3.3 TB/s, the planes in 1 KiB pieces; n = 4096)
 // and by vector instructions from TD on: 4 per residue (conversion, quotient,
 // remainder, byte) against 4 + words / 4 with v_dot4 sums, and the words placed by
 // a shift in powers of two instead of one select chain per word.  Against those:
-// DD n = 4096 (32 planes) 616 -> 496 us, QD (68 planes) 1566 -> 1334 us.
+// DD n = 4096 (32 planes) 616 -> 496 us, QD (68 planes) 1566 -> 1334 us.  The chains
+// of a residue are hidden by wavefronts only: four to a SIMD (operands in LDS, the
+// checks before the products, scalar constants) against two or three took FLOAT DD
+// (37 planes) from 781 to 611 us, QD from 1334 to 1091.
 template <typename T, int C, int NW, int ORIENT>
 __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u_end,
-                              int part, int parts, bool check) {
+                              int part, int parts, bool check, SplitLds<NW> &lds) {
   using U = typename bits_of<T>::type;
   const int64_t nb = live_only ? ceil_div((int64_t)op.nvec, (int64_t)kBlk8) : op.nbp;
   const int64_t kbn = live_only ? ceil_div((int64_t)op.len, (int64_t)kKBlk8) : op.kbp;
@@ -272,12 +289,14 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   if (v < op.nvec) E = vector_exponent<T>(static_cast<const U *>(op.mu)[v], op.float_form);
   const bool finite = E != kZeroExp && E != kNonFinite;
   const int P = finite ? E - op.bits - 32 : 0;  // place of the window's lowest bit: 32 guard bits
-  // Matrix operands of the elements (columns): words 0 .. 7 for the 32x32x32
-  // instruction (with up to 4 words 0 .. 3 for the 32x32x16 one), words 8 .. 11.
-  // x: the elements of lanes 0 .. 31, y: of lanes 32 .. 63.
-  constexpr bool kSmall = NW <= 4, kMore = NW > 8;
-  constexpr int kQ = kSmall ? 2 : 4;  // words per lane of the first instruction
-  uint32_t ox[4][kQ], oy[4][kQ], mx[4][2], my[4][2];
+  // Matrix operands of the elements (columns) in LDS, each wavefront's its own:
+  // words 0 .. 7 for the 32x32x32 instruction (with up to 4 words 0 .. 3 for the
+  // 32x32x16 one), then words 8 .. 11.  Held in registers they left two or three
+  // wavefronts to a SIMD, and the kernel waits on its chains.
+  constexpr bool kSmall = SplitLds<NW>::kSmall, kMore = SplitLds<NW>::kMore;
+  constexpr int kQ = SplitLds<NW>::kQ;
+  auto &first_words = lds.first[t / 64];
+  auto &more_words = lds.more[kMore ? t / 64 : 0];
   bool inexact = false, odd = false;
   uint32_t change[NW] = {};
   T xs[4][C];
@@ -333,17 +352,41 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
 #pragma unroll
     for (int i = NW; i < 12; ++i) W[i] = 0u;
 #pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      const auto sw = __builtin_amdgcn_permlane32_swap(W[i], W[i + kQ], false, false);
-      ox[j][i] = sw[0];
-      oy[j][i] = sw[1];
+    for (int i = 0; i < 2 * kQ; i += 4)
+      *reinterpret_cast<i4v *>(&first_words[j][lane][i]) = i4v{(int)W[i], (int)W[i + 1], (int)W[i + 2], (int)W[i + 3]};
+    if constexpr (kMore)
+      *reinterpret_cast<i4v *>(&more_words[j][lane][0]) = i4v{(int)W[8], (int)W[9], (int)W[10], (int)W[11]};
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // other lanes' words are read from here on
+
+  if (p0 == 0 && v < op.nvec && part == 0) op.exps[v] = E;
+  if (check) {  // before the products: its words per element need not be kept through them
+    auto &seen = lds.seen;
+    auto &rounded = lds.rounded;
+    for (int i = t; i < kBlk8 * NW; i += kThreads) seen[i / NW][i % NW] = 0u;
+    if (t < kBlk8) rounded[t] = 0;
+    __syncthreads();
+    if (inexact) rounded[l & 31] = 1;
+    auto fall_back = [&]() {
+      *op.flag = 1;
+      if (op.any) *op.any = 1;
+    };
+    if (odd) fall_back();
+    if (kb == 0) {
+  #pragma unroll
+      for (int i = 0; i < NW; ++i) atomicOr(&seen[l & 31][i], change[i]);
     }
-    if constexpr (kMore) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const auto sw = __builtin_amdgcn_permlane32_swap(W[8 + i], W[10 + i], false, false);
-        mx[j][i] = sw[0];
-        my[j][i] = sw[1];
+    __syncthreads();
+    if (t < kBlk8) {
+      const int vt = (int)(vb * kBlk8) + t;
+      if (vt < op.nvec) {
+        int add = rounded[t];
+        if (kb == 0 && !last_grid_covered<NW>(seen[t], op.bits, op.slice_bits, op.passes)) add |= 2;
+        // bit 0: an element was rounded; bit 1: the slices may reach further down
+        if (add & ~*(volatile int *)&op.state[vt]) {
+          const int old = atomicOr(&op.state[vt], add);
+          if ((old | add) == 3) fall_back();
+        }
       }
     }
   }
@@ -354,23 +397,20 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     i16v acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0;
-    uint32_t o[kQ];
-#pragma unroll
-    for (int i = 0; i < kQ; ++i) {
-      o[i] = y ? oy[j][i] : ox[j][i];
-      asm volatile("" : "+v"(o[i]));  // formed at its place: all products at once take too many registers
-    }
+    const int col = lane % 32 + (y ? 32 : 0), half = lane / 32;
     if constexpr (kSmall) {
       const int64_t a = *reinterpret_cast<const int64_t *>(kRows.k16[0][rb][lane]);
-      acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(a, (int64_t)((uint64_t)o[0] | ((uint64_t)o[1] << 32)), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(
+          a, *reinterpret_cast<const int64_t *>(&first_words[j][col][2 * half]), acc, 0, 0, 0);
     } else {
       const i4v a = *reinterpret_cast<const i4v *>(kRows.k32[rb][lane]);
-      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, i4v{(int)o[0], (int)o[1], (int)o[kQ - 2], (int)o[kQ - 1]}, acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+          a, *reinterpret_cast<const i4v *>(&first_words[j][col][(2 * kQ - 4) * half]), acc, 0, 0, 0);
     }
     if constexpr (kMore) {
-      const uint32_t(&m)[2] = y ? my[j] : mx[j];
       const int64_t a = *reinterpret_cast<const int64_t *>(kRows.k16[1][rb][lane]);
-      acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(a, (int64_t)((uint64_t)m[0] | ((uint64_t)m[1] << 32)), acc, 0, 0, 0);
+      acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(
+          a, *reinterpret_cast<const int64_t *>(&more_words[j][col][2 * half]), acc, 0, 0, 0);
     }
     return acc;
   };
@@ -378,103 +418,63 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     return j == 0 ? byte : __builtin_amdgcn_perm(byte, word, j == 1 ? 0x03020400u : j == 2 ? 0x03040100u : 0x04020100u);
   };
   // Row blocks of 32 bases: the (first) digits of blocks 0 and 1, then the second
-  // digits of those with squared bases.  Row r of a result: base 32 rb + 8 (r / 4)
-  // + r % 4 in lanes 0 .. 31, four more from 32 on.
+  // digits of those with squared bases.  The halves of the two products of an
+  // element number j (elements of lanes 0 .. 31 and 32 .. 63) are swapped, so that a
+  // register holds one base for all 64 lanes and the constants are scalar.
   const int second = (op.nsq + 31) / 32;
   for (int pass = part; pass < 2 + second; pass += parts) {
     const bool digit2 = pass >= 2;
     const int rb = digit2 ? pass - 2 : pass, end = digit2 && u_end > op.nsq ? op.nsq : u_end;
     if (32 * rb >= end || 32 * rb + 32 <= u_first) continue;
-    float inv[16];
-    int ns[16];
+    auto quotient = [&](int x, int u) { return __float_as_int(__builtin_fmaf((float)x, kBase.inv[32 * rb + u], 12582912.0f)); };
+    uint32_t word[32] = {};  // bases 32 rb + u, bytes j
+    auto swap = [](i16v &x, i16v &y) {  // register r of x: base 8 (r / 4) + r % 4, of y: four more
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const BaseInfo b = kBase.info[32 * rb + 8 * (r / 4) + 4 * (lane / 32) + r % 4];
-      inv[r] = b.inv;
-      ns[r] = -b.s;
-    }
-    auto quotient = [&](int x, int r) { return __float_as_int(__builtin_fmaf((float)x, inv[r], 12582912.0f)); };
-    uint32_t word[2][16] = {};
-    i16v c = product(rb, 0, false);
+      for (int r = 0; r < 16; ++r) {
+        const auto sw = __builtin_amdgcn_permlane32_swap((unsigned)x[r], (unsigned)y[r], false, false);
+        x[r] = (int)sw[0];
+        y[r] = (int)sw[1];
+      }
+    };
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {  // elements j of half y; the next product runs beside the reduction
-      const int j = i % 4, y = i / 4;
-      i16v c1 = c;
-      if (i < 7) c = product(rb, (i + 1) % 4, i + 1 >= 4);
+    for (int j = 0; j < 4; ++j) {
+      i16v x = product(rb, j, false), y = product(rb, j, true);
       if (digit2) {  // c-sum + s h-sum, without its digit 0
-        const i16v h = product(rb + 2, j, y != 0);
+        i16v hx = product(rb + 2, j, false), hy = product(rb + 2, j, true);
+        swap(x, y);
+        swap(hx, hy);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          if (a > 0 && 32 * rb + 8 * a >= end) break;
-#pragma unroll
-          for (int r = 4 * a; r < 4 * a + 4; ++r) {
-            int q = quotient(c1[r], r) - 0x4B400000;
-            if (r == 0 && ns[0] == -256) q = (c1[0] + 128) >> 8;  // the byte 0x80 stands for -128
-            c1[r] = q + h[r];
-          }
+        for (int r = 0; r < 16; ++r) {
+          const int u = 8 * (r / 4) + r % 4;
+          int q = quotient(x[r], u) - 0x4B400000;
+          if (r == 0 && rb == 0) q = (x[0] + 128) >> 8;  // base 256: the byte 0x80 stands for -128
+          x[r] = q + hx[r];
+          y[r] = quotient(y[r], u + 4) - 0x4B400000 + hy[r];
         }
+      } else {
+        swap(x, y);
       }
 #pragma unroll
       for (int a = 0; a < 4; ++a) {
         if (a > 0 && 32 * rb + 8 * a >= end) break;  // no bases from here on
 #pragma unroll
         for (int r = 4 * a; r < 4 * a + 4; ++r) {
-          word[y][r] = insert(j == 0 ? 0u : word[y][r], (uint32_t)(__mul24(quotient(c1[r], r), ns[r]) + c1[r]), j);
-          asm volatile("" : "+v"(word[y][r]));
+          const int u = 8 * a + r % 4;
+          word[u] = insert(word[u], (uint32_t)(__mul24(quotient(x[r], u), kBase.ns[32 * rb + u]) + x[r]), j);
+          word[u + 4] = insert(word[u + 4], (uint32_t)(__mul24(quotient(y[r], u + 4), kBase.ns[32 * rb + u + 4]) + y[r]), j);
+          asm volatile("" : "+v"(word[u]), "+v"(word[u + 4]));
         }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // the rows in the order of their planes
     int8_t *to = dst + (int64_t)(32 * rb - u_first + (digit2 ? u_end - u_first : 0)) * plane;
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      uint32_t w8[8];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const auto w2 = __builtin_amdgcn_permlane32_swap(word[0][4 * a + r], word[1][4 * a + r], false, false);
-        w8[r] = w2[0];
-        w8[r + 4] = w2[1];
-      }
-#pragma unroll
-      for (int r = 0; r < 8; ++r) {
-        const int u = 32 * rb + 8 * a + r;
-        if (u >= u_first && u < end) *reinterpret_cast<uint32_t *>(to) = w8[r];
-        to += plane;
-      }
+    for (int u = 0; u < 32; ++u) {
+      if (32 * rb + u >= u_first && 32 * rb + u < end) *reinterpret_cast<uint32_t *>(to) = word[u];
+      to += plane;
     }
   }
 
-  if (p0 == 0 && v < op.nvec && part == 0) op.exps[v] = E;
-  if (!check) return;
-  __shared__ uint32_t seen[kBlk8][NW];
-  __shared__ int rounded[kBlk8];
-  for (int i = t; i < kBlk8 * NW; i += kThreads) seen[i / NW][i % NW] = 0u;
-  if (t < kBlk8) rounded[t] = 0;
-  __syncthreads();
-  if (inexact) rounded[l & 31] = 1;
-  auto fall_back = [&]() {
-    *op.flag = 1;
-    if (op.any) *op.any = 1;
-  };
-  if (odd) fall_back();
-  if (kb == 0) {
-#pragma unroll
-    for (int i = 0; i < NW; ++i) atomicOr(&seen[l & 31][i], change[i]);
-  }
-  __syncthreads();
-  if (t < kBlk8) {
-    const int vt = (int)(vb * kBlk8) + t;
-    if (vt < op.nvec) {
-      int add = rounded[t];
-      if (kb == 0 && !last_grid_covered<NW>(seen[t], op.bits, op.slice_bits, op.passes)) add |= 2;
-      // bit 0: an element was rounded; bit 1: the slices may reach further down
-      if (add & ~*(volatile int *)&op.state[vt]) {
-        const int old = atomicOr(&op.state[vt], add);
-        if ((old | add) == 3) fall_back();
-      }
-    }
-  }
 }
 
 __device__ __forceinline__ int find_range(const int *prefix, int n, int b) {
@@ -492,7 +492,7 @@ __device__ __forceinline__ int find_range(const int *prefix, int n, int b) {
 // Workgroup (x, y): block x - prefix[i] of operand i, every gridDim.y-th row
 // block of the bases [u_first, u_end) (u_end < 0: every base of the operand).
 template <typename T, int C, int NW>
-__global__ __launch_bounds__(kThreads, 2) void k_residue_split(const ResidueOperand<T> *__restrict__ ops,
+__global__ __launch_bounds__(kThreads, NW > 8 ? 3 : 4) void k_residue_split(const ResidueOperand<T> *__restrict__ ops,
                                                             const int *__restrict__ prefix, int nops, int live_only,
                                                             int u_first, int u_end) {
   const int i = __builtin_amdgcn_readfirstlane(find_range(prefix, nops, blockIdx.x));
@@ -500,10 +500,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_residue_split(const ResidueOper
   const int64_t blk = (int64_t)blockIdx.x - prefix[i];
   const int end = u_end < 0 ? op.nunits : u_end, part = blockIdx.y, parts = gridDim.y;
   const bool check = op.float_form != 0 && u_first == 0 && blockIdx.y == 0;
+  __shared__ SplitLds<NW> lds;
   if (op.orient == 0)
-    residue_block<T, C, NW, 0>(op, blk, live_only != 0, u_first, end, part, parts, check);
+    residue_block<T, C, NW, 0>(op, blk, live_only != 0, u_first, end, part, parts, check, lds);
   else
-    residue_block<T, C, NW, 1>(op, blk, live_only != 0, u_first, end, part, parts, check);
+    residue_block<T, C, NW, 1>(op, blk, live_only != 0, u_first, end, part, parts, check, lds);
 }
 
 // ---------------------------------------------------------------------------
