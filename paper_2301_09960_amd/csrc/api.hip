@@ -544,8 +544,10 @@ hipError_t residue_launch(const Plan &p, char *base, size_t bytes, int *flag, co
   rc.exp_b = reinterpret_cast<int *>(base + p.off_res_exp_b);
   rc.mu_a = base + p.off_res_mu_a;
   rc.mu_b = base + p.off_res_mu_b;
-  rc.state_a = reinterpret_cast<int *>(base + p.off_res_st_a);
-  rc.state_b = reinterpret_cast<int *>(base + p.off_res_st_b);
+  if (rc.float_form) {
+    rc.state_a = reinterpret_cast<int *>(base + p.off_res_st_a);
+    rc.state_b = reinterpret_cast<int *>(base + p.off_res_st_b);
+  }
   rc.clear = reinterpret_cast<uint32_t *>(base + p.off_res_clear);
   rc.clear_words = (int64_t)(p.res_clear_bytes / 4);
   rc.flag = rc.float_form ? flag : nullptr;

@@ -50,8 +50,7 @@ bool residue_plan(int bits, int64_t k, ResiduePlan &p);
 
 // Combine constants of a plan (host memory, kept for the process; a function of
 // (nunits, nsq, nwc) alone): the weight of every plane in balanced base-256
-// digits, as operand blocks (32 digits x 32 planes, 1 KiB) of
-// v_mfma_i32_32x32x32_i8; then M in nwc balanced words; then a multiple of 1 / M
+// digits, a row of bytes (plane by plane, 32 or a multiple) per digit; then M in nwc balanced words; then a multiple of 1 / M
 // as a binary64.
 const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc);
 
@@ -96,7 +95,7 @@ struct ResidueCall {
   int64_t c_stride;
   int *exp_a, *exp_b;    // m and n exponents
   void *mu_a, *mu_b;     // m and n maxima
-  int *state_a, *state_b;  // FLOAT form: m and n words
+  int *state_a, *state_b;  // FLOAT form: m and n words, at the end of what is cleared; INT8 form null
   uint32_t *clear;
   int64_t clear_words;
   int *flag;             // FLOAT form: cleared, then set if the slices must form the product

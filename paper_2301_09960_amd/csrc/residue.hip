@@ -639,6 +639,8 @@ typedef const __attribute__((address_space(4))) uint32_t *const_words;  // scala
 __host__ __device__ constexpr int combine_steps(int nwc) { return nwc <= 8 ? 1 : nwc <= 15 ? 2 : 3; }
 // 32-digit row blocks of nwc words.
 __host__ __device__ constexpr int combine_rows(int nwc) { return (nwc + 7) / 8; }
+// Words of the planes' weights: 4 nwc digits, a byte per plane of the steps.
+__host__ __device__ constexpr int weight_words(int nwc) { return 4 * nwc * combine_steps(nwc) * 8; }
 
 // w up by SH words, and its place down, if its top SH words are zero.
 template <int NWC, int SH>
@@ -821,15 +823,17 @@ __global__ __launch_bounds__(kThreads, 2) void k_residue_combine(const ResidueDe
   // weights: digits of the planes
   i4v wt[RB][KS];
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = 32 * rb + lane % 32;  // results of rows past the last digit are not looked at
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      wt[rb][ks] = reinterpret_cast<const i4v *>(d.table)[(rb * KS + ks) * 64 + lane];
-  const const_words mod = (const_words)d.table + RB * KS * 256;
+      wt[rb][ks] = reinterpret_cast<const i4v *>(d.table)[((row < 4 * NWC ? row : 4 * NWC - 1) * KS + ks) * 2 + lane / 32];
+  }
+  const const_words mod = (const_words)d.table + weight_words(NWC);
   const double inv_m = __longlong_as_double((long long)((uint64_t)mod[NWC] | ((uint64_t)mod[NWC + 1] << 32)));
 
 #pragma unroll 1
-  for (int h = 0; h < 2; ++h) {
+  for (int h = blockIdx.y; h < 2; h += gridDim.y) {
     if (bj * 32 + 8 * quad + 4 * h >= d.n) return;
     const int8_t *src = d.R + blk * 1024 + (h * 32 + lane % 32) * 16 + 4 * quad;
     i4v f[KS][4];  // entry e: its bytes in this lane's 16 planes of a step
@@ -928,6 +932,62 @@ __global__ __launch_bounds__(kThreads) void k_upload(Upload data, int n, uint32_
   for (int64_t i = t; i < n1; i += step) z1[i] = 0u;
 }
 
+// Maxima of the vectors and the (last) upload in one launch, for vectors short
+// enough that a workgroup reads 16 whole ones: no atomics, so nothing to clear for
+// them first, and no shuffles (64 bit ones took most of k_split_max0's 8.5 us on
+// two tiles).  Bound by the latency of its loads, 16 in flight per thread.
+template <typename T>
+struct MaxOperand {
+  const T *X;
+  int64_t sv, sp;
+  int nvec, len, orient;
+  typename bits_of<T>::type *mu;
+};
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, int strips_a, uint32_t *dst,
+                                                            MaxOperand<T> a, MaxOperand<T> b, uint32_t *z0, int64_t n0,
+                                                            uint32_t *z1, int64_t n1) {
+  using U = typename bits_of<T>::type;
+  const int t = threadIdx.x;
+  const int64_t id = blockIdx.x * (int64_t)kThreads + t, step = (int64_t)gridDim.x * kThreads;
+  const bool second = (int)blockIdx.x >= strips_a;
+  const MaxOperand<T> op = second ? b : a;
+  const int v0 = 16 * ((int)blockIdx.x - (second ? strips_a : 0));
+  const int dv = op.orient == 0 ? t % 16 : t / 16, dp = op.orient == 0 ? t / 16 : t % 16;
+  const int v = v0 + dv < op.nvec ? v0 + dv : op.nvec - 1;
+  const T *x = op.X + (int64_t)v * op.sv;
+  U best = 0;
+  for (int p0 = dp; p0 < op.len; p0 += kThreads) {
+    T e[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {  // past the end the last element again
+      const int p = p0 + 16 * i < op.len ? p0 + 16 * i : op.len - 1;
+      e[i] = x[(int64_t)p * op.sp];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const U k = abs_bits(e[i]);
+      best = k > best ? k : best;
+    }
+  }
+  for (int64_t i = id; i < n; i += step) dst[i] = data.w[i];
+  for (int64_t i = id; i < n0; i += step) z0[i] = 0u;
+  for (int64_t i = id; i < n1; i += step) z1[i] = 0u;
+  __shared__ U red[16][17];
+  red[dp][dv] = best;
+  __syncthreads();
+  if (t < 16 && v0 + t < op.nvec) {
+    U k = red[0][t];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) k = red[i][t] > k ? red[i][t] : k;
+    op.mu[v0 + t] = k;
+  }
+}
+// Up to this length (one or two launches less): INT8 DD calls of 64^2 x 64 go from
+// 58 to 49 us, 64^2 x 8192 from 127 to 114, n = 4096 from 2629 to 2584; a single pair
+// of vectors of 100000 would take 989 us against 671 with the tiled maxima.
+constexpr int kBeginLength = 8192;
+
 // Big integers of 32-bit words, for the tables.
 using Big = std::vector<uint32_t>;
 void big_mul(Big &x, uint32_t f) {
@@ -954,10 +1014,17 @@ double big_value(const Big &x) {
   return v;
 }
 
+// Bits of the first n bases, for the plans: they are looked for on every call.
+struct BaseBits {
+  double sum[kNumBases + 1];
+  BaseBits() {
+    sum[0] = 0.0;
+    for (int u = 0; u < kNumBases; ++u) sum[u + 1] = sum[u] + std::log2((double)kHostBases.s[u]);
+  }
+};
 double log2_modulus(int nunits, int nsq) {
-  double l = 0.0;
-  for (int u = 0; u < nunits; ++u) l += (u < nsq ? 2 : 1) * std::log2((double)kHostBases.s[u]);
-  return l;
+  static const BaseBits bits;
+  return bits.sum[nunits] + bits.sum[nsq];
 }
 
 }  // namespace
@@ -968,10 +1035,9 @@ bool residue_plan(int bits, int64_t k, ResiduePlan &p) {
   p.bits = bits;
   p.nunits = 0;
   for (int n = 1; n <= kNumBases; ++n) {
-    double l = log2_modulus(n, 0);
     int sq = 0;
-    while (l < need && sq < n) l += std::log2((double)kHostBases.s[sq++]);
-    if (l < need) continue;
+    while (log2_modulus(n, sq) < need && sq < n) ++sq;
+    if (log2_modulus(n, sq) < need) continue;
     if (p.nunits == 0 || n + 2 * sq <= p.products()) {  // of equal ones that with fewer squares
       p.nunits = n;
       p.nsq = sq;
@@ -997,8 +1063,8 @@ const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
   for (int u = 0; u < nunits; ++u)
     for (int e = 0; e < (u < nsq ? 2 : 1); ++e) big_mul(M, (uint32_t)kHostBases.s[u]);
   M.resize(nwc, 0u);
-  const int RB = combine_rows(nwc), KS = combine_steps(nwc);
-  t.assign((size_t)RB * KS * 256 + nwc + 2, 0u);
+  const int KS = combine_steps(nwc);
+  t.assign((size_t)weight_words(nwc) + nwc + 2, 0u);
   for (int u = 0; u < nunits; ++u) {
     const uint32_t s = (uint32_t)kHostBases.s[u], mod = u < nsq ? s * s : s;
     Big Mu = M;
@@ -1038,14 +1104,12 @@ const std::vector<uint32_t> &residue_table(int nunits, int nsq, int nwc) {
         int digit = (int)((w[j / 4] >> (8 * (j % 4))) & 255u) + carry;
         carry = digit >= 128 ? 1 : 0;
         if (carry) digit -= 256;
-        // digit row j, plane pl: lane j % 32 + 32 (pl % 32 / 16), byte pl % 16
-        const int word = ((j / 32 * KS + pl / 32) * 64 + j % 32 + 32 * (pl % 32 / 16)) * 4 + pl % 16 / 4;
-        t[(size_t)word] |= (uint32_t)(uint8_t)(int8_t)digit << (8 * (pl % 4));
+        t[(size_t)(j * KS * 8 + pl / 4)] |= (uint32_t)(uint8_t)(int8_t)digit << (8 * (pl % 4));
       }
     }
   }
   // M in balanced words, and 2^(32 (nwc - 3)) / M (the top three words over M)
-  const size_t at = (size_t)RB * KS * 256;
+  const size_t at = (size_t)weight_words(nwc);
   uint32_t up = 0;
   for (int i = 0; i < nwc; ++i) {
     const uint64_t w = (uint64_t)M[i] + up;
@@ -1067,7 +1131,7 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 // The descriptors before the table, which is read 16 bytes at a time.
 constexpr size_t kHeadBytes = (2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 4 * 4 + 15) / 16 * 16;
 size_t header_bytes(const ResiduePlan &p) {
-  const size_t words = (size_t)combine_rows(p.nwc) * combine_steps(p.nwc) * 256 + p.nwc + 2;
+  const size_t words = (size_t)weight_words(p.nwc) + p.nwc + 2;
   return up256(kHeadBytes + words * 4);
 }
 
@@ -1119,10 +1183,13 @@ hipError_t combine_launch(int nwc, bool chunks, int64_t blocks, const ResidueDes
     const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }
+  // a workgroup's two half blocks one after the other, or a workgroup each where
+  // that still leaves some CUs idle
+  const dim3 grid((unsigned)blocks, blocks <= 128 ? 2 : 1);
   switch (nwc) {
 #define MP_RESIDUE_COMBINE_CASE(NWC)                                                                             \
   case NWC: {                                                                                                    \
-    hipLaunchKernelGGL((k_residue_combine<T, C, NWC>), dim3((unsigned)blocks), dim3(kThreads), 0, st, descs, prefix, nprod); \
+    hipLaunchKernelGGL((k_residue_combine<T, C, NWC>), grid, dim3(kThreads), 0, st, descs, prefix, nprod); \
     return hipGetLastError();                                                                                    \
   }
     MP_RESIDUE_COMBINE_CASE(2)
@@ -1276,6 +1343,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   h.d.c_stride = rc.c_stride;
 
   hipError_t err = hipSuccess;
+  const bool begin = rc.k <= kBeginLength;
   const size_t hw = kHeadBytes / 4, words = hw + table.size();
   for (size_t at = 0; at < words; at += kUploadWords) {
     Upload up;
@@ -1284,25 +1352,39 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
       up.w[i] = at + i >= hw                  ? table[at + i - hw]
                 : at + i < sizeof(Head) / 4 ? reinterpret_cast<const uint32_t *>(&h)[at + i]
                                             : 0u;
-    const int64_t n0 = at == 0 ? rc.clear_words : 0, n1 = at == 0 && first && rc.flag ? 1 : 0;
-    const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(n0, kThreads)));
-    hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n,
-                       reinterpret_cast<uint32_t *>(rc.arena) + at, rc.clear, n0,
-                       reinterpret_cast<uint32_t *>(rc.flag), n1);
+    uint32_t *dst = reinterpret_cast<uint32_t *>(rc.arena) + at, *flag = reinterpret_cast<uint32_t *>(rc.flag);
+    const bool last = at + n == words;
+    // k_residue_begin writes the maxima: of what is to be cleared the states are left
+    uint32_t *clear = begin ? reinterpret_cast<uint32_t *>(rc.state_a) : rc.clear;
+    const int64_t n0 = last && clear ? rc.clear + rc.clear_words - clear : 0, n1 = last && first && rc.flag ? 1 : 0;
+    if (begin && last) {
+      using U = typename bits_of<T>::type;
+      const int sa = ceil_div(rc.m, 16), sb = ceil_div(rc.n, 16);
+      const MaxOperand<T> va{a.X, a.sv, a.sp, a.nvec, a.len, 0, static_cast<U *>(rc.mu_a)};
+      const MaxOperand<T> vb{b.X, b.sv, b.sp, b.nvec, b.len, 1, static_cast<U *>(rc.mu_b)};
+      hipLaunchKernelGGL(k_residue_begin<T>, dim3((unsigned)(sa + sb)), dim3(kThreads), 0, st, up, (int)n, sa, dst, va,
+                         vb, clear, n0, flag, n1);
+    } else {
+      const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(n0, (int64_t)kThreads)));
+      hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n, dst, clear, n0, flag, n1);
+    }
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
-  SplitOperand<T> ma = a, mb = b;
-  ma.mu = rc.mu_a;
-  mb.mu = rc.mu_b;
-  if ((err = launch_split_max0(ma, mb, st)) != hipSuccess) return err;
+  if (!begin) {
+    SplitOperand<T> ma = a, mb = b;
+    ma.mu = rc.mu_a;
+    mb.mu = rc.mu_b;
+    if ((err = launch_split_max0(ma, mb, st)) != hipSuccess) return err;
+  }
   const auto *ops = reinterpret_cast<const ResidueOperand<T> *>(rc.arena);
   const auto *descs = reinterpret_cast<const ResidueDesc *>(rc.arena + offsetof(Head, d));
   const auto *prefix = reinterpret_cast<const int *>(rc.arena + offsetof(Head, prefix));
   for (int u0 = 0; u0 < p.nunits;) {
     int u1 = u0 + 1;
     while (u1 < p.nunits && group_planes(u0, u1 + 1, p.nsq) <= room) ++u1;
-    // a grid of few blocks spreads the row blocks over gridDim.y
-    const int parts = u1 > 32 && ba + bb <= 512 ? 2 : 1;
+    // a grid of few blocks spreads the row blocks over gridDim.y, one pass each or two
+    const int passes = 2 + (p.nsq + 31) / 32;
+    const int parts = u1 - u0 <= 32 && p.nsq <= u0 ? 1 : ba + bb <= 128 ? passes : ba + bb <= 512 ? 2 : 1;
     if ((err = split_launch<T, C>(p.nw, dim3((unsigned)(ba + bb), (unsigned)parts), ops, prefix, 2, 0, u0, u1, st)) !=
         hipSuccess)
       return err;

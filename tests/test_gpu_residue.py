@@ -112,6 +112,23 @@ def test_integers_are_exact(mp):
     assert np.all(got == want)
 
 
+@pytest.mark.parametrize("mode", ["float", "int8"])
+@pytest.mark.parametrize("m,n,k", [(1, 17, 48), (16, 15, 255), (17, 16, 257), (33, 1, 1041), (2, 18, 8192), (18, 2, 8193)])
+def test_maxima_of_whole_vectors(mp, mode, m, n, k):
+    """The largest element at a vector's end, at the edges of 16 vectors and 256
+    elements, and on both sides of the longest vectors read in one piece: with
+    a maximum too small the integers would not fit their words."""
+    rng = np.random.default_rng(7)
+    a, b = rng.integers(-2 ** 20, 2 ** 20, (k, m)), rng.integers(-2 ** 20, 2 ** 20, (n, k))
+    a[k - 1, m - 1], b[n - 1, k - 1], a[0, 0], b[0, 0] = 2 ** 50, -2 ** 50, 2 ** 49 + 1, 2 ** 48 + 3
+    A = np.stack([a.astype(np.float64), np.zeros((k, m))])
+    B = np.stack([b.astype(np.float64), np.zeros((n, k))])
+    C = mp.gemm("dd", dev(A), dev(B), mode=mode).cpu().numpy()
+    want = b.astype(object) @ a.astype(object)
+    got = np.vectorize(lambda x, y: int(x) + int(y), otypes=[object])(C[0], C[1])
+    assert np.all(got == want)
+
+
 def slices(mp, fmt, A, B):
     """The product from binary64/binary32 slices: a slice count set by the
     caller is Algorithm 1 with that many slices."""
