@@ -12,6 +12,8 @@
 // (dd.h) or TD (mc.h) arithmetic in a fixed order, so a factorization is
 // reproducible.
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "dd.h"
 #include "internal.h"
@@ -112,28 +114,60 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_diag(Mat<Num> A, int j0, int 
   }
 }
 
-// The same factorization with the block held in LDS (K <= kDiagLds): the
-// operations and their order are those of k_lu_diag, so the factors are
-// identical; each column's chain waits on LDS instead of the L2.
+// The value of lane `src` (the same for the whole wavefront) in all lanes.
+template <typename Num>
+__device__ __forceinline__ Num read_num(const Num &v, int src) {
+  Num o;
+#pragma unroll
+  for (int r = 0; r < Comps<Num>::C; ++r) {
+    const long long x = __double_as_longlong(Comps<Num>::get(v, r));
+    const int lo = __builtin_amdgcn_readlane((int)x, src), hi = __builtin_amdgcn_readlane((int)(x >> 32), src);
+    Comps<Num>::set(o, r, __longlong_as_double(((long long)hi << 32) | (unsigned)lo));
+  }
+  return o;
+}
+
+// The same factorization for K <= kDiagLds, a thread per entry: the operations of
+// every entry and their order are those of k_lu_diag, so the factors are
+// identical.  Bound by the chain of the pivots: update, division, hand over.  A
+// step passes on its column of L, its row of U and the diagonal entry after it
+// through LDS, and the threads of the next column form the next pivot themselves,
+// so a step has one barrier; with the block in LDS and two barriers a block of 32
+// took 25 us (DD), now 22: 0.55 us a step, of it some 0.3 the division.
 constexpr int kDiagLds = 32;
 
 template <typename Num>
 __global__ __launch_bounds__(kLuThreads) void k_lu_diag_lds(Mat<Num> A, int j0, int K) {
-  __shared__ Num blk[kDiagLds * kDiagLds];  // column-major, leading dimension K
-  for (int idx = threadIdx.x; idx < K * K; idx += kLuThreads) blk[idx] = A.get(j0 + idx % K, j0 + idx / K);
+  static_assert(kDiagLds * kDiagLds == kLuThreads, "a thread per entry");
+  __shared__ Num below[2][kDiagLds], right[2][kDiagLds], diag[2];
+  const int i = threadIdx.x % kDiagLds, l = threadIdx.x / kDiagLds;
+  const bool inside = i < K && l < K;
+  Num a = inside ? A.get(j0 + i, j0 + l) : nzero<Num>();
+  if (threadIdx.x == 0) diag[1] = a;
   __syncthreads();
-  for (int j = 0; j < K; ++j) {
-    const Num piv = blk[j + j * K];
-    for (int i = j + 1 + (int)threadIdx.x; i < K; i += kLuThreads) blk[i + j * K] = ndiv(blk[i + j * K], piv);
-    __syncthreads();
-    const int r = K - j - 1;
-    for (int idx = threadIdx.x; idx < r * r; idx += kLuThreads) {
-      const int i = j + 1 + idx % r, l = j + 1 + idx / r;
-      blk[i + l * K] = nfms(blk[i + l * K], blk[i + j * K], blk[j + l * K]);
+  if (inside) {
+    if (l == 0 && i > 0) {
+      a = ndiv(a, diag[1]);
+      below[0][i] = a;
+    }
+    if (i == 0) right[0][l] = a;
+    if (i == 1 && l == 1) diag[0] = a;
+  }
+  __syncthreads();
+  for (int j = 0; j < K - 1; ++j) {
+    const int now = j & 1, then = now ^ 1;
+    if (inside && i > j && l > j) {
+      a = nfms(a, below[now][i], right[now][l]);
+      if (l == j + 1 && i > j + 1) {
+        a = ndiv(a, nfms(diag[now], below[now][j + 1], right[now][j + 1]));
+        below[then][i] = a;
+      }
+      if (i == j + 1) right[then][l] = a;
+      if (i == j + 2 && l == j + 2) diag[then] = a;
     }
     __syncthreads();
   }
-  for (int idx = threadIdx.x; idx < K * K; idx += kLuThreads) A.put(j0 + idx % K, j0 + idx / K, blk[idx]);
+  if (inside) A.put(j0 + i, j0 + l, a);
 }
 
 template <typename Num>
@@ -170,112 +204,163 @@ __global__ __launch_bounds__(256) void k_trsm_upper(Mat<Num> A, int j0, int K, i
   }
 }
 
-// The same two solves with one wavefront per column (row), for K <= kSweepMax:
-// the vector sits in LDS and is swept left to right; at step q the lanes
-// update the entries after q with x_q.  Every entry receives the same
-// operations in the same order as in the kernels above (the subtractions for
-// q = 0, 1, ... and then, for U, the product with 1 / u_qq), so the results
-// are identical; the chain per wavefront is K steps instead of K^2 / 2, and
-// the reciprocals of U's diagonal are formed before it, all at once.
+// Both solves for K <= kSweepMax, one wavefront per column of A12 or row of A21:
+// its entries lie in registers (entry t in lane t % 64, E of them per lane), and
+// at step q the lanes update the entries after q with x_q, which is read from its
+// lane.  Every entry receives the same operations in the same order as in the
+// kernels above (the subtractions for q = 0, 1, ... and then, for U, the product
+// with 1 / u_qq), so the results are identical; the chain per wavefront is K steps
+// instead of K^2 / 2, and the reciprocals of U's diagonal are formed before it, all
+// at once.
+//
+// Bound by that chain (product, subtraction and, for U, the product with the
+// reciprocal: some 30 dependent binary64 operations a step).  The multipliers of
+// Q steps go through LDS, read along memory for L and for U and one chunk ahead:
+// read by each step for itself they cost an L2 round trip a step, for U a cache
+// line per lane.  DD, n = 2048, K = 128: 66 + 85 us a panel on average in two
+// launches, now 69 in one; the widest panels (15 wavefronts a CU) are bound by the
+// binary64 rate instead.
 constexpr int kSweepMax = 512;
 constexpr int kSweepWaves = 4;
 
-// KMAX: the largest K of the instance.  With KMAX <= kDiagLds the K x K
-// diagonal block is also staged in LDS, so each step of the chain reads it
-// there; the operations are the same either way.
-template <typename Num, int KMAX>
-__global__ __launch_bounds__(64 * kSweepWaves) void k_trsm_lower_sweep(Mat<Num> A, int j0, int K, int n) {
-  constexpr bool kStage = KMAX <= kDiagLds;
-  __shared__ Num col[kSweepWaves][KMAX];
-  __shared__ Num blk[kStage ? KMAX * KMAX : 1];
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int l = j0 + K + blockIdx.x * kSweepWaves + w;
-  const bool live = l < n;
-  if constexpr (kStage)
-    for (int idx = threadIdx.x; idx < K * K; idx += 64 * kSweepWaves) blk[idx] = A.get(j0 + idx % K, j0 + idx / K);
-  if (live)
-    for (int i = lane; i < K; i += 64) col[w][i] = A.get(j0 + i, l);
-  __syncthreads();
-  for (int q = 0; q < K - 1; ++q) {
-    if (live) {
-      const Num xq = col[w][q];
-      for (int i = q + 1 + lane; i < K; i += 64) {
-        Num lq;
-        if constexpr (kStage)
-          lq = blk[i + q * K];
-        else
-          lq = A.get(j0 + i, j0 + q);
-        col[w][i] = nfms(col[w][i], lq, xq);
-      }
-    }
-    __syncthreads();
-  }
-  if (live)
-    for (int i = lane; i < K; i += 64) A.put(j0 + i, l, col[w][i]);
+template <typename F, int... I>
+__device__ __forceinline__ void each(F &f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
 }
 
-template <typename Num, int KMAX>
-__global__ __launch_bounds__(64 * kSweepWaves) void k_trsm_upper_sweep(Mat<Num> A, int j0, int K, int n) {
-  constexpr bool kStage = KMAX <= kDiagLds;
-  __shared__ Num row[kSweepWaves][KMAX];
-  __shared__ Num inv[KMAX];
-  __shared__ Num blk[kStage ? KMAX * KMAX : 1];
-  const int w = threadIdx.x / 64, lane = threadIdx.x % 64;
-  const int i = j0 + K + blockIdx.x * kSweepWaves + w;
-  const bool live = i < n;
-  if constexpr (kStage)
-    for (int idx = threadIdx.x; idx < K * K; idx += 64 * kSweepWaves) blk[idx] = A.get(j0 + idx % K, j0 + idx / K);
-  for (int t = threadIdx.x; t < K; t += 64 * kSweepWaves) inv[t] = ninv(A.get(j0 + t, j0 + t));
-  if (live)
-    for (int t = lane; t < K; t += 64) row[w][t] = A.get(i, j0 + t);
-  __syncthreads();
-  for (int q = 0; q < K; ++q) {
-    if (live) {
-      // every lane forms x_q; lane 0 stores it
-      const Num xq = nmul(row[w][q], inv[q]);
-      if (lane == 0) row[w][q] = xq;
-      for (int t = q + 1 + lane; t < K; t += 64) {
-        Num uq;
-        if constexpr (kStage)
-          uq = blk[q + t * K];
-        else
-          uq = A.get(j0 + q, j0 + t);
-        row[w][t] = nfms(row[w][t], xq, uq);
+template <typename Num, int E>
+__global__ __launch_bounds__(64 * kSweepWaves) void k_panel_sweep(Mat<Num> A, int j0, int K, int n, int lower_blocks) {
+  constexpr int C = Comps<Num>::C, Q = E <= 2 ? 16 : 32 / E, N = Q * E / kSweepWaves;
+  __shared__ double mul[C][Q][64 * E + 1];
+  __shared__ Num inv[64 * E];
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64), lane = threadIdx.x % 64;
+  const bool upper = (int)blockIdx.x >= lower_blocks;
+  const int vec = j0 + K + ((int)blockIdx.x - (upper ? lower_blocks : 0)) * kSweepWaves + w;
+  const bool live = vec < n;
+  Num x[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int t = 64 * e + lane;
+    x[e] = !live || t >= K ? nzero<Num>() : upper ? A.get(vec, j0 + t) : A.get(j0 + t, vec);
+  }
+  Num ahead[N];  // the next chunk's multipliers, of step q for entry t
+  auto place = [&](int s, int &q, int &t) {
+    const int idx = (int)threadIdx.x + 64 * kSweepWaves * s;
+    q = upper ? idx % Q : idx / (64 * E);
+    t = upper ? idx / Q : idx % (64 * E);
+  };
+  auto load = [&](int q0) {
+#pragma unroll
+    for (int s = 0; s < N; ++s) {
+      int q, t;
+      place(s, q, t);
+      q += q0;
+      ahead[s] = q >= K || t >= K ? nzero<Num>() : upper ? A.get(j0 + q, j0 + t) : A.get(j0 + t, j0 + q);
+    }
+  };
+  load(0);
+  if (upper)
+    for (int t = threadIdx.x; t < K; t += 64 * kSweepWaves) inv[t] = ninv(A.get(j0 + t, j0 + t));
+  auto sweep = [&](auto of) {  // the steps whose x_q lie in register e
+    constexpr int e = decltype(of)::value;
+    for (int first = 0; first < 64 && 64 * e + first < K; first += Q) {
+      const int q0 = 64 * e + first, steps = K - q0 < Q ? K - q0 : Q;
+      __syncthreads();
+#pragma unroll
+      for (int s = 0; s < N; ++s) {
+        int q, t;
+        place(s, q, t);
+#pragma unroll
+        for (int r = 0; r < C; ++r) mul[r][q][t] = Comps<Num>::get(ahead[s], r);
+      }
+      __syncthreads();
+      if (q0 + Q < K) load(q0 + Q);
+      for (int part = 0; part < steps; part += 4) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = part + u;
+          if (q >= steps) break;
+          Num f[E];
+#pragma unroll
+          for (int d = e; d < E; ++d)
+#pragma unroll
+            for (int r = 0; r < C; ++r) Comps<Num>::set(f[d], r, mul[r][q][64 * d + lane]);
+          Num xq = read_num(x[e], first + q);
+          if (upper) {
+            xq = nmul(xq, inv[q0 + q]);
+            if (lane == first + q) x[e] = xq;
+            if (lane > first + q) x[e] = nfms(x[e], xq, f[e]);
+#pragma unroll
+            for (int d = e + 1; d < E; ++d) x[d] = nfms(x[d], xq, f[d]);
+          } else {
+            if (lane > first + q) x[e] = nfms(x[e], f[e], xq);
+#pragma unroll
+            for (int d = e + 1; d < E; ++d) x[d] = nfms(x[d], f[d], xq);
+          }
+        }
       }
     }
-    __syncthreads();
+  };
+  each(sweep, std::make_integer_sequence<int, E>{});
+  if (!live) return;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int t = 64 * e + lane;
+    if (t >= K) continue;
+    if (upper)
+      A.put(vec, j0 + t, x[e]);
+    else
+      A.put(j0 + t, vec, x[e]);
   }
-  if (live)
-    for (int t = lane; t < K; t += 64) A.put(i, j0 + t, row[w][t]);
 }
 
 // Both panel sweeps for a K x K diagonal block at (j0, j0), rows and columns up
 // to `end`.
 template <typename Num>
 void launch_sweeps(const Mat<Num> &M, int j0, int K, int end, hipStream_t st) {
-  const dim3 grid((unsigned)ceil_div(end - j0 - K, kSweepWaves));
-  if (K <= kDiagLds) {
-    hipLaunchKernelGGL((k_trsm_lower_sweep<Num, kDiagLds>), grid, dim3(64 * kSweepWaves), 0, st, M, j0, K, end);
-    hipLaunchKernelGGL((k_trsm_upper_sweep<Num, kDiagLds>), grid, dim3(64 * kSweepWaves), 0, st, M, j0, K, end);
-  } else {
-    hipLaunchKernelGGL((k_trsm_lower_sweep<Num, kSweepMax>), grid, dim3(64 * kSweepWaves), 0, st, M, j0, K, end);
-    hipLaunchKernelGGL((k_trsm_upper_sweep<Num, kSweepMax>), grid, dim3(64 * kSweepWaves), 0, st, M, j0, K, end);
-  }
+  const int blocks = (int)ceil_div(end - j0 - K, kSweepWaves);
+  const dim3 grid((unsigned)(2 * blocks)), wg(64 * kSweepWaves);
+  if (K <= 64)
+    hipLaunchKernelGGL((k_panel_sweep<Num, 1>), grid, wg, 0, st, M, j0, K, end, blocks);
+  else if (K <= 128)
+    hipLaunchKernelGGL((k_panel_sweep<Num, 2>), grid, wg, 0, st, M, j0, K, end, blocks);
+  else if (K <= 256)
+    hipLaunchKernelGGL((k_panel_sweep<Num, 4>), grid, wg, 0, st, M, j0, K, end, blocks);
+  else
+    hipLaunchKernelGGL((k_panel_sweep<Num, 8>), grid, wg, 0, st, M, j0, K, end, blocks);
 }
 
+// Diagonal blocks wider than kInner are factored in inner blocks of kInner (see
+// lu_panel).
+constexpr int kInner = 32;
+
 // A[r0 + i, c0 + l] -= sum over q in [q0, q0 + kb) of A[r0 + i, q] A[q, c0 + l]
-// (q ascending), thread per entry: the trailing update inside a diagonal block
-// factored in inner blocks.
+// (q ascending, kb <= kInner), thread per entry: the trailing update inside a
+// diagonal block factored in inner blocks.  Bound by latency (at most a few dozen
+// workgroups): the operands come in one round of loads and the chain reads them
+// from LDS; read from memory along the chain the update took 13.2 us (DD, K = 128,
+// on average), now 5.3.
+constexpr int kRankTile = 16;
+
 template <typename Num>
-__global__ __launch_bounds__(256) void k_rank_update(Mat<Num> A, int r0, int c0, int rows, int cols, int q0,
-                                                     int kb) {
-  const int64_t total = (int64_t)rows * cols;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < total; idx += (int64_t)gridDim.x * 256) {
-    const int i = r0 + (int)(idx % rows), l = c0 + (int)(idx / rows);
-    Num s = A.get(i, l);
-    for (int q = q0; q < q0 + kb; ++q) s = nfms(s, A.get(i, q), A.get(q, l));
-    A.put(i, l, s);
+__global__ __launch_bounds__(kRankTile *kRankTile) void k_rank_update(Mat<Num> A, int r0, int c0, int rows, int cols,
+                                                                      int q0, int kb) {
+  __shared__ Num left[kInner][kRankTile], top[kRankTile][kInner + 1];
+  const int i0 = r0 + (int)blockIdx.x * kRankTile, l0 = c0 + (int)blockIdx.y * kRankTile;
+  const int t = threadIdx.x, i = i0 + t % kRankTile, l = l0 + t / kRankTile;
+  const bool inside = i < r0 + rows && l < c0 + cols;
+  Num s = inside ? A.get(i, l) : nzero<Num>();
+#pragma unroll
+  for (int idx = t; idx < kInner * kRankTile; idx += kRankTile * kRankTile) {
+    const int row = i0 + idx % kRankTile, ql = idx / kRankTile;
+    left[ql][idx % kRankTile] = row < r0 + rows && ql < kb ? A.get(row, q0 + ql) : nzero<Num>();
+    const int qt = idx % kInner, col = l0 + idx / kInner;
+    top[idx / kInner][qt] = col < c0 + cols && qt < kb ? A.get(q0 + qt, col) : nzero<Num>();
   }
+  __syncthreads();
+#pragma unroll 4
+  for (int q = 0; q < kb; ++q) s = nfms(s, left[q][t % kRankTile], top[t / kRankTile][q]);
+  if (inside) A.put(i, l, s);
 }
 
 // out = A[r0 .. r0 + rows, c0 .. c0 + cols) as a contiguous DD matrix
@@ -306,28 +391,39 @@ __global__ __launch_bounds__(256) void k_sub_block(Mat<Num> A, int r0, int c0, i
 
 // Blocked solve of L U x = b (x holds b on entry): blocks of kSolveB rows.
 // Forward: one wavefront solves the block's rows against the unit lower
-// diagonal block (lane per row, x_q passed by shuffle), then every later row
+// diagonal block (lane per row, x_q read from its lane), then every later row
 // subtracts the block's contribution (k_solve_update).  Backward: the same
 // from the last block up, with the product by the reciprocal of U's diagonal
 // entry (each lane forms its own before the chain).  Every entry's operations
 // come in a fixed order, so the solve is reproducible.
 constexpr int kSolveB = 64;
 
-template <typename Num>
-__device__ __forceinline__ Num shfl_num(const Num &v, int src) {
-  Num o;
-#pragma unroll
-  for (int r = 0; r < Comps<Num>::C; ++r) Comps<Num>::set(o, r, __shfl(Comps<Num>::get(v, r), src, 64));
-  return o;
-}
+// The diagonal blocks' multipliers are read kSolveAhead steps at a time and as many
+// ahead: read by each step for itself, a step waited on the L2 (25 us a block of 64
+// in DD, now 12 and 14).
+constexpr int kSolveAhead = 8;
 
 template <typename Num>
 __global__ __launch_bounds__(64) void k_solve_fwd_diag(Mat<Num> A, int n, double *x, int b0, int B) {
   const int lane = threadIdx.x, i = b0 + lane;
   Num xi = lane < B ? vget<Num>(x, n, i) : nzero<Num>();
-  for (int q = 0; q < B - 1; ++q) {
-    const Num xq = shfl_num(xi, q);
-    if (lane > q && lane < B) xi = nfms(xi, A.get(i, b0 + q), xq);
+  Num f[kSolveAhead], next[kSolveAhead];
+  auto load = [&](Num(&to)[kSolveAhead], int q0) {
+#pragma unroll
+    for (int d = 0; d < kSolveAhead; ++d) to[d] = lane < B && q0 + d < B ? A.get(i, b0 + q0 + d) : nzero<Num>();
+  };
+  load(next, 0);
+  for (int q0 = 0; q0 < B; q0 += kSolveAhead) {
+#pragma unroll
+    for (int d = 0; d < kSolveAhead; ++d) f[d] = next[d];
+    load(next, q0 + kSolveAhead);
+#pragma unroll
+    for (int d = 0; d < kSolveAhead; ++d) {
+      const int q = q0 + d;
+      if (q >= B - 1) break;
+      const Num xq = read_num(xi, q);
+      if (lane > q && lane < B) xi = nfms(xi, f[d], xq);
+    }
   }
   if (lane < B) vput<Num>(x, n, i, xi);
 }
@@ -337,11 +433,25 @@ __global__ __launch_bounds__(64) void k_solve_bwd_diag(Mat<Num> A, int n, double
   const int lane = threadIdx.x, i = b0 + lane;
   Num xi = lane < B ? vget<Num>(x, n, i) : nzero<Num>();
   Num inv = nzero<Num>();
+  Num f[kSolveAhead], next[kSolveAhead];
+  auto load = [&](Num(&to)[kSolveAhead], int q0) {
+#pragma unroll
+    for (int d = 0; d < kSolveAhead; ++d) to[d] = lane < B && q0 - d >= 0 ? A.get(i, b0 + q0 - d) : nzero<Num>();
+  };
+  load(next, B - 1);
   if (lane < B) inv = ninv(A.get(i, i));
-  for (int q = B - 1; q >= 0; --q) {
-    if (lane == q) xi = nmul(xi, inv);
-    const Num xq = shfl_num(xi, q);
-    if (lane < q) xi = nfms(xi, A.get(i, b0 + q), xq);
+  for (int q0 = B - 1; q0 >= 0; q0 -= kSolveAhead) {
+#pragma unroll
+    for (int d = 0; d < kSolveAhead; ++d) f[d] = next[d];
+    load(next, q0 - kSolveAhead);
+#pragma unroll
+    for (int d = 0; d < kSolveAhead; ++d) {
+      const int q = q0 - d;
+      if (q < 0) break;
+      if (lane == q) xi = nmul(xi, inv);
+      const Num xq = read_num(xi, q);
+      if (lane < q) xi = nfms(xi, f[d], xq);
+    }
   }
   if (lane < B) vput<Num>(x, n, i, xi);
 }
@@ -362,8 +472,10 @@ __global__ __launch_bounds__(256) void k_solve_update(Mat<Num> A, int n, double 
   const int per = (B + kSolveChunks - 1) / kSolveChunks;
   const int q0 = b0 + c * per, q1 = std::min(b0 + B, q0 + per);
   Num p = nzero<Num>();  // minus the run's sum
-  if (live)
+  if (live) {
+#pragma unroll 8
     for (int q = q0; q < q1; ++q) p = nfms(p, A.get(i, q), vget<Num>(x, n, q));
+  }
   part[c][rl] = p;
   __syncthreads();
   if (live && c == 0) {
@@ -377,12 +489,10 @@ __global__ __launch_bounds__(256) void k_solve_update(Mat<Num> A, int n, double 
 unsigned grid_for(int64_t work) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>(ceil_div(work, 256), 8192)); }
 
 // Diagonal blocks wider than kInner are factored in inner blocks of kInner:
-// the unblocked kernel on the inner diagonal block (in LDS), the two panel
+// the unblocked kernel on the inner diagonal block, the two panel
 // solves restricted to the diagonal block, and a rank-kInner update of its
 // rest (DD at n = 2048: K = 512 170 -> 13.6 ms, and K = 64 12.0 -> 10.7 ms
 // once blocks of up to kInner were held in LDS).
-constexpr int kInner = 32;
-
 template <typename Num>
 hipError_t lu_panel(double *A, int64_t ld, int64_t plane, int j0, int K, int n, hipStream_t st) {
   const Mat<Num> M{A, ld, plane};
@@ -395,8 +505,9 @@ hipError_t lu_panel(double *A, int64_t ld, int64_t plane, int j0, int K, int n, 
       launch_lu_diag<Num>(M, jj, kb, st);
       if (r == 0) break;
       launch_sweeps<Num>(M, jj, kb, end, st);
-      hipLaunchKernelGGL((k_rank_update<Num>), dim3(grid_for((int64_t)r * r)), dim3(256), 0, st, M, jj + kb, jj + kb,
-                         r, r, jj, kb);
+      const unsigned tiles = (unsigned)ceil_div(r, kRankTile);
+      hipLaunchKernelGGL((k_rank_update<Num>), dim3(tiles, tiles), dim3(kRankTile * kRankTile), 0, st, M, jj + kb,
+                         jj + kb, r, r, jj, kb);
     }
   }
   if (j0 + K < n && K <= kSweepMax) {

@@ -203,3 +203,78 @@ def test_lu_edge_cases(mp):
     mp.dd_lu(E, 8)
     with pytest.raises(mp.MpgemmError):
         mp.dd_lu(torch.zeros((2, 4, 4), dtype=torch.float64, device="cuda"), 0)
+
+
+def two_sum(a, b):
+    s = a + b
+    t = s - a
+    return s, (a - (s - t)) + (b - t)
+
+
+def fast_two_sum(a, b):
+    s = a + b
+    return s, b - (s - a)
+
+
+def two_prod(a, b):
+    """Exact product by splitting both factors in 26 and 27 bits (Dekker)."""
+    p = a * b
+    c, d = 134217729.0 * a, 134217729.0 * b
+    ah, bh = c - (c - a), d - (d - b)
+    al, bl = a - ah, b - bh
+    return p, ((ah * bh - p) + ah * bl + al * bh) + al * bl
+
+
+def dd_sub(a, b):
+    s, e = two_sum(a[0], -b[0])
+    t, f = two_sum(a[1], -b[1])
+    s, e = fast_two_sum(s, e + t)
+    return fast_two_sum(s, e + f)
+
+
+def dd_mul(a, b):
+    p, e = two_prod(a[0], b[0])
+    return fast_two_sum(p, e + (a[0] * b[1] + a[1] * b[0]))
+
+
+def dd_inv(b):
+    one, zero = np.ones_like(b[0]), np.zeros_like(b[0])
+    q1 = one / b[0]
+    r = dd_sub((one, zero), dd_mul((q1, zero), b))
+    q2 = r[0] / b[0]
+    r = dd_sub(r, dd_mul((q2, zero), b))
+    hi, lo = fast_two_sum(q1, q2)
+    return dd_sub((hi, lo), (-(r[0] / b[0]), zero))
+
+
+@pytest.mark.parametrize("K,rest", [(2, 3), (31, 5), (33, 1), (63, 9), (64, 4), (65, 6), (100, 3), (128, 5), (129, 2),
+                                    (256, 4), (257, 3), (512, 2)])
+def test_panel_solves_bit_for_bit(mp, K, rest):
+    """U12 and L21 of the first panel are the plain substitutions with the L11 and
+    U11 that came out, operation by operation, at the edges of the kernels' lanes,
+    registers and chunks; K = 512 is the longest they take."""
+    import torch
+    n = K + rest
+    A = dd_dominant(n, seed=K)
+    dA = torch.from_numpy(A.copy()).cuda()
+    mp.lu("dd", dA, K)
+    at = lambda X: (np.ascontiguousarray(X[0].T), np.ascontiguousarray(X[1].T))  # (i, j)
+    src, LU = at(A), at(dA.cpu().numpy())
+    u = tuple(c[:K, K:].copy() for c in src)
+    for q in range(K - 1):
+        new = dd_sub(tuple(c[q + 1:] for c in u),
+                     dd_mul(tuple(c[q + 1:K, q, None] for c in LU), tuple(c[None, q] for c in u)))
+        for c, x in zip(u, new):
+            c[q + 1:] = x
+    low = tuple(c[K:, :K].copy() for c in src)
+    inv = dd_inv(tuple(np.diag(c)[:K].copy() for c in LU))
+    for q in range(K):
+        xq = dd_mul(tuple(c[:, q] for c in low), tuple(np.broadcast_to(c[q], (rest,)) for c in inv))
+        for c, x in zip(low, xq):
+            c[:, q] = x
+        new = dd_sub(tuple(c[:, q + 1:] for c in low),
+                     dd_mul(tuple(x[:, None] for x in xq), tuple(c[q, None, q + 1:K] for c in LU)))
+        for c, x in zip(low, new):
+            c[:, q + 1:] = x
+    for r in range(2):
+        assert np.array_equal(LU[r][:K, K:], u[r]) and np.array_equal(LU[r][K:, :K], low[r])
