@@ -1217,17 +1217,38 @@ hipError_t combine_launch(int nwc, bool chunks, int64_t blocks, const ResidueDes
   }
 }
 
+// Groups of the bases for `wgs` tiles and k chunks, `slots` workgroups running
+// together: of the counts that fill 1, 2, ... rounds the one with the least rounds
+// times products a round, with a quarter of a product for a round's start.  Against
+// the first count that fills one round (9 tiles in 29 groups ran 261 workgroups in
+// two rounds): INT8 DD n = 640 76 -> 66 us, 1100 193 -> 150, 3000 1717 -> 1284; QD
+// FLOAT 3000 4727 -> 3358.
+int base_groups(int64_t wgs, int slots, int bases, int products) {
+  int best = 1;
+  double least = 0.0;
+  for (int rounds = (int)std::min<int64_t>(1 << 20, ceil_div(wgs, (int64_t)slots)), last = rounds + 7; rounds <= last; ++rounds) {
+    const int g = (int)std::min<int64_t>(bases, (int64_t)rounds * slots / wgs);
+    const double cost = rounds * ((double)ceil_div(products, g) + 0.25);
+    if (least == 0.0 || cost < least) {
+      least = cost;
+      best = g;
+    }
+    if (g == bases) break;
+  }
+  return best;
+}
+
 hipError_t gemm_launch(int cfg, const ResiduePlan &p, const int8_t *A, const int8_t *B, const Shape &s, int u_first,
                        int u_end, int m, int n, int8_t *R, hipStream_t st) {
   const int tb = int8_tile_blocks(cfg);
   const int64_t tiles = (s.mbp / tb) * (s.nbp / tb);
   if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
-  // small products: the units (independent results) spread over gridDim.z
-  // until the grid fills the chip (256 workgroups of the 256 x 256 tiles, one
-  // per CU; 512 of the smaller ones)
+  // the bases (independent results) spread over gridDim.z, so that the last of the
+  // workgroups that run together (one of the 256 x 256 tiles per CU, two of the
+  // smaller ones) are as many as the others
   const int64_t nchunks = ceil_div(s.kbp, (int64_t)kChunkBlocks);
-  const int64_t wgs = tiles * nchunks, want = cfg == 1 ? 512 : 256;
-  const int groups = wgs >= want ? 1 : (int)std::min<int64_t>(u_end - u_first, ceil_div(want, wgs));
+  const int groups = base_groups(tiles * nchunks, cfg == 1 ? 512 : 256, u_end - u_first,
+                                 residue_pairs_below(u_end, p.nsq) - residue_pairs_below(u_first, p.nsq));
   const dim3 grid((unsigned)tiles, (unsigned)nchunks, (unsigned)groups);
   if (cfg == 1)
     hipLaunchKernelGGL(k_gemm_residue<1>, grid, dim3(64 * Int8Cfg<1>::WM * Int8Cfg<1>::WN), 0, st, A, B, s.mbp, s.nbp,

@@ -129,6 +129,18 @@ def test_maxima_of_whole_vectors(mp, mode, m, n, k):
     assert np.all(got == want)
 
 
+@pytest.mark.parametrize("mode,m,n,k", [("int8", 640, 600, 50), ("float", 1100, 1050, 64), ("int8", 2180, 300, 33),
+                                        ("float", 4200, 4100, 48), ("int8", 200, 4352, 32)])
+def test_every_grouping_of_the_bases(mp, mode, m, n, k):
+    """Tiles short of one round of the chip and past it, whose bases are cut into
+    different groups: products of small integers, exact in binary64."""
+    rng = np.random.default_rng(11)
+    a = rng.integers(-2 ** 15, 2 ** 15, (k, m)).astype(np.float64)
+    b = rng.integers(-2 ** 15, 2 ** 15, (n, k)).astype(np.float64)
+    C = mp.gemm("dd", dev(np.stack([a, 0 * a])), dev(np.stack([b, 0 * b])), mode=mode).cpu().numpy()
+    assert np.array_equal(C[0], b @ a) and not C[1].any()
+
+
 def slices(mp, fmt, A, B):
     """The product from binary64/binary32 slices: a slice count set by the
     caller is Algorithm 1 with that many slices."""
