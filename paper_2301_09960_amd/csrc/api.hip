@@ -253,6 +253,7 @@ size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 struct Plan {
   int fmt, mode, C, D, rho;
   int int8_cfg;  // INT8 GEMM tile configuration the slices are padded for
+  int res_cfg;   // and the residues
   size_t elem;  // bytes per slice element
   int64_t mbp, nbp, kbp;
   size_t off_resid_a, off_resid_b, off_pack_a, off_pack_b, off_mu_a, off_mu_b, off_exp_a, off_exp_b, off_sums, total;
@@ -322,7 +323,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
     // residues share.  A count that the caller set is Algorithm 1 with that many
     // slices.
     if (automatic && m > 0 && n > 0 && g_opt.last_slice == 0 && float_residue_plan(fmt, D, k, p.res)) {
-      p.int8_cfg = int8_tile_config(m, n, g_opt.int8_tile);
+      p.res_cfg = residue_tile_config(m, n, g_opt.int8_tile);
       o = 0;
       p.off_res_clear = 0;
       p.off_res_mu_a = take((size_t)m * comp);
@@ -333,7 +334,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
       p.off_res_exp_a = take((size_t)m * 4);
       p.off_res_exp_b = take((size_t)n * 4);
       p.off_arena = o;
-      take(residue_bytes(p.res, p.int8_cfg, m, n, k));
+      take(residue_bytes(p.res, p.res_cfg, m, n, k));
       p.off_flag = std::max(o, p.slices_total);
       p.total = p.off_flag + 256;
     } else {
@@ -345,6 +346,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
     p.elem = 1;
     p.rho = 0;
     p.int8_cfg = int8_tile_config(m, n, g_opt.int8_tile);
+    p.res_cfg = residue_tile_config(m, n, g_opt.int8_tile);
     p.mbp = nblocks8_padded(m, int8_tile_blocks(p.int8_cfg));
     p.nbp = nblocks8_padded(n, int8_tile_blocks(p.int8_cfg));
     p.kbp = kblocks8_padded(k);
@@ -370,7 +372,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
     if (m > 0 && n > 0 && k > 0 && p.C <= 4 && !residue_plan(7 * D - 1, k, p.res)) p.res.nunits = 0;
   }
   p.slices_total = p.total = o;
-  if (p.res.nunits > 0) p.total = std::max(o, p.off_arena + align256(residue_bytes(p.res, p.int8_cfg, m, n, k)));
+  if (p.res.nunits > 0) p.total = std::max(o, p.off_arena + align256(residue_bytes(p.res, p.res_cfg, m, n, k)));
   return p;
 }
 
@@ -620,7 +622,7 @@ hipError_t residue_launch(const Plan &p, char *base, size_t bytes, int *flag, co
                           hipStream_t st) {
   ResidueCall rc{};
   rc.plan = p.res;
-  rc.cfg = p.int8_cfg;
+  rc.cfg = p.res_cfg;
   rc.float_form = p.mode == MPGEMM_MODE_FLOAT;
   rc.slice_bits = rc.float_form ? (sizeof(T) == 8 ? 53 : 24) - p.rho : 0;
   rc.passes = p.D;

@@ -102,6 +102,8 @@ struct ResidueCall {
   char *arena;
   size_t arena_bytes;
 };
+// Tile configuration of one m x n product by residues (cfg > 0 forces one).
+int residue_tile_config(int64_t m, int64_t n, int cfg);
 size_t residue_bytes(const ResiduePlan &p, int cfg, int64_t m, int64_t n, int64_t k);
 template <typename T, int C>
 hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,

@@ -1261,6 +1261,20 @@ hipError_t gemm_launch(int cfg, const ResiduePlan &p, const int8_t *A, const int
 
 }  // namespace
 
+// The 256 x 256 tiles, except for a product within one of them, which the smaller
+// tiles spread over more CUs (200^2 x 100: INT8 DD 29.8 -> 26.0 us, QD FLOAT 55.7 ->
+// 46.5), and where padding to them takes more than 1.4 times the area of the 128 x
+// 128 ones (n = 640, 1.44 times: 66.5 -> 58.5 and 148 -> 122).  At 1.2 to 1.4 the two
+// are within 4 % (n = 1100: INT8 DD 150 and 148, FLOAT DD 161 and 165), and at 1.0 the
+// smaller tiles lose at most sizes (n = 2180: 756 and 844, QD 1974 and 2250); with the
+// operands in the caches they gain (n = 512: QD 85.6 and 78.8) or not (DD 45.1 and
+// 46.5).
+int residue_tile_config(int64_t m, int64_t n, int cfg) {
+  if (cfg >= 1 && cfg <= 4) return cfg;
+  const int64_t tiles3 = ceil_div(m, 256) * ceil_div(n, 256), tiles1 = ceil_div(m, 128) * ceil_div(n, 128);
+  return tiles3 == 1 || 20 * tiles3 > 7 * tiles1 ? 1 : 3;
+}
+
 size_t residue_bytes(const ResiduePlan &p, int cfg, int64_t m, int64_t n, int64_t k) {
   const Shape s = shape_of(cfg, m, n, k);
   return header_bytes(p) + (size_t)p.nplanes * (size_t)(s.a_plane + s.b_plane + p.nchunks * s.r_plane);
