@@ -1,21 +1,23 @@
 """Benchmark: Ozaki-scheme DD and QD GEMM at n = 4096 on one MI355X.
 
 One step = one DD and one QD product C = A B at m = n = k = 4096 (synthetic
-inputs, exponent spread e ~ U{0..16}, binary64 slices on the FP64 matrix
-cores), each a full pass of the path: split of A and B, every slice product
-of the triangle, error-free accumulation into C.  Inputs are resident in HBM
-before the timed region.  ``value`` is the whole job's effective 2 n^3 / s.
+inputs, exponent spread e ~ U{0..16}, the FLOAT form with the automatic slice
+count), each a full pass of the path: split of A and B into residues, every
+residue product on the INT8 matrix cores, the Chinese remainder into C (the
+binary64 slices stand behind it for inputs whose spread needs them).  Inputs are
+resident in HBM before the timed region.  ``value`` is the whole job's effective 2 n^3 / s.
 
 Extra objects on the JSON line:
-  roofline     -- the dominant kernel (the fused slice-product GEMM of the QD
-                  call) against the FP64 matrix peak: algorithmic slice-GEMM
-                  flops per launch, D (D + 1) / 2 x 2 n^3, over its average
-                  launch time measured with HIP events on its stream.
+  roofline     -- the dominant kernel (the residue GEMM of the QD call) against
+                  the INT8 matrix peak: operations per launch, products x 2 n^3,
+                  over the time of everything after the split (the GEMM, the
+                  combine, and the fallback's kernels that exit at once),
+                  measured with HIP events on its stream.
   cpu_baseline -- the CPU oracle's Ozaki product timed on a bounded sample.
-  stages       -- per format: split and fused-GEMM milliseconds per call.
-  int8         -- the same products with INT8 digit slices on the INT8 matrix
-                  cores (precision form), timed the same way; speedup over
-                  the binary64-slice form at the same error bound.
+  stages       -- per format: milliseconds of the split and of what follows it.
+  int8         -- the same products in the INT8 form (the product of the operands
+                  rounded to D digits, by residues), timed the same way; speedup
+                  over the FLOAT form at the same error bound.
   data_chosen_pairs -- the same products with the slice products chosen
                   from the data (per-tile pair sets, certified by
                   construction): call time, mean pairs per tile, certificate.
@@ -47,8 +49,8 @@ METRIC = "DD/QD GEMM 2n³/s at n=4096, %MFMA peak, INT8 vs FP64 slices; served p
 FP64_MFMA_PEAK_TFLOPS = 78.6
 FP32_MFMA_PEAK_TFLOPS = 157.3
 INT8_MFMA_PEAK_TOPS = 5000.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_gemm_plain_qd_n4096.json")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2301_09960_amd", "csrc", "gemm_fp.hip")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_gemm_residue_qd_n4096.json")
+GEMM_SOURCE = os.path.join(ROOT, "paper_2301_09960_amd", "csrc", "residue.hip")
 
 
 def log(msg):
@@ -108,6 +110,37 @@ MODES_HELP = """measurement modes besides the benchmark line:
       (FETCH_SIZE, WRITE_SIZE in KiB per dispatch), each scaled by what the
       counter reads for the plain 1 GiB copies of --copy-calibration
 """
+
+
+def residue_products(fmt, mode, D, k):
+    """INT8 products and operand planes of one call by residues (csrc/residue.h):
+    the cheapest set of pairwise coprime bases below 257, the first of them squared
+    for two products and a plane more each, that covers 2.1 k 2^(2 bits).  (0, 0)
+    where the slices form it."""
+    if mode == "int8":
+        bits = 7 * D - 1
+    else:
+        if k < 48:
+            return 0, 0
+        S = 24 if fmt == "ts" else 53
+        b = S - (S + max(0, int(k - 1).bit_length()) + 1) // 2
+        bits = max(D * (b + 1) + 2, 116 if fmt == "ts" else 0)
+    bases = []
+    for x in range(256, 28, -1):
+        if all(np.gcd(x, y) == 1 for y in bases):
+            bases.append(x)
+    logs = np.log2(bases)
+    need = 2.0 * bits + np.log2(k) + 1.07
+    best = (0, 0)
+    for n in range(1, len(bases) + 1):
+        have, squares = logs[:n].sum(), 0
+        while have < need and squares < n:
+            have += logs[squares]
+            squares += 1
+        if have >= need:
+            if best == (0, 0) or n + 2 * squares <= best[0]:
+                best = (n + 2 * squares, n + squares)
+    return best
 
 
 def source_hash(path):
@@ -179,17 +212,17 @@ def run_batched(mp, torch, pool, fmt, count=512, seed=31, mode="float"):
     _, gms = mp.profile_read()
     flops = float(np.sum(2.0 * m * n * k))
     gpu_ms = float(np.mean(gms))
-    Ds = np.array([mp.num_slices(fmt, mode, int(kk)) for kk in k], dtype=np.float64)
-    slice_flops = float(np.sum(Ds * (Ds + 1) / 2 * 2.0 * m * n * k))
-    peak = INT8_MFMA_PEAK_TOPS if mode == "int8" else FP64_MFMA_PEAK_TFLOPS
+    # INT8 operations of the products by residues (k below 48 in the FLOAT form: slices, left out)
+    count8 = {int(kk): residue_products(fmt, mode, mp.num_slices(fmt, mode, int(kk)), int(kk))[0] for kk in set(k)}
+    ops = float(sum(count8[int(kk)] * 2.0 * mm * nn * kk for mm, nn, kk in zip(m, n, k)))
     return {
         "products": count,
         "mode": mode,
         "sum_2mnk": flops,
         "launch_ms": round(gpu_ms, 3),
         "effective_gflops": round(flops / (gpu_ms * 1e-3) / 1e9, 1),
-        "slice_gemm_tflops": round(slice_flops / (gpu_ms * 1e-3) / 1e12, 2),
-        "mfma_frac": round(slice_flops / (gpu_ms * 1e-3) / 1e12 / peak, 4),
+        "int8_tops": round(ops / (gpu_ms * 1e-3) / 1e12, 2),
+        "int8_mfma_frac": round(ops / (gpu_ms * 1e-3) / 1e12 / INT8_MFMA_PEAK_TOPS, 4),
         "wall_ms_per_batch": round((t1 - t0) * 1e3 / reps, 3),
         "max_slices": mp.last_num_slices(),
     }
@@ -243,14 +276,15 @@ def sweep_grid(torch, mp, sizes, reps):
         C = torch.empty((W.FORMATS[fmt][0], n, n), dtype=dA.dtype, device="cuda")
         split_ms, gemm_ms = _timed_calls(torch, mp, lambda: mp.gemm(fmt, dA, dB, C, mode=mode), reps)
         D = mp.last_num_slices()
-        ops = D * (D + 1) / 2 * 2.0 * n ** 3
-        kind = "int8" if mode == "int8" else ("float32" if fmt == "ts" else "float64")
+        products, _ = residue_products(fmt, mode, D, n)
+        kind = "int8" if products else ("float32" if fmt == "ts" else "float64")
+        ops = (products or D * (D + 1) / 2) * 2.0 * n ** 3
         rate = ops / (gemm_ms * 1e-3) / 1e12
         print(json.dumps({
             "fmt": fmt, "n": n, "E": E, "mode": mode, "D": D,
             "split_ms": round(split_ms, 3), "gemm_ms": round(gemm_ms, 3),
             "effective_gflops": round(2.0 * n ** 3 / ((split_ms + gemm_ms) * 1e-3) / 1e9, 1),
-            "slice_rate": round(rate, 2), "slice_rate_unit": "TOP/s" if mode == "int8" else "TFLOP/s",
+            "slice_rate": round(rate, 2), "slice_rate_unit": "TOP/s" if kind == "int8" else "TFLOP/s",
             "peak_frac": round(rate / SWEEP_PEAK[kind], 4)}), flush=True)
         del dA, dB, C
 
@@ -266,7 +300,8 @@ def sweep_nd(torch, mp, sizes, reps, E=16):
             C = torch.empty((c, n, n), dtype=torch.float64, device="cuda")
             split_ms, gemm_ms = _timed_calls(torch, mp, lambda: mp.gemm_nd(dA, dB, C), reps)
             D = mp.nd_num_slices(c, n)
-            ops = D * (D + 1) / 2 * 2.0 * n ** 3
+            # up to four components by residues, longer expansions by digit products
+            ops = (residue_products(fmt, "int8", D, n)[0] if c <= 4 else D * (D + 1) / 2) * 2.0 * n ** 3
             print(json.dumps({
                 "components": c, "bits": 53 * c, "n": n, "E": E, "mode": "int8", "D": D,
                 "split_ms": round(split_ms, 3), "gemm_ms": round(gemm_ms, 3),
@@ -463,31 +498,35 @@ def main():
         sp = split_ms[idx::len(fmts)]
         gm = gemm_ms[idx::len(fmts)]
         D = slices[f]
-        slice_flops = D * (D + 1) / 2 * 2.0 * n ** 3
-        peak = FP32_MFMA_PEAK_TFLOPS if f == "ts" else FP64_MFMA_PEAK_TFLOPS
+        products, planes = residue_products(f, "float", D, n)
+        kind = "int8" if products else ("float32" if f == "ts" else "float64")
         g_avg = float(np.mean(gm))
+        rate = (products or D * (D + 1) / 2) * 2.0 * n ** 3 / (g_avg * 1e-3) / 1e12
         c, w = W.FORMATS[f][0], (4 if f == "ts" else 8)
-        split_bytes = (c * w + D * w) * 2.0 * n * n  # read A and B once, write D slices of each
+        # read A and B once, write the residue planes of each, or D slices
+        split_bytes = (c * w + (planes or D * w)) * 2.0 * n * n
         stages[f] = {
             "D": D,
+            "products": products or D * (D + 1) // 2,
             "split_ms": round(float(np.mean(sp)), 3),
             "split_gbs_algorithmic": round(split_bytes / (float(np.mean(sp)) * 1e-3) / 1e9, 1),
             "gemm_kernel_ms": round(g_avg, 3),
             "effective_gflops": round(2.0 * n ** 3 / ((float(np.mean(sp)) + g_avg) * 1e-3) / 1e9, 1),
-            "slice_gemm_tflops": round(slice_flops / (g_avg * 1e-3) / 1e12, 2),
-            "mfma_frac": round(slice_flops / (g_avg * 1e-3) / 1e12 / peak, 4),
+            "rate": round(rate, 2),
+            "rate_unit": "TOP/s (INT8)" if kind == "int8" else "TFLOP/s",
+            "mfma_frac": round(rate / SWEEP_PEAK[kind], 4),
         }
     dom = max(fmts, key=lambda f: stages[f]["gemm_kernel_ms"])
-    D = slices[dom]
-    peak = FP32_MFMA_PEAK_TFLOPS if dom == "ts" else FP64_MFMA_PEAK_TFLOPS
-    achieved = D * (D + 1) / 2 * 2.0 * n ** 3 / (stages[dom]["gemm_kernel_ms"] * 1e-3) / 1e12
-    kernel_key = f"k_gemm_plain<{'float' if dom == 'ts' else 'double'},{W.FORMATS[dom][0]}> n={n}"
+    by_residues = stages[dom]["rate_unit"].startswith("TOP/s")
+    peak = INT8_MFMA_PEAK_TOPS if by_residues else FP32_MFMA_PEAK_TFLOPS if dom == "ts" else FP64_MFMA_PEAK_TFLOPS
+    kernel_key = (f"k_gemm_residue {dom} n={n}" if by_residues else
+                  f"k_gemm_plain<{'float' if dom == 'ts' else 'double'},{W.FORMATS[dom][0]}> n={n}")
     roofline = {
         "bound": "mfma",
-        "achieved": round(achieved, 3),
+        "achieved": round(stages[dom]["rate"], 3),
         "peak": peak,
-        "unit": "TFLOP/s",
-        "frac": round(achieved / peak, 4),
+        "unit": "TOP/s" if by_residues else "TFLOP/s",
+        "frac": round(stages[dom]["rate"] / peak, 4),
         "traffic": traffic_for(kernel_key),
         "kernel": kernel_key,
     }
@@ -500,12 +539,14 @@ def main():
             D8 = mp.num_slices(f, "int8", n)
             call_ms = float(np.mean(isp[idx::len(fmts)])) + float(np.mean(igm[idx::len(fmts)]))
             gemm8 = float(np.mean(igm[idx::len(fmts)]))
-            ops = D8 * (D8 + 1) / 2 * 2.0 * n ** 3
+            products, planes = residue_products(f, "int8", D8, n)
+            ops = products * 2.0 * n ** 3
             split8 = float(np.mean(isp[idx::len(fmts)]))
             int8[f] = {
                 "D": D8,
+                "products": products,
                 "split_ms": round(split8, 3),
-                "split_gbs_algorithmic": round((W.FORMATS[f][0] * 8 + D8) * 2.0 * n * n / (split8 * 1e-3) / 1e9, 1),
+                "split_gbs_algorithmic": round((W.FORMATS[f][0] * 8 + planes) * 2.0 * n * n / (split8 * 1e-3) / 1e9, 1),
                 "gemm_and_combine_ms": round(gemm8, 3),
                 "effective_gflops": round(2.0 * n ** 3 / (call_ms * 1e-3) / 1e9, 1),
                 "int8_tops": round(ops / (gemm8 * 1e-3) / 1e12, 1),
@@ -678,7 +719,7 @@ def main():
         "data": "synthetic",
         "config": {
             "workload": f"Ozaki GEMM {'+'.join(x.upper() for x in fmts)} m=n=k={n}, e~U{{0..{args.E}}}, "
-                        f"binary64 slices on FP64 matrix cores",
+                        f"FLOAT form by residues on INT8 matrix cores",
             "n": n,
             "formats": fmts,
             "slices": slices,

@@ -262,11 +262,13 @@ int mpgemm_tile_layout(int fmt);
 int mpgemm_load_tune_file(const char *path);
 
 /*
- * Tile configuration of the INT8-form kernel, per host thread: 0 automatic
- * (256 x 256 tiles with 8 wavefronts unless padding to them more than doubles
- * the area padded to 128 x 128, else 128 x 128), 1 = 128 x 128 with 4
- * wavefronts, 2 = 256 x 256 with 4, 3 = 256 x 256 with 8, 4 = 256 x 256 with
- * 16.  Slices are padded to the chosen tile.  Returns -1 for other values.
+ * Tile configuration of the INT8 matrix products, per host thread: 0 automatic
+ * (256 x 256 tiles with 8 wavefronts, or 128 x 128 where the product fits one of
+ * those or padding to them costs more than 1.4 times the area), 1 = 128 x 128 with
+ * 4 wavefronts, 3 = 256 x 256 with 8.  2 (256 x 256 with 4) and 4 (with 16) hold
+ * for the digit products of longer expansions (mpgemm_nd), whose automatic choice
+ * is 256 x 256 unless padding more than doubles the area; products by residues run
+ * them as 3.  Operands are padded to the chosen tile.  Returns -1 for other values.
  */
 int mpgemm_set_int8_tile(int cfg);
 
