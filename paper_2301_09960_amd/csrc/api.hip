@@ -966,8 +966,12 @@ int run_dd_noalloc(int m, int n, int k, const double *A, int lda, const double *
   g_opt.last_slices = D;
   if (m == 0 || n == 0) return 0;
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(double), 2, m, n, ldc, (int64_t)ldc * n, st));
-  const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
+  Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
   if (p.slices_total > kScratchBytes) return MPGEMM_ERR_TOO_LARGE;
+  // The residues may go in blocks of C, the first written before the last is
+  // split: a C that shares memory with an operand takes the slices.
+  auto apart = [&](const double *X, int64_t elements) { return X + elements <= Cm || Cm + 2 * (int64_t)ldc * n <= X; };
+  if (!apart(A, 2 * (int64_t)lda * k) || !apart(B, 2 * (int64_t)ldb * n)) p.res.nunits = 0;
   char *base = nullptr;
   if ((s = scratch_of_current_device(&base))) return s;
   return hip_status(launch_product<double, 2>(p, base, kScratchBytes, reinterpret_cast<int *>(base + kScratchBytes), m, n, k, A,

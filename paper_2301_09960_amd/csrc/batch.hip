@@ -260,21 +260,27 @@ struct ResidueBatch {
            hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
   }
 
-  // The launch sequence (descriptors at off_ops, off_descs of the workspace).
+  // The launch sequence in two parts (descriptors at off_ops, off_descs of the workspace).
   template <typename T, int C>
-  hipError_t launch(char *ws, size_t off_ops, size_t off_descs, hipStream_t st) const {
+  hipError_t launch_split(char *ws, size_t off_ops, hipStream_t st) const {
     if (slots.empty()) return hipSuccess;
     const auto *ops = reinterpret_cast<const ResidueOperand<T> *>(ws + off_ops);
-    const auto *descs = reinterpret_cast<const ResidueDesc *>(ws + off_descs);
     const int n = (int)slots.size();
-    const int *pre0 = reinterpret_cast<const int *>(ws + off_static), *preb = pre0 + 2 * n + 1, *prec = preb + 2 * n + 1;
+    const int *pre0 = reinterpret_cast<const int *>(ws + off_static), *preb = pre0 + 2 * n + 1;
     hipError_t e = launch_fill32(ws + off_zero, (int64_t)(zero_bytes / 4), 0u, st);
     if (e == hipSuccess) e = launch_residue_max_batched<T>(ops, pre0, 2 * n, tiles0, st);
     if (e == hipSuccess) e = launch_residue_split_batched<T, C>(nw, ops, preb, 2 * n, (int)blocks, st);
-    if (e == hipSuccess)
-      e = launch_gemm_residue_batched(descs, reinterpret_cast<const int4 *>(ws + off_items), nitems1, nitems3,
-                                      reinterpret_cast<const int *>(ws + off_bounds),
-                                      reinterpret_cast<int *>(ws + off_counter), st);
+    return e;
+  }
+  template <typename T, int C>
+  hipError_t launch_products(char *ws, size_t off_descs, hipStream_t st) const {
+    if (slots.empty()) return hipSuccess;
+    const auto *descs = reinterpret_cast<const ResidueDesc *>(ws + off_descs);
+    const int n = (int)slots.size();
+    const int *prec = reinterpret_cast<const int *>(ws + off_static) + 4 * n + 2;
+    hipError_t e = launch_gemm_residue_batched(descs, reinterpret_cast<const int4 *>(ws + off_items), nitems1, nitems3,
+                                               reinterpret_cast<const int *>(ws + off_bounds),
+                                               reinterpret_cast<int *>(ws + off_counter), st);
     for (int i = 0; i < n && e == hipSuccess;) {
       int j = i;
       int64_t sum = 0;
@@ -476,16 +482,20 @@ struct PlainBatch {
            hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
   }
 
-  // The launch sequence, with the descriptors at `off` of the workspace.
-  hipError_t launch(char *ws, size_t off, int gemm_layout, hipStream_t st) const {
+  // The launch sequence in two parts, with the descriptors at `off` of the workspace.
+  hipError_t launch_split(char *ws, size_t off, hipStream_t st) const {
     if (slots.empty()) return hipSuccess;
     const int n = 2 * (int)slots.size();
     const int *pre0 = reinterpret_cast<const int *>(ws + off_static), *prep = pre0 + n + 1, *pref = prep + n + 1;
     const int *any = off_any == SIZE_MAX ? nullptr : reinterpret_cast<const int *>(ws + off_any);
-    hipError_t e = launch_split_plain_batched<T, C>(reinterpret_cast<const SplitOperand<T> *>(ws + off), pre0, prep,
-                                                    pref, n, tiles0, tilesp, stripsf, fused_nt, dpass, ws + off_mu,
-                                                    (int64_t)(mu_bytes / 4), any, st);
-    if (e == hipSuccess) e = launch_fill32(ws + off_counter, kXcds, 0u, st);
+    return launch_split_plain_batched<T, C>(reinterpret_cast<const SplitOperand<T> *>(ws + off), pre0, prep, pref, n,
+                                            tiles0, tilesp, stripsf, fused_nt, dpass, ws + off_mu,
+                                            (int64_t)(mu_bytes / 4), any, st);
+  }
+  hipError_t launch_products(char *ws, size_t off, int gemm_layout, hipStream_t st) const {
+    if (slots.empty()) return hipSuccess;
+    const int *any = off_any == SIZE_MAX ? nullptr : reinterpret_cast<const int *>(ws + off_any);
+    hipError_t e = launch_fill32(ws + off_counter, kXcds, 0u, st);
     if (e == hipSuccess)
       e = launch_gemm_plain_batched<T, C>(reinterpret_cast<const PlainGemmDesc *>(ws + off + ops_bytes()),
                                           reinterpret_cast<const int2 *>(ws + off_items),
@@ -652,9 +662,13 @@ struct FormatPlan : BatchPlan {
     hipStream_t &cs = bc.capture[device & 63];
     if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return MPGEMM_ERR_HIP;
     if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return MPGEMM_ERR_HIP;
-    hipError_t e = plain.launch(ws, off_desc + off_plain, layout, cs);
-    if (e == hipSuccess) e = res.template launch<T, C>(ws, off_desc + off_ops, off_desc + off_res, cs);
-    if (e == hipSuccess) e = fallback.launch(ws, off_desc + off_fallback, layout, cs);
+    // every operand is read before the first C is written: C may be an operand
+    hipError_t e = plain.launch_split(ws, off_desc + off_plain, cs);
+    if (e == hipSuccess) e = res.template launch_split<T, C>(ws, off_desc + off_ops, cs);
+    if (e == hipSuccess) e = fallback.launch_split(ws, off_desc + off_fallback, cs);
+    if (e == hipSuccess) e = plain.launch_products(ws, off_desc + off_plain, layout, cs);
+    if (e == hipSuccess) e = res.template launch_products<T, C>(ws, off_desc + off_res, cs);
+    if (e == hipSuccess) e = fallback.launch_products(ws, off_desc + off_fallback, layout, cs);
     hipGraph_t captured = nullptr;
     const hipError_t e2 = hipStreamEndCapture(cs, &captured);
     if (e != hipSuccess || e2 != hipSuccess || !captured) {

@@ -81,6 +81,7 @@ struct ResidueDesc {
   int nunits, nsq, nplanes, nchunks, groups, bits, m, n, ldc;
   void *C;
   int64_t c_stride;
+  const int *skip;        // FLOAT form: where set, C is left to the slices, whose split may read A or B from it
 };
 
 // One product by residues.  clear: device memory holding the maxima and, in the

@@ -813,6 +813,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_residue_combine(const ResidueDe
   constexpr int RB = combine_rows(NWC), KS = combine_steps(NWC);
   const int p = __builtin_amdgcn_readfirstlane(find_range(prefix, nprod, blockIdx.x));
   const ResidueDesc d = descs[p];
+  if (d.skip && *d.skip) return;
   const int64_t blk = (int64_t)blockIdx.x - prefix[p];
   const int lane = threadIdx.x % 64, quad = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
   const int64_t bi = blk % d.mbp, bj = blk / d.mbp;
@@ -1376,6 +1377,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   h.d.ldc = rc.ldc;
   h.d.C = Cout;
   h.d.c_stride = rc.c_stride;
+  h.d.skip = rc.flag;
 
   hipError_t err = hipSuccess;
   const bool begin = rc.k <= kBeginLength;

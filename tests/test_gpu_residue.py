@@ -263,3 +263,51 @@ def test_fixed_scratch_takes_the_product_in_parts(mp, mode, m, n, k):
     finally:
         mp.set_mode("dd", old)
     assert st == 0 and torch.equal(got, want)
+
+
+def noalloc(mp, A, B, C, mode):
+    import ctypes
+    import torch
+    P = ctypes.c_void_p
+    (k, m), n = A.shape[1:], B.shape[1]
+    old = mp.get_mode("dd")
+    mp.set_mode("dd", mode)
+    try:
+        st = mp.lib().mpgemm_dd_noalloc(m, n, k, P(A.data_ptr()), m, P(B.data_ptr()), k, P(C.data_ptr()), m,
+                                        P(torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+    finally:
+        mp.set_mode("dd", old)
+    assert st == 0
+    return C
+
+
+@pytest.mark.parametrize("mode,gap", [("float", False), ("float", True), ("int8", False)])
+@pytest.mark.parametrize("into", ["A", "B"])
+def test_result_in_the_place_of_an_operand(mp, mode, gap, into):
+    """C may be A or B, also where the slices take over: one product, a batch
+    whose products write each other's operands, and the fixed scratch."""
+    import torch
+    n = 96
+    A, B = with_gap("dd", n, n, n, n // 2) if gap else W.gen_pair("dd", n, n, n, E=4, seed=n)
+    dA, dB = dev(A), dev(B)
+    want = mp.gemm("dd", dA, dB, mode=mode).clone()
+    a, b = dA.clone(), dB.clone()
+    assert torch.equal(mp.gemm("dd", a, b, a if into == "A" else b, mode=mode), want)
+    As, Bs = [dA.clone() for _ in range(3)], [dB.clone() for _ in range(3)]
+    Cs = [(As if into == "A" else Bs)[(i + 1) % 3] for i in range(3)]
+    for C in mp.gemm_batched("dd", As, Bs, Cs, mode=mode):
+        assert torch.equal(C, want)
+    m = 1000 if mode == "float" else 700  # FLOAT: the fixed scratch takes it in blocks of C
+    A, B = W.gen_pair("dd", m, m, 60, E=4, seed=7)
+    side = torch.zeros((2, m, m), dtype=torch.float64, device="cuda")
+    flat = side.reshape(-1)
+    a, b = dev(A), dev(B)
+    apart = noalloc(mp, a, b, torch.zeros_like(side), mode)
+    x = a if into == "A" else b
+    shared = flat[:x.numel()].reshape(x.shape)
+    shared.copy_(x)
+    got = noalloc(mp, shared if into == "A" else a, b if into == "A" else shared, side, mode)
+    # slices against residues: both within the bound of the format
+    scale = np.abs(B[0]) @ np.abs(A[0])
+    assert np.all(((got[0] - apart[0]) + (got[1] - apart[1])).abs().cpu().numpy() <= 2.0 ** -99 * scale)
