@@ -3,7 +3,7 @@
 // and the Chinese remainder combination into the components of C.
 //
 // k_residue_split: one workgroup per 32 x 32 block of an operand.  The element's
-// integer W is formed in 32-bit words, rounded to nearest on 32 guard bits, and
+// integer W is formed in 32-bit words, rounded to nearest (ties to even), and
 // written in signed bytes; its residues modulo 32 bases are a matrix product
 // (bases x bytes) (bytes x elements) with the residues of 256^j on the INT8 matrix
 // cores, each reduced by one binary32 quotient.  Each plane of the block is
@@ -253,6 +253,40 @@ __device__ __forceinline__ void window_add_shifted(uint32_t (&w)[N], int64_t M, 
   for (int i = 0; i < N; ++i) w[i] = __builtin_addc(w[i], a[i], carry, &carry);
 }
 
+// Whether an element at or just below half a step of its grid rounds up (nearest,
+// ties to even).  g: its guard word, the floors of the components in 2^P added up;
+// odd: the lowest bit above it.  Ties are common in short data (no floor cut
+// anything off: g decides).  Else what the floors left, the fraction of a component
+// or a whole one below 2^P, is added to the distance from a half in the components'
+// order, which for normalized expansions leaves its sign exact.
+template <typename T, int C>
+__device__ __forceinline__ bool rounds_up(const T (&x)[C], int P, uint32_t g, bool odd) {
+  bool lost = false;
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    int64_t M;
+    int q;
+    parts_of(x[r], M, q);
+    const int sh = q >= P ? 0 : P - q < 63 ? P - q : 63;
+    lost = lost || (M & ((int64_t(1) << sh) - 1)) != 0;
+  }
+  if (!lost) return g > 0x80000000u - (odd ? 1u : 0u);
+  double d = (double)(int)(g - 0x80000000u), left[C];
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    int64_t M;
+    int q;
+    parts_of(x[r], M, q);
+    const int sh = q >= P ? 0 : P - q < 63 ? P - q : 63;
+    const bool below = sh > 0 && M >> sh == -1;  // its floor is -1: whole instead
+    d += below ? 1.0 : 0.0;
+    left[r] = ldexp((double)(below ? M : M & ((int64_t(1) << sh) - 1)), q < P ? q - P : 0);
+  }
+#pragma unroll
+  for (int r = 0; r < C; ++r) d += left[r];
+  return d > 0.0 || (d == 0.0 && odd);
+}
+
 template <int NW>
 struct SplitLds {
   static constexpr bool kSmall = NW <= 4, kMore = NW > 8;
@@ -329,7 +363,8 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     }
     inexact = inexact || w[0] != 0u;
     uint32_t W[12];  // signed bytes with the sum W: W + 0x80..80, each byte less 128
-    uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits
+    uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits, ties to even
+    if (w[0] - (0x80000000u - C) <= (uint32_t)C) carry = rounds_up<T, C>(xs[j], P, w[0], (w[1] & 1u) != 0u) ? 1u : 0u;
 #pragma unroll
     for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(w[i + 1], 0u, carry, &carry);
     if (check && kb == 0) {  // the changes of bits but the last ones of the element

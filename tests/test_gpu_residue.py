@@ -311,3 +311,40 @@ def test_result_in_the_place_of_an_operand(mp, mode, gap, into):
     # slices against residues: both within the bound of the format
     scale = np.abs(B[0]) @ np.abs(A[0])
     assert np.all(((got[0] - apart[0]) + (got[1] - apart[1])).abs().cpu().numpy() <= 2.0 ** -99 * scale)
+
+
+@pytest.mark.parametrize("fmt", ["dd", "td", "qd"])
+@pytest.mark.parametrize("D", [1, 2, 7, 17])
+def test_elements_round_to_nearest_even(mp, fmt, D):
+    """Elements at and next to half a step of their grid, with the lower components
+    above, below and on both sides of it: C is the element rounded to nearest,
+    ties to even (a product with a unit vector), exactly."""
+    from fractions import Fraction
+    c = COMPS[fmt]
+    bits = 7 * D - 1
+    u = 2.0 ** -bits  # E = 0: |x| < 1, the largest 0.75
+    rows = []
+    for h in (0, 1, 2, 3, 2 ** min(bits, 50) // 3, 2 ** min(bits, 50) // 3 + 1):
+        for sign in (1.0, -1.0):
+            for tail in ((0, 0), (1, 0), (-1, 0), (1, -1), (-1, 1), (1, 1), (-1, -1)):
+                lead = (h + 0.5) * 2.0 ** -min(bits, 50) * sign
+                x = [lead, 0.0, 0.0, 0.0]
+                if bits > 50:  # the half step is in a lower component
+                    x[0] = h * 2.0 ** -50 * sign
+                    x[1] = 0.5 * u * sign
+                at = 2 if bits > 50 else 1
+                for r, t in enumerate(tail):
+                    if at + r < c:
+                        x[at + r] = t * abs(lead if bits <= 50 else x[1]) * 2.0 ** (-60 * (r + 1))
+                rows.append(x[:c])
+    m, k = len(rows), 3
+    A = np.zeros((c, k, m))
+    A[:, 1, :] = np.array(rows).T
+    A[0, 2, :] = 0.75
+    B = np.zeros((c, 1, k))
+    B[0, 0, 1] = 1.0
+    say(f"rounding {fmt} D={D}: {m} elements")
+    C = mp.gemm(fmt, dev(A), dev(B), mode="int8", slices=D).cpu().numpy()
+    for i, x in enumerate(rows):
+        steps = sum(map(Fraction, x)) / Fraction(u)
+        assert sum(Fraction(float(v)) for v in C[:, 0, i]) == round(steps) * Fraction(u), (x, C[:, 0, i])
