@@ -301,15 +301,21 @@ int mpgemm_last_num_slices(void);
 
 /*
  * Workspace.  mpgemm_workspace_bytes gives the device bytes a call of this
- * shape needs (D = 0: automatic).  mpgemm_set_workspace attaches caller-owned
+ * shape takes (D = 0: automatic): what its residue planes need, up to 8 GiB or, if
+ * that is more, to 5/4 of what its slices (digits) need, which is the least that a
+ * call can do with.  In less than all its planes need a product is formed in groups
+ * of moduli and blocks of C, with the same result; where C shares memory with an
+ * operand, or the planes of one tile do not fit, it is formed from the slices
+ * (digits).  mpgemm_set_workspace attaches caller-owned
  * device memory (at least 256-byte aligned) for this host thread's later calls;
- * NULL detaches it.  A call that finds the attached workspace too small returns
- * MPGEMM_ERR_WORKSPACE without enqueuing work.  Work on different streams must
- * not share one attached workspace concurrently.  Without one, a call on the
+ * NULL detaches it.  A call that finds the attached workspace smaller than its
+ * slices returns MPGEMM_ERR_WORKSPACE without enqueuing work.  Work on different
+ * streams must not share one attached workspace concurrently.  Without one, a call on the
  * default stream takes a kept workspace (up to 256 MiB each, 1 GiB a device, for
  * the life of the process or until memory runs out), and other calls one from the
  * device's stream-ordered pool (hipMallocAsync, kept allocated after release);
- * callers that keep several streams busy at once
+ * where the device has not that much left, as much as the slices need.
+ * Callers that keep several streams busy at once
  * should attach one workspace per stream instead, since growing the pool under
  * such load has stalled the calling thread for up to seconds.
  */
@@ -478,10 +484,10 @@ int mpgemm_nd_debug_products(int c, int m, int n, int k, const double *A, int ld
  * forbid hipMalloc): the same product as mpgemm_dd (the thread's slice form
  * and slice count, the same kernels, the same C bit for bit), with its
  * workspace in a fixed device array of MPGEMM_NOALLOC_SCRATCH_BYTES that the
- * library holds on each device it runs on until the process ends.  A shape
- * whose workspace (mpgemm_workspace_bytes(MPGEMM_DD, mode, m, n, k, 0)) exceeds
- * it returns MPGEMM_ERR_TOO_LARGE without enqueuing work (for example
- * m = n = k = 1024 needs 128 MiB with binary64 slices).  Every call on a device
+ * library holds on each device it runs on until the process ends (a product whose
+ * residue planes need more is formed in parts, as in a small workspace).  A shape
+ * whose slices (digits) exceed it returns MPGEMM_ERR_TOO_LARGE without enqueuing
+ * work (for example m = n = k = 1024 needs 128 MiB with binary64 slices).  Every call on a device
  * shares that device's array: calls that overlap on one device (on different
  * streams, or from different threads) race and must be serialized by the
  * caller; calls queued on one stream are ordered and safe.  The first call on

@@ -262,8 +262,22 @@ struct Plan {
   ResiduePlan res;
   size_t off_res_clear, res_clear_bytes;  // maxima and states, cleared together
   size_t off_res_mu_a, off_res_mu_b, off_res_st_a, off_res_st_b, off_res_exp_a, off_res_exp_b, off_arena, off_flag;
-  size_t slices_total;  // without the residues
+  size_t slices_total;  // without the residues: no call can do with less
+  size_t room;          // what the residues may use of the workspace (from its start)
 };
+
+// What a call takes for its residues: all that they need, unless that is beyond
+// both a quarter more than the slices take (which is what the call took before it
+// had residues) and this much.  The residue planes of C take 32 to 85 bytes an
+// entry, so a large C of short rows would need many times its operands and itself
+// (QD 65536^2 x 256: 286 GB).  In less, the product is formed in blocks of C, which
+// costs the split of an operand once more for each halving: DD 32768^2 x 128 takes
+// 34.8 ms with all planes (37 GB), 34.1 in 8 GiB and 31.9 to 33.1 in 1 to 4; QD 16384^2
+// x 64 16.8 (18 GB), 16.9 and 16.9 to 18.9; DD 20000^2 x 2000 43.1 (19 GB) and 44.4.
+constexpr size_t kResidueRoom = size_t(8) << 30;
+size_t residue_room(size_t need, size_t slices) {
+  return std::min(need, std::max(slices + align256(slices / 4), kResidueRoom));
+}
 
 // Smallest inner dimension for which the FLOAT form goes by residues: its check
 // reads changes of bits off the first 32 elements of a vector (residue.hip), and
@@ -335,7 +349,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
       p.off_res_exp_b = take((size_t)n * 4);
       p.off_arena = o;
       take(residue_bytes(p.res, p.res_cfg, m, n, k));
-      p.off_flag = std::max(o, p.slices_total);
+      p.room = p.off_flag = std::max(residue_room(o, p.slices_total), p.slices_total);
       p.total = p.off_flag + 256;
     } else {
       p.res.nunits = 0;
@@ -372,8 +386,32 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
     if (m > 0 && n > 0 && k > 0 && p.C <= 4 && !residue_plan(7 * D - 1, k, p.res)) p.res.nunits = 0;
   }
   p.slices_total = p.total = o;
-  if (p.res.nunits > 0) p.total = std::max(o, p.off_arena + align256(residue_bytes(p.res, p.res_cfg, m, n, k)));
+  if (p.res.nunits > 0)
+    p.total = std::max(o, residue_room(p.off_arena + align256(residue_bytes(p.res, p.res_cfg, m, n, k)), o));
+  p.room = p.total;
   return p;
+}
+
+// Whether a matrix of `count` elements of T shares no memory with C.
+template <typename T>
+bool apart(const T *X, int64_t count, const T *Cm, int64_t ccount) {
+  return X + count <= Cm || Cm + ccount <= X;
+}
+
+// Fits p to a workspace of `bytes` (at least p.slices_total): the residues in what
+// there is of it, or none where they do not fit, or where the blocks of C they would
+// take are written before the operands are read for the last (C not apart from them).
+void fit_plan(Plan &p, size_t bytes, int m, int n, int k, bool c_apart) {
+  if (p.res.nunits == 0) return;
+  if (p.mode == MPGEMM_MODE_FLOAT) {
+    p.room = p.off_flag = std::min(p.off_flag, (bytes - 256) & ~size_t(255));
+    if (bytes < p.slices_total + 256) p.res.nunits = 0;
+  } else {
+    p.room = std::min(p.room, bytes);
+  }
+  if (p.res.nunits == 0) return;
+  const ResidueFit fit = residue_fit(p.res, p.res_cfg, m, n, k, p.room - p.off_arena);
+  if (fit == ResidueFit::kNone || (fit == ResidueFit::kBlocks && !c_apart)) p.res.nunits = 0;
 }
 
 // Workspaces kept between calls on the default stream.  A call takes one for the
@@ -457,6 +495,7 @@ KeptWorkspaces g_kept;
 // allocation on the stream that is released (to the device's pool) at its end.
 struct Workspace {
   char *base = nullptr;
+  size_t bytes = 0;
   bool owned = false;
   hipStream_t st = nullptr;
   int dev = 0;
@@ -482,11 +521,15 @@ void keep_pool_memory(int dev) {
   g_pool_ready[dev] = true;
 }
 
-int acquire(Workspace &ws, size_t bytes, hipStream_t st) {
+// `bytes`, or, where they cannot be had, as much of them as there is but no less
+// than `least`.
+int acquire(Workspace &ws, size_t bytes, size_t least, hipStream_t st) {
   ws.st = st;
+  ws.bytes = bytes;
   if (g_opt.ws) {
-    if (g_opt.ws_bytes < bytes) return MPGEMM_ERR_WORKSPACE;
+    if (g_opt.ws_bytes < least) return MPGEMM_ERR_WORKSPACE;
     ws.base = static_cast<char *>(g_opt.ws);
+    ws.bytes = std::min(bytes, g_opt.ws_bytes);
     return 0;
   }
   int dev = 0;
@@ -497,19 +540,28 @@ int acquire(Workspace &ws, size_t bytes, hipStream_t st) {
     return 0;
   }
   void *p = nullptr;
-  if (hipMallocAsync(&p, bytes > 0 ? bytes : 256, st) != hipSuccess || !p) {
+  auto allocate = [&](size_t size) {
+    if (hipMallocAsync(&p, size > 0 ? size : 256, st) == hipSuccess && p) return true;
     (void)hipGetLastError();
+    p = nullptr;
+    return false;
+  };
+  if (!allocate(bytes)) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
-        !g_kept.give_back(dev) || hipMallocAsync(&p, bytes > 0 ? bytes : 256, st) != hipSuccess || !p) {
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
       (void)hipGetLastError();
       return MPGEMM_ERR_WORKSPACE;
+    }
+    if (!g_kept.give_back(dev) || !allocate(bytes)) {
+      if (least >= bytes || !allocate(least)) return MPGEMM_ERR_WORKSPACE;
+      ws.bytes = least;
     }
   }
   ws.base = static_cast<char *>(p);
   ws.owned = true;
   return 0;
 }
+int acquire(Workspace &ws, size_t bytes, hipStream_t st) { return acquire(ws, bytes, bytes, st); }
 
 // Called on entry by every call that launches work.  It also clears the
 // thread's last-error slot: the launches below report their own failures
@@ -613,11 +665,10 @@ hipError_t gemm_launch(const Plan &p, char *base, int m, int n, int k, T *Cout, 
   return hipErrorInvalidValue;
 }
 
-// The product by residues on the workspace at `base` (`bytes` of it), laid out
-// by plan p; `between` is recorded after the split.  flag: FLOAT form, a device
+// The product by residues on the workspace at `base`, laid out by plan p; `between` is recorded after the split.  flag: FLOAT form, a device
 // word outside that workspace's shared part.
 template <typename T, int C>
-hipError_t residue_launch(const Plan &p, char *base, size_t bytes, int *flag, const SplitOperand<T> &a,
+hipError_t residue_launch(const Plan &p, char *base, int *flag, const SplitOperand<T> &a,
                           const SplitOperand<T> &b, int m, int n, int k, T *Cm, int ldc, hipEvent_t between,
                           hipStream_t st) {
   ResidueCall rc{};
@@ -643,18 +694,18 @@ hipError_t residue_launch(const Plan &p, char *base, size_t bytes, int *flag, co
   rc.clear_words = (int64_t)(p.res_clear_bytes / 4);
   rc.flag = rc.float_form ? flag : nullptr;
   rc.arena = base + p.off_arena;
-  rc.arena_bytes = bytes - p.off_arena;
+  rc.arena_bytes = p.room - p.off_arena;
   return launch_residue<T, C>(rc, a, b, Cm, between, st);
 }
 
-// The launch sequence of one product on the workspace at `base` (`bytes` of
-// it), laid out by plan p: the residues where the plan has them, and the slices
+// The launch sequence of one product on the workspace at `base`, laid out by plan
+// p (p.room of it for the residues): the residues where the plan has them, and the slices
 // (split, then the fused slice products and accumulation) otherwise, or in the
 // FLOAT form where the residue split finds on the device that it must have them.
 // With `profile`, records the thread's stage-timing events if they are enabled.
 // With `keep_slices` the slices and their exponents are formed in any case.
 template <typename T, int C>
-hipError_t launch_product(const Plan &p, char *base, size_t bytes, int *flag, int m, int n, int k, const T *A, int lda,
+hipError_t launch_product(const Plan &p, char *base, int *flag, int m, int n, int k, const T *A, int lda,
                           const T *B, int ldb, T *Cm, int ldc, bool profile, bool keep_slices, hipStream_t st) {
   SplitOperand<T> a = operand_a(A, m, k, lda, p, base), b = operand_b(B, k, n, ldb, p, base);
   const bool prof = profile && g_prof.on;
@@ -666,7 +717,7 @@ hipError_t launch_product(const Plan &p, char *base, size_t bytes, int *flag, in
   hipError_t e = hipSuccess;
   const bool residues = C <= 4 && p.res.nunits > 0;
   if constexpr (C <= 4) {
-    if (residues) e = residue_launch<T, C>(p, base, bytes, flag, a, b, m, n, k, Cm, ldc, ev[1], st);
+    if (residues) e = residue_launch<T, C>(p, base, flag, a, b, m, n, k, Cm, ldc, ev[1], st);
   }
   if (!residues || p.mode == MPGEMM_MODE_FLOAT) {
     const int *run_if = residues ? flag : nullptr;
@@ -686,12 +737,23 @@ hipError_t launch_product(const Plan &p, char *base, size_t bytes, int *flag, in
   return e;
 }
 
-// launch_product on a workspace of p.total bytes.
+// launch_product with the flag in the workspace.
 template <typename T, int C>
 hipError_t launch_product(const Plan &p, char *base, int m, int n, int k, const T *A, int lda, const T *B, int ldb,
                           T *Cm, int ldc, bool profile, bool keep_slices, hipStream_t st) {
-  return launch_product<T, C>(p, base, p.off_flag > 0 ? p.off_flag : p.total, reinterpret_cast<int *>(base + p.off_flag),
-                              m, n, k, A, lda, B, ldb, Cm, ldc, profile, keep_slices, st);
+  return launch_product<T, C>(p, base, reinterpret_cast<int *>(base + p.off_flag), m, n, k, A, lda, B, ldb, Cm, ldc,
+                              profile, keep_slices, st);
+}
+
+// Takes a workspace for one product of plan p and fits the plan to it.
+template <typename T, int C>
+int acquire_product(Workspace &ws, Plan &p, int m, int n, int k, const T *A, int lda, const T *B, int ldb, const T *Cm,
+                    int ldc, hipStream_t st) {
+  const int s = acquire(ws, p.total, p.slices_total, st);
+  if (s) return s;
+  const int64_t cc = (int64_t)C * ldc * n;
+  fit_plan(p, ws.bytes, m, n, k, apart(A, (int64_t)C * lda * k, Cm, cc) && apart(B, (int64_t)C * ldb * n, Cm, cc));
+  return 0;
 }
 
 // One product in the given form with D slices (arguments already validated).
@@ -702,9 +764,9 @@ int run_with(int fmt, int mode, int D, bool automatic, int m, int n, int k, cons
   g_opt.last_slices = D;
   if (m == 0 || n == 0) return 0;
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(T), C, m, n, ldc, (int64_t)ldc * n, st));
-  const Plan p = make_plan(fmt, mode, m, n, k, D, automatic, C);
+  Plan p = make_plan(fmt, mode, m, n, k, D, automatic, C);
   Workspace ws;
-  if ((s = acquire(ws, p.total, st))) return s;
+  if ((s = acquire_product<T, C>(ws, p, m, n, k, A, lda, B, ldb, Cm, ldc, st))) return s;
   return hip_status(launch_product<T, C>(p, ws.base, m, n, k, A, lda, B, ldb, Cm, ldc, true, false, st));
 }
 
@@ -913,14 +975,17 @@ int run_ds(int m, int n, int k, const double *Ahi, const float *Alo, int lda, co
     if (e == hipSuccess) e = launch_zero_matrix(Clo, 4, 1, m, n, ldc, 0, st);
     return hip_status(e);
   }
-  const Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
+  Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
   const size_t a_bytes = align256((size_t)2 * m * k * 8), b_bytes = align256((size_t)2 * k * n * 8);
   const size_t c_bytes = align256((size_t)2 * m * n * 8);
   Workspace ws;
-  if ((s = acquire(ws, p.total + a_bytes + b_bytes + c_bytes, st))) return s;
-  double *Add = reinterpret_cast<double *>(ws.base + p.total);
-  double *Bdd = reinterpret_cast<double *>(ws.base + p.total + a_bytes);
-  double *Cdd = reinterpret_cast<double *>(ws.base + p.total + a_bytes + b_bytes);
+  const size_t copies = a_bytes + b_bytes + c_bytes;
+  if ((s = acquire(ws, p.total + copies, p.slices_total + copies, st))) return s;
+  const size_t room = (ws.bytes - copies) & ~size_t(255);
+  fit_plan(p, room, m, n, k, true);
+  double *Add = reinterpret_cast<double *>(ws.base + room);
+  double *Bdd = reinterpret_cast<double *>(ws.base + room + a_bytes);
+  double *Cdd = reinterpret_cast<double *>(ws.base + room + a_bytes + b_bytes);
   hipError_t e = launch_ds_to_dd(m, k, Ahi, Alo, lda, Add, st);
   if (e == hipSuccess) e = launch_ds_to_dd(k, n, Bhi, Blo, ldb, Bdd, st);
   if (e == hipSuccess) e = launch_product<double, 2>(p, ws.base, m, n, k, Add, m, Bdd, k, Cdd, m, true, false, st);
@@ -968,14 +1033,13 @@ int run_dd_noalloc(int m, int n, int k, const double *A, int lda, const double *
   if (k == 0) return hip_status(launch_zero_matrix(Cm, sizeof(double), 2, m, n, ldc, (int64_t)ldc * n, st));
   Plan p = make_plan(MPGEMM_DD, mode, m, n, k, D, automatic_slices(MPGEMM_DD, mode));
   if (p.slices_total > kScratchBytes) return MPGEMM_ERR_TOO_LARGE;
-  // The residues may go in blocks of C, the first written before the last is
-  // split: a C that shares memory with an operand takes the slices.
-  auto apart = [&](const double *X, int64_t elements) { return X + elements <= Cm || Cm + 2 * (int64_t)ldc * n <= X; };
-  if (!apart(A, 2 * (int64_t)lda * k) || !apart(B, 2 * (int64_t)ldb * n)) p.res.nunits = 0;
+  const int64_t cc = 2 * (int64_t)ldc * n;
+  p.room = kScratchBytes;
+  p.off_flag = kScratchBytes;  // behind it
+  fit_plan(p, kScratchBytes + 256, m, n, k, apart(A, 2 * (int64_t)lda * k, Cm, cc) && apart(B, 2 * (int64_t)ldb * n, Cm, cc));
   char *base = nullptr;
   if ((s = scratch_of_current_device(&base))) return s;
-  return hip_status(launch_product<double, 2>(p, base, kScratchBytes, reinterpret_cast<int *>(base + kScratchBytes), m, n, k, A,
-                                               lda, B, ldb, Cm, ldc, false, false, st));
+  return hip_status(launch_product<double, 2>(p, base, m, n, k, A, lda, B, ldb, Cm, ldc, false, false, st));
 }
 
 template <typename T, int C>
@@ -1019,7 +1083,7 @@ int debug_split_t(int fmt, int mode, int operand, int rows, int cols, const T *X
   if (rows == 0 || cols == 0) return 0;
   const Plan p = make_plan(fmt, mode, m, n, k, D, false);
   Workspace ws;
-  if ((s = acquire(ws, p.total, st))) return s;
+  if ((s = acquire(ws, p.slices_total, st))) return s;
   SplitOperand<T> a = operand_a(operand == 0 ? X : (const T *)nullptr, m, k, ldx, p, ws.base);
   SplitOperand<T> b = operand_b(operand == 1 ? X : (const T *)nullptr, k, n, ldx, p, ws.base);
   hipError_t e = split_both<T, C>(a, b, p, st);
@@ -1047,7 +1111,7 @@ int debug_products_t(int fmt, int mode, int m, int n, int k, const T *A, int lda
   if (m == 0 || n == 0 || k == 0) return 0;
   const Plan p = make_plan(fmt, mode, m, n, k, D, false, C);
   Workspace ws;
-  if ((s = acquire(ws, p.total, st))) return s;
+  if ((s = acquire(ws, p.slices_total, st))) return s;
   const SplitOperand<T> sa = operand_a(A, m, k, lda, p, ws.base), sb = operand_b(B, k, n, ldb, p, ws.base);
   hipError_t e = split_both<T, C>(sa, sb, p, st);
   const int sel = mode == MPGEMM_MODE_FLOAT ? (a - 1) * D + (b - 1) : a;
@@ -1071,7 +1135,7 @@ int certify_run(int fmt, int mode, int D, bool automatic, int m, int n, int k, c
       e = launch_zero_matrix(Cm, sizeof(T), C, m, n, ldc, (int64_t)ldc * n, st);
     return hip_status(e);
   }
-  const Plan p = make_plan(fmt, mode, m, n, k, D, automatic, C);
+  Plan p = make_plan(fmt, mode, m, n, k, D, automatic, C);
   // |A_0| and |B_0| go into the slice buffers in the binary64 packed layout
   SplitOperand<T> ca{}, cb{};
   ca.nbp = nblocks_padded(m);
@@ -1082,7 +1146,7 @@ int certify_run(int fmt, int mode, int D, bool automatic, int m, int n, int k, c
        (size_t)D * p.nbp * p.kbp * 1024 < (size_t)cb.nbp * cb.kbp * 256 * 8))
     return MPGEMM_ERR_UNSUPPORTED;  // fewer than about 8 digit planes
   Workspace ws;
-  if ((s = acquire(ws, p.total, st))) return s;
+  if ((s = acquire_product<T, C>(ws, p, m, n, k, A, lda, B, ldb, Cm, ldc, st))) return s;
   const SplitOperand<T> a = operand_a(A, m, k, lda, p, ws.base), b = operand_b(B, k, n, ldb, p, ws.base);
   hipError_t e = launch_product<T, C>(p, ws.base, m, n, k, A, lda, B, ldb, Cm, ldc, false, true, st);
   ca = a;

@@ -106,6 +106,11 @@ struct ResidueCall {
 // Tile configuration of one m x n product by residues (cfg > 0 forces one).
 int residue_tile_config(int64_t m, int64_t n, int cfg);
 size_t residue_bytes(const ResiduePlan &p, int cfg, int64_t m, int64_t n, int64_t k);
+// How launch_residue forms a product in an arena of a size: with every operand
+// element read before C is written (whole), in blocks of C one after the other, or
+// not at all.
+enum class ResidueFit { kNone, kBlocks, kWhole };
+ResidueFit residue_fit(const ResiduePlan &p, int cfg, int m, int n, int k, size_t arena);
 template <typename T, int C>
 hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,
                           hipEvent_t between, hipStream_t st);

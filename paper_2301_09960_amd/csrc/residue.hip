@@ -1316,32 +1316,66 @@ size_t residue_bytes(const ResiduePlan &p, int cfg, int64_t m, int64_t n, int64_
   return header_bytes(p) + (size_t)p.nplanes * (size_t)(s.a_plane + s.b_plane + p.nchunks * s.r_plane);
 }
 
+namespace {
+
+// How a product is formed in an arena: whole, with `room` operand planes at a time
+// (all of them where they fit), or, where its result planes alone take more than
+// half of an arena that not everything fits, as two blocks of C of which the first
+// is m x n (m = 0: not even one tile fits).
+struct Pieces {
+  bool whole = true;
+  int room = 0, m = 0, n = 0;
+  Pieces(const ResiduePlan &p, int cfg, int m_, int n_, int k, size_t arena) {
+    const Shape s = shape_of(cfg, m_, n_, k);
+    const size_t result = (size_t)p.nplanes * p.nchunks * s.r_plane;
+    const int64_t left = (int64_t)arena - (int64_t)header_bytes(p) - (int64_t)result;
+    room = (int)std::min<int64_t>(p.nplanes, left < 0 ? 0 : left / (s.a_plane + s.b_plane));
+    if (room == p.nplanes || (2 * result <= arena && room >= 2)) return;
+    whole = false;
+    // halves of the longer side of C, at a tile edge
+    const int longer = std::max(m_, n_), half = (int)(ceil_div(longer, 2 * 256) * 256);
+    if (half >= longer) return;  // one tile
+    m = m_ >= n_ ? half : m_;
+    n = m_ >= n_ ? n_ : half;
+  }
+};
+
+}  // namespace
+
+ResidueFit residue_fit(const ResiduePlan &p, int cfg, int m, int n, int k, size_t arena) {
+  const Pieces piece(p, cfg, m, n, k, arena);
+  if (piece.whole) return ResidueFit::kWhole;
+  if (piece.m == 0) return ResidueFit::kNone;
+  const int m2 = piece.m < m ? m - piece.m : m, n2 = piece.m < m ? n : n - piece.n;
+  return residue_fit(p, cfg, piece.m, piece.n, k, arena) == ResidueFit::kNone ||
+                 residue_fit(p, cfg, m2, n2, k, arena) == ResidueFit::kNone
+             ? ResidueFit::kNone
+             : ResidueFit::kBlocks;
+}
+
 template <typename T, int C>
 hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,
                           hipEvent_t between, bool first, hipStream_t st) {
   const ResiduePlan &p = rc.plan;
   const Shape s = shape_of(rc.cfg, rc.m, rc.n, rc.k);
   // arena: the uploaded descriptors and table, the result planes, then as many
-  // operand planes as fit (all of them, except in a fixed scratch, where a
-  // product whose result planes alone take half of it goes in blocks of C)
+  // operand planes as fit (Pieces)
+  const Pieces piece(p, rc.cfg, rc.m, rc.n, rc.k, rc.arena_bytes);
   const size_t head = header_bytes(p), result = (size_t)p.nplanes * p.nchunks * s.r_plane;
-  const int64_t left = (int64_t)rc.arena_bytes - (int64_t)head - (int64_t)result;
-  const int room = (int)std::min<int64_t>(p.nplanes, left < 0 ? 0 : left / (s.a_plane + s.b_plane));
-  if (room < p.nplanes && (2 * result > rc.arena_bytes || room < 2)) {
-    // halves of the longer side of C, at a tile edge
+  const int room = piece.room;
+  if (!piece.whole) {
+    if (piece.m == 0) return hipErrorInvalidValue;  // does not fit
     ResidueCall lo = rc, hi = rc;
     SplitOperand<T> a2 = a, b2 = b;
     T *C2 = Cout;
-    if (rc.m >= rc.n) {
-      lo.m = (int)(ceil_div(rc.m, 2 * 256) * 256);
-      if (lo.m >= rc.m) return hipErrorInvalidValue;  // one tile: does not fit
+    lo.m = piece.m;
+    lo.n = piece.n;
+    if (lo.m < rc.m) {
       hi.m = rc.m - lo.m;
       hi.exp_a += lo.m;
       a2.X += lo.m * a.sv;
       C2 += lo.m;
     } else {
-      lo.n = (int)(ceil_div(rc.n, 2 * 256) * 256);
-      if (lo.n >= rc.n) return hipErrorInvalidValue;
       hi.n = rc.n - lo.n;
       hi.exp_b += lo.n;
       b2.X += lo.n * b.sv;

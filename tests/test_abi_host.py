@@ -145,6 +145,28 @@ def test_workspace_bytes(L):
     assert mp.workspace_bytes("ts", "float", 65, 1, 33, 1) >= 1 * 128 * 64 * 4 + 1 * 64 * 64 * 4
 
 
+@pytest.mark.parametrize("fmt,mode,m,n,k", [("dd", "float", 65536, 65536, 256), ("qd", "float", 65536, 65536, 256),
+                                            ("qd", "float", 57344, 57344, 4096), ("qd", "float", 32768, 32768, 1024),
+                                            ("td", "float", 1 << 20, 1 << 20, 48), ("ts", "float", 60000, 50000, 64),
+                                            ("dd", "int8", 1, 1, 1 << 20), ("qd", "int8", 3000, 70, 1 << 20),
+                                            ("dd", "int8", 65536, 65536, 64), ("dd", "float", 300, 200, 100)])
+def test_workspace_is_bounded_by_the_slices(L, fmt, mode, m, n, k):
+    """The residue planes grow with m n: a call takes at most 8 GiB for them, or
+    a quarter more than its slices or digits alone need."""
+    import paper_2301_09960_amd as mp
+    D = mp.num_slices(fmt, mode, k)
+    c, w = mp.COMPONENTS[fmt], 4 if fmt == "ts" else 8
+    up = lambda x, t: -(-x // t) * t
+    if mode == "float":  # slices padded to 64 rows and 32 k, residuals, maxima and exponents
+        pm, pn, pk = up(m, 64), up(n, 64), up(k, 32)
+        slices = D * (pm + pn) * pk * w + c * (m + n) * k * w + D * (m + n) * (w + 4)
+    else:  # digits padded to 256 rows and 64 k, 32-bit sums of each diagonal in every k chunk
+        pm, pn, pk = up(m, 256), up(n, 256), up(k, 64)
+        chunks = -(-k // (2 ** 31 // (4096 * D) - 64))  # of 2^31 / (64^2 D) k, the 32-bit sums' range
+        slices = D * (pm + pn) * pk + 4 * D * pm * pn * chunks + (m + n) * 12
+    assert mp.workspace_bytes(fmt, mode, m, n, k) <= max(1.25 * slices, 8 << 30) + (1 << 20)
+
+
 def test_tuning_file_tables(L, tmp_path):
     import paper_2301_09960_amd as mp
     f = tmp_path / "tune.txt"
