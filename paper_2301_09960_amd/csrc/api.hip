@@ -563,6 +563,16 @@ int acquire(Workspace &ws, size_t bytes, size_t least, hipStream_t st) {
 }
 int acquire(Workspace &ws, size_t bytes, hipStream_t st) { return acquire(ws, bytes, bytes, st); }
 
+bool allocate_device(char **p, size_t bytes, int dev) {
+  for (int tries = 0; tries < 2; ++tries) {
+    if (hipMalloc(reinterpret_cast<void **>(p), bytes) == hipSuccess && *p) return true;
+    (void)hipGetLastError();
+    if (tries == 0 && !g_kept.give_back(dev)) break;
+  }
+  *p = nullptr;
+  return false;
+}
+
 // Called on entry by every call that launches work.  It also clears the
 // thread's last-error slot: the launches below report their own failures
 // through hipGetLastError, so an error left there by an earlier, unrelated
@@ -769,6 +779,27 @@ int run_with(int fmt, int mode, int D, bool automatic, int m, int n, int k, cons
   if ((s = acquire_product<T, C>(ws, p, m, n, k, A, lda, B, ldb, Cm, ldc, st))) return s;
   return hip_status(launch_product<T, C>(p, ws.base, m, n, k, A, lda, B, ldb, Cm, ldc, true, false, st));
 }
+
+template <typename T, int C>
+int run_product(int fmt, int mode, int D, bool automatic, int m, int n, int k, const T *A, int lda, const T *B,
+                int ldb, T *Cm, int ldc, hipStream_t st) {
+  void *const attached = g_opt.ws;  // not for the batches, whose stages are timed as one
+  const bool profiled = g_prof.on;
+  g_opt.ws = nullptr;
+  g_prof.on = false;
+  const int s = run_with<T, C>(fmt, mode, D, automatic, m, n, k, A, lda, B, ldb, Cm, ldc, st);
+  g_opt.ws = attached;
+  g_prof.on = profiled;
+  return s;
+}
+template int run_product<double, 2>(int, int, int, bool, int, int, int, const double *, int, const double *, int,
+                                    double *, int, hipStream_t);
+template int run_product<double, 3>(int, int, int, bool, int, int, int, const double *, int, const double *, int,
+                                    double *, int, hipStream_t);
+template int run_product<double, 4>(int, int, int, bool, int, int, int, const double *, int, const double *, int,
+                                    double *, int, hipStream_t);
+template int run_product<float, 3>(int, int, int, bool, int, int, int, const float *, int, const float *, int,
+                                   float *, int, hipStream_t);
 
 // Slice counts chosen from the data (mpgemm_set_num_slices(fmt, FLOAT,
 // MPGEMM_SLICES_DATA)): kMaxPairLim slices are made, the certificate's

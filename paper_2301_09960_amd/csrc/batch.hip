@@ -3,7 +3,9 @@
 //
 // A batch plan (per host thread, device, stream and shape: format, slice
 // form, and every product's m, n, k and D) owns one device workspace holding
-// every product's planes, maxima and exponents, plus
+// every product's maxima and exponents and the planes of the products that are
+// formed at one time (all of them, or run by run where they would take too much:
+// FormatPlan), plus
 //   - the descriptors of all operands and products (rewritten before every
 //     launch: they carry the caller's pointers),
 //   - prefix sums of the split work per operand and the work items of the
@@ -15,7 +17,8 @@
 // maxima, the max-exponent launch and dmax pass launches), clear the work
 // counter, and one persistent GEMM over (product, tile) items.  In the FLOAT form
 // the residue products' slice launches follow, and end at once unless the split
-// flagged a product.  Kernels take the caller's pointers from the descriptors, so
+// flagged a product; the slices take the place of the operands' residue planes, so
+// their split comes behind the residue GEMM.  Kernels take the caller's pointers from the descriptors, so
 // a cached graph is replayed with new pointers after one small host-to-device
 // copy of the descriptors.
 #include <hip/hip_runtime.h>
@@ -109,13 +112,20 @@ struct ResidueBatch {
     int m, n, k, D, cfg, groups = 1;
     ResiduePlan plan;
     int64_t mbp, nbp, kbp;
-    size_t a, b, r, exp_a, exp_b, mu_a, mu_b, st_a, st_b, table;
+    size_t a, b, r;  // planes, counted from `scratch`
+    size_t exp_a, exp_b, mu_a, mu_b, st_a, st_b, table;
+    size_t operand_bytes() const {
+      return align256((size_t)plan.nplanes * mbp * kbp * 1024) + align256((size_t)plan.nplanes * nbp * kbp * 1024);
+    }
+    size_t result_bytes() const { return align256((size_t)plan.nplanes * plan.nchunks * mbp * nbp * 1024); }
   };
   std::vector<Slot> slots;
   int nw = 0, tiles0 = 0, nitems1 = 0, nitems3 = 0;
   int64_t blocks = 0, blocksc = 0;
-  size_t off_planes = 0, planes_bytes = 0, off_static = 0, off_tables = 0, off_items = 0, off_bounds = 0, off_counter = 0,
-         off_zero = 0, zero_bytes = 0;
+  size_t scratch = 0, planes_bytes = 0;  // where the planes' part of the workspace begins; the operands' planes
+  bool shared = false;                   // other runs write to it
+  size_t off_ran = 0;  // FLOAT form: a word set once slices have been written to the operands' planes
+  size_t off_static = 0, off_tables = 0, off_items = 0, off_bounds = 0, off_counter = 0, off_zero = 0, zero_bytes = 0;
   bool float_form = false;
   size_t off_flags = 0;            // FLOAT form: a word set if any product is flagged, then one per product
   std::vector<int> prefix;         // 2 n + 1 max tiles, 2 n + 1 split blocks, n + 1 combine blocks
@@ -126,7 +136,7 @@ struct ResidueBatch {
   int nops() const { return 2 * (int)slots.size(); }
   size_t ops_bytes(size_t elem) const { return (size_t)nops() * elem; }
 
-  void add(int g, int m, int n, int k, int D, const ResiduePlan &plan, int cfg) {
+  static Slot slot(int g, int m, int n, int k, int D, const ResiduePlan &plan, int cfg) {
     Slot s;
     s.g = g;
     s.m = m;
@@ -139,24 +149,36 @@ struct ResidueBatch {
     s.mbp = nblocks8_padded(m, tb);
     s.nbp = nblocks8_padded(n, tb);
     s.kbp = kblocks8_padded(k);
-    slots.push_back(s);
+    return s;
   }
 
-  // Places everything in the workspace (take: bytes -> offset); elem: bytes of a maximum.
+  // The planes, counted from `scratch`: the operands' from 0 on, the results' from
+  // max(their end, after) on.  Returns the end of all.
+  size_t place_planes(size_t after) {
+    size_t o = 0;
+    for (Slot &s : slots) {
+      s.a = o;
+      s.b = o + align256((size_t)s.plan.nplanes * s.mbp * s.kbp * 1024);
+      o += s.operand_bytes();
+    }
+    planes_bytes = o;
+    o = std::max(o, after);
+    for (Slot &s : slots) {
+      s.r = o;
+      o += s.result_bytes();
+    }
+    return o;
+  }
+
+  // Places everything but the planes in the workspace (take: bytes -> offset);
+  // elem: bytes of a maximum.
   template <typename Take>
   void layout(Take take, size_t elem, bool float_slices) {
     float_form = float_slices;
     // products of one combine size together: each size has its launch
     std::stable_sort(slots.begin(), slots.end(), [](const Slot &a, const Slot &b) { return a.plan.nwc < b.plan.nwc; });
     for (Slot &s : slots) nw = std::max(nw, s.plan.nw);
-    off_planes = take(0);
     for (Slot &s : slots) {
-      s.a = take((size_t)s.plan.nplanes * s.mbp * s.kbp * 1024);
-      s.b = take((size_t)s.plan.nplanes * s.nbp * s.kbp * 1024);
-    }
-    planes_bytes = take(0) - off_planes;
-    for (Slot &s : slots) {
-      s.r = take((size_t)s.plan.nplanes * s.plan.nchunks * s.mbp * s.nbp * 1024);
       s.exp_a = take((size_t)s.m * 4);
       s.exp_b = take((size_t)s.n * 4);
     }
@@ -180,7 +202,10 @@ struct ResidueBatch {
       const int64_t kbl = ceil_div((int64_t)s.k, (int64_t)kKBlk8);
       pre0[2 * i + 1] = pre0[2 * i] + tiles64(s.m, s.k);
       pre0[2 * i + 2] = pre0[2 * i + 1] + tiles64(s.n, s.k);
-      preb[2 * i + 1] = preb[2 * i] + (int)(ceil_div((int64_t)s.m, (int64_t)kBlk8) * kbl);
+      // A's blocks cover the padding of k, which has to be zero in one operand (it is
+      // cleared with the plan, and written where something else may lie there since:
+      // ResidueOperand::padded); that of m and n takes part in no element of C
+      preb[2 * i + 1] = preb[2 * i] + (int)(ceil_div((int64_t)s.m, (int64_t)kBlk8) * s.kbp);
       preb[2 * i + 2] = preb[2 * i + 1] + (int)(ceil_div((int64_t)s.n, (int64_t)kBlk8) * kbl);
       // blocks of its combine launch, counted from the launch's first product
       const bool first = i == 0 || slots[i - 1].plan.nwc != s.plan.nwc;
@@ -206,6 +231,7 @@ struct ResidueBatch {
     off_tables = take(tables.size() * 4);
     off_items = take(items.size() * sizeof(int4));
     off_bounds = take(sizeof(bounds));
+    off_ran = take(4);
   }
 
   void make_items() {
@@ -249,18 +275,19 @@ struct ResidueBatch {
       for (const Item &it : *v) items.push_back(make_int4(it.slot, it.tile, it.chunk, it.group));
   }
 
-  // Static device data of a new plan.  The split writes only blocks that hold
-  // elements: the planes' padding is cleared here, once, and stays zero.
+  // Static device data of a new plan.  Planes of zeros in the padding also leave the
+  // matrix cores less to do than what lay there (the clock follows their power).
   bool upload(char *ws) const {
     if (slots.empty()) return true;
-    return hipMemset(ws + off_planes, 0, planes_bytes) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess &&
+    return hipMemset(ws + scratch, 0, planes_bytes) == hipSuccess && hipMemset(ws + off_ran, 0, 4) == hipSuccess &&
+           hipStreamSynchronize(nullptr) == hipSuccess &&
            hipMemcpy(ws + off_static, prefix.data(), prefix.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
            hipMemcpy(ws + off_tables, tables.data(), tables.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
            hipMemcpy(ws + off_items, items.data(), items.size() * sizeof(int4), hipMemcpyHostToDevice) == hipSuccess &&
            hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
   }
 
-  // The launch sequence in two parts (descriptors at off_ops, off_descs of the workspace).
+  // The launch sequence in three parts (descriptors at off_ops, off_descs of the workspace).
   template <typename T, int C>
   hipError_t launch_split(char *ws, size_t off_ops, hipStream_t st) const {
     if (slots.empty()) return hipSuccess;
@@ -272,15 +299,19 @@ struct ResidueBatch {
     if (e == hipSuccess) e = launch_residue_split_batched<T, C>(nw, ops, preb, 2 * n, (int)blocks, st);
     return e;
   }
-  template <typename T, int C>
-  hipError_t launch_products(char *ws, size_t off_descs, hipStream_t st) const {
+  hipError_t launch_gemm(char *ws, size_t off_descs, hipStream_t st) const {
     if (slots.empty()) return hipSuccess;
+    return launch_gemm_residue_batched(reinterpret_cast<const ResidueDesc *>(ws + off_descs),
+                                       reinterpret_cast<const int4 *>(ws + off_items), nitems1, nitems3,
+                                       reinterpret_cast<const int *>(ws + off_bounds),
+                                       reinterpret_cast<int *>(ws + off_counter), st);
+  }
+  template <typename T, int C>
+  hipError_t launch_combine(char *ws, size_t off_descs, hipStream_t st) const {
     const auto *descs = reinterpret_cast<const ResidueDesc *>(ws + off_descs);
     const int n = (int)slots.size();
     const int *prec = reinterpret_cast<const int *>(ws + off_static) + 4 * n + 2;
-    hipError_t e = launch_gemm_residue_batched(descs, reinterpret_cast<const int4 *>(ws + off_items), nitems1, nitems3,
-                                               reinterpret_cast<const int *>(ws + off_bounds),
-                                               reinterpret_cast<int *>(ws + off_counter), st);
+    hipError_t e = hipSuccess;
     for (int i = 0; i < n && e == hipSuccess;) {
       int j = i;
       int64_t sum = 0;
@@ -321,19 +352,20 @@ struct ResidueBatch {
           o.any = reinterpret_cast<int *>(ws + off_flags);
           o.flag = o.any + i + 1;
         }
-        o.planes = reinterpret_cast<int8_t *>(ws + (side == 0 ? s.a : s.b));
+        o.planes = reinterpret_cast<int8_t *>(ws + scratch + (side == 0 ? s.a : s.b));
         o.nbp = side == 0 ? s.mbp : s.nbp;
         o.kbp = s.kbp;
         o.mu = ws + (side == 0 ? s.mu_a : s.mu_b);
         o.exps = reinterpret_cast<int *>(ws + (side == 0 ? s.exp_a : s.exp_b));
         o.nunits = s.plan.nunits;
         o.nsq = s.plan.nsq;
+        o.padded = shared ? nullptr : reinterpret_cast<const int *>(ws + off_ran);
         ops[2 * i + side] = o;
       }
       ResidueDesc d{};
-      d.A = reinterpret_cast<const int8_t *>(ws + s.a);
-      d.B = reinterpret_cast<const int8_t *>(ws + s.b);
-      d.R = reinterpret_cast<int8_t *>(ws + s.r);
+      d.A = reinterpret_cast<const int8_t *>(ws + scratch + s.a);
+      d.B = reinterpret_cast<const int8_t *>(ws + scratch + s.b);
+      d.R = reinterpret_cast<int8_t *>(ws + scratch + s.r);
       d.table = reinterpret_cast<const uint32_t *>(tab) + s.table;
       d.EA = reinterpret_cast<const int *>(ws + s.exp_a);
       d.EB = reinterpret_cast<const int *>(ws + s.exp_b);
@@ -373,13 +405,16 @@ struct PlainBatch {
     int g;  // product of the batch
     int m, n, k, D, rho;
     int64_t mbp, nbp, kbp;
-    size_t resid_a, resid_b, pack_a, pack_b, mu_a, mu_b, exp_a, exp_b;
+    size_t resid_a, resid_b, pack_a, pack_b;  // counted from `scratch`
+    size_t mu_a, mu_b, exp_a, exp_b;
     bool fused_a, fused_b;  // operand split by the fused kernel (no residual)
     size_t flag;            // offset of its condition word (SIZE_MAX: always formed)
   };
   std::vector<Slot> slots;
+  size_t scratch = 0, scratch_bytes = 0;  // of the residuals and slices
   size_t off_static = 0, off_items = 0, off_bounds = 0, off_counter = 0, off_mu = 0, mu_bytes = 0;
   size_t off_any = SIZE_MAX;  // condition word of all launches
+  size_t off_ran = SIZE_MAX;  // set by launches that run
   int tiles0 = 0, tilesp = 0, stripsf = 0, dpass = 0;
   int fused_nt = 512;  // threads of the fused-split workgroups
   std::vector<int> prefix;  // 2 n + 1 max tiles, 2 n + 1 pass tiles, 2 n + 1 fused strips
@@ -389,7 +424,7 @@ struct PlainBatch {
   size_t ops_bytes() const { return 2 * slots.size() * sizeof(SplitOperand<T>); }
   size_t stage_bytes() const { return ops_bytes() + slots.size() * sizeof(PlainGemmDesc); }
 
-  void add(int g, int m, int n, int k, int D) {
+  static Slot slot(int g, int m, int n, int k, int D) {
     Slot s{};
     s.g = g;
     s.m = m;
@@ -401,12 +436,23 @@ struct PlainBatch {
     s.nbp = nblocks_padded(n);
     s.kbp = kblocks_padded(k);
     s.flag = SIZE_MAX;
-    slots.push_back(s);
+    return s;
+  }
+  // Bytes of its slices, and of its residuals where the fused kernel does not split it.
+  static size_t scratch_of(const Slot &s, int split_kernel) {
+    const bool fused = split_kernel == 0 && fused_threads<T, C>(s.kbp * kKBlk) > 0;
+    return (size_t)s.D * (s.mbp + s.nbp) * s.kbp * 256 * sizeof(T) +
+           (fused || s.D <= 1 ? 0 : (size_t)C * (s.m + s.n) * s.k * sizeof(T));
   }
 
   template <typename Take>
   void layout(Take take, int split_kernel) {
     const size_t w = sizeof(T);
+    auto take_scratch = [&](size_t bytes) {
+      const size_t at = scratch_bytes;
+      scratch_bytes += align256(bytes);
+      return at;
+    };
     // one fused-split launch: 512-thread workgroups when every product's vectors
     // allow them, else 1024
     for (const Slot &s : slots)
@@ -414,10 +460,10 @@ struct PlainBatch {
     for (Slot &s : slots) {
       s.fused_a = split_kernel == 0 && fused_strips<T, C>(OperandShape{s.kbp, s.mbp, s.m}, fused_nt) >= 0;
       s.fused_b = split_kernel == 0 && fused_strips<T, C>(OperandShape{s.kbp, s.nbp, s.n}, fused_nt) >= 0;
-      s.resid_a = take(s.D > 1 && !s.fused_a ? (size_t)C * s.m * s.k * w : 0);
-      s.resid_b = take(s.D > 1 && !s.fused_b ? (size_t)C * s.k * s.n * w : 0);
-      s.pack_a = take((size_t)s.D * s.mbp * s.kbp * 256 * w);
-      s.pack_b = take((size_t)s.D * s.nbp * s.kbp * 256 * w);
+      s.resid_a = take_scratch(s.D > 1 && !s.fused_a ? (size_t)C * s.m * s.k * w : 0);
+      s.resid_b = take_scratch(s.D > 1 && !s.fused_b ? (size_t)C * s.k * s.n * w : 0);
+      s.pack_a = take_scratch((size_t)s.D * s.mbp * s.kbp * 256 * w);
+      s.pack_b = take_scratch((size_t)s.D * s.nbp * s.kbp * 256 * w);
       s.exp_a = take((size_t)s.D * s.m * 4);
       s.exp_b = take((size_t)s.D * s.n * 4);
     }
@@ -501,7 +547,8 @@ struct PlainBatch {
                                           reinterpret_cast<const int2 *>(ws + off_items),
                                           reinterpret_cast<const int *>(ws + off_bounds),
                                           reinterpret_cast<int *>(ws + off_counter),
-                                          std::min((int)items.size(), kPersistentGrid), gemm_layout, any, st);
+                                          std::min((int)items.size(), kPersistentGrid), gemm_layout, any,
+                                          off_ran == SIZE_MAX ? nullptr : reinterpret_cast<int *>(ws + off_ran), st);
     return e;
   }
 
@@ -523,8 +570,8 @@ struct PlainBatch {
         o.nvec = side == 0 ? s.m : s.n;
         o.len = s.k;
         o.orient = side;
-        o.resid = reinterpret_cast<T *>(ws + (side == 0 ? s.resid_a : s.resid_b));
-        o.packed = ws + (side == 0 ? s.pack_a : s.pack_b);
+        o.resid = reinterpret_cast<T *>(ws + scratch + (side == 0 ? s.resid_a : s.resid_b));
+        o.packed = ws + scratch + (side == 0 ? s.pack_a : s.pack_b);
         o.nbp = side == 0 ? s.mbp : s.nbp;
         o.kbp = s.kbp;
         o.mu = ws + (side == 0 ? s.mu_a : s.mu_b);
@@ -536,8 +583,8 @@ struct PlainBatch {
         ops[2 * i + side] = o;
       }
       PlainGemmDesc d{};
-      d.Apk = ws + s.pack_a;
-      d.Bpk = ws + s.pack_b;
+      d.Apk = ws + scratch + s.pack_a;
+      d.Bpk = ws + scratch + s.pack_b;
       d.mbp = s.mbp;
       d.nbp = s.nbp;
       d.kbp = s.kbp;
@@ -559,7 +606,9 @@ struct BatchPlan {
   bool automatic = true;  // slice counts chosen by the library
   hipStream_t stream = nullptr;
   std::vector<int> m, n, k, D;
-  ResidueBatch res;  // the products formed by residues
+  bool any_order = false;   // every operand is read before the first C is written
+  bool needs_apart = false; // built for C's apart from all operands (any_order = false, and it makes use of it)
+  std::vector<int> alone;   // products formed by a call of their own
   bool empty = true;
   char *ws = nullptr;
   size_t off_desc = 0, desc_bytes = 0, total = 0;
@@ -598,77 +647,151 @@ BatchCache &cache() {
   return *g_batch;
 }
 
-// A plan of one format: the products by slices, by residues, and, in the FLOAT
-// form, the residue products again by slices where the split flagged them.
+// A plan of one format: the products by slices, and runs of products by residues
+// with, in the FLOAT form, their slices where the residue split flags them.  The
+// runs come one after the other and share the workspace of their planes: one run
+// holds all products unless their planes exceed residue_room.  A product whose planes
+// alone do so is formed by a call of its own.  Both write some C before the last
+// operand is read; with any_order (C's that share memory with operands) FLOAT
+// products that do not fit in one run go by slices, INT8 ones in one run all the same.
 template <typename T, int C>
 struct FormatPlan : BatchPlan {
-  PlainBatch<T, C> plain, fallback;
-  size_t off_plain = 0, off_fallback = 0, off_ops = 0, off_res = 0;  // descriptors, from off_desc
+  struct Run {
+    ResidueBatch res;
+    PlainBatch<T, C> fallback;
+    size_t off_fallback = 0, off_ops = 0, off_res = 0;  // descriptors, from off_desc
+  };
+  PlainBatch<T, C> plain;
+  std::vector<Run> runs;
+
+  // Bytes of the digits and sums that an INT8 product took before it had residues.
+  static size_t digit_bytes(int64_t m, int64_t n, int64_t k, int D, int cfg) {
+    const int tb = int8_tile_blocks(cfg);
+    const int64_t mbp = nblocks8_padded(m, tb), nbp = nblocks8_padded(n, tb), kbp = kblocks8_padded(k);
+    return (size_t)D * 1024 * ((mbp + nbp) * kbp + 4 * ceil_div(kbp, (int64_t)int8_kblocks_per_chunk(D)) * mbp * nbp);
+  }
+
+  // Deals the products to `plain`, `runs` and `alone`.
+  int deal() {
+    const int count = (int)m.size();
+    const bool slices = mode == MPGEMM_MODE_FLOAT;
+    std::vector<ResidueBatch::Slot> res;
+    size_t least = 0, operands = 0, packed = 0, results = 0;  // of the slices or digits; of the residues
+    for (int g = 0; g < count; ++g) {
+      if (m[g] <= 0 || n[g] <= 0 || k[g] <= 0) continue;
+      const auto ps = PlainBatch<T, C>::slot(g, m[g], n[g], k[g], D[g]);
+      const int cfg = batch_int8_cfg(m[g], n[g], int8_tile);
+      ResiduePlan rp;
+      if (!slices) {
+        if (!residue_plan(7 * D[g] - 1, k[g], rp)) return MPGEMM_ERR_TOO_LARGE;  // none: D <= 40, k <= 2^20
+        least += digit_bytes(m[g], n[g], k[g], D[g], cfg);
+      } else {
+        const size_t own = PlainBatch<T, C>::scratch_of(ps, split_kernel);
+        least += own;
+        if (!automatic || last_slice != 0 || !float_residue_plan(fmt, D[g], k[g], rp)) {
+          plain.slots.push_back(ps);
+          continue;
+        }
+        packed += own;
+      }
+      res.push_back(ResidueBatch::slot(g, m[g], n[g], k[g], D[g], rp, cfg));
+      operands += res.back().operand_bytes();
+      results += res.back().result_bytes();
+    }
+    const size_t all = std::max(operands, packed) + results, room = residue_room(all, least);
+    const bool fits = all <= room;
+    if (any_order && !fits && slices) {
+      for (const auto &s : res) plain.slots.push_back(PlainBatch<T, C>::slot(s.g, s.m, s.n, s.k, s.D));
+      return 0;
+    }
+    size_t ro = 0, rp = 0, rr = 0;  // of the run being filled
+    for (const auto &s : res) {
+      const auto ps = PlainBatch<T, C>::slot(s.g, s.m, s.n, s.k, s.D);
+      const size_t o = s.operand_bytes(), r = s.result_bytes(),
+                   q = slices ? PlainBatch<T, C>::scratch_of(ps, split_kernel) : 0;
+      if (!fits && !any_order) {
+        if (std::max(o, q) + r > room) {
+          alone.push_back(s.g);
+          continue;
+        }
+        if (!runs.empty() && std::max(ro + o, rp + q) + rr + r > room) runs.emplace_back(), ro = rp = rr = 0;
+      }
+      if (runs.empty()) runs.emplace_back();
+      runs.back().res.slots.push_back(s);
+      if (slices) runs.back().fallback.slots.push_back(ps);
+      ro += o;
+      rp += q;
+      rr += r;
+    }
+    needs_apart = runs.size() > 1 || !alone.empty();
+    return 0;
+  }
 
   int build() {
-    const int count = (int)m.size();
+    const int s = deal();
+    if (s) return s;
+    empty = plain.slots.empty() && runs.empty();
     size_t o = 0;
     auto take = [&](size_t bytes) {
       const size_t at = o;
       o += align256(bytes);
       return at;
     };
-    for (int g = 0; g < count; ++g) {
-      if (m[g] <= 0 || n[g] <= 0 || k[g] <= 0) continue;
-      empty = false;
-      ResiduePlan rp;
-      if (mode == MPGEMM_MODE_INT8) {
-        if (!residue_plan(7 * D[g] - 1, k[g], rp)) return MPGEMM_ERR_TOO_LARGE;  // none: D <= 40, k <= 2^20
-      } else if (!automatic || last_slice != 0 || !float_residue_plan(fmt, D[g], k[g], rp)) {
-        plain.add(g, m[g], n[g], k[g], D[g]);
-        continue;
-      } else {
-        fallback.add(g, m[g], n[g], k[g], D[g]);
-      }
-      res.add(g, m[g], n[g], k[g], D[g], rp, batch_int8_cfg(m[g], n[g], int8_tile));
-    }
     plain.layout(take, split_kernel);
-    fallback.layout(take, split_kernel);
-    res.layout(take, sizeof(T), mode == MPGEMM_MODE_FLOAT);
-    if (res.blocks > 0x7fffffffLL || res.blocksc > 0x7fffffffLL) return MPGEMM_ERR_TOO_LARGE;
-    for (size_t i = 0; i < res.slots.size(); ++i)
-      for (auto &f : fallback.slots)
-        if (f.g == res.slots[i].g) f.flag = res.off_flags + 4 * (i + 1);
-    fallback.off_any = res.off_flags;
+    size_t planes = 0;
+    for (Run &r : runs) {
+      r.fallback.layout(take, split_kernel);
+      r.res.layout(take, sizeof(T), mode == MPGEMM_MODE_FLOAT);
+      if (r.res.blocks > 0x7fffffffLL || r.res.blocksc > 0x7fffffffLL) return MPGEMM_ERR_TOO_LARGE;
+      planes = std::max(planes, r.res.place_planes(r.fallback.scratch_bytes));
+      for (size_t i = 0; i < r.res.slots.size(); ++i)
+        for (auto &f : r.fallback.slots)
+          if (f.g == r.res.slots[i].g) f.flag = r.res.off_flags + 4 * (i + 1);
+      r.fallback.off_any = r.res.off_flags;
+      r.fallback.off_ran = r.res.off_ran;
+      r.res.shared = runs.size() > 1;
+    }
     off_desc = take(0);
-    off_plain = 0;
-    off_fallback = off_plain + plain.stage_bytes();
-    off_ops = off_fallback + fallback.stage_bytes();
-    off_res = off_ops + res.ops_bytes(sizeof(ResidueOperand<T>));
-    desc_bytes = off_res + res.slots.size() * sizeof(ResidueDesc);
+    desc_bytes = plain.stage_bytes();
+    for (Run &r : runs) {
+      r.off_fallback = desc_bytes;
+      r.off_ops = r.off_fallback + r.fallback.stage_bytes();
+      r.off_res = r.off_ops + r.res.ops_bytes(sizeof(ResidueOperand<T>));
+      desc_bytes = r.off_res + r.res.slots.size() * sizeof(ResidueDesc);
+    }
     take(desc_bytes);
+    plain.scratch = take(plain.scratch_bytes);
+    const size_t scratch = take(planes);
+    for (Run &r : runs) r.fallback.scratch = r.res.scratch = scratch;
     total = o;
 
-    if (hipMalloc(&ws, total > 0 ? total : 256) != hipSuccess) {
-      (void)hipGetLastError();
-      ws = nullptr;
-      return MPGEMM_ERR_WORKSPACE;
-    }
+    if (!allocate_device(&ws, total > 0 ? total : 256, device)) return MPGEMM_ERR_WORKSPACE;
     if (hipHostMalloc(&stage, desc_bytes > 0 ? desc_bytes : 64, hipHostMallocDefault) != hipSuccess) {
       (void)hipGetLastError();
       stage = nullptr;
       return MPGEMM_ERR_WORKSPACE;
     }
     if (hipEventCreateWithFlags(&stage_done, hipEventDisableTiming) != hipSuccess) return MPGEMM_ERR_HIP;
-    if (!plain.upload(ws) || !fallback.upload(ws) || !res.upload(ws)) return MPGEMM_ERR_HIP;
+    if (!plain.upload(ws)) return MPGEMM_ERR_HIP;
+    for (const Run &r : runs)
+      if (!r.fallback.upload(ws) || !r.res.upload(ws)) return MPGEMM_ERR_HIP;
 
     // capture the launch sequence on a private stream
     BatchCache &bc = cache();
     hipStream_t &cs = bc.capture[device & 63];
     if (!cs && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) return MPGEMM_ERR_HIP;
     if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) return MPGEMM_ERR_HIP;
-    // every operand is read before the first C is written: C may be an operand
-    hipError_t e = plain.launch_split(ws, off_desc + off_plain, cs);
-    if (e == hipSuccess) e = res.template launch_split<T, C>(ws, off_desc + off_ops, cs);
-    if (e == hipSuccess) e = fallback.launch_split(ws, off_desc + off_fallback, cs);
-    if (e == hipSuccess) e = plain.launch_products(ws, off_desc + off_plain, layout, cs);
-    if (e == hipSuccess) e = res.template launch_products<T, C>(ws, off_desc + off_res, cs);
-    if (e == hipSuccess) e = fallback.launch_products(ws, off_desc + off_fallback, layout, cs);
+    // with one run every operand is read before the first C is written: C may be an operand
+    hipError_t e = plain.launch_split(ws, off_desc, cs);
+    for (size_t i = 0; i < runs.size(); ++i) {
+      const Run &r = runs[i];
+      if (e == hipSuccess) e = r.res.template launch_split<T, C>(ws, off_desc + r.off_ops, cs);
+      if (e == hipSuccess) e = r.res.launch_gemm(ws, off_desc + r.off_res, cs);
+      if (e == hipSuccess) e = r.fallback.launch_split(ws, off_desc + r.off_fallback, cs);
+      if (e == hipSuccess) e = r.res.template launch_combine<T, C>(ws, off_desc + r.off_res, cs);
+      if (e == hipSuccess) e = r.fallback.launch_products(ws, off_desc + r.off_fallback, layout, cs);
+    }
+    if (e == hipSuccess) e = plain.launch_products(ws, off_desc, layout, cs);
     hipGraph_t captured = nullptr;
     const hipError_t e2 = hipStreamEndCapture(cs, &captured);
     if (e != hipSuccess || e2 != hipSuccess || !captured) {
@@ -687,12 +810,36 @@ struct FormatPlan : BatchPlan {
   // Descriptors carrying this call's pointers, into the pinned stage.
   void write(const T *const *A, const int *lda, const T *const *B, const int *ldb, T *const *Cm, const int *ldc) {
     char *to = static_cast<char *>(stage);
-    plain.write(ws, to + off_plain, last_slice, A, lda, B, ldb, Cm, ldc);
-    fallback.write(ws, to + off_fallback, last_slice, A, lda, B, ldb, Cm, ldc);
-    res.write<T>(ws, reinterpret_cast<ResidueOperand<T> *>(to + off_ops), reinterpret_cast<ResidueDesc *>(to + off_res),
-                 A, lda, B, ldb, Cm, ldc);
+    plain.write(ws, to, last_slice, A, lda, B, ldb, Cm, ldc);
+    for (const Run &r : runs) {
+      r.fallback.write(ws, to + r.off_fallback, last_slice, A, lda, B, ldb, Cm, ldc);
+      r.res.template write<T>(ws, reinterpret_cast<ResidueOperand<T> *>(to + r.off_ops),
+                              reinterpret_cast<ResidueDesc *>(to + r.off_res), A, lda, B, ldb, Cm, ldc);
+    }
   }
 };
+
+// Whether no C of the batch shares memory with an operand of it.
+template <typename T, int C>
+bool all_apart(int count, const int *m, const int *n, const int *k, const T *const *A, const int *lda,
+               const T *const *B, const int *ldb, T *const *Cm, const int *ldc) {
+  std::vector<std::pair<const T *, const T *>> ops;  // [begin, end)
+  for (int g = 0; g < count; ++g) {
+    if (m[g] <= 0 || n[g] <= 0 || k[g] <= 0) continue;
+    ops.push_back({A[g], A[g] + (int64_t)C * lda[g] * k[g]});
+    ops.push_back({B[g], B[g] + (int64_t)C * ldb[g] * n[g]});
+  }
+  std::sort(ops.begin(), ops.end());
+  for (size_t i = 1; i < ops.size(); ++i) ops[i].second = std::max(ops[i].second, ops[i - 1].second);
+  for (int g = 0; g < count; ++g) {
+    if (m[g] <= 0 || n[g] <= 0) continue;
+    const T *end = Cm[g] + (int64_t)C * ldc[g] * n[g];
+    // of the operands that begin before C's end, the last end
+    const auto it = std::lower_bound(ops.begin(), ops.end(), std::make_pair(end, (const T *)nullptr));
+    if (it != ops.begin() && (it - 1)->second > Cm[g]) return false;
+  }
+  return true;
+}
 
 template <typename T, int C>
 int run_batched(int fmt, int count, const int *m, const int *n, const int *k, const T *const *A, const int *lda,
@@ -731,17 +878,18 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
 
   BatchCache &bc = cache();
   FormatPlan<T, C> *plan = nullptr;
-  for (BatchPlan *p : bc.plans)
-    if (p->device == dev && p->stream == st && p->fmt == fmt && p->mode == mode && p->layout == layout &&
-        p->int8_tile == int8_tile_override() && p->split_kernel == split_kernel_override() &&
-        p->last_slice == last_slice_option() && p->automatic == automatic &&
-        (int)p->m.size() == count &&
-        std::equal(p->m.begin(), p->m.end(), m) && std::equal(p->n.begin(), p->n.end(), n) &&
-        std::equal(p->k.begin(), p->k.end(), k) && p->D == Ds) {
-      plan = static_cast<FormatPlan<T, C> *>(p);  // the format decides T and C
-      break;
-    }
-  if (!plan) {
+  // The plan of this shape (any_order as in FormatPlan), built if there is none.
+  auto plan_of = [&](bool any_order) -> int {
+    for (BatchPlan *p : bc.plans)
+      if (p->device == dev && p->stream == st && p->fmt == fmt && p->mode == mode && p->layout == layout &&
+          p->int8_tile == int8_tile_override() && p->split_kernel == split_kernel_override() &&
+          p->last_slice == last_slice_option() && p->automatic == automatic && p->any_order == any_order &&
+          (int)p->m.size() == count &&
+          std::equal(p->m.begin(), p->m.end(), m) && std::equal(p->n.begin(), p->n.end(), n) &&
+          std::equal(p->k.begin(), p->k.end(), k) && p->D == Ds) {
+        plan = static_cast<FormatPlan<T, C> *>(p);  // the format decides T and C
+        return 0;
+      }
     if ((int)bc.plans.size() >= kMaxPlans) {
       auto oldest = std::min_element(bc.plans.begin(), bc.plans.end(),
                                      [](const BatchPlan *a, const BatchPlan *b) { return a->last_use < b->last_use; });
@@ -750,29 +898,54 @@ int run_batched(int fmt, int count, const int *m, const int *n, const int *k, co
       delete *oldest;
       bc.plans.erase(oldest);
     }
-    plan = new FormatPlan<T, C>();
-    plan->device = dev;
-    plan->stream = st;
-    plan->fmt = fmt;
-    plan->mode = mode;
-    plan->layout = layout;
-    plan->int8_tile = int8_tile_override();
-    plan->split_kernel = split_kernel_override();
-    plan->last_slice = last_slice_option();
-    plan->automatic = automatic;
-    plan->m.assign(m, m + count);
-    plan->n.assign(n, n + count);
-    plan->k.assign(k, k + count);
-    plan->D = Ds;
-    s = plan->build();
-    if (s) {
-      plan->release();
-      delete plan;
-      return s;
+    auto *made = new FormatPlan<T, C>();
+    made->device = dev;
+    made->stream = st;
+    made->fmt = fmt;
+    made->mode = mode;
+    made->layout = layout;
+    made->int8_tile = int8_tile_override();
+    made->split_kernel = split_kernel_override();
+    made->last_slice = last_slice_option();
+    made->automatic = automatic;
+    made->any_order = any_order;
+    made->m.assign(m, m + count);
+    made->n.assign(n, n + count);
+    made->k.assign(k, k + count);
+    made->D = Ds;
+    const int status = made->build();
+    if (status) {
+      made->release();
+      delete made;
+      return status;
     }
-    bc.plans.push_back(plan);
+    bc.plans.push_back(made);
+    plan = made;
+    return 0;
+  };
+  auto apart = [&] { return all_apart<T, C>(count, m, n, k, A, lda, B, ldb, Cm, ldc); };
+  auto product = [&](int g) {
+    return run_product<T, C>(fmt, mode, Ds[g], automatic, m[g], n[g], k[g], A[g], lda[g], B[g], ldb[g], Cm[g], ldc[g],
+                             st);
+  };
+  s = plan_of(false);
+  if (s == MPGEMM_ERR_WORKSPACE) {
+    // the device has not that much left: one product after the other, each in its
+    // own workspace, or all by slices
+    if (apart()) {
+      for (int g = 0; g < count; ++g)
+        if (m[g] > 0 && n[g] > 0 && k[g] > 0 && (s = product(g)) != 0) return s;
+      set_last_slices(*std::max_element(Ds.begin(), Ds.end()));
+      return 0;
+    }
+    s = plan_of(true);
   }
+  if (s == 0 && plan->needs_apart && !apart()) s = plan_of(true);
+  if (s) return s;
   plan->last_use = ++bc.clock;
+  for (int g : plan->alone)
+    if ((s = product(g)) != 0) return s;
+  if (!plan->alone.empty()) set_last_slices(*std::max_element(Ds.begin(), Ds.end()));
   if (plan->empty) return 0;
 
   // the stage may still feed the previous launch's descriptor copy

@@ -472,10 +472,11 @@ __global__ __launch_bounds__(64 * Layout<LAYOUT>::WM * Layout<LAYOUT>::WN, waves
 template <typename T, int C, int LAYOUT>
 __global__ __launch_bounds__(64 * Layout<LAYOUT>::WM * Layout<LAYOUT>::WN, waves_of(LAYOUT, C, (int)sizeof(T))) void k_gemm_plain_batched(
     const PlainGemmDesc *__restrict__ descs, const int2 *__restrict__ items, const int *__restrict__ bounds,
-    int *__restrict__ counters, const int *__restrict__ run_if) {
+    int *__restrict__ counters, const int *__restrict__ run_if, int *__restrict__ ran) {
   __shared__ __attribute__((aligned(16))) T lds[stages_of<T>()][stage_elems<T>()];
   __shared__ int next;
   if (!runs(run_if)) return;
+  if (ran && threadIdx.x == 0) *ran = 1;
   for (;;) {
     if (threadIdx.x == 0) next = take_item(counters, bounds, blockIdx.x);
     __syncthreads();
@@ -547,20 +548,20 @@ hipError_t launch_gemm_plain_pruned(const void *Apk, const void *Bpk, int64_t mb
 
 template <typename T, int C>
 hipError_t launch_gemm_plain_batched(const PlainGemmDesc *descs, const int2 *items, const int *bounds,
-                                     int *counters, int grid, int layout, const int *run_if, hipStream_t st) {
+                                     int *counters, int grid, int layout, const int *run_if, int *ran, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
   switch (layout) {
     case 2:
       hipLaunchKernelGGL((k_gemm_plain_batched<T, C, 2>), dim3((unsigned)grid), dim3(threads_of(2)), 0, st, descs,
-                         items, bounds, counters, run_if);
+                         items, bounds, counters, run_if, ran);
       break;
     case 3:
       hipLaunchKernelGGL((k_gemm_plain_batched<T, C, 3>), dim3((unsigned)grid), dim3(threads_of(3)), 0, st, descs,
-                         items, bounds, counters, run_if);
+                         items, bounds, counters, run_if, ran);
       break;
     default:
       hipLaunchKernelGGL((k_gemm_plain_batched<T, C, 1>), dim3((unsigned)grid), dim3(threads_of(1)), 0, st, descs,
-                         items, bounds, counters, run_if);
+                         items, bounds, counters, run_if, ran);
   }
   return hipGetLastError();
 }
@@ -569,7 +570,7 @@ hipError_t launch_gemm_plain_batched(const PlainGemmDesc *descs, const int2 *ite
   template hipError_t launch_gemm_plain<T, C>(const void *, const void *, int64_t, int64_t, int64_t, int, int, int, \
                                               T *, int, int64_t, int, double *, int, int, const int *, hipStream_t); \
   template hipError_t launch_gemm_plain_batched<T, C>(const PlainGemmDesc *, const int2 *, const int *, int *, int, \
-                                                      int, const int *, hipStream_t);                                            \
+                                                      int, const int *, int *, hipStream_t);                                     \
   template hipError_t launch_gemm_plain_pruned<T, C>(const void *, const void *, int64_t, int64_t, int64_t, int, int, \
                                                      int, T *, int, int64_t, const int8_t *, int, hipStream_t);
 MP_GEMM_INST(double, 2)

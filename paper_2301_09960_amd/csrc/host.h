@@ -35,6 +35,19 @@ int check_device_cached();
 
 int hip_status(hipError_t e);
 
+// What a call takes for residues that need `need` bytes and whose slices (digits)
+// take `slices`.
+size_t residue_room(size_t need, size_t slices);
+
+// hipMalloc on the device (the current one); the workspaces kept between calls are
+// given back where it fails at first.
+bool allocate_device(char **p, size_t bytes, int dev);
+
+// One product as its own call forms it, in a workspace of its own (arguments valid).
+template <typename T, int C>
+int run_product(int fmt, int mode, int D, bool automatic, int m, int n, int k, const T *A, int lda, const T *B,
+                int ldb, T *Cm, int ldc, hipStream_t st);
+
 // Stage-timing hooks (mpgemm_profile_*): events before/after a unit of work.
 bool profiling();
 void profile_mark3(hipEvent_t (&ev)[3]);

@@ -122,10 +122,11 @@ hipError_t launch_split_plain_batched(const SplitOperand<T> *ops, const int *pre
 
 // Persistent GEMM over a batch: items (product index, tile index) in device
 // memory, in kXcds per-XCD lists (bounds: kXcds + 1 running offsets; counters:
-// kXcds words, cleared by the caller; take_item).
+// kXcds words, cleared by the caller; take_item).  ran (may be null) is set where
+// run_if lets it run.
 template <typename T, int C>
 hipError_t launch_gemm_plain_batched(const PlainGemmDesc *descs, const int2 *items, const int *bounds, int *counters,
-                                     int grid, int layout, const int *run_if, hipStream_t st);
+                                     int grid, int layout, const int *run_if, int *ran, hipStream_t st);
 
 // Largest |leading component| of each vector of both operands, as a bit
 // pattern into op.mu (nvec words, cleared first by the caller).

@@ -70,6 +70,7 @@ struct ResidueOperand {
   int *state;            // float_form: one word per vector, cleared first
   int *flag, *any;       // float_form: set when the slices must be used instead (any may be null)
   int nunits, nsq;
+  const int *padded;     // where it is given and 0 the padding of k is zero already
 };
 
 struct ResidueDesc {
@@ -117,9 +118,8 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
 
 
 // Many products at once (batch.hip): descriptors, prefix sums and work items in
-// device memory.  The residue split writes only blocks that hold elements (the
-// planes' padding was cleared once); prefix: running sums of these blocks per
-// operand, and of the 32 x 32 blocks of C per product for the combine.  nw is the
+// device memory.  The residue split writes the blocks that hold elements, and A's
+// padding of k; prefix: running sums of these blocks per operand, and of the 32 x 32 blocks of C per product for the combine.  nw is the
 // batch's largest; a combine launch takes products of one nwc
 // (chunks: some of them have several k chunks).  Items (product, tile, k chunk, unit group) as two
 // sets of kXcds per-XCD lists (take_item): nitems1 of 128 x 128 tiles, then

@@ -318,6 +318,14 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   const int t = threadIdx.x, l = t >> 2, lane = t % 64;
   const int v = (int)(vb * kBlk8) + (l & 31);
   const int p0 = (int)(kb * kKBlk8) + 16 * (l >> 5) + 4 * (t & 3);
+  const int64_t plane = op.nbp * op.kbp * 1024;
+  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
+  if (kb * kKBlk8 >= op.len) {  // padding of k
+    if (part == 0 && (!op.padded || *op.padded != 0))
+      for (int u = 0, n = group_planes(u_first, u_end, op.nsq); u < n; ++u)
+        *reinterpret_cast<uint32_t *>(dst + u * plane) = 0u;
+    return;
+  }
 
   int E = kZeroExp;
   if (v < op.nvec) E = vector_exponent<T>(static_cast<const U *>(op.mu)[v], op.float_form);
@@ -364,7 +372,10 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     inexact = inexact || w[0] != 0u;
     uint32_t W[12];  // signed bytes with the sum W: W + 0x80..80, each byte less 128
     uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits, ties to even
-    if (w[0] - (0x80000000u - C) <= (uint32_t)C) carry = rounds_up<T, C>(xs[j], P, w[0], (w[1] & 1u) != 0u) ? 1u : 0u;
+    const bool near_half = w[0] - (0x80000000u - C) <= (uint32_t)C;
+    if (__builtin_expect(__any(near_half), 0)) {
+      if (near_half) carry = rounds_up<T, C>(xs[j], P, w[0], (w[1] & 1u) != 0u) ? 1u : 0u;
+    }
 #pragma unroll
     for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(w[i + 1], 0u, carry, &carry);
     if (check && kb == 0) {  // the changes of bits but the last ones of the element
@@ -426,8 +437,6 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
     }
   }
 
-  const int64_t plane = op.nbp * op.kbp * 1024;
-  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
   auto product = [&](int rb, int j, bool y) {  // 32 bases of row block rb, 32 elements j
     i16v acc;
 #pragma unroll

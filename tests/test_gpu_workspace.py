@@ -149,3 +149,103 @@ def test_large_result_of_short_rows():
     for i0, i1, j0, j1 in [(0, 700, 0, 800), (7900, 8200, 7900, 8300), (15000, m, 15100, n), (8100, 8300, 100, 5000)]:
         part = mp.gemm("dd", A[:, :, i0:i1].contiguous(), B[:, j0:j1].contiguous())
         assert torch.equal(C[:, j0:j1, i0:i1], part), (i0, j0)
+
+
+def held(f):
+    """Device memory that a call leaves allocated outside torch's allocator."""
+    import torch
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    f()
+    torch.cuda.synchronize()
+    return before - torch.cuda.mem_get_info()[0]
+
+
+def test_batch_plan_shares_planes_and_slices():
+    """The slices behind a FLOAT batch's residues lie in their planes' place: a plan
+    of square products takes little more than the slices alone."""
+    import torch
+    import paper_2301_09960_amd as mp
+    n, count = 1000, 20
+    A, B = operands("dd", n, n, n, 4)
+    Cs = [torch.empty((2, n, n), dtype=torch.float64, device="cuda") for _ in range(count)]
+    mp.batched_cache_clear()
+    D = mp.num_slices("dd", "float", n)
+    sliced = held(lambda: mp.gemm_batched("dd", [A] * count, [B] * count, Cs, slices=D))
+    mp.batched_cache_clear()
+    both = held(lambda: mp.gemm_batched("dd", [A] * count, [B] * count, Cs))
+    mp.batched_cache_clear()
+    print(f"plan: slices {sliced >> 20} MiB, with residues {both >> 20} MiB", flush=True)
+    assert sliced >= count * D * 2 * n * n * 8
+    assert both <= 1.5 * sliced
+
+
+def tall(m, n, k, seed, front=0):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    A = torch.zeros((2, k, m), dtype=torch.float64, device="cuda")
+    B = torch.zeros((2, n, k), dtype=torch.float64, device="cuda")
+    A[0] = torch.rand((k, m), generator=g, device="cuda", dtype=torch.float64) - 0.5
+    B[0] = torch.rand((n, k), generator=g, device="cuda", dtype=torch.float64) - 0.5
+    A[1], B[1] = A[0] * 2.0 ** -55, B[0] * -2.0 ** -56
+    A[:, :front] = 0
+    return A, B
+
+
+@pytest.mark.parametrize("shapes", [[(7000, 6800, 64)] * 6 + [(300, 200, 90), (100, 90, 30)],
+                                    [(300, 200, 90), (15900, 15700, 48), (65, 600, 129)]])
+def test_batch_in_runs(shapes):
+    """Batches whose planes exceed 8 GiB: run by run, a product beyond it alone by
+    its own call, each bit for bit as its single call; with a C in an operand's
+    memory by slices; and the first way again."""
+    import torch
+    import paper_2301_09960_amd as mp
+    mp.batched_cache_clear()
+    pairs = [tall(m, n, k, i) for i, (m, n, k) in enumerate(shapes)]
+    As, Bs = [a for a, _ in pairs], [b for _, b in pairs]
+    Cs = [torch.empty((2, n, m), dtype=torch.float64, device="cuda") for m, n, _ in shapes]
+    for attempt in range(2):
+        for C in Cs:
+            C.fill_(-1.0)
+        used = held(lambda: mp.gemm_batched("dd", As, Bs, Cs))
+        print(f"runs, attempt {attempt}: plan {used >> 20} MiB", flush=True)
+        assert used <= (9 << 30)
+        for i, (a, b) in enumerate(pairs):
+            assert torch.equal(Cs[i], mp.gemm("dd", a, b)), (attempt, shapes[i])
+        if attempt == 0:  # the last C where another product's A lies, which has entries enough
+            host = Cs[-1]
+            last = len(shapes) - 1
+            flat = torch.zeros(max(As[0].numel(), host.numel()), dtype=torch.float64, device="cuda")
+            shared_a = flat[: As[0].numel()].reshape(As[0].shape)
+            shared_a.copy_(As[0])
+            shared_c = flat[: host.numel()].reshape(host.shape)
+            mp.gemm_batched("dd", [shared_a] + As[1:], Bs, Cs[:-1] + [shared_c])
+            torch.cuda.synchronize()
+            for i, (a, b) in enumerate(pairs):
+                got = shared_c if i == last else Cs[i]
+                k = shapes[i][2]
+                assert torch.equal(got, mp.gemm("dd", a, b, slices=mp.num_slices("dd", "float", k))), shapes[i]
+            del flat, shared_a, shared_c
+    mp.batched_cache_clear()
+
+
+def test_batch_padding_after_the_slices():
+    """Odd numbers of k blocks: the slices of a flagged call lie in the planes'
+    padding of k, which the next calls of the plan need to be zero."""
+    import torch
+    import paper_2301_09960_amd as mp
+    shapes = [(70, 90, 90), (33, 40, 150), (200, 130, 65)]
+    plain = [operands("dd", *s, 20 + i) for i, s in enumerate(shapes)]
+    gaps = []
+    for A, B in plain:  # short leading data, and full mantissas 2^-90 below in one row
+        A2 = torch.zeros_like(A)
+        A2[0] = torch.round(A[0] * 256) / 256
+        A2[0, -1, 1] = A[0, -1, 1] * 2.0 ** -90
+        A2[1, -1, 1] = A2[0, -1, 1] * 2.0 ** -54
+        gaps.append((A2, B))
+    mp.batched_cache_clear()
+    for pairs in (gaps, plain, gaps, plain):
+        Cs = mp.gemm_batched("dd", [a for a, _ in pairs], [b for _, b in pairs])
+        torch.cuda.synchronize()
+        for C, (a, b) in zip(Cs, pairs):
+            assert torch.equal(C, mp.gemm("dd", a, b))
