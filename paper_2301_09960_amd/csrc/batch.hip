@@ -384,6 +384,7 @@ struct ResidueBatch {
       d.ldc = ldc[g];
       d.C = Cm[g];
       d.c_stride = (int64_t)ldc[g] * s.n;
+      if (float_form) d.skip = reinterpret_cast<const int *>(ws + off_flags) + i + 1;
       descs[i] = d;
     }
   }

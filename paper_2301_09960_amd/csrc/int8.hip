@@ -106,7 +106,7 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
   int g0, g1;
   diagonal_group(D, blockIdx.z, gridDim.z, g0, g1);
   const SumsWork work{g0, g1, S, plane, mbp, chunk, nchunks};
-  gemm_int8_tile<CFG>(work, Apk, Bpk, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, lds);
+  gemm_int8_tile<CFG>(work, Apk, Bpk, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, 0, lds);
 }
 
 // Diagonal-sum planes are blocked: the 32 x 32 block (bi, bj) of C holds, for

@@ -116,14 +116,16 @@ struct PairCursor {
 // whole tile, so a load costs one 64-bit add; and the loads of the next step
 // are spread between this step's matrix-core instructions (one per kEvery),
 // which keeps the matrix cores fed where a burst of LDS-direct loads would
-// stall them.  The 256 x 256 configuration with its 2-stage ring issues them
+// stall them.  With `quit` (uniform) nothing is formed: it is looked at behind the
+// first loads, whose latency covers that of a word just read (in front of them it
+// took 0.9 of 17 us, TD 200 x 150 x 333).  The 256 x 256 configuration with its 2-stage ring issues them
 // over the first three quarters of the step (one per 3 instructions instead of
 // one per 4), so that the last ones land before the step ends.
 template <int CFG, typename Work>
 __device__ __forceinline__ void gemm_int8_tile(const Work &work, const int8_t *__restrict__ Apk,
                                                const int8_t *__restrict__ Bpk, int64_t mbp, int64_t nbp, int64_t kbp,
                                                int64_t kb0, int nks, int last, int m, int n, int tm, int tn,
-                                               int8_t *lds) {
+                                               int quit, int8_t *lds) {
   using G = Int8Cfg<CFG>;
   constexpr int TB = G::TB, WM = G::WM, WN = G::WN, KSB = G::KSB, NS = G::NS;
   constexpr int BI = TB / WM, BJ = TB / WN;
@@ -210,6 +212,11 @@ __device__ __forceinline__ void gemm_int8_tile(const Work &work, const int8_t *_
       for (int j = 0; j < kL; ++j) load_lds16(src + piece(j, lks), dst + loff[j]);
       advance();
     }
+
+  if (__builtin_amdgcn_readfirstlane(quit)) {
+    wait_vm<0>();
+    return;
+  }
 
   // A wavefront whose blocks are all padding (rows from m or columns from n
   // on) has no matrix-core work: it only moves its share of the panels, at the

@@ -623,8 +623,10 @@ struct ResidueWork {
 template <int CFG>
 __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k_gemm_residue(
     const int8_t *__restrict__ A, const int8_t *__restrict__ B, int64_t mbp, int64_t nbp, int64_t kbp, int u_first,
-    int u_end, int nsq, int nplanes, int m, int n, int8_t *__restrict__ R, int64_t plane) {
+    int u_end, int nsq, int nplanes, int m, int n, int8_t *__restrict__ R, int64_t plane,
+    const int *__restrict__ skip) {
   __shared__ __attribute__((aligned(16))) int8_t lds[Int8Cfg<CFG>::NS * int8_stage_bytes<CFG>()];
+  const int quit = skip ? *skip : 0;
   constexpr int TB = Int8Cfg<CFG>::TB, KSB = Int8Cfg<CFG>::KSB;
   int tm, tn;
   int8_tile_coords(blockIdx.x, gridDim.x, (int)(mbp / TB), (int)(nbp / TB), tm, tn);
@@ -634,7 +636,7 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
   const int64_t kb1 = kb0 + kChunkBlocks < kbp ? kb0 + kChunkBlocks : kbp;
   const int nks = (int)ceil_div(kb1 - kb0, KSB), last = (int)(kb1 - kb0) - (nks - 1) * KSB;
   const ResidueWork work{u0, u1, u_first, u_end - u_first, nsq, nplanes - nsq, R + (int64_t)blockIdx.y * nplanes * plane, plane, mbp};
-  gemm_int8_tile<CFG>(work, A, B, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, lds);
+  gemm_int8_tile<CFG>(work, A, B, mbp, nbp, kbp, kb0, nks, last, m, n, tm, tn, quit, lds);
 }
 
 // Persistent GEMM of a batch in tile configuration CFG: each workgroup takes
@@ -655,6 +657,7 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
     if (it < 0) break;
     const int4 w = items[it];
     const ResidueDesc &d = descs[w.x];
+    if (d.skip && *d.skip) continue;
     const int tiles_m = (int)(d.mbp / TB);
     const int tm = w.y % tiles_m, tn = w.y / tiles_m;
     const int64_t kb0 = (int64_t)w.z * kChunkBlocks;
@@ -669,7 +672,7 @@ __global__ __launch_bounds__(64 * Int8Cfg<CFG>::WM * Int8Cfg<CFG>::WN, 1) void k
                            d.R + (int64_t)w.z * d.nplanes * d.plane,
                            d.plane,
                            d.mbp};
-    gemm_int8_tile<CFG>(work, d.A, d.B, d.mbp, d.nbp, d.kbp, kb0, nks, last, d.m, d.n, tm, tn, lds);
+    gemm_int8_tile<CFG>(work, d.A, d.B, d.mbp, d.nbp, d.kbp, kb0, nks, last, d.m, d.n, tm, tn, 0, lds);
   }
 }
 
@@ -814,7 +817,7 @@ __global__ __launch_bounds__(kThreads) void k_residue_fold(const ResidueDesc *__
                                                            const int *__restrict__ prefix, int nprod) {
   const int p = __builtin_amdgcn_readfirstlane(find_range(prefix, nprod, blockIdx.x));
   const ResidueDesc d = descs[p];
-  if (d.nchunks <= 1) return;
+  if (d.nchunks <= 1 || (d.skip && *d.skip)) return;
   int8_t *at = d.R + ((int64_t)blockIdx.x - prefix[p]) * 1024 + 4 * threadIdx.x;
   for (int u = 0; u < d.nunits; ++u) {
     const BaseInfo b = kBase.info[u];
@@ -1284,7 +1287,7 @@ int base_groups(int64_t wgs, int slots, int bases, int products) {
 }
 
 hipError_t gemm_launch(int cfg, const ResiduePlan &p, const int8_t *A, const int8_t *B, const Shape &s, int u_first,
-                       int u_end, int m, int n, int8_t *R, hipStream_t st) {
+                       int u_end, int m, int n, int8_t *R, const int *skip, hipStream_t st) {
   const int tb = int8_tile_blocks(cfg);
   const int64_t tiles = (s.mbp / tb) * (s.nbp / tb);
   if (tiles > 0x7fffffffLL) return hipErrorInvalidValue;
@@ -1297,10 +1300,10 @@ hipError_t gemm_launch(int cfg, const ResiduePlan &p, const int8_t *A, const int
   const dim3 grid((unsigned)tiles, (unsigned)nchunks, (unsigned)groups);
   if (cfg == 1)
     hipLaunchKernelGGL(k_gemm_residue<1>, grid, dim3(64 * Int8Cfg<1>::WM * Int8Cfg<1>::WN), 0, st, A, B, s.mbp, s.nbp,
-                       s.kbp, u_first, u_end, p.nsq, p.nplanes, m, n, R, s.r_plane);
+                       s.kbp, u_first, u_end, p.nsq, p.nplanes, m, n, R, s.r_plane, skip);
   else  // every 256 x 256 configuration
     hipLaunchKernelGGL(k_gemm_residue<3>, grid, dim3(64 * Int8Cfg<3>::WM * Int8Cfg<3>::WN), 0, st, A, B, s.mbp, s.nbp,
-                       s.kbp, u_first, u_end, p.nsq, p.nplanes, m, n, R, s.r_plane);
+                       s.kbp, u_first, u_end, p.nsq, p.nplanes, m, n, R, s.r_plane, skip);
   return hipGetLastError();
 }
 
@@ -1504,7 +1507,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
         hipSuccess)
       return err;
     if (between && u0 == 0) (void)hipEventRecord(between, st);
-    if ((err = gemm_launch(rc.cfg, p, Ap, Bp, s, u0, u1, rc.m, rc.n, R, st)) != hipSuccess) return err;
+    if ((err = gemm_launch(rc.cfg, p, Ap, Bp, s, u0, u1, rc.m, rc.n, R, rc.flag, st)) != hipSuccess) return err;
     u0 = u1;
   }
   return combine_launch<T, C>(p.nwc, p.nchunks > 1, s.mbp * s.nbp, descs, prefix + 2, 1, st);
