@@ -11,7 +11,7 @@
 //   - prefix sums of the split work per operand and the work items of the
 //     persistent GEMM kernels, in one list per XCD (written once).
 // The graph holds, for the products by residues: clear the maxima and work
-// counters, one max-exponent launch, one residue split over all operands'
+// counters, one max-exponent launch (and the FLOAT form's samples), one residue split over all operands'
 // blocks, the persistent INT8 GEMMs over (product, tile, k chunk, unit group)
 // items and the combine; for those by slices: the split (fused, or clear the
 // maxima, the max-exponent launch and dmax pass launches), clear the work
@@ -120,7 +120,7 @@ struct ResidueBatch {
     size_t result_bytes() const { return align256((size_t)plan.nplanes * plan.nchunks * mbp * nbp * 1024); }
   };
   std::vector<Slot> slots;
-  int nw = 0, tiles0 = 0, nitems1 = 0, nitems3 = 0;
+  int nw = 0, tiles0 = 0, strips = 0, nitems1 = 0, nitems3 = 0;
   int64_t blocks = 0, blocksc = 0;
   size_t scratch = 0, planes_bytes = 0;  // where the planes' part of the workspace begins; the operands' planes
   bool shared = false;                   // other runs write to it
@@ -128,7 +128,7 @@ struct ResidueBatch {
   size_t off_static = 0, off_tables = 0, off_items = 0, off_bounds = 0, off_counter = 0, off_zero = 0, zero_bytes = 0;
   bool float_form = false;
   size_t off_flags = 0;            // FLOAT form: a word set if any product is flagged, then one per product
-  std::vector<int> prefix;         // 2 n + 1 max tiles, 2 n + 1 split blocks, n + 1 combine blocks
+  std::vector<int> prefix;         // 2 n + 1 max tiles, 2 n + 1 split blocks, n + 1 combine blocks, 2 n + 1 sampled strips
   std::vector<uint32_t> tables;    // the distinct combine tables
   std::vector<int4> items;
   int bounds[2 * (kXcds + 1)] = {};
@@ -194,14 +194,16 @@ struct ResidueBatch {
     zero_bytes = take(0) - off_zero;
 
     const int n = (int)slots.size();
-    prefix.assign((size_t)2 * (2 * n + 1) + n + 1, 0);
-    int *pre0 = prefix.data(), *preb = pre0 + 2 * n + 1, *prec = preb + 2 * n + 1;
+    prefix.assign((size_t)3 * (2 * n + 1) + n + 1, 0);
+    int *pre0 = prefix.data(), *preb = pre0 + 2 * n + 1, *prec = preb + 2 * n + 1, *pres = prec + n + 1;
     std::vector<std::pair<std::array<int, 3>, size_t>> known;
     for (int i = 0; i < n; ++i) {
       Slot &s = slots[i];
       const int64_t kbl = ceil_div((int64_t)s.k, (int64_t)kKBlk8);
       pre0[2 * i + 1] = pre0[2 * i] + tiles64(s.m, s.k);
       pre0[2 * i + 2] = pre0[2 * i + 1] + tiles64(s.n, s.k);
+      pres[2 * i + 1] = pres[2 * i] + ceil_div(s.m, 16);
+      pres[2 * i + 2] = pres[2 * i + 1] + ceil_div(s.n, 16);
       // A's blocks cover the padding of k, which has to be zero in one operand (it is
       // cleared with the plan, and written where something else may lie there since:
       // ResidueOperand::padded); that of m and n takes part in no element of C
@@ -225,6 +227,7 @@ struct ResidueBatch {
       s.table = at;
     }
     tiles0 = pre0[2 * n];
+    strips = pres[2 * n];
     blocks = preb[2 * n];
     make_items();
     off_static = take(prefix.size() * 4);
@@ -296,6 +299,8 @@ struct ResidueBatch {
     const int *pre0 = reinterpret_cast<const int *>(ws + off_static), *preb = pre0 + 2 * n + 1;
     hipError_t e = launch_fill32(ws + off_zero, (int64_t)(zero_bytes / 4), 0u, st);
     if (e == hipSuccess) e = launch_residue_max_batched<T>(ops, pre0, 2 * n, tiles0, st);
+    if (e == hipSuccess && float_form)
+      e = launch_residue_sample<T, C>(ops, preb + 2 * n + 1 + n + 1, 2 * n, strips, st);
     if (e == hipSuccess) e = launch_residue_split_batched<T, C>(nw, ops, preb, 2 * n, (int)blocks, st);
     return e;
   }

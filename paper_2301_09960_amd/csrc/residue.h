@@ -67,7 +67,7 @@ struct ResidueOperand {
   int64_t nbp, kbp;
   void *mu;              // maxima (launch_split_max0)
   int *exps;
-  int *state;            // float_form: one word per vector, cleared first
+  int *state;            // float_form: one word per vector, from the samples (launch_residue_sample)
   int *flag, *any;       // float_form: set when the slices must be used instead (any may be null)
   int nunits, nsq;
   const int *padded;     // where it is given and 0 the padding of k is zero already
@@ -85,8 +85,8 @@ struct ResidueDesc {
   const int *skip;        // FLOAT form: where set, C is left to the slices, whose split may read A or B from it
 };
 
-// One product by residues.  clear: device memory holding the maxima and, in the
-// FLOAT form, the states, cleared by the call.  arena: a call takes
+// One product by residues.  clear: device memory holding the maxima, cleared by the
+// call where it has to be.  arena: a call takes
 // residue_bytes() of it; with less, the product is formed in parts (bases, then
 // blocks of C), with the same result.
 struct ResidueCall {
@@ -97,7 +97,7 @@ struct ResidueCall {
   int64_t c_stride;
   int *exp_a, *exp_b;    // m and n exponents
   void *mu_a, *mu_b;     // m and n maxima
-  int *state_a, *state_b;  // FLOAT form: m and n words, at the end of what is cleared; INT8 form null
+  int *state_a, *state_b;  // FLOAT form: m and n words; INT8 form null
   uint32_t *clear;
   int64_t clear_words;
   int *flag;             // FLOAT form: cleared, then set if the slices must form the product
@@ -127,6 +127,10 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
 template <typename T>
 hipError_t launch_residue_max_batched(const ResidueOperand<T> *ops, const int *prefix, int nops, int tiles,
                                       hipStream_t st);
+// FLOAT form, behind the maxima: states from samples (residue.hip) of the operands'
+// vectors, in strips of 16; prefix: running sums of the strips.
+template <typename T, int C>
+hipError_t launch_residue_sample(const ResidueOperand<T> *ops, const int *prefix, int nops, int strips, hipStream_t st);
 template <typename T, int C>
 hipError_t launch_residue_split_batched(int nw, const ResidueOperand<T> *ops, const int *prefix, int nops, int blocks,
                                         hipStream_t st);

@@ -199,29 +199,66 @@ __device__ __forceinline__ int vector_exponent(typename bits_of<T>::type mu, int
 // pass's.  An element whose bits i and i - 1 differ, with nonzero bits below
 // them, leaves |r| > 2^(i - 1) under any grid above 2^i, so e >= i and the next
 // grid is at least 2^(i - b); with i = g - 1, the usual case, a pass falls b + 1
-// bits.  The places where some of the first 32 elements of the vector has such a
-// change give a lower bound of all D grids (last_grid_covered); random mantissas
-// have one at nearly every place.  A vector is safe if that bound says so, or if
-// every element of it is exact on the fixed grid.  A vector that is neither, or
-// that holds lower components as large as leading ones, sets the flag: the
-// product is then formed from the slices.
-template <int NW>
+// bits.  The places where some element of the vector has such a change give a lower
+// bound of all D grids (last_grid_covered); random mantissas have one at nearly
+// every place, so 32 elements that are not zero settle a vector: its first ones, or,
+// where zeros are among them (triangular, banded, sparse operands), others (settle_strip,
+// in the launch that finds the maxima).  A vector is safe if that bound says so, or if
+// every element of it is exact on the fixed grid.  A vector that is neither, or that
+// holds lower components as large as leading ones, sets the flag: the product is then
+// formed from the slices.
+constexpr int kChangeWords = 12;  // places 0 .. kMaxResidueBits + 1 and the words of a component that starts below them
+static_assert(kMaxResidueBits / 32 + 3 <= kChangeWords, "three words a component");
 __device__ __forceinline__ bool last_grid_covered(const uint32_t *changes, int bits, int b, int passes) {
   int g = bits - b;  // places count from the fixed grid
   for (int a = 1; a < passes; ++a) {
     int i = -1;  // the highest change below the grid
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
+    for (int w = (g - 1) >> 5; w >= 0 && i < 0; --w) {
       const int top = g - 32 * w;  // places below g in this word
-      const uint32_t m = top >= 32 ? 0xffffffffu : top > 0 ? (1u << top) - 1u : 0u;
-      const uint32_t c = changes[w] & m;
+      const uint32_t c = changes[w] & (top >= 32 ? 0xffffffffu : (1u << top) - 1u);
       if (c) i = 32 * w + 31 - __clz((int)c);
     }
-    if (i < 0) return false;
     g = i - b;
     if (g < 1) return false;  // one place to spare for the rounding of the leading components
   }
   return true;
+}
+
+// ORs the changes of an element, places from 2^(E - bits) up, into `changes`.  A component's two's complement has those of the element between its
+// own last change (a borrow of the component below goes no higher) and its sign, so
+// each is placed for itself, without its last change and the place above it.  An
+// element whose components overlap, or exceed 2^E, adds none.
+template <typename T, int C>
+__device__ __forceinline__ void add_changes(const T (&x)[C], int E, int bits, uint32_t *changes) {
+  uint64_t c[C];
+  int off[C], above = E + 1;
+  bool apart = true;
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    int64_t M;
+    int q;
+    parts_of(x[r], M, q);
+    c[r] = (uint64_t)M ^ ((uint64_t)M << 1);
+    const uint64_t low = c[r] & (0u - c[r]);
+    c[r] &= ~(low | (low << 1));
+    off[r] = q - (E - bits);
+    if (M != 0) {
+      apart = apart && q + (sizeof(T) == 8 ? 53 : 24) <= above;
+      above = q;
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    if (!apart || off[r] <= -64) continue;
+    const int at = off[r] > 0 ? off[r] : 0, sh = at & 31;
+    const uint64_t u = off[r] < 0 ? c[r] >> -off[r] : c[r];
+    const uint64_t lo = u << sh;
+    const uint32_t hi = sh ? (uint32_t)(u >> (64 - sh)) : 0u;
+    uint32_t *to = changes + (at >> 5);
+    if ((uint32_t)lo) atomicOr(to, (uint32_t)lo);
+    if (lo >> 32) atomicOr(to + 1, (uint32_t)(lo >> 32));
+    if (hi) atomicOr(to + 2, hi);
+  }
 }
 
 // Adds M 2^off (two's complement, off >= 0) into the words w: the three words of
@@ -287,15 +324,109 @@ __device__ __forceinline__ bool rounds_up(const T (&x)[C], int P, uint32_t g, bo
   return d > 0.0 || (d == 0.0 && odd);
 }
 
+// The integer W of one element in NW words, rounded to nearest on 32 guard bits, ties
+// to even.  With `check`: whether bits were cut off, and whether a lower component is
+// as large as leading ones (an infinity or NaN too).
+template <typename T, int C, int NW>
+__device__ __forceinline__ void element_words(const T (&x)[C], int E, int P, bool check, uint32_t (&W)[12],
+                                              bool &inexact, bool &odd) {
+  uint32_t w[NW + 1];
+#pragma unroll
+  for (int i = 0; i <= NW; ++i) w[i] = 0u;
+#pragma unroll
+  for (int r = 0; r < C; ++r) {
+    int64_t M;
+    int q;
+    parts_of(x[r], M, q);
+    const int off = q - P;
+    const int sh = off >= 0 ? 0 : off > -63 ? -off : 63;
+    if (check) {
+      if (r > 0 && M != 0 && q + (sizeof(T) == 8 ? 53 : 24) > E - 20) odd = true;
+      inexact = inexact || (M & ((int64_t(1) << sh) - 1)) != 0;
+    }
+    window_add_shifted<NW + 1>(w, M >> sh, off < 0 ? 0 : off);
+  }
+  inexact = inexact || w[0] != 0u;
+  uint32_t carry = w[0] >> 31;
+  const bool near_half = w[0] - (0x80000000u - C) <= (uint32_t)C;
+  if (__builtin_expect(__any(near_half), 0)) {
+    if (near_half) carry = rounds_up<T, C>(x, P, w[0], (w[1] & 1u) != 0u) ? 1u : 0u;
+  }
+#pragma unroll
+  for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(w[i + 1], 0u, carry, &carry);
+}
+
+// The same from the words of W (any element's).
+template <int NW>
+__device__ __forceinline__ void add_word_changes(const uint32_t (&W)[12], uint32_t (&change)[NW]) {
+  bool more = false;  // a change further down
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    uint32_t c = W[i] ^ ((W[i] << 1) | (i > 0 ? W[i > 0 ? i - 1 : 0] >> 31 : 0u));
+    const bool here = c != 0u;
+    if (!more && here) {  // the lowest change, and the place above it
+      const uint32_t low = c & (0u - c);
+      c &= ~(low | (low << 1));
+    }
+    more = more || here;
+    change[i] |= c;
+  }
+}
+
+// State of a vector in the FLOAT form's check.
+constexpr int kRounded = 1;    // an element was rounded
+constexpr int kUnsettled = 2;  // its first 32 elements leave open how far down its slices reach
+constexpr int kSettled = 4;    // others say: no further than the fixed grid
+
 template <int NW>
 struct SplitLds {
   static constexpr bool kSmall = NW <= 4, kMore = NW > 8;
   static constexpr int kQ = kSmall ? 2 : 4;  // words per lane of the first instruction
   __attribute__((aligned(16))) uint32_t first[kThreads / 64][4][64][2 * kQ];
   __attribute__((aligned(16))) uint32_t more[kMore ? kThreads / 64 : 1][4][64][4];
-  uint32_t seen[kBlk8][NW];
+  uint32_t seen[kBlk8][NW | 1];  // rows in different banks
   int rounded[kBlk8];
 };
+
+// The first place p0 + 16 i of a vector's element that is not zero, or len.
+template <typename T>
+__device__ __forceinline__ int find_nonzero(const T *x, int64_t sp, int p0, int len) {
+  for (int p = p0; p < len; p += 64) {
+    T e[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) e[j] = p + 16 * j < len ? x[(int64_t)(p + 16 * j) * sp] : T(0);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if (abs_bits(e[j]) != 0) return p + 16 * j;
+  }
+  return len;
+}
+template <typename T, int C>
+__device__ __forceinline__ void load_element(const T *x, int64_t comp_stride, int64_t sp, int p, int len, T (&e)[C]) {
+#pragma unroll
+  for (int r = 0; r < C; ++r) e[r] = p < len ? x[r * comp_stride + (int64_t)p * sp] : T(0);
+}
+
+// kSettled where sampled elements settle a vector.  A workgroup takes 16 vectors, a
+// thread of it every 16th element of one (x), with exponent E: the first two of them
+// that are not zero.  changes: the vector's, cleared before the last barrier.
+template <typename T, int C>
+__device__ __forceinline__ int settle_strip(const T *x, int64_t comp_stride, int64_t sp, int len, int dp, int E,
+                                            int bits, int slice_bits, int passes, uint32_t *changes) {
+  const bool finite = E != kZeroExp && E != kNonFinite;
+  if (finite) {
+    int p = dp - 16;
+#pragma unroll 1
+    for (int j = 0; j < 2; ++j) {
+      T e[C];
+      p = find_nonzero(x, sp, p + 16, len);
+      load_element<T, C>(x, comp_stride, sp, p, len, e);
+      add_changes<T, C>(e, E, bits, changes);
+    }
+  }
+  __syncthreads();
+  return finite && last_grid_covered(changes, bits, slice_bits, passes) ? kSettled : 0;
+}
 
 // Bound by memory for DD (1.6 GB at 3.3 TB/s, the planes in 1 KiB pieces; n = 4096)
 // and by vector instructions from TD on: 4 per residue (conversion, quotient,
@@ -339,6 +470,7 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   constexpr int kQ = SplitLds<NW>::kQ;
   auto &first_words = lds.first[t / 64];
   auto &more_words = lds.more[kMore ? t / 64 : 0];
+  const int flagged = op.flag ? __hip_atomic_load(op.flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
   bool inexact = false, odd = false;
   uint32_t change[NW] = {};
   T xs[4][C];
@@ -352,47 +484,10 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     __builtin_amdgcn_sched_barrier(0);  // one element after another: their words together take too many registers
-    uint32_t w[NW + 1];
-#pragma unroll
-    for (int i = 0; i <= NW; ++i) w[i] = 0u;
-#pragma unroll
-    for (int r = 0; r < C; ++r) {
-      const T xr = xs[j][r];
-      int64_t M;
-      int q;
-      parts_of(xr, M, q);
-      const int off = q - P;
-      const int sh = off >= 0 ? 0 : off > -63 ? -off : 63;
-      if (check) {
-        if (r > 0 && M != 0 && q + (sizeof(T) == 8 ? 53 : 24) > E - 20) odd = true;  // also infinities and NaN
-        inexact = inexact || (M & ((int64_t(1) << sh) - 1)) != 0;
-      }
-      window_add_shifted<NW + 1>(w, M >> sh, off < 0 ? 0 : off);
-    }
-    inexact = inexact || w[0] != 0u;
-    uint32_t W[12];  // signed bytes with the sum W: W + 0x80..80, each byte less 128
-    uint32_t carry = w[0] >> 31;  // round to nearest on the guard bits, ties to even
-    const bool near_half = w[0] - (0x80000000u - C) <= (uint32_t)C;
-    if (__builtin_expect(__any(near_half), 0)) {
-      if (near_half) carry = rounds_up<T, C>(xs[j], P, w[0], (w[1] & 1u) != 0u) ? 1u : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(w[i + 1], 0u, carry, &carry);
-    if (check && kb == 0) {  // the changes of bits but the last ones of the element
-      bool more = false;     // a change further down
-#pragma unroll
-      for (int i = 0; i < NW; ++i) {
-        uint32_t c = W[i] ^ ((W[i] << 1) | (i > 0 ? W[i > 0 ? i - 1 : 0] >> 31 : 0u));
-        const bool here = c != 0u;
-        if (!more && here) {  // the lowest change, and the place above it
-          const uint32_t low = c & (0u - c);
-          c &= ~(low | (low << 1));
-        }
-        more = more || here;
-        change[i] |= c;
-      }
-    }
-    carry = 0u;
+    uint32_t W[12];  // then in signed bytes with the sum W: W + 0x80..80, each byte less 128
+    element_words<T, C, NW>(xs[j], E, P, check, W, inexact, odd);
+    if (check && kb == 0) add_word_changes<NW>(W, change);
+    uint32_t carry = 0u;
 #pragma unroll
     for (int i = 0; i < NW; ++i) W[i] = __builtin_addc(W[i], 0x80808080u, carry, &carry) ^ 0x80808080u;
 #pragma unroll
@@ -407,36 +502,36 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
 
   if (p0 == 0 && v < op.nvec && part == 0) op.exps[v] = E;
   if (check) {  // before the products: its words per element need not be kept through them
-    auto &seen = lds.seen;
-    auto &rounded = lds.rounded;
-    for (int i = t; i < kBlk8 * NW; i += kThreads) seen[i / NW][i % NW] = 0u;
-    if (t < kBlk8) rounded[t] = 0;
-    __syncthreads();
-    if (inexact) rounded[l & 31] = 1;
     auto fall_back = [&]() {
       *op.flag = 1;
       if (op.any) *op.any = 1;
     };
+    if (kb == 0)
+      for (int i = t; i < kBlk8 * NW; i += kThreads) lds.seen[i / NW][i % NW] = 0u;
+    if (t < kBlk8) lds.rounded[t] = 0;
+    __syncthreads();
     if (odd) fall_back();
+    if (inexact) lds.rounded[l & 31] = 1;
     if (kb == 0) {
-  #pragma unroll
-      for (int i = 0; i < NW; ++i) atomicOr(&seen[l & 31][i], change[i]);
+#pragma unroll
+      for (int i = 0; i < NW; ++i) atomicOr(&lds.seen[l & 31][i], change[i]);
     }
     __syncthreads();
     if (t < kBlk8) {
       const int vt = (int)(vb * kBlk8) + t;
       if (vt < op.nvec) {
-        int add = rounded[t];
-        if (kb == 0 && !last_grid_covered<NW>(seen[t], op.bits, op.slice_bits, op.passes)) add |= 2;
-        // bit 0: an element was rounded; bit 1: the slices may reach further down
+        int add = lds.rounded[t] ? kRounded : 0;
+        if (kb == 0 && !last_grid_covered(lds.seen[t], op.bits, op.slice_bits, op.passes)) add |= kUnsettled;
         if (add & ~*(volatile int *)&op.state[vt]) {
-          const int old = atomicOr(&op.state[vt], add);
-          if ((old | add) == 3) fall_back();
+          const int now = atomicOr(&op.state[vt], add) | add;
+          if ((now & (kRounded | kUnsettled | kSettled)) == (kRounded | kUnsettled)) fall_back();
         }
       }
     }
   }
 
+  // a product known to go by slices needs no planes (a late look would do)
+  if (__builtin_amdgcn_readfirstlane(flagged) != 0) return;
   auto product = [&](int rb, int j, bool y) {  // 32 bases of row block rb, 32 elements j
     i16v acc;
 #pragma unroll
@@ -518,7 +613,6 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
       to += plane;
     }
   }
-
 }
 
 __device__ __forceinline__ int find_range(const int *prefix, int n, int b) {
@@ -968,7 +1062,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_residue_combine(const ResidueDe
 // Host data on its way to the device inside kernel arguments: no copy, so the
 // sequence can be captured and keeps no host buffer.  Also clears two regions.
 // ---------------------------------------------------------------------------
-constexpr int kUploadWords = 960;
+constexpr int kUploadWords = 976;
 struct Upload {
   uint32_t w[kUploadWords];
 };
@@ -984,17 +1078,24 @@ __global__ __launch_bounds__(kThreads) void k_upload(Upload data, int n, uint32_
 // enough that a workgroup reads 16 whole ones: no atomics, so nothing to clear for
 // them first, and no shuffles (64 bit ones took most of k_split_max0's 8.5 us on
 // two tiles).  Bound by the latency of its loads, 16 in flight per thread.
+//
+// In the FLOAT form strips with zeros among a vector's first 32 elements take their
+// samples here (settle_strip).
 template <typename T>
 struct MaxOperand {
   const T *X;
-  int64_t sv, sp;
+  int64_t comp_stride, sv, sp;
   int nvec, len, orient;
   typename bits_of<T>::type *mu;
+  int *state;
 };
-template <typename T>
+struct GridOfSlices {
+  int bits, slice_bits, passes;  // bits = 0: INT8 form, no samples
+};
+template <typename T, int C>
 __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, int strips_a, uint32_t *dst,
-                                                            MaxOperand<T> a, MaxOperand<T> b, uint32_t *z0, int64_t n0,
-                                                            uint32_t *z1, int64_t n1) {
+                                                            MaxOperand<T> a, MaxOperand<T> b, GridOfSlices grid,
+                                                            int *flag) {
   using U = typename bits_of<T>::type;
   const int t = threadIdx.x;
   const int64_t id = blockIdx.x * (int64_t)kThreads + t, step = (int64_t)gridDim.x * kThreads;
@@ -1005,6 +1106,7 @@ __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, 
   const int v = v0 + dv < op.nvec ? v0 + dv : op.nvec - 1;
   const T *x = op.X + (int64_t)v * op.sv;
   U best = 0;
+  bool zeros = false;  // among the first 32 elements
   for (int p0 = dp; p0 < op.len; p0 += kThreads) {
     T e[16];
 #pragma unroll
@@ -1017,19 +1119,53 @@ __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, 
       const U k = abs_bits(e[i]);
       best = k > best ? k : best;
     }
+    if (p0 == dp) zeros = abs_bits(e[0]) == 0 || abs_bits(e[1]) == 0;
   }
   for (int64_t i = id; i < n; i += step) dst[i] = data.w[i];
-  for (int64_t i = id; i < n0; i += step) z0[i] = 0u;
-  for (int64_t i = id; i < n1; i += step) z1[i] = 0u;
+  if (id == 0 && flag) *flag = 0;
   __shared__ U red[16][17];
+  __shared__ uint32_t changes[16][kChangeWords];
   red[dp][dv] = best;
-  __syncthreads();
+  if (t < 16 * kChangeWords) changes[t / kChangeWords][t % kChangeWords] = 0u;
+  const bool settle = __syncthreads_or(grid.bits > 0 && zeros);
   if (t < 16 && v0 + t < op.nvec) {
     U k = red[0][t];
 #pragma unroll
     for (int i = 1; i < 16; ++i) k = red[i][t] > k ? red[i][t] : k;
     op.mu[v0 + t] = k;
+    if (grid.bits > 0 && !settle) op.state[v0 + t] = 0;
   }
+  if (settle) {
+    U k = red[0][dv];
+    for (int i = 1; i < 16; ++i) k = red[i][dv] > k ? red[i][dv] : k;
+    const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp, vector_exponent<T>(k, 1), grid.bits,
+                                     grid.slice_bits, grid.passes, changes[dv]);
+    if (dp == 0 && v0 + dv < op.nvec) op.state[v0 + dv] = s;
+  }
+}
+
+// The same for vectors whose maxima are known: workgroup x - prefix[i] of operand i.
+// The states are cleared.
+template <typename T, int C>
+__global__ __launch_bounds__(kThreads) void k_residue_sample(const ResidueOperand<T> *__restrict__ ops,
+                                                             const int *__restrict__ prefix, int nops) {
+  using U = typename bits_of<T>::type;
+  const int i = __builtin_amdgcn_readfirstlane(find_range(prefix, nops, blockIdx.x));
+  const ResidueOperand<T> &op = ops[i];
+  const int t = threadIdx.x, v0 = 16 * ((int)blockIdx.x - prefix[i]);
+  const int dv = op.orient == 0 ? t % 16 : t / 16, dp = op.orient == 0 ? t / 16 : t % 16;
+  const int v = v0 + dv < op.nvec ? v0 + dv : op.nvec - 1;
+  const T *x = op.X + (int64_t)v * op.sv;
+  __shared__ uint32_t changes[16][kChangeWords];
+  if (t < 16 * kChangeWords) changes[t / kChangeWords][t % kChangeWords] = 0u;
+  bool zeros = false;
+#pragma unroll
+  for (int j = 0; j < 32; j += 16) zeros = zeros || dp + j >= op.len || abs_bits(x[(int64_t)(dp + j) * op.sp]) == 0;
+  if (!__syncthreads_or(zeros)) return;
+  const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp,
+                                   vector_exponent<T>(static_cast<const U *>(op.mu)[v], 1), op.bits, op.slice_bits,
+                                   op.passes, changes[dv]);
+  if (dp == 0 && v0 + dv < op.nvec) op.state[v0 + dv] = s;
 }
 // Up to this length (one or two launches less): INT8 DD calls of 64^2 x 64 go from
 // 58 to 49 us, 64^2 x 8192 from 127 to 114, n = 4096 from 2629 to 2584; a single pair
@@ -1177,7 +1313,7 @@ namespace {
 size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // The descriptors before the table, which is read 16 bytes at a time.
-constexpr size_t kHeadBytes = (2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 4 * 4 + 15) / 16 * 16;
+constexpr size_t kHeadBytes = (2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 6 * 4 + 15) / 16 * 16;
 size_t header_bytes(const ResiduePlan &p) {
   const size_t words = (size_t)weight_words(p.nwc) + p.nwc + 2;
   return up256(kHeadBytes + words * 4);
@@ -1366,6 +1502,13 @@ ResidueFit residue_fit(const ResiduePlan &p, int cfg, int m, int n, int k, size_
 }
 
 template <typename T, int C>
+hipError_t launch_residue_sample(const ResidueOperand<T> *ops, const int *prefix, int nops, int strips, hipStream_t st) {
+  if (strips <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_residue_sample<T, C>), dim3((unsigned)strips), dim3(kThreads), 0, st, ops, prefix, nops);
+  return hipGetLastError();
+}
+
+template <typename T, int C>
 hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const SplitOperand<T> &b, T *Cout,
                           hipEvent_t between, bool first, hipStream_t st) {
   const ResiduePlan &p = rc.plan;
@@ -1373,7 +1516,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   // arena: the uploaded descriptors and table, the result planes, then as many
   // operand planes as fit (Pieces)
   const Pieces piece(p, rc.cfg, rc.m, rc.n, rc.k, rc.arena_bytes);
-  const size_t head = header_bytes(p), result = (size_t)p.nplanes * p.nchunks * s.r_plane;
+  const size_t result = (size_t)p.nplanes * p.nchunks * s.r_plane;
   const int room = piece.room;
   if (!piece.whole) {
     if (piece.m == 0) return hipErrorInvalidValue;  // does not fit
@@ -1402,14 +1545,14 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     if (err == hipSuccess) err = launch_residue<T, C>(hi, a2, b2, C2, nullptr, false, st);
     return err;
   }
-  int8_t *R = reinterpret_cast<int8_t *>(rc.arena + head);
+  int8_t *R = reinterpret_cast<int8_t *>(rc.arena + header_bytes(p));
   int8_t *Ap = R + result, *Bp = Ap + (size_t)room * s.a_plane;
 
   const std::vector<uint32_t> &table = residue_table(p.nunits, p.nsq, p.nwc);
   struct Head {
     ResidueOperand<T> op[2];
     ResidueDesc d;
-    int prefix[4];  // of the split blocks, then of the product
+    int prefix[6];  // of the split blocks, of the product, of the sampled strips
   } h{};
   static_assert(sizeof(Head) <= kHeadBytes && sizeof(Head) % 4 == 0, "uploaded in words");
   for (int i = 0; i < 2; ++i) {
@@ -1440,6 +1583,8 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
   if (ba + bb > 0x7fffffffLL) return hipErrorInvalidValue;
   h.prefix[0] = 0;
   h.prefix[1] = (int)ba;
+  const int sa = ceil_div(rc.m, 16), sb = ceil_div(rc.n, 16);
+  h.prefix[5] = sa;
   h.d.R = R;
   h.d.table = reinterpret_cast<const uint32_t *>(rc.arena + kHeadBytes);
   h.d.EA = rc.exp_a;
@@ -1470,33 +1615,37 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
       up.w[i] = at + i >= hw                  ? table[at + i - hw]
                 : at + i < sizeof(Head) / 4 ? reinterpret_cast<const uint32_t *>(&h)[at + i]
                                             : 0u;
-    uint32_t *dst = reinterpret_cast<uint32_t *>(rc.arena) + at, *flag = reinterpret_cast<uint32_t *>(rc.flag);
+    uint32_t *dst = reinterpret_cast<uint32_t *>(rc.arena) + at;
     const bool last = at + n == words;
-    // k_residue_begin writes the maxima: of what is to be cleared the states are left
-    uint32_t *clear = begin ? reinterpret_cast<uint32_t *>(rc.state_a) : rc.clear;
-    const int64_t n0 = last && clear ? rc.clear + rc.clear_words - clear : 0, n1 = last && first && rc.flag ? 1 : 0;
+    int *flag = last && first ? rc.flag : nullptr;
     if (begin && last) {
       using U = typename bits_of<T>::type;
-      const int sa = ceil_div(rc.m, 16), sb = ceil_div(rc.n, 16);
-      const MaxOperand<T> va{a.X, a.sv, a.sp, a.nvec, a.len, 0, static_cast<U *>(rc.mu_a)};
-      const MaxOperand<T> vb{b.X, b.sv, b.sp, b.nvec, b.len, 1, static_cast<U *>(rc.mu_b)};
-      hipLaunchKernelGGL(k_residue_begin<T>, dim3((unsigned)(sa + sb)), dim3(kThreads), 0, st, up, (int)n, sa, dst, va,
-                         vb, clear, n0, flag, n1);
+      const MaxOperand<T> va{a.X, a.comp_stride, a.sv, a.sp, a.nvec, a.len, 0, static_cast<U *>(rc.mu_a), rc.state_a};
+      const MaxOperand<T> vb{b.X, b.comp_stride, b.sv, b.sp, b.nvec, b.len, 1, static_cast<U *>(rc.mu_b), rc.state_b};
+      const GridOfSlices grid{rc.float_form ? p.bits : 0, rc.slice_bits, rc.passes};
+      hipLaunchKernelGGL((k_residue_begin<T, C>), dim3((unsigned)(sa + sb)), dim3(kThreads), 0, st, up, (int)n, sa, dst,
+                         va, vb, grid, flag);
     } else {
+      const int64_t n0 = last ? rc.clear_words : 0;
       const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(n0, (int64_t)kThreads)));
-      hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n, dst, clear, n0, flag, n1);
+      hipLaunchKernelGGL(k_upload, dim3((unsigned)blocks), dim3(kThreads), 0, st, up, (int)n, dst, rc.clear, n0,
+                         reinterpret_cast<uint32_t *>(flag), (int64_t)(flag ? 1 : 0));
     }
     if ((err = hipGetLastError()) != hipSuccess) return err;
   }
+  const auto *prefix = reinterpret_cast<const int *>(rc.arena + offsetof(Head, prefix));
   if (!begin) {
     SplitOperand<T> ma = a, mb = b;
     ma.mu = rc.mu_a;
     mb.mu = rc.mu_b;
     if ((err = launch_split_max0(ma, mb, st)) != hipSuccess) return err;
+    if (rc.float_form &&
+        (err = launch_residue_sample<T, C>(reinterpret_cast<const ResidueOperand<T> *>(rc.arena), prefix + 4, 2, sa + sb,
+                                           st)) != hipSuccess)
+      return err;
   }
   const auto *ops = reinterpret_cast<const ResidueOperand<T> *>(rc.arena);
   const auto *descs = reinterpret_cast<const ResidueDesc *>(rc.arena + offsetof(Head, d));
-  const auto *prefix = reinterpret_cast<const int *>(rc.arena + offsetof(Head, prefix));
   for (int u0 = 0; u0 < p.nunits;) {
     int u1 = u0 + 1;
     while (u1 < p.nunits && group_planes(u0, u1 + 1, p.nsq) <= room) ++u1;
@@ -1552,6 +1701,7 @@ hipError_t launch_residue_combine_batched(int nwc, bool chunks, const ResidueDes
 #define MP_RESIDUE_INST(T, C)                                                                                   \
   template hipError_t launch_residue<T, C>(const ResidueCall &, const SplitOperand<T> &, const SplitOperand<T> &, T *, \
                                            hipEvent_t, hipStream_t);                                            \
+  template hipError_t launch_residue_sample<T, C>(const ResidueOperand<T> *, const int *, int, int, hipStream_t); \
   template hipError_t launch_residue_split_batched<T, C>(int, const ResidueOperand<T> *, const int *, int, int, \
                                                          hipStream_t);                                          \
   template hipError_t launch_residue_combine_batched<T, C>(int, bool, const ResidueDesc *, const int *, int, int64_t, \

@@ -348,3 +348,70 @@ def test_elements_round_to_nearest_even(mp, fmt, D):
     for i, x in enumerate(rows):
         steps = sum(map(Fraction, x)) / Fraction(u)
         assert sum(Fraction(float(v)) for v in C[:, 0, i]) == round(steps) * Fraction(u), (x, C[:, 0, i])
+
+
+def structured(fmt, shape, m, n, k, seed):
+    """Operands with structural zeros and a spread of exponents that the fixed grid
+    cuts off: A (c, k, m) keeps the elements (p, i) of the pattern."""
+    A, B = W.gen_pair(fmt, m, n, k, E=50, seed=seed)
+    p, i = np.arange(k)[:, None], np.arange(m)[None, :]
+    rng = np.random.default_rng(seed)
+    keep = {"front": p >= 40, "lower": p * m >= (i - 8) * k, "upper": p * m <= (i + 8) * k,
+            "band": np.abs(p * m - i * k) <= 12 * max(m, k), "blocks": ((p // 48 + i // 16) % 3 == 0) & (p >= 33),
+            "sparse": rng.random((k, m)) < 24.0 / k}[shape]
+    return A * keep, B
+
+
+def flagged(mp, fmt, A, B):
+    """The product, and whether it was left to the slices: the word behind the rest
+    of an attached workspace."""
+    import torch
+    (k, m), n = A.shape[1:], B.shape[1]
+    ws = torch.empty(mp.workspace_bytes(fmt, "float", m, n, k), dtype=torch.uint8, device="cuda")
+    mp.set_workspace(ws)
+    try:
+        C = mp.gemm(fmt, A, B)
+        torch.cuda.synchronize()
+    finally:
+        mp.set_workspace(None)
+    return C, bool(ws[-256:-252].cpu().view(torch.int32)[0])
+
+
+@pytest.mark.parametrize("fmt", ["dd", "td", "qd", "ts"])
+@pytest.mark.parametrize("shape,m,n,k", [("front", 70, 66, 200), ("lower", 150, 40, 160), ("upper", 90, 33, 300),
+                                         ("band", 200, 50, 220), ("blocks", 130, 70, 500), ("sparse", 40, 60, 1000),
+                                         ("front", 33, 20, 8300), ("sparse", 18, 17, 9000)])
+def test_structural_zeros_keep_the_residues(mp, orc, fmt, shape, m, n, k):
+    """Triangular, banded, sparse operands, and zeros in front, are settled by the
+    elements that are not zero: the product is not left to the slices, as either
+    operand, meets the bound of its grid, and is the same in a batch."""
+    import torch
+    say(f"structured {fmt} {shape} {m}x{n}x{k}")
+    A, B = structured(fmt, shape, m, n, k, seed=k + m)
+    dA, dB = dev(A), dev(B)
+    C, left = flagged(mp, fmt, dA, dB)
+    assert not left
+    D = mp.last_num_slices()
+    rows = [0, m // 2, m - 1]
+    diff, absab, _ = orc.exact_check(A, B, C.cpu().numpy(), rows=rows)
+    single = fmt == "ts"
+    b = (24 if single else 53) - orc.rho(24 if single else 53, k)
+    bits = max(D * (b + 1) + 2, 116 if single else 0)
+    wide = A[:, :, rows].astype(np.float64), B.astype(np.float64)
+    assert np.all(diff <= rounding_bound(*wide, bits - 1, COMPS[fmt] * (24 / 53 if single else 1), absab))
+    # the transposed product: the same entries
+    tA, tB = dB.permute(0, 2, 1).contiguous(), dA.permute(0, 2, 1).contiguous()
+    Ct, left = flagged(mp, fmt, tA, tB)
+    assert not left and torch.equal(Ct.permute(0, 2, 1), C)
+    X, Y = W.gen_pair(fmt, 50, 60, 70, E=8, seed=1)
+    out = mp.gemm_batched(fmt, [dA, dev(X), tA], [dB, dev(Y), tB])
+    assert torch.equal(out[0], C) and torch.equal(out[2].permute(0, 2, 1), C)
+
+
+def test_slices_are_needed(mp):
+    """The word the test above reads is set where a fixed grid would cut off what the
+    slices follow, and not for a dense operand."""
+    A, B = with_gap("dd", 70, 66, 200, 5)
+    assert flagged(mp, "dd", dev(A), dev(B))[1]
+    A, B = W.gen_pair("dd", 70, 66, 200, E=50, seed=1)
+    assert not flagged(mp, "dd", dev(A), dev(B))[1]
