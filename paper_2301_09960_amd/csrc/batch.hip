@@ -766,7 +766,9 @@ struct FormatPlan : BatchPlan {
       desc_bytes = r.off_res + r.res.slots.size() * sizeof(ResidueDesc);
     }
     take(desc_bytes);
+    o = (o + 4095) & ~size_t(4095);  // the planes' blocks at multiples of their 1 KiB
     plain.scratch = take(plain.scratch_bytes);
+    o = (o + 4095) & ~size_t(4095);
     const size_t scratch = take(planes);
     for (Run &r : runs) r.fallback.scratch = r.res.scratch = scratch;
     total = o;

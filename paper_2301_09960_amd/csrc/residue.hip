@@ -1314,9 +1314,16 @@ size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
 // The descriptors before the table, which is read 16 bytes at a time.
 constexpr size_t kHeadBytes = (2 * sizeof(ResidueOperand<double>) + sizeof(ResidueDesc) + 6 * 4 + 15) / 16 * 16;
+// The planes behind them begin at a multiple of their blocks' 1 KiB: blocks across two
+// of these cost the QD combine 3 % (n = 4096).
+constexpr size_t kBlockBytes = 1024;
 size_t header_bytes(const ResiduePlan &p) {
   const size_t words = (size_t)weight_words(p.nwc) + p.nwc + 2;
-  return up256(kHeadBytes + words * 4);
+  return up256(kHeadBytes + words * 4) + kBlockBytes - 256;
+}
+char *planes_of(char *arena, const ResiduePlan &p) {
+  const uintptr_t end = reinterpret_cast<uintptr_t>(arena) + header_bytes(p);
+  return reinterpret_cast<char *>(end / kBlockBytes * kBlockBytes);
 }
 
 struct Shape {
@@ -1545,7 +1552,7 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
     if (err == hipSuccess) err = launch_residue<T, C>(hi, a2, b2, C2, nullptr, false, st);
     return err;
   }
-  int8_t *R = reinterpret_cast<int8_t *>(rc.arena + header_bytes(p));
+  int8_t *R = reinterpret_cast<int8_t *>(planes_of(rc.arena, p));
   int8_t *Ap = R + result, *Bp = Ap + (size_t)room * s.a_plane;
 
   const std::vector<uint32_t> &table = residue_table(p.nunits, p.nsq, p.nwc);
