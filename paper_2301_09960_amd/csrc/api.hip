@@ -521,8 +521,24 @@ void keep_pool_memory(int dev) {
   g_pool_ready[dev] = true;
 }
 
-// `bytes`, or, where they cannot be had, as much of them as there is but no less
-// than `least`.
+// Stream-ordered memory on the device (the current one), or null; where it fails at
+// first the kept workspaces are given back (not under capture).
+char *allocate_on(hipStream_t st, size_t bytes, int dev) {
+  for (int tries = 0; tries < 2; ++tries) {
+    void *p = nullptr;
+    if (hipMallocAsync(&p, bytes > 0 ? bytes : 256, st) == hipSuccess && p) return static_cast<char *>(p);
+    (void)hipGetLastError();
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone ||
+        (tries == 0 && !g_kept.give_back(dev)))
+      break;
+  }
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+// `bytes`, or, where they cannot be had, what there is of them in an attached
+// workspace, and otherwise little more than `least`, which no call does without.
 int acquire(Workspace &ws, size_t bytes, size_t least, hipStream_t st) {
   ws.st = st;
   ws.bytes = bytes;
@@ -539,25 +555,12 @@ int acquire(Workspace &ws, size_t bytes, size_t least, hipStream_t st) {
     ws.dev = dev;
     return 0;
   }
-  void *p = nullptr;
-  auto allocate = [&](size_t size) {
-    if (hipMallocAsync(&p, size > 0 ? size : 256, st) == hipSuccess && p) return true;
-    (void)hipGetLastError();
-    p = nullptr;
-    return false;
-  };
-  if (!allocate(bytes)) {
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) != hipSuccess || capture != hipStreamCaptureStatusNone) {
-      (void)hipGetLastError();
-      return MPGEMM_ERR_WORKSPACE;
-    }
-    if (!g_kept.give_back(dev) || !allocate(bytes)) {
-      if (least >= bytes || !allocate(least)) return MPGEMM_ERR_WORKSPACE;
-      ws.bytes = least;
-    }
+  ws.base = allocate_on(st, bytes, dev);
+  if (!ws.base && least + 256 < bytes) {  // and a flag word, for the residues in it
+    ws.bytes = least + 256;
+    ws.base = allocate_on(st, ws.bytes, dev);
   }
-  ws.base = static_cast<char *>(p);
+  if (!ws.base) return MPGEMM_ERR_WORKSPACE;
   ws.owned = true;
   return 0;
 }
@@ -1272,13 +1275,12 @@ int lu_t(int fmt, int n, double *A, int lda, int K, hipStream_t stream) {
   const int64_t plane = (int64_t)lda * n;
   const int Kmax = std::min(K, n);
   const int rmax = n - std::min(Kmax, n);
-  void *buf = nullptr;
+  char *buf = nullptr;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return MPGEMM_ERR_HIP;
   const size_t bytes = rmax > 0 ? (size_t)C * 8 * ((size_t)2 * rmax * Kmax + (size_t)rmax * rmax) : 0;
-  if (bytes && (hipMallocAsync(&buf, bytes, stream) != hipSuccess || !buf)) {
-    (void)hipGetLastError();
-    return MPGEMM_ERR_WORKSPACE;
-  }
-  double *bl = static_cast<double *>(buf), *bu = bl + (size_t)C * rmax * Kmax, *P = bu + (size_t)C * rmax * Kmax;
+  if (bytes && !(buf = allocate_on(stream, bytes, dev))) return MPGEMM_ERR_WORKSPACE;
+  double *bl = reinterpret_cast<double *>(buf), *bu = bl + (size_t)C * rmax * Kmax, *P = bu + (size_t)C * rmax * Kmax;
   hipError_t e = hipSuccess;
   const int mode = g_opt.mode[fmt];
   for (int j0 = 0; j0 < n && e == hipSuccess && s == 0; j0 += K) {

@@ -249,3 +249,53 @@ def test_batch_padding_after_the_slices():
         torch.cuda.synchronize()
         for C, (a, b) in zip(Cs, pairs):
             assert torch.equal(C, mp.gemm("dd", a, b))
+
+
+def trim_pool():
+    """Frees what the device's stream-ordered pool keeps."""
+    import ctypes
+    import torch
+    torch.cuda.synchronize()
+    hip, pool = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p()
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), torch.cuda.current_device()) == 0
+    assert hip.hipMemPoolTrimTo(pool, ctypes.c_size_t(0)) == 0
+
+
+def test_when_memory_is_short():
+    """A device with less memory left than a call takes: a single product makes do
+    with what its slices need, a batch goes product by product; the results are the
+    usual ones."""
+    import torch
+    import paper_2301_09960_amd as mp
+    shapes = [(9000, 8800, 64), (8800, 9000, 80), (300, 200, 90), (17000, 16500, 48)]
+    pairs = [tall(m, n, k, i) for i, (m, n, k) in enumerate(shapes)]
+    Cs = [torch.empty((2, n, m), dtype=torch.float64, device="cuda") for m, n, _ in shapes]
+    mp.batched_cache_clear()
+    ws = torch.empty(max(mp.workspace_bytes("dd", "float", *s) for s in shapes), dtype=torch.uint8, device="cuda")
+    mp.set_workspace(ws)
+    try:
+        want = [mp.gemm("dd", a, b) for a, b in pairs]
+        torch.cuda.synchronize()
+    finally:
+        mp.set_workspace(None)
+    del ws
+    torch.cuda.empty_cache()
+    trim_pool()
+    filler = []
+    try:
+        while (free := torch.cuda.mem_get_info()[0]) > (6 << 30):
+            filler.append(torch.empty(min(free - (5 << 30), 64 << 30), dtype=torch.uint8, device="cuda"))
+        print(f"{free >> 20} MiB left", flush=True)
+        assert mp.workspace_bytes("dd", "float", *shapes[3]) > free
+        mp.gemm_batched("dd", [a for a, _ in pairs[:3]], [b for _, b in pairs[:3]], Cs[:3])
+        for C, w in zip(Cs[:3], want):
+            assert torch.equal(C, w)
+        mp.gemm("dd", *pairs[3], Cs[3])
+        assert torch.equal(Cs[3], want[3])
+        assert mp.last_num_slices() == mp.num_slices("dd", "float", 48)
+    finally:
+        del filler
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        mp.batched_cache_clear()
+        trim_pool()
