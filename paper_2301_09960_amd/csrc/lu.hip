@@ -96,24 +96,6 @@ struct Mat {
 
 constexpr int kLuThreads = 1024;
 
-// Unblocked LU of the K x K block at (j0, j0), in one workgroup: for each
-// column, divide below the pivot, then the rank-1 update of the rest.
-template <typename Num>
-__global__ __launch_bounds__(kLuThreads) void k_lu_diag(Mat<Num> A, int j0, int K) {
-  for (int j = 0; j < K; ++j) {
-    const Num piv = A.get(j0 + j, j0 + j);
-    for (int i = j + 1 + (int)threadIdx.x; i < K; i += kLuThreads)
-      A.put(j0 + i, j0 + j, ndiv(A.get(j0 + i, j0 + j), piv));
-    __syncthreads();
-    const int r = K - j - 1;
-    for (int idx = threadIdx.x; idx < r * r; idx += kLuThreads) {
-      const int i = j + 1 + idx % r, l = j + 1 + idx / r;
-      A.put(j0 + i, j0 + l, nfms(A.get(j0 + i, j0 + l), A.get(j0 + i, j0 + j), A.get(j0 + j, j0 + l)));
-    }
-    __syncthreads();
-  }
-}
-
 // The value of lane `src` (the same for the whole wavefront) in all lanes.
 template <typename Num>
 __device__ __forceinline__ Num read_num(const Num &v, int src) {
@@ -127,9 +109,9 @@ __device__ __forceinline__ Num read_num(const Num &v, int src) {
   return o;
 }
 
-// The same factorization for K <= kDiagLds, a thread per entry: the operations of
-// every entry and their order are those of k_lu_diag, so the factors are
-// identical.  Bound by the chain of the pivots: update, division, hand over.  A
+// Unblocked LU of the K x K block at (j0, j0), K <= kDiagLds, in one workgroup, a
+// thread per entry: for each column, divide below the pivot, then the rank-1 update
+// of the rest.  Bound by the chain of the pivots: update, division, hand over.  A
 // step passes on its column of L, its row of U and the diagonal entry after it
 // through LDS, and the threads of the next column form the next pivot themselves,
 // so a step has one barrier; with the block in LDS and two barriers a block of 32
@@ -137,7 +119,7 @@ __device__ __forceinline__ Num read_num(const Num &v, int src) {
 constexpr int kDiagLds = 32;
 
 template <typename Num>
-__global__ __launch_bounds__(kLuThreads) void k_lu_diag_lds(Mat<Num> A, int j0, int K) {
+__global__ __launch_bounds__(kLuThreads) void k_lu_diag(Mat<Num> A, int j0, int K) {
   static_assert(kDiagLds * kDiagLds == kLuThreads, "a thread per entry");
   __shared__ Num below[2][kDiagLds], right[2][kDiagLds], diag[2];
   const int i = threadIdx.x % kDiagLds, l = threadIdx.x / kDiagLds;
@@ -168,14 +150,6 @@ __global__ __launch_bounds__(kLuThreads) void k_lu_diag_lds(Mat<Num> A, int j0, 
     __syncthreads();
   }
   if (inside) A.put(j0 + i, j0 + l, a);
-}
-
-template <typename Num>
-void launch_lu_diag(const Mat<Num> &M, int j0, int K, hipStream_t st) {
-  if (K <= kDiagLds)
-    hipLaunchKernelGGL((k_lu_diag_lds<Num>), dim3(1), dim3(kLuThreads), 0, st, M, j0, K);
-  else
-    hipLaunchKernelGGL((k_lu_diag<Num>), dim3(1), dim3(kLuThreads), 0, st, M, j0, K);
 }
 
 // U12 = L11^-1 A12 in place: thread per column l of A12, forward substitution
@@ -496,13 +470,14 @@ unsigned grid_for(int64_t work) { return (unsigned)std::max<int64_t>(1, std::min
 template <typename Num>
 hipError_t lu_panel(double *A, int64_t ld, int64_t plane, int j0, int K, int n, hipStream_t st) {
   const Mat<Num> M{A, ld, plane};
+  static_assert(kInner <= kDiagLds, "an inner block fits the unblocked kernel");
   if (K <= kInner) {
-    launch_lu_diag<Num>(M, j0, K, st);
+    hipLaunchKernelGGL((k_lu_diag<Num>), dim3(1), dim3(kLuThreads), 0, st, M, j0, K);
   } else {
     const int end = j0 + K;
     for (int jj = j0; jj < end; jj += kInner) {
       const int kb = std::min(kInner, end - jj), r = end - jj - kb;
-      launch_lu_diag<Num>(M, jj, kb, st);
+      hipLaunchKernelGGL((k_lu_diag<Num>), dim3(1), dim3(kLuThreads), 0, st, M, jj, kb);
       if (r == 0) break;
       launch_sweeps<Num>(M, jj, kb, end, st);
       const unsigned tiles = (unsigned)ceil_div(r, kRankTile);
