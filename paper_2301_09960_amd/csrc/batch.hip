@@ -121,7 +121,7 @@ struct ResidueBatch {
   };
   std::vector<Slot> slots;
   int nw = 0, tiles0 = 0, strips = 0, nitems1 = 0, nitems3 = 0;
-  int64_t blocks = 0, blocksc = 0;
+  int blocks = 0;
   size_t scratch = 0, planes_bytes = 0;  // where the planes' part of the workspace begins; the operands' planes
   bool shared = false;                   // other runs write to it
   size_t off_ran = 0;  // FLOAT form: a word set once slices have been written to the operands' planes
@@ -212,7 +212,6 @@ struct ResidueBatch {
       // blocks of its combine launch, counted from the launch's first product
       const bool first = i == 0 || slots[i - 1].plan.nwc != s.plan.nwc;
       prec[i] = first ? 0 : prec[i - 1] + (int)(slots[i - 1].mbp * slots[i - 1].nbp);
-      blocksc += s.mbp * s.nbp;
       const std::array<int, 3> key{s.plan.nunits, s.plan.nsq, s.plan.nwc};
       size_t at = SIZE_MAX;
       for (const auto &kn : known)
@@ -290,6 +289,18 @@ struct ResidueBatch {
            hipMemcpy(ws + off_bounds, bounds, sizeof(bounds), hipMemcpyHostToDevice) == hipSuccess;
   }
 
+  // Whether every block and work item can be numbered in an int.
+  bool countable() const {
+    int64_t split = 0, combine = 0, tiles = 0, groups = 0;
+    for (const Slot &s : slots) {
+      split += (s.mbp + s.nbp) * s.kbp;
+      combine += s.mbp * s.nbp;
+      tiles += ceil_div((int64_t)s.m + s.n + 64, (int64_t)64) * ceil_div((int64_t)s.k, (int64_t)64);
+      groups += s.mbp * s.nbp / 16 * s.plan.nchunks * s.plan.nunits;
+    }
+    return std::max(std::max(split, combine), std::max(tiles, groups)) <= 0x7fffffffLL;
+  }
+
   // The launch sequence in three parts (descriptors at off_ops, off_descs of the workspace).
   template <typename T, int C>
   hipError_t launch_split(char *ws, size_t off_ops, hipStream_t st) const {
@@ -301,7 +312,7 @@ struct ResidueBatch {
     if (e == hipSuccess) e = launch_residue_max_batched<T>(ops, pre0, 2 * n, tiles0, st);
     if (e == hipSuccess && float_form)
       e = launch_residue_sample<T, C>(ops, preb + 2 * n + 1 + n + 1, 2 * n, strips, st);
-    if (e == hipSuccess) e = launch_residue_split_batched<T, C>(nw, ops, preb, 2 * n, (int)blocks, st);
+    if (e == hipSuccess) e = launch_residue_split_batched<T, C>(nw, ops, preb, 2 * n, blocks, st);
     return e;
   }
   hipError_t launch_gemm(char *ws, size_t off_descs, hipStream_t st) const {
@@ -743,12 +754,13 @@ struct FormatPlan : BatchPlan {
       o += align256(bytes);
       return at;
     };
+    for (const Run &r : runs)
+      if (!r.res.countable()) return MPGEMM_ERR_TOO_LARGE;
     plain.layout(take, split_kernel);
     size_t planes = 0;
     for (Run &r : runs) {
       r.fallback.layout(take, split_kernel);
       r.res.layout(take, sizeof(T), mode == MPGEMM_MODE_FLOAT);
-      if (r.res.blocks > 0x7fffffffLL || r.res.blocksc > 0x7fffffffLL) return MPGEMM_ERR_TOO_LARGE;
       planes = std::max(planes, r.res.place_planes(r.fallback.scratch_bytes));
       for (size_t i = 0; i < r.res.slots.size(); ++i)
         for (auto &f : r.fallback.slots)
