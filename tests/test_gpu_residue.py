@@ -415,3 +415,39 @@ def test_slices_are_needed(mp):
     assert flagged(mp, "dd", dev(A), dev(B))[1]
     A, B = W.gen_pair("dd", 70, 66, 200, E=50, seed=1)
     assert not flagged(mp, "dd", dev(A), dev(B))[1]
+
+
+def exact_integers(m, n, k):
+    """Operands of small integers and their exact product, equal in binary64."""
+    rng = np.random.default_rng(m + n + k)
+    a = rng.integers(-2 ** 15, 2 ** 15, (k, m)).astype(np.float64)
+    b = rng.integers(-2 ** 15, 2 ** 15, (n, k)).astype(np.float64)
+    return dev(np.stack([a, 0 * a])), dev(np.stack([b, 0 * b])), b @ a
+
+
+@pytest.mark.parametrize("mode", ["int8", "float"])
+@pytest.mark.parametrize("tile", [1, 3])
+@pytest.mark.parametrize("m,n,k", [(70, 66, 32769), (33, 300, 65536), (300, 40, 70001)])
+def test_k_chunks_on_several_blocks(mp, mode, tile, m, n, k):
+    """Chunks of k on more than one block of C, in both forms and tile sizes."""
+    say(f"chunks {mode} tile {tile} {m}x{n}x{k}")
+    A, B, want = exact_integers(m, n, k)
+    mp.set_int8_tile(tile)
+    try:
+        C = mp.gemm("dd", A, B, mode=mode).cpu().numpy()
+    finally:
+        mp.set_int8_tile(0)
+    assert np.array_equal(C[0], want) and not C[1].any()
+
+
+@pytest.mark.parametrize("mode", ["int8", "float"])
+def test_k_chunks_in_a_batch(mp, mode):
+    """A batch of products with one, two and three chunks, some of one combine launch."""
+    shapes = [(70, 66, 100), (65, 34, 32769), (40, 130, 70000), (33, 33, 33000), (300, 290, 32768)]
+    data = [exact_integers(*s) for s in shapes]
+    say(f"chunks in a batch {mode}")
+    for _ in range(2):
+        Cs = mp.gemm_batched("dd", [d[0] for d in data], [d[1] for d in data], mode=mode)
+        for C, (_, _, want), s in zip(Cs, data, shapes):
+            C = C.cpu().numpy()
+            assert np.array_equal(C[0], want) and not C[1].any(), s
