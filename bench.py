@@ -17,7 +17,9 @@ Extra objects on the JSON line:
   stages       -- per format: milliseconds of the split and of what follows it.
   int8         -- the same products in the INT8 form (the product of the operands
                   rounded to D digits, by residues), timed the same way; speedup
-                  over the FLOAT form at the same error bound.
+                  over the FLOAT form, and over binary64 slices (Algorithm 1 as
+                  written, the FLOAT form with its slice count set by the caller),
+                  at the same error bound.
   data_chosen_pairs -- the same products with the slice products chosen
                   from the data (per-tile pair sets, certified by
                   construction): call time, mean pairs per tile, certificate.
@@ -50,7 +52,9 @@ FP64_MFMA_PEAK_TFLOPS = 78.6
 FP32_MFMA_PEAK_TFLOPS = 157.3
 INT8_MFMA_PEAK_TOPS = 5000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_gemm_residue_qd_n4096.json")
-GEMM_SOURCE = os.path.join(ROOT, "paper_2301_09960_amd", "csrc", "residue.hip")
+# the residue GEMM: its kernel, the tile loop that issues its loads, its plans and the planes' layout
+GEMM_SOURCES = [os.path.join(ROOT, "paper_2301_09960_amd", "csrc", f)
+                for f in ("residue.hip", "int8_tile.h", "residue.h", "layout.h")]
 
 
 def log(msg):
@@ -87,7 +91,8 @@ def parse():
     ap.add_argument("--kernel", help="substring of the kernel's name")
     ap.add_argument("--label", default="", help="name written into the summary (default: --kernel)")
     ap.add_argument("--algorithmic-bytes", type=float)
-    ap.add_argument("--source", help="the kernel's source file (hashed)")
+    ap.add_argument("--source", action="append", default=[],
+                    help="a source file of the kernel (hashed; default: those of the residue GEMM)")
     ap.add_argument("--command", action="append", default=[], help="command of a run, recorded as given")
     ap.add_argument("--out", default="")
     return ap.parse_args()
@@ -105,7 +110,7 @@ MODES_HELP = """measurement modes besides the benchmark line:
       the simple in-format products (DD, TS, D+S; with and without LDS
       staging; Section 4.4) beside the Ozaki products of the same inputs
   python bench.py --traffic --fetch DIR1 --write DIR2 --kernel NAME
-      --algorithmic-bytes B --source FILE [--out traffic.json]
+      --algorithmic-bytes B [--source FILE ...] [--out traffic.json]
       HBM bytes per launch of one kernel from two rocprofv3 --pmc runs
       (FETCH_SIZE, WRITE_SIZE in KiB per dispatch), each scaled by what the
       counter reads for the plain 1 GiB copies of --copy-calibration
@@ -143,9 +148,12 @@ def residue_products(fmt, mode, D, k):
     return best
 
 
-def source_hash(path):
-    with open(path, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+def source_hash(paths):
+    h = hashlib.sha256()
+    for path in paths:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def traffic_for(kernel_key):
@@ -156,7 +164,7 @@ def traffic_for(kernel_key):
             t = json.load(f)
     except (OSError, ValueError):
         return None
-    if t.get("source_sha256_16") != source_hash(GEMM_SOURCE) or t.get("kernel") != kernel_key:
+    if t.get("source_sha256_16") != source_hash(GEMM_SOURCES) or t.get("kernel") != kernel_key:
         return None
     return t.get("bytes_per_launch")
 
@@ -431,9 +439,9 @@ def run_mixed_batch(mp, torch, pool, mode="float", seed=31):
 def main():
     args = parse()
     if args.traffic:
-        if not (args.fetch and args.write and args.kernel and args.source and args.algorithmic_bytes):
+        if not (args.fetch and args.write and args.kernel and args.algorithmic_bytes):
             raise SystemExit("--traffic needs --fetch, --write, --kernel, --algorithmic-bytes and --source")
-        summ = traffic_summary(args.fetch, args.write, args.kernel, args.algorithmic_bytes, args.source,
+        summ = traffic_summary(args.fetch, args.write, args.kernel, args.algorithmic_bytes, args.source or GEMM_SOURCES,
                                args.label or args.kernel, args.command)
         text = json.dumps(summ, indent=1)
         if args.out:
@@ -471,23 +479,25 @@ def main():
     slices = {f: mp.num_slices(f, "float", n) for f in fmts}
     torch.cuda.synchronize()
 
-    def timed(mode):
+    def timed(mode, D=None):
+        """Steps in a form; D: {format: slice count} set by the caller."""
+        name = mode if D is None else f"{mode} slices"
         for w in range(args.warmup):
             for f in fmts:
-                mp.gemm(f, *inputs[f], outs[f], mode=mode)
+                mp.gemm(f, *inputs[f], outs[f], mode=mode, slices=D and D[f])
             torch.cuda.synchronize()
-            log(f"{mode}: warmup step {w + 1}/{args.warmup} done")
+            log(f"{name}: warmup step {w + 1}/{args.warmup} done")
         mp.profile_enable(True)
         torch.cuda.synchronize()
         t_start = time.perf_counter()
         for _ in range(args.steps):
             for f in fmts:
-                mp.gemm(f, *inputs[f], outs[f], mode=mode)
+                mp.gemm(f, *inputs[f], outs[f], mode=mode, slices=D and D[f])
         torch.cuda.synchronize()
         t_end = time.perf_counter()
         mp.profile_enable(False)
         sp, gm = mp.profile_read()
-        log(f"{mode}: timed {args.steps} steps in {t_end - t_start:.3f} s")
+        log(f"{name}: timed {args.steps} steps in {t_end - t_start:.3f} s")
         return t_start, t_end, sp, gm
 
     t0, t1, split_ms, gemm_ms = timed("float")
@@ -534,8 +544,11 @@ def main():
     int8 = None
     if not args.no_int8 and all(f != "ts" for f in fmts):
         i0, i1, isp, igm = timed("int8")
+        _, _, ssp, sgm = timed("float", slices)
         int8 = {"wall_speedup": round((t1 - t0) / (i1 - i0), 3)}
         for idx, f in enumerate(fmts):
+            float_ms = stages[f]["split_ms"] + stages[f]["gemm_kernel_ms"]
+            slices_ms = float(np.mean(ssp[idx::len(fmts)])) + float(np.mean(sgm[idx::len(fmts)]))
             D8 = mp.num_slices(f, "int8", n)
             call_ms = float(np.mean(isp[idx::len(fmts)])) + float(np.mean(igm[idx::len(fmts)]))
             gemm8 = float(np.mean(igm[idx::len(fmts)]))
@@ -551,8 +564,9 @@ def main():
                 "effective_gflops": round(2.0 * n ** 3 / (call_ms * 1e-3) / 1e9, 1),
                 "int8_tops": round(ops / (gemm8 * 1e-3) / 1e12, 1),
                 "int8_mfma_frac": round(ops / (gemm8 * 1e-3) / 1e12 / INT8_MFMA_PEAK_TOPS, 4),
-                "speedup_vs_float_slices": round(
-                    (stages[f]["split_ms"] + stages[f]["gemm_kernel_ms"]) / call_ms, 3),
+                "speedup_vs_float": round(float_ms / call_ms, 3),
+                "float_slices_ms": round(slices_ms, 3),
+                "speedup_vs_float_slices": round(slices_ms / call_ms, 3),
             }
             if not args.no_certify:
                 # equal accuracy: the certificate of the INT8 result (one
@@ -578,8 +592,8 @@ def main():
                     "D": Dc,
                     "log2_worst_bound_ratio": round(float(np.log2(float(wc.cpu()[0]))), 2),
                     "call_ms": round(cms, 3),
-                    "speedup_vs_float_slices": round(
-                        (stages[f]["split_ms"] + stages[f]["gemm_kernel_ms"]) / cms, 3),
+                    "speedup_vs_float": round(float_ms / cms, 3),
+                    "speedup_vs_float_slices": round(slices_ms / cms, 3),
                 }
                 log(f"int8 {f} certified: {int8[f]['certified']}")
 
