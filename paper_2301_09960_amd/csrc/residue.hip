@@ -227,11 +227,11 @@ __device__ __forceinline__ bool last_grid_covered(const uint32_t *changes, int b
 // ORs the changes of an element, places from 2^(E - bits) up, into `changes`.  A component's two's complement has those of the element between its
 // own last change (a borrow of the component below goes no higher) and its sign, so
 // each is placed for itself, without its last change and the place above it.  An
-// element whose components overlap, or exceed 2^E, adds none.
+// element whose components overlap or touch, or exceed 2^E, adds none.
 template <typename T, int C>
 __device__ __forceinline__ void add_changes(const T (&x)[C], int E, int bits, uint32_t *changes) {
   uint64_t c[C];
-  int off[C], above = E + 1;
+  int off[C], above = E + 2;
   bool apart = true;
 #pragma unroll
   for (int r = 0; r < C; ++r) {
@@ -243,7 +243,7 @@ __device__ __forceinline__ void add_changes(const T (&x)[C], int E, int bits, ui
     c[r] &= ~(low | (low << 1));
     off[r] = q - (E - bits);
     if (M != 0) {
-      apart = apart && q + (sizeof(T) == 8 ? 53 : 24) <= above;
+      apart = apart && q + (sizeof(T) == 8 ? 53 : 24) < above;
       above = q;
     }
   }
