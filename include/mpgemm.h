@@ -174,7 +174,11 @@ int mpgemm_ds_simple(int staging, int m, int n, int k, const double *Ahi, const 
  * (up to 6 shapes; releasing the least recently used one synchronizes the
  * device); later calls with the same shape replay it after one copy of this
  * call's pointers.  The cached workspace of a shape stays allocated until it
- * is released or mpgemm_batched_cache_clear is called.  Batched calls of one
+ * is released or mpgemm_batched_cache_clear is called.  It holds the planes of all
+ * products up to the limits of a single call's (mpgemm_workspace_bytes); beyond them
+ * the products are formed run after run, and where the device has not that much left
+ * one after the other, unless a C shares memory with an operand: then from slices.
+ * Batched calls of one
  * shape on one stream must not be issued from two host threads at once.
  * Both slice forms (the thread's mode for the format).  In the INT8 form each
  * product takes a tile configuration by its size (two persistent launches,
@@ -325,12 +329,14 @@ int mpgemm_set_workspace(void *dev_ptr, size_t bytes);
 /*
  * C = AB with an a-posteriori certificate.  Computes C exactly as mpgemm_<fmt>
  * does, in the thread's slice form and with its slice count, then bounds its
- * error from the same split (Algorithm 1, Section 3; in the INT8 form digit
+ * error from the split of Algorithm 1 (Section 3; in the INT8 form digit
  * plane s is the slice, at most 2^(E - 7 (s - 1)), the remainder at most
  * 2^(E - 7 D)):
  * with A = A_s + RA (slices plus the remainder after D passes) and likewise B,
  * AB - C = (the pairs a + b > D + 1 that are not formed) + A_s RB + RA B + (the
- * rounding of the sum to c components).  Each part is bounded per entry from
+ * rounding of the sum to c components).  A product by residues leaves no pairs
+ * out, and the remainders of its operands, rounded once, are within the bounds of
+ * these, so that the same sum bounds its error.  Each part is bounded per entry from
  * the slice exponents, the remainder bound of the last pass, the row sums of
  * |A| and column sums of |B|, and one extra binary64 product |A_0||B_0| of the
  * leading components, which also gives a lower bound of (|A||B|)_ij.

@@ -299,8 +299,9 @@ class _options:
 def gemm(fmt, A, B, C=None, *, mode=None, slices=None, stream=None):
     """C = A B (Ozaki scheme) for torch tensors in the conventions above.
 
-    ``mode``: 'float' (binary64/binary32 slices) or 'int8'; ``slices``: D
-    (None/0 = automatic).  Enqueued on ``stream`` (default: the current
+    ``mode``: 'float' (binary64/binary32 slices; by residues what the automatic
+    number of them stands for) or 'int8'; ``slices``: D (None/0 = automatic).
+    Enqueued on ``stream`` (default: the current
     stream); returns C without synchronizing.
     """
     import torch

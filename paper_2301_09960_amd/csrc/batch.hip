@@ -41,12 +41,12 @@ namespace {
 constexpr int kMaxPlans = 6;
 constexpr int kPersistentGrid = 512;  // 2 workgroups per CU on 256 CUs
 
-// Tile configuration of one product of an INT8 batch: the one set for the
+// Tile configuration of one product by residues of a batch: the one set for the
 // thread (2 and 4 run as 3); else the 256 x 256 tiles unless padding to them
-// exceeds 1.5 times the area padded to 128 x 128.  In batches of products of
-// 64 to 1024 rows the 128 x 128 tiles run at about two thirds of the rate of
-// the 256 x 256 ones per padded operation (1.03 against 1.55 POP/s), not at
-// half as in one large product, whose rule takes twice the area.
+// exceeds 1.5 times the area padded to 128 x 128.  Against one configuration for all
+// products (by this rule, 128 x 128, 256 x 256): 128 QD products of 64 to 1024 in the
+// FLOAT form 3347, 3471 and 3477 us; 256 DD ones, INT8, 2993, 2991 and 3069; 64 DD
+// ones of 64 to 300, INT8, 322, 287 and 315; 200 QD ones of 64 to 200 917, 886, 1086.
 int batch_int8_cfg(int64_t m, int64_t n, int cfg_override) {
   if (cfg_override >= 1) return int8_tile_config(m, n, cfg_override) == 1 ? 1 : 3;
   const int64_t area3 = ceil_div(m, 256) * ceil_div(n, 256) * 4, area1 = ceil_div(m, 128) * ceil_div(n, 128);

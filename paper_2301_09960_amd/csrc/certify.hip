@@ -1,4 +1,4 @@
-// A-posteriori error certificate of the slice product (binary64/binary32 or INT8 slices).
+// A-posteriori error certificate of a product (binary64/binary32 or INT8 slices).
 //
 // With D slices per row of A and column of B (Algorithm 1, Section 3), write
 // A = A_s + RA and B = B_s + RB, where A_s is the sum of the slices and RA the
@@ -6,11 +6,23 @@
 // a + b <= D + 1 (the pairs the statement after Fig. 1 keeps) differs from AB by
 //   AB - C_tri = sum_{a,b <= D, a + b > D + 1} A_a B_b + A_s RB + RA B,
 // and the computed C differs from C_tri by the rounding of the accumulation to
-// c components.  Per entry (i, j) this file bounds each part from quantities
-// the split already produced (in either slice form: an INT8 digit plane is a
+// c components.
+//
+// A product by residues (residue.h) is that of the operands rounded to a fixed grid,
+// A = A_f + RA', all pairs included: AB - C_res = A_f RB' + RA' B, and C is C_res
+// rounded once.  Its remainders are bounded by those of the slices: in the INT8 form
+// the grid is that of the last digit and the rounding to nearest, |RA'| <= u_D / 2; in
+// the FLOAT form a vector is either exact on the fixed grid (RA' = 0) or its grid is no
+// coarser than the one the last pass had (last_grid_covered, residue.hip; the products
+// of other vectors go by slices), and |RA'| is at most half a step of it.  So the terms
+// below hold for it too; T1 is then nothing that was left out, and only keeps the bound
+// of the two ways the same.
+//
+// Per entry (i, j) this file bounds each part from the slices' exponents (formed for
+// this alone where C came from residues; in either slice form: an INT8 digit plane is a
 // slice on the fixed grid of E - 6 - 7 (s - 1)), and bounds (|A||B|)_ij from below:
 //   T1 = k sum_{dropped (a, b)} 2^(eA_a,i + eB_b,j)      |A_a,ip| <= 2^eA_a,i
-//   T2 = rB_j (rsA_i + k rA_i)                             |A_s| <= |A| + |RA|
+//   T2 = rB_j (rsA_i + k rA_i)                             |A_s|, |A_f| <= |A| + |RA|
 //   T3 = rA_i csB_j
 //   T4 = 2^(4 - S c) UB_ij                                 final rounding of C
 // with rA_i the bound on the remainder after the last slice (remainder_bound),

@@ -20,9 +20,9 @@
 // the components read off the leading bits of X.
 //
 // Measured at n = 4096, E = 16 (before: the digit pairs of int8.hip): DD 32
-// products, 8.43 -> 3.00 ms (GEMM 8.14 -> 2.09 ms, 2.10 POP/s); QD 73 products,
-// 28.2 -> 6.86 ms (GEMM 27.1 -> 4.64 ms).  256 DD products of 64 to 1024 as one
-// batch: 4.68 -> 4.02 ms.
+// products, 8.58 -> 2.65 ms (GEMM 8.14 -> 2.16 ms, 2.04 POP/s); QD 72 products,
+// 28.9 -> 6.00 ms (GEMM 27.1 -> 4.58 ms).  256 DD products of 64 to 1024 as one
+// batch: 4.69 -> 2.93 ms.
 #include "residue.h"
 
 #include <algorithm>
@@ -435,7 +435,8 @@ __device__ __forceinline__ int settle_strip(const T *x, int64_t comp_stride, int
 // DD n = 4096 (32 planes) 616 -> 496 us, QD (68 planes) 1566 -> 1334 us.  The chains
 // of a residue are hidden by wavefronts only: four to a SIMD (operands in LDS, the
 // checks before the products, scalar constants) against two or three took FLOAT DD
-// (37 planes) from 781 to 611 us, QD from 1334 to 1091.
+// (37 planes) from 781 to 611 us, QD from 1334 to 1091; now 593 and 1113, ties to even
+// included (12 and 30 us).
 template <typename T, int C, int NW, int ORIENT>
 __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u_end,
                               int part, int parts, bool check, SplitLds<NW> &lds) {
@@ -1080,7 +1081,9 @@ __global__ __launch_bounds__(kThreads) void k_upload(Upload data, int n, uint32_
 // two tiles).  Bound by the latency of its loads, 16 in flight per thread.
 //
 // In the FLOAT form strips with zeros among a vector's first 32 elements take their
-// samples here (settle_strip).
+// samples here (settle_strip).  For all strips, with the split's own look at the first
+// elements left out, that took DD 64^3 from 30.4 to 31.5 us and TD 200 x 150 x 333 from
+// 50.4 to 51.3.
 template <typename T>
 struct MaxOperand {
   const T *X;
