@@ -175,7 +175,7 @@ int mpgemm_ds_simple(int staging, int m, int n, int k, const double *Ahi, const 
  * device); later calls with the same shape replay it after one copy of this
  * call's pointers.  The cached workspace of a shape stays allocated until it
  * is released or mpgemm_batched_cache_clear is called.  It holds the planes of all
- * products up to the limits of a single call's (mpgemm_workspace_bytes); beyond them
+ * products up to 8 GiB or 7/4 of what their slices (digits) take; beyond that
  * the products are formed run after run, and where the device has not that much left
  * one after the other, unless a C shares memory with an operand: then from slices.
  * Batched calls of one

@@ -275,8 +275,8 @@ struct Plan {
 // 34.8 ms with all planes (37 GB), 34.1 in 8 GiB and 31.9 to 33.1 in 1 to 4; QD 16384^2
 // x 64 16.8 (18 GB), 16.9 and 16.9 to 18.9; DD 20000^2 x 2000 43.1 (19 GB) and 44.4.
 constexpr size_t kResidueRoom = size_t(8) << 30;
-size_t residue_room(size_t need, size_t slices) {
-  return std::min(need, std::max(slices + align256(slices / 4), kResidueRoom));
+size_t residue_room(size_t need, size_t slices, int quarters) {
+  return std::min(need, std::max(align256(slices / 4 * quarters), kResidueRoom));
 }
 
 // Smallest inner dimension for which the FLOAT form goes by residues: its check
@@ -349,7 +349,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
       p.off_res_exp_b = take((size_t)n * 4);
       p.off_arena = o;
       take(residue_bytes(p.res, p.res_cfg, m, n, k));
-      p.room = p.off_flag = std::max(residue_room(o, p.slices_total), p.slices_total);
+      p.room = p.off_flag = std::max(residue_room(o, p.slices_total, 5), p.slices_total);
       p.total = p.off_flag + 256;
     } else {
       p.res.nunits = 0;
@@ -387,7 +387,7 @@ Plan make_plan(int fmt, int mode, int64_t m, int64_t n, int64_t k, int D, bool a
   }
   p.slices_total = p.total = o;
   if (p.res.nunits > 0)
-    p.total = std::max(o, residue_room(p.off_arena + align256(residue_bytes(p.res, p.res_cfg, m, n, k)), o));
+    p.total = std::max(o, residue_room(p.off_arena + align256(residue_bytes(p.res, p.res_cfg, m, n, k)), o, 5));
   p.room = p.total;
   return p;
 }

@@ -35,9 +35,9 @@ int check_device_cached();
 
 int hip_status(hipError_t e);
 
-// What a call takes for residues that need `need` bytes and whose slices (digits)
-// take `slices`.
-size_t residue_room(size_t need, size_t slices);
+// What a call takes for residues that need `need` bytes: at most 8 GiB or so many
+// quarters of what its slices (digits) take, whichever is more.
+size_t residue_room(size_t need, size_t slices, int quarters);
 
 // hipMalloc on the device (the current one); the workspaces kept between calls are
 // given back where it fails at first.
