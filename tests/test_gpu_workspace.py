@@ -299,3 +299,29 @@ def test_when_memory_is_short():
         torch.cuda.empty_cache()
         mp.batched_cache_clear()
         trim_pool()
+
+
+def test_digit_form_batch_in_runs():
+    """INT8 products of long k, whose planes take twice their digits: two runs, in one
+    where a C lies in another product's operand; each as its single call."""
+    import torch
+    import paper_2301_09960_amd as mp
+    shapes = [(20, 24, 300000)] * 8 + [(70, 90, 100)]
+    mp.batched_cache_clear()
+    pairs = [tall(m, n, k, i) for i, (m, n, k) in enumerate(shapes)]
+    As, Bs = [a for a, _ in pairs], [b for _, b in pairs]
+    want = [mp.gemm("dd", a, b, mode="int8") for a, b in pairs]
+    Cs = [torch.empty_like(w) for w in want]
+    used = held(lambda: mp.gemm_batched("dd", As, Bs, Cs, mode="int8"))
+    D = mp.num_slices("dd", "int8", 300000)
+    digits = 8 * D * 2 * 128 * 300032
+    print(f"INT8 runs: plan {used >> 20} MiB, digits {digits >> 20} MiB", flush=True)
+    assert used <= 1.8 * digits
+    for C, w in zip(Cs, want):
+        assert torch.equal(C, w)
+    flat = As[0].clone().reshape(-1)  # the last product's C in the first one's A
+    C = flat[: Cs[-1].numel()].reshape(Cs[-1].shape)
+    mp.gemm_batched("dd", [flat.reshape(As[0].shape)] + As[1:], Bs, Cs[:-1] + [C], mode="int8")
+    for got, w in zip(Cs[:-1] + [C], want):
+        assert torch.equal(got, w)
+    mp.batched_cache_clear()
