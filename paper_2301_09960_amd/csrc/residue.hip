@@ -333,6 +333,7 @@ __device__ __forceinline__ void element_words(const T (&x)[C], int E, int P, boo
   uint32_t w[NW + 1];
 #pragma unroll
   for (int i = 0; i <= NW; ++i) w[i] = 0u;
+  bool whole = false;  // the last component is there, and so all of the element
 #pragma unroll
   for (int r = 0; r < C; ++r) {
     int64_t M;
@@ -340,6 +341,7 @@ __device__ __forceinline__ void element_words(const T (&x)[C], int E, int P, boo
     parts_of(x[r], M, q);
     const int off = q - P;
     const int sh = off >= 0 ? 0 : off > -63 ? -off : 63;
+    if (r == C - 1) whole = M != 0 && (M & ((int64_t(1) << sh) - 1)) == 0;
     if (check) {
       if (r > 0 && M != 0 && q + (sizeof(T) == 8 ? 53 : 24) > E - 20) odd = true;
       inexact = inexact || (M & ((int64_t(1) << sh) - 1)) != 0;
@@ -347,8 +349,8 @@ __device__ __forceinline__ void element_words(const T (&x)[C], int E, int P, boo
     window_add_shifted<NW + 1>(w, M >> sh, off < 0 ? 0 : off);
   }
   inexact = inexact || w[0] != 0u;
-  uint32_t carry = w[0] >> 31;
-  const bool near_half = w[0] - (0x80000000u - C) <= (uint32_t)C;
+  uint32_t carry = w[0] > 0x80000000u - (w[1] & 1u) ? 1u : 0u;
+  const bool near_half = !whole && w[0] - (0x80000000u - C) <= (uint32_t)C;
   if (__builtin_expect(__any(near_half), 0)) {
     if (near_half) carry = rounds_up<T, C>(x, P, w[0], (w[1] & 1u) != 0u) ? 1u : 0u;
   }
