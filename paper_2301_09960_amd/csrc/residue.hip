@@ -452,15 +452,6 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
   const int t = threadIdx.x, l = t >> 2, lane = t % 64;
   const int v = (int)(vb * kBlk8) + (l & 31);
   const int p0 = (int)(kb * kKBlk8) + 16 * (l >> 5) + 4 * (t & 3);
-  const int64_t plane = op.nbp * op.kbp * 1024;
-  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
-  if (kb * kKBlk8 >= op.len) {  // padding of k
-    if (part == 0 && (!op.padded || *op.padded != 0))
-      for (int u = 0, n = group_planes(u_first, u_end, op.nsq); u < n; ++u)
-        *reinterpret_cast<uint32_t *>(dst + u * plane) = 0u;
-    return;
-  }
-
   int E = kZeroExp;
   if (v < op.nvec) E = vector_exponent<T>(static_cast<const U *>(op.mu)[v], op.float_form);
   const bool finite = E != kZeroExp && E != kNonFinite;
@@ -535,6 +526,8 @@ __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool liv
 
   // a product known to go by slices needs no planes (a late look would do)
   if (__builtin_amdgcn_readfirstlane(flagged) != 0) return;
+  const int64_t plane = op.nbp * op.kbp * 1024;
+  int8_t *dst = op.planes + (vb * op.kbp + kb) * 1024 + 4 * t;
   auto product = [&](int rb, int j, bool y) {  // 32 bases of row block rb, 32 elements j
     i16v acc;
 #pragma unroll
@@ -642,6 +635,15 @@ __global__ __launch_bounds__(kThreads, NW > 8 ? 3 : 4) void k_residue_split(cons
   const int end = u_end < 0 ? op.nunits : u_end, part = blockIdx.y, parts = gridDim.y;
   const bool check = op.float_form != 0 && u_first == 0 && blockIdx.y == 0;
   __shared__ SplitLds<NW> lds;
+  if (live_only && op.orient == 0) {  // A's blocks past those with elements: padding of k
+    const int64_t nb = ceil_div((int64_t)op.nvec, (int64_t)kBlk8), kb = blk / nb;
+    if (kb * kKBlk8 >= op.len) {
+      if (op.padded && *op.padded == 0) return;
+      int8_t *to = op.planes + (blk % nb * op.kbp + kb) * 1024 + 4 * threadIdx.x;
+      for (int u = 0; u < end + op.nsq; ++u) *reinterpret_cast<uint32_t *>(to + u * (op.nbp * op.kbp * 1024)) = 0u;
+      return;
+    }
+  }
   if (op.orient == 0)
     residue_block<T, C, NW, 0>(op, blk, live_only != 0, u_first, end, part, parts, check, lds);
   else
