@@ -20,9 +20,9 @@
 // the components read off the leading bits of X.
 //
 // Measured at n = 4096, E = 16 (before: the digit pairs of int8.hip): DD 32
-// products, 8.58 -> 2.65 ms (GEMM 8.14 -> 2.16 ms, 2.04 POP/s); QD 72 products,
+// products, 8.58 -> 2.63 ms (GEMM 8.14 -> 2.16 ms, 2.04 POP/s); QD 72 products,
 // 28.9 -> 6.00 ms (GEMM 27.1 -> 4.58 ms).  256 DD products of 64 to 1024 as one
-// batch: 4.69 -> 2.93 ms.
+// batch: 4.69 -> 2.92 ms.
 #include "residue.h"
 
 #include <algorithm>
@@ -437,8 +437,8 @@ __device__ __forceinline__ int settle_strip(const T *x, int64_t comp_stride, int
 // DD n = 4096 (32 planes) 616 -> 496 us, QD (68 planes) 1566 -> 1334 us.  The chains
 // of a residue are hidden by wavefronts only: four to a SIMD (operands in LDS, the
 // checks before the products, scalar constants) against two or three took FLOAT DD
-// (37 planes) from 781 to 611 us, QD from 1334 to 1091; now 593 and 1113, ties to even
-// included (12 and 30 us).
+// (37 planes) from 781 to 611 us, QD from 1334 to 1091; now 581 and 1087, ties to even
+// included (2 and 9 us).
 template <typename T, int C, int NW, int ORIENT>
 __device__ void residue_block(const ResidueOperand<T> &op, int64_t blk, bool live_only, int u_first, int u_end,
                               int part, int parts, bool check, SplitLds<NW> &lds) {
