@@ -411,10 +411,13 @@ __device__ __forceinline__ void load_element(const T *x, int64_t comp_stride, in
 
 // kSettled where sampled elements settle a vector.  A workgroup takes 16 vectors, a
 // thread of it every 16th element of one (x), with exponent E: the first two of them
-// that are not zero.  changes: the vector's, cleared before the last barrier.
+// that are not zero.  all: room for the changes of the 16 vectors, dv this thread's.
 template <typename T, int C>
-__device__ __forceinline__ int settle_strip(const T *x, int64_t comp_stride, int64_t sp, int len, int dp, int E,
-                                            int bits, int slice_bits, int passes, uint32_t *changes) {
+__device__ __forceinline__ int settle_strip(const T *x, int64_t comp_stride, int64_t sp, int len, int dp, int dv, int E,
+                                            int bits, int slice_bits, int passes, uint32_t (&all)[16][kChangeWords]) {
+  if (threadIdx.x < 16 * kChangeWords) all[threadIdx.x / kChangeWords][threadIdx.x % kChangeWords] = 0u;
+  __syncthreads();
+  uint32_t *changes = all[dv];
   const bool finite = E != kZeroExp && E != kNonFinite;
   if (finite) {
     int p = dp - 16;
@@ -1087,7 +1090,8 @@ __global__ __launch_bounds__(kThreads) void k_upload(Upload data, int n, uint32_
 // In the FLOAT form strips with zeros among a vector's first 32 elements take their
 // samples here (settle_strip).  For all strips, with the split's own look at the first
 // elements left out, that took DD 64^3 from 30.4 to 31.5 us and TD 200 x 150 x 333 from
-// 50.4 to 51.3.
+// 50.4 to 51.3.  Other strips do nothing for it: with the samples' room cleared and the
+// vote counted by every launch, TS 55 x 1218 x 278 took 4.5 - 4.8 us, not 3.8 - 3.9.
 template <typename T>
 struct MaxOperand {
   const T *X;
@@ -1131,10 +1135,12 @@ __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, 
   for (int64_t i = id; i < n; i += step) dst[i] = data.w[i];
   if (id == 0 && flag) *flag = 0;
   __shared__ U red[16][17];
+  __shared__ int some[kThreads / 64];
   __shared__ uint32_t changes[16][kChangeWords];
   red[dp][dv] = best;
-  if (t < 16 * kChangeWords) changes[t / kChangeWords][t % kChangeWords] = 0u;
-  const bool settle = __syncthreads_or(grid.bits > 0 && zeros);
+  if (grid.bits > 0) some[t / 64] = __any(zeros);
+  __syncthreads();
+  const bool settle = grid.bits > 0 && (some[0] | some[1] | some[2] | some[3]) != 0;
   if (t < 16 && v0 + t < op.nvec) {
     U k = red[0][t];
 #pragma unroll
@@ -1145,8 +1151,8 @@ __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, 
   if (settle) {
     U k = red[0][dv];
     for (int i = 1; i < 16; ++i) k = red[i][dv] > k ? red[i][dv] : k;
-    const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp, vector_exponent<T>(k, 1), grid.bits,
-                                     grid.slice_bits, grid.passes, changes[dv]);
+    const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp, dv, vector_exponent<T>(k, 1), grid.bits,
+                                     grid.slice_bits, grid.passes, changes);
     if (dp == 0 && v0 + dv < op.nvec) op.state[v0 + dv] = s;
   }
 }
@@ -1164,14 +1170,13 @@ __global__ __launch_bounds__(kThreads) void k_residue_sample(const ResidueOperan
   const int v = v0 + dv < op.nvec ? v0 + dv : op.nvec - 1;
   const T *x = op.X + (int64_t)v * op.sv;
   __shared__ uint32_t changes[16][kChangeWords];
-  if (t < 16 * kChangeWords) changes[t / kChangeWords][t % kChangeWords] = 0u;
   bool zeros = false;
 #pragma unroll
   for (int j = 0; j < 32; j += 16) zeros = zeros || dp + j >= op.len || abs_bits(x[(int64_t)(dp + j) * op.sp]) == 0;
   if (!__syncthreads_or(zeros)) return;
-  const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp,
+  const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp, dv,
                                    vector_exponent<T>(static_cast<const U *>(op.mu)[v], 1), op.bits, op.slice_bits,
-                                   op.passes, changes[dv]);
+                                   op.passes, changes);
   if (dp == 0 && v0 + dv < op.nvec) op.state[v0 + dv] = s;
 }
 // Up to this length (one or two launches less): INT8 DD calls of 64^2 x 64 go from
