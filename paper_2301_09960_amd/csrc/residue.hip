@@ -1101,9 +1101,9 @@ struct MaxOperand {
   int *state;
 };
 struct GridOfSlices {
-  int bits, slice_bits, passes;  // bits = 0: INT8 form, no samples
+  int bits, slice_bits, passes;
 };
-template <typename T, int C>
+template <typename T, int C>  // C = 0: INT8 form, no samples
 __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, int strips_a, uint32_t *dst,
                                                             MaxOperand<T> a, MaxOperand<T> b, GridOfSlices grid,
                                                             int *flag) {
@@ -1130,30 +1130,32 @@ __global__ __launch_bounds__(kThreads) void k_residue_begin(Upload data, int n, 
       const U k = abs_bits(e[i]);
       best = k > best ? k : best;
     }
-    if (p0 == dp) zeros = abs_bits(e[0]) == 0 || abs_bits(e[1]) == 0;
+    if (C > 0 && p0 == dp) zeros = abs_bits(e[0]) == 0 || abs_bits(e[1]) == 0;
   }
   for (int64_t i = id; i < n; i += step) dst[i] = data.w[i];
   if (id == 0 && flag) *flag = 0;
   __shared__ U red[16][17];
   __shared__ int some[kThreads / 64];
-  __shared__ uint32_t changes[16][kChangeWords];
   red[dp][dv] = best;
-  if (grid.bits > 0) some[t / 64] = __any(zeros);
+  if constexpr (C > 0) some[t / 64] = __any(zeros);
   __syncthreads();
-  const bool settle = grid.bits > 0 && (some[0] | some[1] | some[2] | some[3]) != 0;
   if (t < 16 && v0 + t < op.nvec) {
     U k = red[0][t];
 #pragma unroll
     for (int i = 1; i < 16; ++i) k = red[i][t] > k ? red[i][t] : k;
     op.mu[v0 + t] = k;
-    if (grid.bits > 0 && !settle) op.state[v0 + t] = 0;
   }
-  if (settle) {
-    U k = red[0][dv];
-    for (int i = 1; i < 16; ++i) k = red[i][dv] > k ? red[i][dv] : k;
-    const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp, dv, vector_exponent<T>(k, 1), grid.bits,
-                                     grid.slice_bits, grid.passes, changes);
-    if (dp == 0 && v0 + dv < op.nvec) op.state[v0 + dv] = s;
+  if constexpr (C > 0) {
+    if ((some[0] | some[1] | some[2] | some[3]) != 0) {
+      __shared__ uint32_t changes[16][kChangeWords];
+      U k = red[0][dv];
+      for (int i = 1; i < 16; ++i) k = red[i][dv] > k ? red[i][dv] : k;
+      const int s = settle_strip<T, C>(x, op.comp_stride, op.sp, op.len, dp, dv, vector_exponent<T>(k, 1), grid.bits,
+                                       grid.slice_bits, grid.passes, changes);
+      if (dp == 0 && v0 + dv < op.nvec) op.state[v0 + dv] = s;
+    } else if (t < 16 && v0 + t < op.nvec) {
+      op.state[v0 + t] = 0;
+    }
   }
 }
 
@@ -1641,9 +1643,13 @@ hipError_t launch_residue(const ResidueCall &rc, const SplitOperand<T> &a, const
       using U = typename bits_of<T>::type;
       const MaxOperand<T> va{a.X, a.comp_stride, a.sv, a.sp, a.nvec, a.len, 0, static_cast<U *>(rc.mu_a), rc.state_a};
       const MaxOperand<T> vb{b.X, b.comp_stride, b.sv, b.sp, b.nvec, b.len, 1, static_cast<U *>(rc.mu_b), rc.state_b};
-      const GridOfSlices grid{rc.float_form ? p.bits : 0, rc.slice_bits, rc.passes};
-      hipLaunchKernelGGL((k_residue_begin<T, C>), dim3((unsigned)(sa + sb)), dim3(kThreads), 0, st, up, (int)n, sa, dst,
-                         va, vb, grid, flag);
+      const GridOfSlices grid{p.bits, rc.slice_bits, rc.passes};
+      if (rc.float_form)
+        hipLaunchKernelGGL((k_residue_begin<T, C>), dim3((unsigned)(sa + sb)), dim3(kThreads), 0, st, up, (int)n, sa,
+                           dst, va, vb, grid, flag);
+      else
+        hipLaunchKernelGGL((k_residue_begin<T, 0>), dim3((unsigned)(sa + sb)), dim3(kThreads), 0, st, up, (int)n, sa,
+                           dst, va, vb, grid, flag);
     } else {
       const int64_t n0 = last ? rc.clear_words : 0;
       const int64_t blocks = std::min<int64_t>(256, std::max<int64_t>(4, ceil_div(n0, (int64_t)kThreads)));
